@@ -55,6 +55,7 @@ struct Layout {
   // barrier counters per layer, the abort word — n_zero ints that the set-up kernel clears
   int bar_index, abort_index, n_zero;
   size_t part_phase;   // floats per partial region of one phase of the layer kernel
+  size_t part_floats;  // floats of the whole partial region
 };
 
 // Decomposition of one bf16 matmul into (128-column tile, k split) workgroups: about kTargetWgs
@@ -94,6 +95,40 @@ SplitPlan plan_gemm(int epi, int n_cols, int k, int rows_pad) {
 }
 inline int tiles_of(int n) { return (n + kGemmTileN - 1) / kGemmTileN; }
 
+// Decomposition of one matmul over a panel of 128 or 256 rows (kernels_gemm_wide.hip): the tile width
+// and the number of k splits with the smallest estimated time.  Measured on the 28672 x 4096 and
+// 4096 x 14336 products: a 64-deep chunk takes a workgroup 1.65 us on a 128 x 256 tile and 1.12 us on
+// a 128 x 128 tile, a workgroup about 6 us beside its chunks, one workgroup runs per CU; splitting
+// costs a second launch (about 5 us) and the partial tiles, written and read back at about 5 TB/s.
+SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_part_floats) {
+  const int kb = k / 64, n_rg = rows_pad / 128;
+  SplitPlan best;
+  best.tile_n = 256;
+  best.n_tiles = (n_cols + 255) / 256;
+  best.n_splits = 1;
+  best.k_per_split = k;
+  if (epi == EPI_HEAD) return best;
+  double best_us = 1e30;
+  for (int tile_n = 256; tile_n >= 128; tile_n -= 128) {
+    const int tiles = (n_cols + tile_n - 1) / tile_n;
+    for (int s = 1; s <= 16 && s <= kb; ++s) {
+      const size_t floats = (size_t)s * tiles_of(n_cols) * kGemmTileN * rows_pad;
+      if (s > 1 && floats > max_part_floats) break;
+      const int rounds = (tiles * n_rg * s + 255) / 256, chunks = (kb + s - 1) / s;
+      const double us = rounds * (chunks * (tile_n == 256 ? 1.65 : 1.12) + 6.0) +
+                        (s > 1 ? 5.0 + (double)floats * 8.0 / 5e6 : 0.0);
+      if (us < best_us) {
+        best_us = us;
+        best.tile_n = tile_n;
+        best.n_tiles = tiles;
+        best.n_splits = s;
+      }
+    }
+  }
+  return best;
+}
+constexpr size_t kWidePartFloats = (size_t)12 << 20;   // partial tiles of one wide matmul: at most 48 MB
+
 // Decomposition of one matmul inside the layer kernel: at most max_items (tile, split) items, every
 // split the same whole number of `unit`-deep steps (unit = ring depth x chunk depth of the kernel
 // for this row count).  n_splits = 0: not possible for this shape.
@@ -128,7 +163,7 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
   const int nqkv = qd + 2 * kvd;
   L.rows_max = rows;
   L.rows_pad_max = rp;
-  L.head_tiles = f32 ? 1 : plan_gemm(EPI_HEAD, c.vocab, c.hidden, rp).n_tiles;
+  L.head_tiles = f32 ? 1 : tiles_of(c.vocab);   // 128-column tiles; wide panels use half as many
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   L.anc = take(sizeof(AncMask) * kMaxRows);
@@ -155,18 +190,24 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
     const int ep[4] = {EPI_QKV, EPI_RESID, EPI_SWIGLU, EPI_RESID};
     const int nc[4] = {nqkv, c.hidden, 2 * c.ffn, c.hidden};
     const int ks[4] = {c.hidden, qd, c.hidden, c.ffn};
-    size_t m = 0;
+    // (narrow plans do not depend on the rows, and a workspace also serves passes of fewer rows)
+    size_t m = 0, wide = 0;
     for (int i = 0; i < 4; ++i) {
       const SplitPlan p = plan_gemm(ep[i], nc[i], ks[i], rp);
       const size_t e = (size_t)p.n_splits * p.n_tiles * p.tile_n;
       if (e > m) m = e;
       if (p.n_tiles > L.max_tiles) L.max_tiles = p.n_tiles;
+      for (int r = 128; r <= rp; r += 128) {
+        const size_t f = (size_t)plan_wide(ep[i], nc[i], ks[i], r, kWidePartFloats).n_splits * tiles_of(nc[i]) * kGemmTileN * r;
+        if (f > wide) wide = f;
+      }
     }
     // the layer kernel runs at most kLayerMaxGrid (tile, split) items per matmul and gives each
     // of its matmuls a partial region of its own
     L.part_phase = (size_t)kLayerMaxGrid * kGemmTileN * rp;
     if (kLayerPhases * (size_t)kLayerMaxGrid * kGemmTileN > m) m = kLayerPhases * (size_t)kLayerMaxGrid * kGemmTileN;
-    L.part = take(sizeof(float) * m * rp);
+    L.part_floats = m * rp > wide ? m * rp : wide;
+    L.part = take(sizeof(float) * L.part_floats);
   }
   L.bar_index = L.max_tiles + 1;
   L.abort_index = L.bar_index + kLayerPhases * c.n_layers;
@@ -770,11 +811,18 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       g.next_norm_w = (l + 1 < c.n_layers) ? m->norm_attn[l + 1] : m->final_norm; g.ss_part = ss0;
       return g;
     };
-    const SplitPlan pq = plan_gemm(EPI_QKV, nqkv, c.hidden, rp), po = plan_gemm(EPI_RESID, c.hidden, qd, rp);
-    const SplitPlan pg = plan_gemm(EPI_SWIGLU, 2 * c.ffn, c.hidden, rp), pd = plan_gemm(EPI_RESID, c.hidden, c.ffn, rp);
+    const bool wide = rp > 64;
+    auto plan = [&](int epi, int n_cols, int k) {
+      return wide ? plan_wide(epi, n_cols, k, rp, kWidePartFloats) : plan_gemm(epi, n_cols, k, rp);
+    };
+    auto launch_gemm = [&](const GemmArgs &g) {
+      if (wide) launch_gemm_wide(st, g); else launch_gemm_bf16(st, g);
+    };
+    const SplitPlan pq = plan(EPI_QKV, nqkv, c.hidden), po = plan(EPI_RESID, c.hidden, qd);
+    const SplitPlan pg = plan(EPI_SWIGLU, 2 * c.ffn, c.hidden), pd = plan(EPI_RESID, c.hidden, c.ffn);
     auto timed_gemm = [&](const GemmArgs &g, double bytes) {
       TimedLaunch tl(opts->timer, TRISPEC_K_GEMM, st, bytes);
-      launch_gemm_bf16(st, g);
+      launch_gemm(g);
     };
     const double b_qkv = (double)nqkv * c.hidden * es, b_o = (double)c.hidden * qd * es;
     const double b_gu = 2.0 * c.ffn * c.hidden * es, b_dn = (double)c.hidden * c.ffn * es;
@@ -863,20 +911,21 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       }
     }
     {
-      GemmArgs g = base(EPI_HEAD, h, pan_h, ss0, hid_tiles, c.hidden, c.vocab, plan_gemm(EPI_HEAD, c.vocab, c.hidden, rp));
+      GemmArgs g = base(EPI_HEAD, h, pan_h, ss0, hid_tiles, c.hidden, c.vocab, plan(EPI_HEAD, c.vocab, c.hidden));
       g.seg[0] = {m->p_lm_head, c.vocab, 0};
       g.n_seg = 1;
       hs.n_tiles = g.n_tiles;
       g.hs = hs;
       g.debug_logits = opts->debug_logits;
       TimedLaunch tl(opts->timer, TRISPEC_K_HEAD, st, (double)c.vocab * c.hidden * es);
-      launch_gemm_bf16(st, g);
+      launch_gemm(g);
     }
     if (opts->adapter_w) {
       // the adapter on the final-norm features: the LM head's operand panels and 1/rms again, another
       // matrix, a plain fp32 result (+ bias)
-      SplitPlan pa = plan_gemm(EPI_RESID, opts->adapter_dim, c.hidden, rp);
-      if (pa.n_splits > 1 && pa.n_tiles > L.max_tiles) {   // no counters for that many tiles: one split
+      SplitPlan pa = wide ? plan_wide(EPI_PLAIN, opts->adapter_dim, c.hidden, rp, L.part_floats)
+                          : plan_gemm(EPI_PLAIN, opts->adapter_dim, c.hidden, rp);
+      if (!wide && pa.n_splits > 1 && pa.n_tiles > L.max_tiles) {   // no counters for that many tiles: one split
         pa.n_splits = 1;
         pa.k_per_split = (int)align_up(c.hidden, (c.hidden % 256 == 0) ? 256 : 64);
       }
@@ -885,7 +934,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       g.n_seg = 1;
       g.out = opts->adapter_out;
       g.bias = opts->adapter_bias;
-      launch_gemm_bf16(st, g);
+      launch_gemm(g);
     }
     if (opts->hidden_out)   // x after the last layer, the final norm's weight, the sums of squares the last down projection left
       launch_export_hidden(st, c.dtype, x, m->final_norm, ss0, hid_tiles, rows, rp, c.hidden, c.rms_eps,

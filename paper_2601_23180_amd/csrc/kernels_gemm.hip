@@ -1,7 +1,7 @@
 // Weight-streaming small-M matmul on the matrix cores (bf16 weights, fp32 accumulate) with the
 // surrounding element-wise work fused in.
 //
-//   y[r][n] = rstd[r] * sum_k X[r][k] * W[n][k]        r < rows_pad <= 256
+//   y[r][n] = rstd[r] * sum_k X[r][k] * W[n][k]        r < rows_pad <= 64
 //
 // At these row counts the product is bound by streaming W from HBM once, so the layout serves
 // the W stream.  W is read from the PACKED copy made once by k_pack_weights: for every 32-row
@@ -12,7 +12,7 @@
 // passes through LDS and is never re-read.  (Reading row-major W with the same operand layout
 // touches 32 rows x 32 bytes per instruction and reaches ~75 % of the contiguous rate.)
 //
-// The activation panel X (at most 256 rows) is what the four wavefronts of a workgroup share.
+// The activation panel X (at most 64 rows; more rows: kernels_gemm_wide.hip) is what the four wavefronts of a workgroup share.
 // It arrives as two bf16 panels, a high part and a low part (hi = round(v), lo = round(v - hi),
 // written once by whichever kernel produced the activation — splitting it here would repeat the
 // conversion in every one of the hundreds of workgroups and costs more issue slots than the
@@ -272,25 +272,18 @@ void launch_pack_weights(hipStream_t st, const void *w, int n_rows, int k, void 
 template <int EPI>
 static void dispatch(hipStream_t st, const GemmArgs &a) {
   dim3 grid(a.n_tiles, a.n_splits), block(256);
-  // (the 4-deep W ring does not fit the register file next to the accumulators of 256 rows)
 #define TS_LAUNCH(MB_, KC_)                                                                   \
   do {                                                                                        \
-    bool deep = false;                                                                        \
-    if constexpr (MB_ < 8) {                                                                  \
-      deep = a.k_per_split % (4 * KC_) == 0 && a.k % (4 * KC_) == 0;                          \
-      if (deep) hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, false, 4>), grid, block, 0, st, a); \
-    }                                                                                         \
-    if (deep) break;                                                                          \
-    if (a.k_per_split % (2 * KC_) == 0 && a.k % (2 * KC_) == 0)                               \
+    if (a.k_per_split % (4 * KC_) == 0 && a.k % (4 * KC_) == 0)                               \
+      hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, false, 4>), grid, block, 0, st, a);      \
+    else if (a.k_per_split % (2 * KC_) == 0 && a.k % (2 * KC_) == 0)                          \
       hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, false, 2>), grid, block, 0, st, a);      \
     else                                                                                      \
       hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, true, 1>), grid, block, 0, st, a);       \
   } while (0)
   switch (a.rows_pad) {
     case 32: TS_LAUNCH(1, 256); break;
-    case 64: TS_LAUNCH(2, 128); break;
-    case 128: TS_LAUNCH(4, 64); break;
-    default: TS_LAUNCH(8, 64); break;
+    default: TS_LAUNCH(2, 128); break;   // 64; larger panels: kernels_gemm_wide.hip
   }
 #undef TS_LAUNCH
 }
