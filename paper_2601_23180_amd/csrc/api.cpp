@@ -58,42 +58,79 @@ struct Layout {
   size_t part_floats;  // floats of the whole partial region
 };
 
-// Decomposition of one bf16 matmul into (128-column tile, k split) workgroups: about kTargetWgs
-// workgroups in all (two fit on a CU), every k split a whole number of 256-deep steps (512 when
-// long enough) when the reduction allows it, and at least 512 deep.
 struct SplitPlan {
   int tile_n, n_tiles, n_splits, k_per_split;
+  int stream = 0;
 };
-constexpr int kTargetWgs = 192;   // swept 128 .. 384 at the 8B shape: 192 - 224 is the flat optimum
 constexpr int kLayerMaxGrid = 256;   // workgroups of the layer kernel (one per CU)
 constexpr int kLayerSplitCap = 8;    // k splits of one matmul inside the layer kernel
 // Longest wait at a device-side barrier, in ticks of the 100 MHz wall clock (2 s: three orders of
 // magnitude above a whole pass).  trispec_debug_set_spin_limit changes it (tests of the expiry path).
 unsigned long long g_spin_limit = 200000000ull;
 
-SplitPlan plan_gemm(int epi, int n_cols, int k, int rows_pad) {
-  (void)rows_pad;
-  SplitPlan p;
-  p.tile_n = kGemmTileN;
-  // SWIGLU: n_cols = 2 * ffn, a tile holds tile_n/2 gate columns and the matching up columns
-  p.n_tiles = (n_cols + p.tile_n - 1) / p.tile_n;
-  if (epi == EPI_HEAD) {
-    p.n_splits = 1;
-    p.k_per_split = (int)align_up(k, (k % 256 == 0) ? 256 : 64);
-    return p;
+// Decomposition of one matmul over at most 64 rows into (column tile, k split) workgroups.
+//
+// Two kernels.  The 128-column kernel (kernels_gemm.hip) shares the activation panel among its four
+// wavefronts through LDS and has the better stream; it needs reductions of whole chunk pairs.  In the
+// streaming kernel (kernels_gemm_stream.hip) the wavefronts share out the reduction, which allows
+// narrow tiles: less of a partial tile to publish and to add up at the end, where a short matmul spends
+// half its time, against an activation panel read once per 32 or 64 columns.  Measured, 60 rows:
+// 2048 x 6144 22.6 us (128 columns) / 15.7 us (32), 2048 x 2048 14.6 / 10.2, QKV 4096 x 2048 19.0 /
+// 15.0 (64), 6144 x 4096 25.0 / 24.1; gate + up 24576 x 4096 44.2 / 48.1, 6144 x 1024 over 9 rows
+// 8.9 / 9.8; QKV over 32 rows and less: 10.3 / 10.4 and 16.8 / 18.7.  So the two residual products and
+// QKV over more than 32 rows take the streaming kernel, as does whatever the other one cannot: k not a
+// multiple of its chunk pair.  A head of 128 with its own norm needs all of its columns in one tile.
+constexpr int kTargetWgs = 192;   // 128-column kernel; swept 128 .. 384 at the 8B shape: 192 - 224 is the flat optimum
+SplitPlan plan_gemm(int epi, int n_cols, int k, int rows_pad, int head_dim, bool qk_norm) {
+  const int kb = k / 64, mb = rows_pad / 32;
+  const bool whole_head = epi == EPI_QKV && qk_norm && head_dim == 128;
+  SplitPlan wide;   // the 128-column kernel: k splits of whole 512-deep (256-deep) steps, at least 512 deep
+  wide.tile_n = kGemmTileN;
+  wide.n_tiles = (n_cols + kGemmTileN - 1) / kGemmTileN;
+  wide.n_splits = 1;
+  wide.k_per_split = k;
+  const bool chunks = k % (256 * (3 - mb)) == 0;
+  if (epi != EPI_HEAD && chunks) {
+    int s = (kTargetWgs + wide.n_tiles / 2) / wide.n_tiles;
+    if (s > k / 512) s = k / 512;
+    if (s < 1) s = 1;
+    const int per = (k + s - 1) / s;
+    wide.k_per_split = (int)align_up((size_t)per, k % 512 == 0 && (mb == 1 || per >= 1024) ? 512 : 256);
+    wide.n_splits = (k + wide.k_per_split - 1) / wide.k_per_split;
   }
-  int s = (kTargetWgs + p.n_tiles / 2) / p.n_tiles;
-  const int max_by_k = k / 512 > 0 ? k / 512 : 1;
-  if (s > max_by_k) s = max_by_k;
-  if (s > kMaxSplitK) s = kMaxSplitK;
-  if (s < 1) s = 1;
-  const int per = (k + s - 1) / s;
-  const int unit = (k % 256 != 0) ? 64 : ((per >= 1024 && k % 512 == 0) ? 512 : 256);
-  p.k_per_split = (int)align_up((size_t)per, unit);
-  p.n_splits = (k + p.k_per_split - 1) / p.k_per_split;
-  return p;
+  if (chunks && (epi == EPI_HEAD || epi == EPI_SWIGLU || (epi == EPI_QKV && (whole_head || mb == 1)))) return wide;
+  SplitPlan p = wide;
+  p.stream = 1;
+  p.k_per_split = k;
+  if (epi == EPI_HEAD) return p;
+  // The smallest estimated time over tile widths and splits whose workgroups run all at once (one per
+  // CU): a workgroup draws weights and activations at about 65 GB/s, needs 4 - 9 us beside that
+  // (growing with its tile) and another 3.5 us to meet the other splits.  A residual product
+  // stays with 128 columns where nothing is gained: over more than 32 rows where 64 columns would win over
+  // 32 (4096 x 12288: 37.0 us for 32, 32.3 - 33.7 for 64, 31.8 for 128), over fewer where 32 would (1024 x
+  // 2048 and 1024 x 3072 over 9 rows: 9.0 us either way, and 32 columns leave the reader four times the
+  // sums of squares; 2048 x 6144, 64 columns: 14.7 -> 12.2).
+  const bool resid = epi == EPI_RESID || epi == EPI_PLAIN;   // the results of any 32 columns stand for themselves
+  double best_us = 1e30;
+  for (int tn = whole_head ? 128 : (resid ? 32 : 64); tn <= (whole_head ? 128 : 64); tn *= 2) {
+    const int tiles = (n_cols + tn - 1) / tn;
+    const double fixed = tn == 32 ? 4.0 : (mb == 1 ? 5.2 : 9.0);
+    for (int s = 1; s <= 16 && s <= kb && (s == 1 || tiles * s <= 256); ++s) {
+      const double bytes = (double)((kb + s - 1) / s) * 64.0 * (2.0 * tn + 4.0 * rows_pad);
+      const double us = ((tiles * s + 255) / 256) * (bytes / 65e3 + fixed) + (s > 1 ? 3.5 : 0.0);
+      if (us < best_us) {
+        best_us = us;
+        p.tile_n = tn;
+        p.n_tiles = tiles;
+        p.n_splits = s;
+      }
+    }
+  }
+  return chunks && epi == EPI_RESID && p.tile_n == (mb == 2 ? 64 : 32) ? wide : p;
 }
 inline int tiles_of(int n) { return (n + kGemmTileN - 1) / kGemmTileN; }
+// entries per row of the sums of squares that a matmul with tiles of tile_n columns leaves
+inline int ss_tiles_of(int n, int tile_n) { return tile_n < kGemmTileN ? (n + tile_n - 1) / tile_n : tiles_of(n); }
 
 // Decomposition of one matmul over a panel of 128 or 256 rows (kernels_gemm_wide.hip): the tile width
 // and the number of k splits with the smallest estimated time.  Measured on the 28672 x 4096 and
@@ -186,27 +223,23 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
     if (2 * c.ffn > m) m = 2 * c.ffn;
     L.part = take(sizeof(float) * (size_t)rp * m);
   } else {
-    // split-K partial tiles: the largest of splits x tiles x tile width over the matmuls of a layer
+    // split-K partial tiles: the largest of splits x tiles x tile width x rows over the matmuls of a
+    // layer and over the panels up to this one (a workspace also serves passes of fewer rows)
     const int ep[4] = {EPI_QKV, EPI_RESID, EPI_SWIGLU, EPI_RESID};
     const int nc[4] = {nqkv, c.hidden, 2 * c.ffn, c.hidden};
     const int ks[4] = {c.hidden, qd, c.hidden, c.ffn};
-    // (narrow plans do not depend on the rows, and a workspace also serves passes of fewer rows)
-    size_t m = 0, wide = 0;
-    for (int i = 0; i < 4; ++i) {
-      const SplitPlan p = plan_gemm(ep[i], nc[i], ks[i], rp);
-      const size_t e = (size_t)p.n_splits * p.n_tiles * p.tile_n;
-      if (e > m) m = e;
-      if (p.n_tiles > L.max_tiles) L.max_tiles = p.n_tiles;
-      for (int r = 128; r <= rp; r += 128) {
-        const size_t f = (size_t)plan_wide(ep[i], nc[i], ks[i], r, kWidePartFloats).n_splits * tiles_of(nc[i]) * kGemmTileN * r;
-        if (f > wide) wide = f;
+    size_t floats = (size_t)kLayerPhases * kLayerMaxGrid * kGemmTileN * rp;
+    for (int i = 0; i < 4; ++i)
+      for (int r = 32; r <= 256; r *= 2) {
+        const SplitPlan p = r <= 64 ? plan_gemm(ep[i], nc[i], ks[i], r, c.head_dim, c.qk_norm != 0) : plan_wide(ep[i], nc[i], ks[i], r, kWidePartFloats);
+        if (r <= 64 && p.n_tiles > L.max_tiles) L.max_tiles = p.n_tiles;
+        const size_t f = (size_t)p.n_splits * (r <= 64 ? p.n_tiles * p.tile_n : tiles_of(nc[i]) * kGemmTileN) * r;
+        if (r <= rp && f > floats) floats = f;
       }
-    }
     // the layer kernel runs at most kLayerMaxGrid (tile, split) items per matmul and gives each
     // of its matmuls a partial region of its own
     L.part_phase = (size_t)kLayerMaxGrid * kGemmTileN * rp;
-    if (kLayerPhases * (size_t)kLayerMaxGrid * kGemmTileN > m) m = kLayerPhases * (size_t)kLayerMaxGrid * kGemmTileN;
-    L.part_floats = m * rp > wide ? m * rp : wide;
+    L.part_floats = floats;
     L.part = take(sizeof(float) * L.part_floats);
   }
   L.bar_index = L.max_tiles + 1;
@@ -214,7 +247,7 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
   L.n_zero = L.abort_index + 1;
   L.counters = take(sizeof(int32_t) * L.n_zero);
   // sums of squares per (tile, row): two buffers, a matmul reads its producer's while writing its own
-  L.ss_part = take(2 * sizeof(float) * (size_t)tiles_of(c.hidden) * rp);   // sized for the narrower tile
+  L.ss_part = take(2 * sizeof(float) * (size_t)ss_tiles_of(c.hidden, 32) * rp);   // sized for the narrowest tile
   const int group = c.n_q_heads / c.n_kv_heads;
   const size_t prow = f32 ? 0 : (size_t)batch * c.n_kv_heads * kMaxAttnSplits * group * max_nodes;
   L.attn_o = take(sizeof(float) * prow * c.head_dim);
@@ -744,10 +777,10 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
     at.q = ws + L.q;
     at.q_panel = pan_q;
     // ss[0]: written by the embedding (1 tile) and by every down projection; ss[1]: by every O projection
-    float *ss0 = (float *)(ws + L.ss_part), *ss1 = ss0 + (size_t)tiles_of(c.hidden) * rp;
+    float *ss0 = (float *)(ws + L.ss_part), *ss1 = ss0 + (size_t)ss_tiles_of(c.hidden, 32) * rp;
     launch_embed_norm(st, c.dtype, draft_tokens, m->embed, m->norm_attn[0], rows, c.hidden, c.vocab, c.rms_eps,
                       x, h, (size_t)(rp / 32), ss0, status);
-    const int hid_tiles = tiles_of(c.hidden);
+    int o_tiles = tiles_of(c.hidden), dn_tiles = o_tiles;   // sums of squares per row that the O / down projections leave
     auto base = [&](int epi, const void *xin, size_t xpanel, const float *ss_in, int ss_tiles, int k,
                     int n_total, const SplitPlan &p) {
       GemmArgs g;
@@ -763,6 +796,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       g.rows = rows;
       g.rows_pad = rp;
       g.tile_n = p.tile_n;
+      g.stream = p.stream;
       g.n_tiles = p.n_tiles;
       g.n_splits = p.n_splits;
       g.k_per_split = p.k_per_split;
@@ -796,7 +830,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       return g;
     };
     auto mk_gu = [&](int l, const SplitPlan &p, const void *h_in) {
-      GemmArgs g = base(EPI_SWIGLU, h_in, pan_h, ss1, hid_tiles, c.hidden, 2 * c.ffn, p);
+      GemmArgs g = base(EPI_SWIGLU, h_in, pan_h, ss1, o_tiles, c.hidden, 2 * c.ffn, p);
       g.seg[0] = {m->p_gate[l], c.ffn, 0};
       g.seg[1] = {m->p_up[l], c.ffn, c.ffn};
       g.n_seg = 2;
@@ -813,10 +847,10 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
     };
     const bool wide = rp > 64;
     auto plan = [&](int epi, int n_cols, int k) {
-      return wide ? plan_wide(epi, n_cols, k, rp, kWidePartFloats) : plan_gemm(epi, n_cols, k, rp);
+      return wide ? plan_wide(epi, n_cols, k, rp, kWidePartFloats) : plan_gemm(epi, n_cols, k, rp, c.head_dim, c.qk_norm != 0);
     };
     auto launch_gemm = [&](const GemmArgs &g) {
-      if (wide) launch_gemm_wide(st, g); else launch_gemm_bf16(st, g);
+      if (wide) launch_gemm_wide(st, g); else if (g.stream) launch_gemm_stream(st, g); else launch_gemm_bf16(st, g);
     };
     const SplitPlan pq = plan(EPI_QKV, nqkv, c.hidden), po = plan(EPI_RESID, c.hidden, qd);
     const SplitPlan pg = plan(EPI_SWIGLU, 2 * c.ffn, c.hidden), pd = plan(EPI_RESID, c.hidden, c.ffn);
@@ -873,6 +907,8 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
 
     if (!layered) {
       int ss0_tiles = 1;
+      o_tiles = ss_tiles_of(c.hidden, po.tile_n);
+      dn_tiles = ss_tiles_of(c.hidden, pd.tile_n);
       for (int l = 0; l < c.n_layers; ++l) {
         char *kl = (char *)kv->k + (size_t)l * kv_layer, *vl = (char *)kv->v + (size_t)l * kv_layer;
         timed_gemm(mk_qkv(l, pq, ss0_tiles), b_qkv);
@@ -881,7 +917,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
         timed_gemm(mk_gu(l, pg, h), b_gu);
         timed_gemm(mk_dn(l, pd, x, x), b_dn);
         export_layer(l, x);
-        ss0_tiles = hid_tiles;
+        ss0_tiles = dn_tiles;
       }
     } else {
       timed_gemm(mk_qkv(0, pq, 1), b_qkv);
@@ -896,7 +932,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
         la.ph[0] = mk_o(l, lo, x, x2, h2);
         la.ph[1] = mk_gu(l, lg, h2);
         la.ph[2] = mk_dn(l, ld, x2, x);
-        if (more) la.ph[3] = mk_qkv(l + 1, lq, hid_tiles);
+        if (more) la.ph[3] = mk_qkv(l + 1, lq, dn_tiles);
         for (int p = 0; p < kLayerPhases; ++p) la.ph[p].part = part + (size_t)p * L.part_phase;
         la.bar = counters + L.bar_index + kLayerPhases * l;
         la.abort_word = counters + L.abort_index;
@@ -911,7 +947,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       }
     }
     {
-      GemmArgs g = base(EPI_HEAD, h, pan_h, ss0, hid_tiles, c.hidden, c.vocab, plan(EPI_HEAD, c.vocab, c.hidden));
+      GemmArgs g = base(EPI_HEAD, h, pan_h, ss0, dn_tiles, c.hidden, c.vocab, plan(EPI_HEAD, c.vocab, c.hidden));
       g.seg[0] = {m->p_lm_head, c.vocab, 0};
       g.n_seg = 1;
       hs.n_tiles = g.n_tiles;
@@ -924,12 +960,10 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       // the adapter on the final-norm features: the LM head's operand panels and 1/rms again, another
       // matrix, a plain fp32 result (+ bias)
       SplitPlan pa = wide ? plan_wide(EPI_PLAIN, opts->adapter_dim, c.hidden, rp, L.part_floats)
-                          : plan_gemm(EPI_PLAIN, opts->adapter_dim, c.hidden, rp);
-      if (!wide && pa.n_splits > 1 && pa.n_tiles > L.max_tiles) {   // no counters for that many tiles: one split
-        pa.n_splits = 1;
-        pa.k_per_split = (int)align_up(c.hidden, (c.hidden % 256 == 0) ? 256 : 64);
-      }
-      GemmArgs g = base(EPI_PLAIN, h, pan_h, ss0, hid_tiles, c.hidden, opts->adapter_dim, pa);
+                          : plan_gemm(EPI_PLAIN, opts->adapter_dim, c.hidden, rp, c.head_dim, c.qk_norm != 0);
+      if (!wide && (pa.n_tiles > L.max_tiles || (size_t)pa.n_splits * pa.n_tiles * pa.tile_n * rp > L.part_floats))
+        pa.n_splits = 1;   // no counters for that many tiles, or no room
+      GemmArgs g = base(EPI_PLAIN, h, pan_h, ss0, dn_tiles, c.hidden, opts->adapter_dim, pa);
       g.seg[0] = {opts->adapter_w, opts->adapter_dim, 0};
       g.n_seg = 1;
       g.out = opts->adapter_out;
@@ -937,7 +971,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       launch_gemm(g);
     }
     if (opts->hidden_out)   // x after the last layer, the final norm's weight, the sums of squares the last down projection left
-      launch_export_hidden(st, c.dtype, x, m->final_norm, ss0, hid_tiles, rows, rp, c.hidden, c.rms_eps,
+      launch_export_hidden(st, c.dtype, x, m->final_norm, ss0, dn_tiles, rows, rp, c.hidden, c.rms_eps,
                            opts->hidden_out);
   }
 

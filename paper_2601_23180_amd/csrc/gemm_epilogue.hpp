@@ -2,7 +2,7 @@
 // of wavefronts per workgroup and of 32-column sub-tiles per wavefront.
 #pragma once
 
-#include "device_util.hpp"
+#include "gemm_tile.hpp"
 
 namespace ts {
 
@@ -74,41 +74,16 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, f32x16 (&acc)[N
   if (EPI == EPI_HEAD) {
     // ---- per row, reduce this tile's TN logits to (l1, column, l2, sum exp)
     float *tl = (float *)lds;
-    constexpr int PARTS = TN / 16;        // threads scanning one row, 16 columns each
-    constexpr int RP = NT / PARTS;        // rows per scan pass
-    const int srow = tid / PARTS, part = tid % PARTS;
-    // (row_scale is applied when the tile is read back: the scan thread owns one row)
+    __syncthreads();
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      __syncthreads();
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          tl[(8 * (e >> 2) + 4 * g + (e & 3)) * (TN + 4) + (wave * NB + nb) * 32 + ln] = acc[nb][mb][e];
-      __syncthreads();
-#pragma unroll
-      for (int rp = 0; rp < 32; rp += RP) {
-        const int lr = rp + srow, r = mb * 32 + lr;
-        const float rsc = (a.ss_in != nullptr && r < a.rows) ? s_rs[r] : 1.0f;
-        Top2 t = top2_empty();
-        const int cbase = tile * TN + part * 16;
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-          const float v = tl[lr * (TN + 4) + part * 16 + c] * rsc;
-          if (cbase + c < a.n_total) {
-            top2_push(t, v, cbase + c);
-            if (a.debug_logits != nullptr && r < a.rows) a.debug_logits[(size_t)r * a.n_total + cbase + c] = v;
-          }
-        }
-#pragma unroll
-        for (int o = 1; o < PARTS; o <<= 1) t = top2_merge(t, top2_shfl_xor(t, o));
-        if (part == 0 && r < a.rows) {
-          const size_t o = (size_t)r * a.hs.n_tiles + tile;
-          a.hs.l1[o] = t.l1; a.hs.l2[o] = t.l2; a.hs.sumexp[o] = t.s; a.hs.ent[o] = t.t; a.hs.idx[o] = t.idx;
-        }
-      }
-    }
+          tl[(mb * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * (TN + 4) + (wave * NB + nb) * 32 + ln] = acc[nb][mb][e];
+    __syncthreads();
+    head_rows<TN, NT, MB * 32, TN + 4>(a, tl, s_rs, tile, 0);
     return;
   }
 
@@ -225,37 +200,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, f32x16 (&acc)[N
       };
       // the group size is the number of splits itself where that is small: no load is wasted on a
       // clamped duplicate (a 256-row partial tile is 128 KB per split)
-      if constexpr (MG * 32 >= 256) {
-        // 256-row tiles: the workgroup is out of registers here (rotary tables or residual rows are
-        // held across the reduction), so two splits of 8 vectors at a time
-        constexpr int UB8 = PER < 8 ? PER : 8;
-#pragma unroll 1
-        for (int ub = 0; ub < PER; ub += UB8) {
-          f32x4 sum[UB8];
-#pragma unroll
-          for (int u = 0; u < UB8; ++u) sum[u] = *(const f32x4 *)(p0 + (size_t)(ub + u) * NT * 4);
-          for (int s = 1; s < a.n_splits; s += 2) {
-            const bool two = s + 1 < a.n_splits;
-            const float *pa = p0 + (size_t)s * split_stride, *pb = pa + (two ? split_stride : 0);
-            f32x4 va[UB8], vb[UB8];
-#pragma unroll
-            for (int u = 0; u < UB8; ++u) {
-              va[u] = *(const f32x4 *)(pa + (size_t)(ub + u) * NT * 4);
-              vb[u] = *(const f32x4 *)(pb + (size_t)(ub + u) * NT * 4);
-            }
-#pragma unroll
-            for (int u = 0; u < UB8; ++u) {
-              sum[u] += va[u];
-              if (two) sum[u] += vb[u];
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < UB8; ++u) {
-            const int idx = tid + (ub + u) * NT, r = idx / (TN / 4), c = (idx % (TN / 4)) * 4;
-            *(f32x4 *)(tl + r * EPI_LD + c) = sum[u];
-          }
-        }
-      } else
       switch (a.n_splits) {
         case 2: reduce_groups(SplitGroup<2>{}); break;
         case 3: reduce_groups(SplitGroup<3>{}); break;
@@ -366,16 +310,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, f32x16 (&acc)[N
         bf16 *dst = (bf16 *)a.act_out;   // operand layout of the down projection (K = ffn)
         store_bf16x4<WT>(dst + ol_offset(r, feat, 0, MB), hi);
         store_bf16x4<WT>(dst + ol_offset(r, feat, 1, MB), lo);
-      }
-    } else if constexpr (EPI == EPI_PLAIN) {
-      // ---- y = (x W^T) / rms + bias, written as it is (the adapter on the exported features)
-      constexpr int Q4 = TN / 4;
-      for (int t = tid; t < MG * 32 * Q4; t += NT) {
-        const int lr = t / Q4, c = (t % Q4) * 4, r = row0 + lr, col = tile * TN + c;
-        if (r >= a.rows || col >= a.n_total) continue;
-        f32x4 v = reduced4(lr, c) * s_rs[r];
-        if (a.bias != nullptr) v += *(const f32x4 *)(a.bias + col);
-        *(f32x4 *)(a.out + (size_t)r * a.n_total + col) = v;
       }
     } else {
       // ---- EPI_RESID: x += y; per-row sum of squares of the new x over this tile's columns.

@@ -4,9 +4,50 @@
 // themselves and k_gemm_finish, which adds up split-K partial tiles).
 #pragma once
 
+#include <type_traits>
+
 #include "device_util.hpp"
 
 namespace ts {
+
+template <int N>
+using IC = std::integral_constant<int, N>;
+
+// Sums of squares of ROWS rows from the per-(tile, row) entries, in two parts: issue() requests the
+// first entries, finish() adds everything up (ascending tiles within a thread, threads in ascending
+// order) and leaves 1/rms in s_rs[0 .. ROWS).  s_tmp: NT floats.  Ends with a barrier.
+template <int NT, int ROWS, int PRE = 16>
+struct RowScale {
+  static constexpr int Q = NT / ROWS;   // threads per row; each requests PRE entries ahead
+  float x[PRE];
+  __device__ __forceinline__ void issue(const GemmArgs &a, int row0) {
+    if (a.ss_in == nullptr) return;
+    const int r = min(row0 + (int)threadIdx.x % ROWS, a.rows_pad - 1), q = threadIdx.x / ROWS;
+#pragma unroll
+    for (int u = 0; u < PRE; ++u) x[u] = a.ss_in[(size_t)min(q + Q * u, a.ss_tiles - 1) * a.rows_pad + r];
+  }
+  __device__ __forceinline__ void finish(const GemmArgs &a, int row0, float *s_tmp, float *s_rs) {
+    const int tid = threadIdx.x;
+    if (a.ss_in != nullptr) {
+      const int r = min(row0 + tid % ROWS, a.rows_pad - 1), q = tid / ROWS;
+      float v = 0.f;
+#pragma unroll
+      for (int u = 0; u < PRE; ++u) v += (q + Q * u < a.ss_tiles) ? x[u] : 0.f;
+      for (int t = q + Q * PRE; t < a.ss_tiles; t += Q) v += a.ss_in[(size_t)t * a.rows_pad + r];
+      s_tmp[tid] = v;
+    }
+    __syncthreads();
+    if (tid < ROWS) {
+      float ss = 0.f;
+      if (a.ss_in != nullptr) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) ss += s_tmp[q * ROWS + tid];
+      }
+      s_rs[tid] = a.ss_in != nullptr ? 1.0f / sqrtf(ss / (float)a.k + a.eps) : 1.0f;
+    }
+    __syncthreads();
+  }
+};
 
 // Columns that one entry of the per-(tile, row) sums of squares covers.
 template <int TN>
@@ -30,6 +71,18 @@ struct TileEpilogue {
   f32x4 pre_b[EPI == EPI_QKV ? QKV_PASSES : 1];
   bf16x4 pre_nw;
 
+  // Where 4 rotation pairs sit: columns c_lo .. and c_lo + off .. of the tile, features j .. and
+  // j + d/2 .. of head `head` of the concatenated q, k, v heads.  A 64-column tile holds a head of 64,
+  // or one half of the pairs of a head of 128 (features 32p .. 32p + 31 and 64 + 32p ..).
+  struct Pair { int c_lo, off, j, head; };
+  static __device__ __forceinline__ Pair qkv_pair(int tile, int qi, int d) {
+    if constexpr (TN == 64) {
+      if (d == 128) return {qi * 4, 32, 32 * (tile & 1) + qi * 4, tile >> 1};
+    }
+    const int half = d >> 1, hl = (qi * 4) / half, j = qi * 4 - hl * half;
+    return {hl * d + j, half, j, (tile * TN + hl * d) / d};
+  }
+
   __device__ __forceinline__ void preload(const GemmArgs &a, int tile, int row0) {
     const int tid = threadIdx.x;
     if constexpr (EPI == EPI_QKV) {
@@ -37,7 +90,7 @@ struct TileEpilogue {
 #pragma unroll
       for (int u = 0; u < QKV_PASSES; ++u) {
         const int t = tid + u * NT, r = min(row0 + t / QG, a.rows - 1), qi = t % QG;
-        const int j = qi * 4 - ((qi * 4) / half) * half;
+        const int j = qkv_pair(tile, qi, a.head_dim).j;
         pre_a[u] = *(const f32x4 *)(a.cos_t + r * half + j);
         pre_b[u] = *(const f32x4 *)(a.sin_t + r * half + j);
       }
@@ -63,14 +116,13 @@ struct TileEpilogue {
       for (int u = 0; u < QKV_PASSES; ++u) {
         const int t = tid + u * NT;
         const int lr = t / QG, qi = t - lr * QG, r = row0 + lr;
-        const int hl = (qi * 4) / half, j = qi * 4 - hl * half;   // head within the tile, first pair
-        const int c_lo = hl * d + j;                          // tile-local column of the low elements
-        const int col = tile * TN + c_lo;                     // global column
+        const Pair pr = qkv_pair(tile, qi, d);
+        const int j = pr.j, hh = pr.head;                     // first pair, head (q heads, k heads, v heads)
+        const int col = hh * d + j;                           // global column
         const bool live = lr < RB && r < a.rows && col < a.n_total;
-        const int hh = col / d;                               // global head index (q heads, k heads, v heads)
         const int lrc = lr < RB ? lr : 0;
         const float rsc = live ? rs[lrc] : 0.f;
-        f32x4 lo = red(lrc, c_lo) * rsc, hi = red(lrc, c_lo + half) * rsc;
+        f32x4 lo = red(lrc, pr.c_lo) * rsc, hi = red(lrc, pr.c_lo + pr.off) * rsc;
         if (a.q_norm_w != nullptr) {
           // RMSNorm of a query / key head over its d features: the half / 4 consecutive lanes that hold
           // the head add their sums of squares (every lane takes part: no early exit above)
@@ -131,14 +183,15 @@ struct TileEpilogue {
         }
       }
     } else if constexpr (EPI == EPI_SWIGLU) {
-      // every 128 columns of the product: 64 gate columns, then the matching 64 up columns
-      constexpr int FQ = TN / 8;   // groups of 4 features per row
+      // every 128 columns of the product (all of them where the tile is narrower): the gate columns,
+      // then as many matching up columns
+      constexpr int FQ = TN / 8, H = TN < 128 ? TN / 2 : 64;   // groups of 4 features per row, gate columns in a row
       for (int t = tid; t < RB * FQ; t += NT) {
         const int lr = t / FQ, f = (t % FQ) * 4, r = row0 + lr;
-        const int feat = tile * (TN / 2) + f, c = (f >> 6) * 128 + (f & 63);
+        const int feat = tile * (TN / 2) + f, c = (f / H) * 2 * H + f % H;
         if (r >= a.rows || feat >= a.ffn) continue;
         const float rsc = rs[lr];
-        const f32x4 gt = red(lr, c) * rsc, up = red(lr, c + 64) * rsc;
+        const f32x4 gt = red(lr, c) * rsc, up = red(lr, c + H) * rsc;
         bf16x4 hi, lo;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

@@ -44,7 +44,7 @@
 
 namespace ts {
 
-template <int MB, int KC, int EPI, bool RAGGED, int DEPTH>
+template <int MB, int KC, int EPI, int DEPTH>
 __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
   constexpr int KB = KC / 64;                 // 64-deep k blocks per chunk
   constexpr int FRAGS = KB * 4 * MB * 2;      // 1 KB operand fragments per chunk (operand layout)
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
   __shared__ int s_last;
   __shared__ float s_rs[kMaxRows];   // 1/rms of the rows of the matmul's input
-  __shared__ float s_rsp[4 * kMaxRows];
+  __shared__ float s_tmp[4 * kMaxRows];
 
   const int tid = threadIdx.x, lane = tid & 63;
   // scalar: what is selected by it (this wavefront's weight segment) is then fetched with scalar
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
   // Workgroups that run side by side start at different depths of their k range (and wrap
   // around), so that they do not all walk the memory channels in lockstep.  The order of the
   // additions is still a fixed function of (tile, split).
-  const int rot = RAGGED ? 0 : (int)((blockIdx.x * 11u + blockIdx.y * 5u) % (unsigned)n_chunks);
+  const int rot = (int)((blockIdx.x * 11u + blockIdx.y * 5u) % (unsigned)n_chunks);
   auto rc = [&](int c) { const int cc = c + rot; return cc >= n_chunks ? cc - n_chunks : cc; };
 
   // ---- this wavefront's packed sub-tile.  Plain tiles: 4 consecutive sub-tiles of the
@@ -98,10 +98,20 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
   // wavefront copies fragments wave*XV .. wave*XV + XV-1, 16 bytes per lane each
   const bf16 *xg = (const bf16 *)a.x + ((size_t)(k_begin >> 6) * 4 * MB * 2 + wave * XV) * 512 + lane * 8;
 
-  // 1/rms of every row of the matmul's INPUT (used by the epilogue): the loads go out here, ahead
-  // of the stream, and are consumed after it.
+  // 1/rms of every row of the matmul's INPUT (used by the epilogue).  With the deep ring, requested ahead
+  // of everything else and finished with the prologue: up to 128 entries a row come in one round trip (a
+  // residual product in 32-column tiles leaves one per 32 columns); fetched after the stream they cost
+  // 4 us.  With the shallow one, for short reductions over few columns, requested here and finished after
+  // the stream: the barrier in the prologue would cost them 0.5 us each.
+  constexpr bool EARLY = DEPTH > 2;
+  RowScale<256, MB * 32, 16 * MB> scale;
   float rs_in[(MB + 1) / 2][8];
-  rstd_load<256, MB>(a, rs_in);
+  if constexpr (EARLY) {
+    scale.issue(a, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  } else {
+    rstd_load<256, MB>(a, rs_in);
+  }
 
   f32x16 acc[MB];
 #pragma unroll
@@ -124,32 +134,27 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
   // sched_barrier pins the load issue points; the compiler would otherwise sink every load to
   // just before its first use and expose the whole memory latency once per chunk.
   bf16x8 w[DEPTH][KB][4];
-  uint4 xr[XV];
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // native vector: stays in registers
+  // One register stage of the panel.  Loads come back in order, so the wait for it is also one for every
+  // weight load before it; a second stage (a chunk more of weights in flight) is slower all the same:
+  // 44.2 -> 48.9 us on the 24576 x 4096 product over 60 rows, 16.8 -> 18.6 on 6144 x 4096 over one.
+  u32x4 xr[XV];
 
   auto load_w_block = [&](int set, int c, int kb) {
     const int k = rc(c) * KC + kb * 64;
-    const bf16 *p = wrow + (size_t)((!RAGGED || k < klen) ? (k >> 6) : 0) * 2048;
+    const bf16 *p = wrow + (size_t)(k >> 6) * 2048;
 #pragma unroll
     for (int j = 0; j < 4; ++j) w[set][kb][j] = __builtin_nontemporal_load((const bf16x8 *)(p + 512 * j));
   };
   auto load_x = [&](int c) {
-    const bool ok = !RAGGED || (c * KC < klen);
-    const bf16 *src = xg + (size_t)(ok ? rc(c) : 0) * FRAGS * 512;
+    const bf16 *src = xg + (size_t)rc(c) * FRAGS * 512;
 #pragma unroll
-    for (int i = 0; i < XV; ++i) {
-      uint4 v = *(const uint4 *)(src + i * 512);
-      if (RAGGED) {
-        // fragment (wave*XV + i) belongs to k block kb of the chunk; blocks past the split are zero
-        const int kb = (wave * XV + i) / (4 * MB * 2);
-        if (!ok || c * KC + kb * 64 >= klen) v = make_uint4(0, 0, 0, 0);
-      }
-      xr[i] = v;
-    }
+    for (int i = 0; i < XV; ++i) xr[i] = *(const u32x4 *)(src + i * 512);
   };
-  auto store_x = [&](int buf) {
+  auto store_x = [&](int buf) {    // -> LDS stage buf (chunk parity)
     unsigned char *dst = lds + buf * BUF + (wave * XV) * 1024 + lane * 16;
 #pragma unroll
-    for (int i = 0; i < XV; ++i) *(uint4 *)(dst + i * 1024) = xr[i];
+    for (int i = 0; i < XV; ++i) *(u32x4 *)(dst + i * 1024) = xr[i];
   };
   // One chunk of MFMAs, software pipelined: step t = (k block, j) needs four A fragments
   // (row block 0/1 x hi/lo); they are read from LDS two steps ahead into a 2-slot register ring,
@@ -185,60 +190,45 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
     }
   };
 
-  if (RAGGED) {
-    // simple one-chunk-ahead loop with bounds logic (odd shapes only)
-    load_x(0);
+  // n_chunks is a multiple of DEPTH (DEPTH even).  The prologue issues its loads in the order
+  // the steady state does (X of a chunk before the W refill of the same step), so the wait
+  // counts merged at the loop head are the steady-state ones.
+  load_x(0);
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) load_w_block(0, 0, kb);
-    store_x(0);
-    __syncthreads();
-    for (int c = 0; c + 1 < n_chunks; ++c) {
-      load_x(c + 1);
-      compute_chunk(0, c & 1, c + 1, true);
-      store_x((c + 1) & 1);
-      __syncthreads();
-    }
-    compute_chunk(0, (n_chunks - 1) & 1, 0, false);
-  } else {
-    // n_chunks is a multiple of DEPTH (DEPTH even).  The prologue issues its loads in the order
-    // the steady state does (X of a chunk before the W refill of the same step), so the wait
-    // counts merged at the loop head are the steady-state ones.
-    load_x(0);
+  for (int kb = 0; kb < KB; ++kb) load_w_block(0, 0, kb);
+  __builtin_amdgcn_sched_barrier(0);
+  store_x(0);
+  load_x(1);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) load_w_block(0, 0, kb);
-    __builtin_amdgcn_sched_barrier(0);
-    store_x(0);
-    load_x(1);
-    __builtin_amdgcn_sched_barrier(0);
+  for (int d = 1; d < DEPTH; ++d)
 #pragma unroll
-    for (int d = 1; d < DEPTH; ++d)
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) load_w_block(d, d, kb);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-    int c0 = 0;
-    for (; c0 + DEPTH < n_chunks; c0 += DEPTH) {
-#pragma unroll
-      for (int d = 0; d < DEPTH; ++d) {
-        store_x((d + 1) & 1);                       // chunk c0+d+1
-        load_x(min(c0 + d + 2, n_chunks - 1));      // clamped, never a branch
-        __builtin_amdgcn_sched_barrier(0);
-        compute_chunk(d, d & 1, c0 + d + DEPTH, true);
-        __syncthreads();
-      }
-    }
-    // last DEPTH chunks: nothing left to fetch from W
+    for (int kb = 0; kb < KB; ++kb) load_w_block(d, d, kb);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (EARLY) scale.finish(a, 0, s_tmp, s_rs);   // ends with a barrier
+  else __syncthreads();
+  int c0 = 0;
+  for (; c0 + DEPTH < n_chunks; c0 += DEPTH) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
-      if (d + 1 < DEPTH) store_x((d + 1) & 1);
-      if (d + 2 < DEPTH) load_x(c0 + d + 2);
+      store_x((d + 1) & 1);                                    // chunk c0+d+1
+      load_x(min(c0 + d + 2, n_chunks - 1));   // clamped, never a branch
       __builtin_amdgcn_sched_barrier(0);
-      compute_chunk(d, d & 1, 0, false);
-      if (d + 1 < DEPTH) __syncthreads();
+      compute_chunk(d, d & 1, c0 + d + DEPTH, true);
+      __syncthreads();
     }
   }
+  // last DEPTH chunks: nothing left to fetch from W
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) {
+    if (d + 1 < DEPTH) store_x((d + 1) & 1);
+    if (d + 2 < DEPTH) load_x(c0 + d + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    compute_chunk(d, d & 1, 0, false);
+    if (d + 1 < DEPTH) __syncthreads();
+  }
 
-  rstd_finish<256, MB>(a, rs_in, s_rsp, s_rs);
+  if constexpr (!EARLY) rstd_finish<256, MB>(a, rs_in, s_tmp, s_rs);
   __syncthreads();   // every wavefront is done reading the last X stage
   gemm_epilogue<MB, EPI, 4>(a, reinterpret_cast<f32x16(&)[1][MB]>(acc), lds, &s_last, s_rs, tile, split);
 }
@@ -275,11 +265,9 @@ static void dispatch(hipStream_t st, const GemmArgs &a) {
 #define TS_LAUNCH(MB_, KC_)                                                                   \
   do {                                                                                        \
     if (a.k_per_split % (4 * KC_) == 0 && a.k % (4 * KC_) == 0)                               \
-      hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, false, 4>), grid, block, 0, st, a);      \
-    else if (a.k_per_split % (2 * KC_) == 0 && a.k % (2 * KC_) == 0)                          \
-      hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, false, 2>), grid, block, 0, st, a);      \
+      hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, 4>), grid, block, 0, st, a);             \
     else                                                                                      \
-      hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, true, 1>), grid, block, 0, st, a);       \
+      hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, 2>), grid, block, 0, st, a);             \
   } while (0)
   switch (a.rows_pad) {
     case 32: TS_LAUNCH(1, 256); break;
@@ -293,7 +281,6 @@ void launch_gemm_bf16(hipStream_t st, const GemmArgs &a) {
     case EPI_QKV: dispatch<EPI_QKV>(st, a); break;
     case EPI_RESID: dispatch<EPI_RESID>(st, a); break;
     case EPI_SWIGLU: dispatch<EPI_SWIGLU>(st, a); break;
-    case EPI_PLAIN: dispatch<EPI_PLAIN>(st, a); break;
     default: dispatch<EPI_HEAD>(st, a); break;
   }
 }

@@ -21,8 +21,6 @@
 // over the whole chip, adds them up and runs the epilogue.  At 256 rows a tile's partials are a
 // megabyte: one workgroup reading them serially after the last arrival, as the narrow kernels do,
 // took 15 - 20 us of a 77 us projection.
-#include <type_traits>
-
 #include "gemm_tile.hpp"
 
 namespace ts {
@@ -30,45 +28,6 @@ namespace ts {
 namespace {
 
 constexpr int kWideRows = 128;      // rows per workgroup
-
-template <int N>
-using IC = std::integral_constant<int, N>;
-
-// Sums of squares of ROWS rows from the per-(tile, row) entries, in two parts: issue() requests the
-// first entries, finish() adds everything up (ascending tiles within a thread, threads in ascending
-// order) and leaves 1/rms in s_rs[0 .. ROWS).  s_tmp: NT floats.  Ends with a barrier.
-template <int NT, int ROWS>
-struct RowScale {
-  static constexpr int Q = NT / ROWS, PRE = 16;   // threads per row; entries requested ahead
-  float x[PRE];
-  __device__ __forceinline__ void issue(const GemmArgs &a, int row0) {
-    if (a.ss_in == nullptr) return;
-    const int r = min(row0 + (int)threadIdx.x % ROWS, a.rows_pad - 1), q = threadIdx.x / ROWS;
-#pragma unroll
-    for (int u = 0; u < PRE; ++u) x[u] = a.ss_in[(size_t)min(q + Q * u, a.ss_tiles - 1) * a.rows_pad + r];
-  }
-  __device__ __forceinline__ void finish(const GemmArgs &a, int row0, float *s_tmp, float *s_rs) {
-    const int tid = threadIdx.x;
-    if (a.ss_in != nullptr) {
-      const int r = min(row0 + tid % ROWS, a.rows_pad - 1), q = tid / ROWS;
-      float v = 0.f;
-#pragma unroll
-      for (int u = 0; u < PRE; ++u) v += (q + Q * u < a.ss_tiles) ? x[u] : 0.f;
-      for (int t = q + Q * PRE; t < a.ss_tiles; t += Q) v += a.ss_in[(size_t)t * a.rows_pad + r];
-      s_tmp[tid] = v;
-    }
-    __syncthreads();
-    if (tid < ROWS) {
-      float ss = 0.f;
-      if (a.ss_in != nullptr) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) ss += s_tmp[q * ROWS + tid];
-      }
-      s_rs[tid] = a.ss_in != nullptr ? 1.0f / sqrtf(ss / (float)a.k + a.eps) : 1.0f;
-    }
-    __syncthreads();
-  }
-};
 
 }  // namespace
 

@@ -12,7 +12,19 @@ pytestmark = pytest.mark.gpu
 
 TB = SHAPES["tiny_bf16"].with_(n_layers=1, vocab=1000)
 CASES = [
-    # (batch, nodes, shape): more than 64 rows
+    # (batch, nodes, shape): up to 64 rows; fewer 64-deep blocks than wavefronts, k that is no whole number of
+    # chunks, heads of 64 and 128 with and without their own norm, tiles that end past the last column
+    ("row1_one_block", 1, 1, TB.with_(hidden=64, ffn=64, head_dim=64, n_q_heads=1, n_kv_heads=1, lm_head_std=0.8)),
+    ("rows23_ragged_k", 1, 23, TB.with_(hidden=192, ffn=320, n_q_heads=3, n_kv_heads=3, vocab=777, lm_head_std=0.5)),
+    ("rows32_ragged_k_qk_norm", 2, 16, TB.with_(hidden=320, ffn=448, n_q_heads=3, n_kv_heads=1, qk_norm=True,
+                                                lm_head_std=0.4)),
+    ("rows33_head64_qk_norm", 3, 11, TB.with_(hidden=832, ffn=1088, head_dim=64, n_q_heads=6, n_kv_heads=2,
+                                              qk_norm=True, vocab=513, lm_head_std=0.3)),
+    ("rows46_half_heads_many_splits", 2, 23, TB.with_(hidden=1472, ffn=4032, n_q_heads=8, lm_head_std=0.2)),
+    ("rows64_whole_heads", 1, 64, TB.with_(hidden=1344, ffn=1024, n_q_heads=8, qk_norm=True, vocab=129,
+                                           lm_head_std=0.2)),
+    ("rows64_chunks", 4, 16, TB.with_(hidden=2048, ffn=2560, n_q_heads=16, n_kv_heads=8, lm_head_std=0.15)),
+    # more than 64 rows
     ("rows65_one_block", 1, 65, TB.with_(hidden=64, ffn=64, head_dim=64, n_q_heads=1, n_kv_heads=1, lm_head_std=0.8)),
     ("rows96_two_blocks", 3, 32, TB.with_(hidden=128, ffn=128, lm_head_std=0.6)),
     ("rows128_three_blocks_ragged", 2, 64, TB.with_(hidden=192, ffn=320, head_dim=64, n_q_heads=6, n_kv_heads=3,
