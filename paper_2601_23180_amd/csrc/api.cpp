@@ -249,7 +249,7 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
   // sums of squares per (tile, row): two buffers, a matmul reads its producer's while writing its own
   L.ss_part = take(2 * sizeof(float) * (size_t)ss_tiles_of(c.hidden, 32) * rp);   // sized for the narrowest tile
   const int group = c.n_q_heads / c.n_kv_heads;
-  const size_t prow = f32 ? 0 : (size_t)batch * c.n_kv_heads * kMaxAttnSplits * group * max_nodes;
+  const size_t prow = f32 ? 0 : (size_t)batch * c.n_kv_heads * (kMaxAttnSplits + (max_nodes + 31) / 32) * group * max_nodes;
   L.attn_o = take(sizeof(float) * prow * c.head_dim);
   L.attn_m = take(sizeof(float) * prow);
   L.attn_l = take(sizeof(float) * prow);
@@ -670,20 +670,39 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
     // otherwise outweigh the K/V it reads.  A tree of more than 128 query rows per kv head over a
     // long context takes 256-row workgroups (eight waves, 64-key tiles), which stage every K/V
     // tile once instead of once per 128-row group; on shorter contexts the two 128-row groups,
-    // each with its own CU, finish sooner.
+    // each with its own CU, finish sooner.  At most 32 (64) rows over up to 128 (64) keys a CU take
+    // k_attn_few (9 nodes, 16 heads on 8: 1000 keys 11.4 -> 7.7 us, 4096 keys 12.3 -> 10.2; 30 nodes, 2048
+    // keys 12.8 -> 12.0); over more its scattered reads cost more than staging (8192 keys: 15.2 / 15.1 us
+    // for 9 nodes, 17.3 / 23.8 for 30; four sequences of 2048 keys 14.6 / 17.1).
     const int group = c.n_q_heads / c.n_kv_heads;
     const int p_rows = group * n_nodes;
-    at.rows_per_wg = (p_rows > 128 && max_keys >= kAttnWideMinKeys) ? 256 : 128;
+    at.rows_per_wg = p_rows > 128 && max_keys >= kAttnWideMinKeys ? 256 : 128;
+    if (p_rows <= 32 ? B * c.n_kv_heads * max_keys <= 32768 : p_rows <= 64 && B * c.n_kv_heads * max_keys <= 16384)
+      at.rows_per_wg = p_rows <= 32 ? 32 : 64;
     at.n_row_groups = (p_rows + at.rows_per_wg - 1) / at.rows_per_wg;
-    const int per_split = B * c.n_kv_heads * at.n_row_groups;
-    int want = (256 + per_split - 1) / per_split;
+    const int per_split = B * c.n_kv_heads * at.n_row_groups, n_draft = (n_nodes + 31) / 32;
+    int want = (256 + per_split - 1) / per_split, unit = kv->page_table ? 128 : 64, least = 256;
+    if (at.rows_per_wg <= 64) {
+      // 128 keys at least, two workgroups to a CU; up to 16 splits, which the merge fetches in one round
+      // trip, more only when a split would grow past 512 keys
+      unit = least = 128;
+      const int room = 512 / per_split - n_draft;
+      want = max_keys > 16 * 512 ? (max_keys + 511) / 512 : 16;
+      if (want > room) want = room;
+      if (want < 1) want = 1;
+    }
     if (want > kMaxAttnSplits) want = kMaxAttnSplits;
     // (a paged cache: every split starts at a multiple of the largest key tile, so that no tile straddles two pages)
-    int kps = (int)align_up((size_t)((max_keys + want - 1) / want), kv->page_table ? 128 : 64);
-    if (kps < 256) kps = 256;
+    int kps = (int)align_up((size_t)((max_keys + want - 1) / want), unit);
+    if (kps < least) kps = least;
     at.keys_per_split = kps;
     at.n_splits = (max_keys + kps - 1) / kps;
     if (at.n_splits < 1) at.n_splits = 1;
+    // The draft nodes: by workgroups of their own where the context leaves CUs free, else in the merge
+    // kernel (60 nodes, 32 heads, 4096 keys, whose context takes every CU: 17.6 + 10.2 us; with a second
+    // round of workgroups 27.4 + 6.3, with fewer and longer splits no better).
+    at.draft_mode = at.rows_per_wg <= 64 || (at.n_splits + n_draft) * per_split <= 256 ? kDraftOwnGroups : kDraftInMerge;
+    at.n_draft = at.draft_mode == kDraftInMerge ? 0 : n_draft;
   }
   at.part_o = (float *)(ws + L.attn_o);
   at.part_m = (float *)(ws + L.attn_m);

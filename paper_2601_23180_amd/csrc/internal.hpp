@@ -171,10 +171,11 @@ bool launch_layer_bf16(hipStream_t st, const LayerArgs &la, int grid);
 void launch_wait_probe(hipStream_t st, int32_t *counter, int expect, unsigned long long limit,
                        int32_t *abort_word, int32_t *status);
 
+enum { kDraftInMerge = 0, kDraftOwnGroups = 1 };
 struct AttnArgs {
   const void *q;        // fp32 path: [rows_pad, nq*d] fp32 queries; bf16 path: bf16 hi panel, lo q_panel later
   size_t q_panel;
-  int32_t rows_per_wg;  // query rows (group * n_nodes of them per kv head) one workgroup covers: 128 or 256
+  int32_t rows_per_wg;  // query rows (group * n_nodes of them per kv head) one workgroup covers: 32, 64 (k_attn_few), 128 or 256
   int32_t n_row_groups; // ceil(group * n_nodes / rows_per_wg)
   const void *k_cache;  // this layer's K and V^T, addressed through `kv`
   const void *v_cache;
@@ -184,10 +185,12 @@ struct AttnArgs {
   CtxLens ctx;
   int32_t batch, n_nodes, n_q_heads, n_kv_heads, head_dim;
   int32_t keys_per_split;   // multiple of 64
-  int32_t n_splits;
-  float *part_o;        // [B][nkv][n_splits][group*M][d]  unnormalised
-  float *part_m;        // [B][nkv][n_splits][group*M]     running max
-  float *part_l;        // [B][nkv][n_splits][group*M]     sum of exp
+  int32_t n_splits;         // of the context
+  int32_t draft_mode;       // who evaluates the draft nodes
+  int32_t n_draft;          // blocks of 32 draft nodes that leave partials of their own (kDraftInMerge: 0)
+  float *part_o;        // [B][nkv][n_splits + n_draft][group*M][d]  unnormalised
+  float *part_m;        // [B][nkv][n_splits + n_draft][group*M]     running max
+  float *part_l;        // [B][nkv][n_splits + n_draft][group*M]     sum of exp
   void *out;            // fp32 path: [rows_pad, nq*d] fp32; bf16 path: bf16 hi/lo panels
   size_t out_panel;     // panel stride (elements) of out
 };

@@ -4,13 +4,12 @@
 // root path (bit j of anc[i]).  K is cached [slot][d]; V is cached transposed [d][slot] so that
 // both products read matrix-core operands with 16-byte loads.
 //
-// bf16 path, two parts.  (1) Context: one workgroup per (context split, kv head, sequence) streams
-// the cached K/V — no mask is needed there, every context key is visible to every node.
-// (2) Draft nodes: at most 64 keys, of which a node sees only its ancestors; the merge kernel
-// evaluates them in fp32 straight from this pass's unrounded q/k/v projections (the cache gets
-// bf16 copies for later rounds, but the pass itself never reads them back) and folds them in as
-// one more softmax partial.
-// A merge kernel combines the splits in ascending order.
+// bf16 path.  Context: one workgroup per (context split, kv head, sequence) streams the cached K/V — no
+// mask is needed there, every context key is visible to every node.  The draft nodes (masked to each
+// row's root path) are taken in fp32 on this pass's unrounded q/k/v projections: the cache gets bf16
+// copies for later rounds, but the pass itself never reads them back.  Where they are evaluated is up to
+// the host (AttnArgs::draft_mode): in blocks of 32 by workgroups of the same launch, or by the merge
+// kernel, which combines all partials of a row in ascending order.
 #include "device_util.hpp"
 
 namespace ts {
@@ -80,13 +79,127 @@ struct AttnLds {
   static constexpr int kBuf = kBytesK + kBytesV;  // one stage
 };
 
+// Softmax partial of 32 query rows (one wavefront) over the draft nodes 32 kb .. 32 kb + 31: S^T = K Q^T
+// and O^T = V^T P^T with fp32 matrix instructions (32x32x2), operands straight from the projections.
+// Lane (ln, g) holds features g D/2 .. of key / query row ln for the first product; the scores come out
+// with keys 8q + 4g + r in register 4q + r, which is the order in which the second product takes them.
+// 128 instructions of 64 cycles, 3.5 us, beside context workgroups that run longer.  Evaluated by the
+// merge kernel, where every row fetches its ancestors' keys and values for itself, a chain of 128 nodes
+// with 32 heads takes 44 us a layer; the plain merge takes 8.4, the launch before it 18.6 instead of 16.1.
+// s_p: 32 x 32 floats of LDS of this wavefront.
+template <int D>
+__device__ void draft_partial(const AttnArgs &a, int kb, int kvh, int b, int row_block, size_t part_base, float *s_p) {
+  const int lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
+  const int M = a.n_nodes, group = a.n_q_heads / a.n_kv_heads, p_rows = group * M;
+  const int prow = row_block * 32 + ln;
+  if (row_block * 32 >= p_rows) return;   // wave-uniform
+  const int pc = min(prow, p_rows - 1), al = pc / M, node = pc - al * M;
+  const AncMask mask = a.anc[b * M + node];
+  const uint32_t mine = (uint32_t)((kb < 2 ? mask.lo : mask.hi) >> (32 * (kb & 1)));   // ancestors in this block
+  const size_t pi = part_base * p_rows + prow;
+  if (__builtin_amdgcn_ballot_w64(mine != 0) == 0) {   // none for any row
+    if (prow < p_rows && g == 0) { a.part_m[pi] = -INFINITY; a.part_l[pi] = 0.f; }
+    return;
+  }
+  const size_t n_total = (size_t)(a.n_q_heads + 2 * a.n_kv_heads) * D;
+  const float *base = a.qkv + (size_t)b * M * n_total;
+  const float *kp = base + min(kb * 32 + ln, M - 1) * n_total + (size_t)(a.n_q_heads + kvh) * D + g * (D / 2);
+  const float *qp = base + node * n_total + (size_t)(kvh * group + al) * D + g * (D / 2);
+  f32x16 s0, s1;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) s0[e] = s1[e] = 0.f;
+  {
+    f32x4 kv[D / 8], qv[D / 8];
+#pragma unroll
+    for (int t = 0; t < D / 8; ++t) { kv[t] = *(const f32x4 *)(kp + 4 * t); qv[t] = *(const f32x4 *)(qp + 4 * t); }
+#pragma unroll
+    for (int t = 0; t < D / 8; ++t) {
+      s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[t][0], qv[t][0], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[t][1], qv[t][1], s1, 0, 0, 0);
+      s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[t][2], qv[t][2], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[t][3], qv[t][3], s1, 0, 0, 0);
+    }
+  }
+  const float *vp = base + (size_t)(a.n_q_heads + a.n_kv_heads + kvh) * D;
+  float v[16][D / 32];   // all values in one round trip, behind the softmax
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+      v[e][db] = vp[min(kb * 32 + 8 * (e >> 2) + 4 * g + (e & 3), M - 1) * n_total + db * 32 + ln];
+  __builtin_amdgcn_sched_barrier(0);
+  const float scale = 1.44269504088896f / sqrtf((float)D);
+  float p[16], m = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int key = 8 * (e >> 2) + 4 * g + (e & 3);
+    p[e] = (mine >> key) & 1u ? (s0[e] + s1[e]) * scale : -INFINITY;
+    m = fmaxf(m, p[e]);
+  }
+  m = fmaxf(m, __shfl_xor(m, 32, 64));
+  const float m_safe = m == -INFINITY ? 0.f : m;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    p[e] = __builtin_amdgcn_exp2f(p[e] - m_safe);   // 0 for other branches
+    l += p[e];
+  }
+  l += __shfl_xor(l, 32, 64);
+  f32x16 o[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
+  float finite = 0.f;   // stays 0 while every value is finite
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) {
+      finite = __builtin_fmaf(v[e][db], 0.f, finite);
+      o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[e][db], p[e], o[db], 0, 0, 0);
+    }
+  if (__builtin_amdgcn_ballot_w64(finite != 0.f) != 0) {
+    // an infinity or NaN among the values: a weight of 0 would carry it into rows of other branches.
+    // Row by row over the ancestors only.
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s_p[(8 * (e >> 2) + 4 * g + (e & 3)) * 32 + ln] = p[e];
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
+#pragma unroll 1
+    for (int k = 0; k < 32; ++k) {
+      if (!((mine >> k) & 1u)) continue;
+      const float w = s_p[k * 32 + ln];
+      const float *vr = vp + (kb * 32 + k) * n_total + 4 * g;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[db][e] += w * vr[db * 32 + 8 * (e >> 2) + (e & 3)];
+    }
+  }
+  if (prow >= p_rows) return;
+  if (g == 0) {
+    a.part_m[pi] = m * 0.693147180559945f;
+    a.part_l[pi] = l;
+  }
+  float *out = a.part_o + pi * D;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *(f32x4 *)(out + db * 32 + 8 * q + 4 * g) = f32x4{o[db][4 * q], o[db][4 * q + 1], o[db][4 * q + 2], o[db][4 * q + 3]};
+}
+
 // NW waves, each owning RBW blocks of 32 query rows: a workgroup covers 32 * NW * RBW rows.
 // <KT 128, NW 4>: one workgroup per CU.  <KT 64, NW 8>: 256 rows share every staged K/V tile
 // (trees of more than 128 rows read the cache once, not twice) and two waves per SIMD overlap
 // one another's softmax arithmetic and matrix work.
+// DRAFT: some workgroups (splits from n_splits on) take a block of draft nodes each instead.
 // PAGED: the cache is in pages of kKvPage slots (a multiple of KT, and every split starts at a
 // multiple of KT, so a tile never straddles two pages): one scalar page lookup per tile.
-template <int D, int RBW, int KT, int NW, bool PAGED>
+template <int D, int RBW, int KT, int NW, bool PAGED, bool DRAFT>
 __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
   using L = AttnLds<D, KT>;
   constexpr int NT = 64 * NW;
@@ -99,10 +212,18 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
   const int M = a.n_nodes, group = a.n_q_heads / a.n_kv_heads;
   const int p_rows = group * M;
   const int ctx = a.ctx.v[b];
-  const int n_keys = ctx;            // context only; the draft nodes are handled by the merge kernel
+  const int n_keys = ctx;            // context only
   const int k_begin = split * a.keys_per_split;
   const int k_end = min(n_keys, k_begin + a.keys_per_split);
-  const size_t part_base = ((size_t)b * a.n_kv_heads + kvh) * a.n_splits + split;
+  const size_t part_base = ((size_t)b * a.n_kv_heads + kvh) * (a.n_splits + a.n_draft) + split;
+  if constexpr (DRAFT) {
+    if (split >= a.n_splits) {
+#pragma unroll
+      for (int i = 0; i < RBW; ++i)
+        draft_partial<D>(a, split - a.n_splits, kvh, b, rg * NW * RBW + wave + NW * i, part_base, (float *)lds + wave * 1024);
+      return;
+    }
+  }
 
   // ---- this lane's query rows
   int prow[RBW];
@@ -116,7 +237,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
         a.part_m[part_base * p_rows + prow[i]] = -INFINITY;
         a.part_l[part_base * p_rows + prow[i]] = 0.f;
       }
-    return;
+      return;
   }
 
   static_assert(kKvPage % KT == 0, "a tile must not straddle pages");
@@ -341,7 +462,238 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
   }
 }
 
-// Combine the context splits of one (row, kv head) — all `group` query heads that share the kv
+// Context (and draft blocks) for at most 64 query rows per kv head: chains, short trees, single tokens.
+// The kernel above would leave three of its four wavefronts without a row.  Here RB wavefronts side by
+// side hold the row blocks and the KG = 4 / RB groups of them take 32 keys each of every 32 KG keys,
+// operands straight from the cache to registers (a wavefront's keys are its own, so LDS would save
+// nothing); the groups' partials are merged through LDS at the end.  A tile's registers are requested
+// again as soon as it has been used.  What bounds it is one chain of memory round trips: rows and first
+// keys, partials out.  FEWFIG
+template <int D, int RB, bool PAGED>
+__global__ __launch_bounds__(256, 2) void k_attn_few(AttnArgs a) {
+  constexpr int KG = 4 / RB, LD = 33, FW = D / KG / 2;   // key groups; LDS row; features per thread of the merge
+  __shared__ __attribute__((aligned(16))) float s_o[4 * D * LD];
+  __shared__ float s_m[KG][RB * 32], s_l[KG][RB * 32];
+  const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+  const int lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), rb = wave % RB, kg = wave / RB;
+  const int M = a.n_nodes, group = a.n_q_heads / a.n_kv_heads, p_rows = group * M;
+  const size_t part_base = ((size_t)b * a.n_kv_heads + kvh) * (a.n_splits + a.n_draft) + split;
+  if (split >= a.n_splits) {
+    if (wave < RB) draft_partial<D>(a, split - a.n_splits, kvh, b, wave, part_base, s_o + wave * 1024);
+    return;
+  }
+  const int ctx = a.ctx.v[b], k_begin = split * a.keys_per_split, k_end = min(ctx, k_begin + a.keys_per_split);
+  const int prow = rb * 32 + ln;
+  if (k_begin >= k_end) {   // empty split: neutral partial
+    if (kg == 0 && g == 0 && prow < p_rows) {
+      a.part_m[part_base * p_rows + prow] = -INFINITY;
+      a.part_l[part_base * p_rows + prow] = 0.f;
+    }
+    return;
+  }
+  const int cap = PAGED ? kKvPage : a.kv.capacity;   // slots behind kc / vc, and the V^T row stride
+  // Score register e of lane (ln, g) is row 8 (e / 4) + 4 g + e % 4 of S^T.  Row i gets the key that makes
+  // a lane's keys of one second-product step (16 u + 8 g ..) adjacent: V^T then comes in 16-byte pieces.
+  auto key_of = [](int i) { return (i & 0x13) | (i & 4) << 1 | (i & 8) >> 1; };   // bits 2 and 3 swapped
+  auto key_at = [&](int e) { return 16 * (e >> 3) + 8 * g + (e & 7); };
+  bf16x8 kf[D / 16], vf[D / 32][2];
+  // the keys k0 .. k0 + 31; slots past the context hold no token: clamped into the cache here, masked below
+  auto at = [&](const void *cache, int k0, int &slot) {
+    const bf16 *c = (const bf16 *)cache;
+    if (PAGED) {
+      slot = k0 % kKvPage;
+      return c + ((size_t)a.kv.page_of(b, k0) * a.n_kv_heads + kvh) * kKvPage * D;
+    }
+    slot = k0;
+    return c + ((size_t)b * a.n_kv_heads + kvh) * a.kv.capacity * D;
+  };
+  auto load_k = [&](int k0) {
+    int slot;
+    const bf16 *kr = at(a.k_cache, k0, slot);
+    kr += (size_t)min(slot + key_of(ln), cap - 1) * D + 8 * g;
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) kf[t] = *(const bf16x8 *)(kr + 16 * t);
+  };
+  auto load_v = [&](int k0) {
+    int slot;
+    const bf16 *vr = at(a.v_cache, k0, slot) + (size_t)ln * cap;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) vf[db][u] = *(const bf16x8 *)(vr + (size_t)db * 32 * cap + min(slot + 16 * u + 8 * g, cap - 8));
+  };
+  // past the end a group reads the split's last keys again and masks all of them
+  auto clamped = [&](int k0) { return min(k0, (k_end - 1) & ~31); };
+  const int first = k_begin + kg * 32;
+  load_k(clamped(first));
+  bf16x8 qf[D / 16], ql[D / 16];
+  {
+    const int pc = min(prow, p_rows - 1), al = pc / M, r = b * M + pc - al * M;
+    const bf16 *q = (const bf16 *)a.q + (size_t)r * a.n_q_heads * D + (size_t)(kvh * group + al) * D + 8 * g;
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) {
+      qf[t] = *(const bf16x8 *)(q + 16 * t);
+      ql[t] = *(const bf16x8 *)(q + a.q_panel + 16 * t);
+    }
+  }
+  load_v(clamped(first));
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 o[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
+  for (int k0 = first; k0 < k_end; k0 += 32 * KG) {
+    f32x16 sh, sl;   // high and low part of the queries apart: two chains of matrix instructions
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sh[e] = sl[e] = 0.f;
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) {
+      sh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], sh, 0, 0, 0);
+      sl = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], ql[t], sl, 0, 0, 0);
+    }
+    load_k(clamped(k0 + 32 * KG));
+    float s[16], m_new = m_run;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[e] = sh[e] + sl[e];
+    if (k0 + 32 > k_end) {   // wave-uniform: the context ends in here
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (k0 + key_at(e) >= k_end) s[e] = -INFINITY;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (k0 + key_at(e) >= k_end) vf[db][e >> 3][e & 7] = (bf16)0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) m_new = fmaxf(m_new, s[e]);
+    m_new = fmaxf(m_new, __shfl_xor(m_new, 32, 64));
+    const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+    m_run = m_new;
+    float psum = 0.f;
+    bf16x8 ph[2], pl[2];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const float p = __builtin_amdgcn_exp2f(s[e] - m_safe);
+      psum += p;
+      ph[e >> 3][e & 7] = (bf16)p;
+      pl[e >> 3][e & 7] = (bf16)(p - (float)ph[e >> 3][e & 7]);
+    }
+    l_run = l_run * alpha + psum;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][u], ph[u], o[db], 0, 0, 0);
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][u], pl[u], o[db], 0, 0, 0);
+    }
+    load_v(clamped(k0 + 32 * KG));
+  }
+
+  // ---- merge the key groups: O^T [wave][feature][row] through LDS, a thread then takes FW features of a row
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (g == 0) { s_m[kg][prow] = m_run; s_l[kg][prow] = l_run; }
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s_o[(wave * D + db * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * LD + ln] = o[db][e];
+  __syncthreads();
+  if (prow >= p_rows) return;
+  float m = -INFINITY, l = 0.f, w[KG];
+#pragma unroll
+  for (int i = 0; i < KG; ++i) m = fmaxf(m, s_m[i][prow]);
+  const float m_safe = m == -INFINITY ? 0.f : m;
+#pragma unroll
+  for (int i = 0; i < KG; ++i) {
+    w[i] = __builtin_amdgcn_exp2f(s_m[i][prow] - m_safe);   // 0 for a group without keys
+    l += s_l[i][prow] * w[i];
+  }
+  const size_t pi = part_base * p_rows + prow;
+  if (kg == 0 && g == 0) {
+    a.part_m[pi] = m * 0.693147180559945f;   // back to natural-log units
+    a.part_l[pi] = l;
+  }
+  const int f0 = (kg * 2 + g) * FW;
+#pragma unroll
+  for (int q = 0; q < FW / 4; ++q) {
+    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < KG; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += w[i] * s_o[((i * RB + rb) * D + f0 + 4 * q + e) * LD + ln];
+    *(f32x4 *)(a.part_o + pi * D + f0 + 4 * q) = v;
+  }
+}
+
+// Combine the partials of one (row, kv head) — all `group` query heads that share the kv head: context
+// splits, then draft blocks, in ascending order.  Memory round trips, not arithmetic, set its time: up to
+// kMergeBatch partials of a thread are requested at once.  Block = group * d / 2 threads, two adjacent
+// output features each.
+constexpr int kMergeBatch = 20;   // 16 context splits and the draft blocks of 128 nodes
+// e^x through the hardware exp2 (about 1e-7 |x| relative error; the arguments here are <= 0)
+__device__ __forceinline__ float fast_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
+
+template <int D>
+__global__ __launch_bounds__(512) void k_attn_merge(AttnArgs a) {
+  const int r = blockIdx.x, kvh = blockIdx.y, tid = threadIdx.x;
+  const int M = a.n_nodes, group = a.n_q_heads / a.n_kv_heads;
+  const int b = r / M, node = r - b * M;
+  const int p_rows = group * M, n = a.n_splits + a.n_draft;
+  const size_t base = ((size_t)b * a.n_kv_heads + kvh) * n;
+  const int al = tid / (D / 2), f = (tid - al * (D / 2)) * 2;   // head, first feature
+  if (al >= group) return;
+  const int p = al * M + node;
+  float pm[kMergeBatch], pl[kMergeBatch];
+  float2 po[kMergeBatch];
+  auto request = [&](int s0) {
+#pragma unroll
+    for (int i = 0; i < kMergeBatch; ++i) {
+      const size_t idx = (base + min(s0 + i, n - 1)) * p_rows + p;
+      pm[i] = a.part_m[idx];
+      pl[i] = a.part_l[idx];
+      po[i] = *(const float2 *)(a.part_o + idx * D + f);
+    }
+  };
+  request(0);
+  float m_tot = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < kMergeBatch; ++i) m_tot = fmaxf(m_tot, i < n ? pm[i] : -INFINITY);
+  for (int s0 = kMergeBatch; s0 < n; s0 += 16) {   // long contexts only
+    float t[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t[i] = a.part_m[(base + min(s0 + i, n - 1)) * p_rows + p];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) m_tot = fmaxf(m_tot, t[i]);
+  }
+  float num0 = 0.f, num1 = 0.f, den = 0.f;
+  for (int s0 = 0; s0 < n; s0 += kMergeBatch) {
+    if (s0 > 0) request(s0);
+#pragma unroll
+    for (int i = 0; i < kMergeBatch; ++i) {
+      if (s0 + i >= n || pm[i] == -INFINITY) continue;   // no key in it: its o was never written
+      const float w = fast_exp(pm[i] - m_tot);
+      num0 += po[i].x * w;
+      num1 += po[i].y * w;
+      den += pl[i] * w;
+    }
+  }
+  const float o0 = num0 / den, o1 = num1 / den;
+  const bf16 h0 = (bf16)o0, h1 = (bf16)o1;
+  bf16 *dst = (bf16 *)a.out;   // operand layout of the O projection; out_panel = number of 32-row blocks
+  const int kk = (kvh * group + al) * D + f;   // even: both features sit in the same 8-element run
+  bf16 *d0 = dst + ol_offset(r, kk, 0, (int)a.out_panel), *d1 = dst + ol_offset(r, kk, 1, (int)a.out_panel);
+  d0[0] = h0; d0[1] = h1;
+  d1[0] = (bf16)(o0 - (float)h0); d1[1] = (bf16)(o1 - (float)h1);
+}
+
+// The other merge, where the draft nodes have no workgroups of their own: combine the context splits of one (row, kv head) — all `group` query heads that share the kv
 // head — in ascending split order, with the draft-node part: for every ancestor-or-self j of the
 // node, score = q . k_j / sqrt(d) and value v_j, all taken in fp32 from this pass's projections
 // (a.qkv: [row][(nq + 2 nkv) * d], q and k already rotated).
@@ -350,11 +702,8 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
 // the ancestors' keys and the first ancestors' values — in ONE round trip.  Block = group * d / 2 threads, two adjacent output features each;
 // the ancestor list (at most 64 nodes) is scored by (slot x quarter of the features) threads.
 constexpr int kMergePreV = 8;    // ancestors whose values are fetched ahead of the scores
-// e^x through the hardware exp2 (about 1e-7 |x| relative error; the arguments here are <= 0)
-__device__ __forceinline__ float fast_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
-
 template <int D>
-__global__ __launch_bounds__(512) void k_attn_merge(AttnArgs a) {
+__global__ __launch_bounds__(512) void k_attn_merge_tree(AttnArgs a) {
   __shared__ float s_q[kMaxGroup][D];
   __shared__ float s_sc[kMaxGroup][kMaxNodes];
   __shared__ int s_anc[kMaxNodes];
@@ -493,17 +842,35 @@ __global__ __launch_bounds__(512) void k_attn_merge(AttnArgs a) {
 
 template <int D>
 static void launch_attn_bf16_d(hipStream_t st, const AttnArgs &a) {
-  dim3 grid(a.n_splits, a.n_kv_heads, a.batch * a.n_row_groups);
-  if (a.kv.page_table) {
-    if (a.rows_per_wg == 256) hipLaunchKernelGGL((k_attn_bf16<D, 1, 64, 8, true>), grid, dim3(512), 0, st, a);
-    else hipLaunchKernelGGL((k_attn_bf16<D, 1, 128, 4, true>), grid, dim3(256), 0, st, a);
+  dim3 grid(a.n_splits + (a.draft_mode == kDraftOwnGroups ? a.n_draft : 0), a.n_kv_heads, a.batch * a.n_row_groups);
+  const bool paged = a.kv.page_table != nullptr;
+#define TS_ATTN(KT_, NW_, PAGED_, NT_)                                                                                       \
+  do {                                                                                                                       \
+    if (a.draft_mode == kDraftOwnGroups)                                                                                     \
+      hipLaunchKernelGGL((k_attn_bf16<D, 1, KT_, NW_, PAGED_, true>), grid, dim3(NT_), 0, st, a);                            \
+    else                                                                                                                     \
+      hipLaunchKernelGGL((k_attn_bf16<D, 1, KT_, NW_, PAGED_, false>), grid, dim3(NT_), 0, st, a);                           \
+  } while (0)
+  if (a.rows_per_wg == 32) {
+    if (paged) hipLaunchKernelGGL((k_attn_few<D, 1, true>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_attn_few<D, 1, false>), grid, dim3(256), 0, st, a);
+  } else if (a.rows_per_wg == 64) {
+    if (paged) hipLaunchKernelGGL((k_attn_few<D, 2, true>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_attn_few<D, 2, false>), grid, dim3(256), 0, st, a);
+  } else if (a.rows_per_wg == 256) {
+    if (paged) TS_ATTN(64, 8, true, 512);
+    else TS_ATTN(64, 8, false, 512);
   } else {
-    if (a.rows_per_wg == 256) hipLaunchKernelGGL((k_attn_bf16<D, 1, 64, 8, false>), grid, dim3(512), 0, st, a);
-    else hipLaunchKernelGGL((k_attn_bf16<D, 1, 128, 4, false>), grid, dim3(256), 0, st, a);
+    if (paged) TS_ATTN(128, 4, true, 256);
+    else TS_ATTN(128, 4, false, 256);
   }
+#undef TS_ATTN
   const int group = a.n_q_heads / a.n_kv_heads;
   const int merge_threads = group * D / 2 < 64 ? 64 : group * D / 2;   // <= 512 (group <= 8, d <= 128)
-  hipLaunchKernelGGL(k_attn_merge<D>, dim3(a.batch * a.n_nodes, a.n_kv_heads), dim3(merge_threads), 0, st, a);
+  if (a.draft_mode == kDraftInMerge)
+    hipLaunchKernelGGL(k_attn_merge_tree<D>, dim3(a.batch * a.n_nodes, a.n_kv_heads), dim3(merge_threads), 0, st, a);
+  else
+    hipLaunchKernelGGL(k_attn_merge<D>, dim3(a.batch * a.n_nodes, a.n_kv_heads), dim3(merge_threads), 0, st, a);
 }
 
 void launch_attn_bf16(hipStream_t st, const AttnArgs &a) {

@@ -40,3 +40,65 @@ def test_tile_edges(name, batch, nodes, shape):
     seed = 300 + len(name)
     parents = [gen_tree(nodes, 9, 4, seed + b) if nodes > 1 else np.array([-1], dtype=np.int32) for b in range(batch)]
     full_check(make_case(shape, seed, [20 + 17 * b for b in range(batch)], parents), thresholds=(0.0, 0.5))
+
+
+# Who evaluates the draft nodes of an attention call, and with how many rows a workgroup:
+# (batch, nodes, query heads over 2 kv heads, contexts)
+ATTN_CASES = {
+    "rows18_own_workgroups": (1, 9, 4, (300,)),
+    "rows64_page_ends": (2, 32, 4, (256, 257)),
+    "rows58_batch": (3, 29, 4, (0, 31, 1500)),
+    "rows4_one_node_long": (1, 1, 8, (9000,)),
+    "rows200_own_workgroups": (1, 100, 4, (300,)),
+    "rows512_chain_blocks": (1, 128, 8, (65,)),
+    "rows128_unequal": (8, 32, 8, (13000, 300, 64, 0, 77, 12999, 500, 9)),
+    "rows80_in_merge": (4, 40, 4, (13000, 128, 0, 5000)),
+}
+
+
+def attn_case(name):
+    from gpu_helpers import Case
+    from workloads import gen_draft_tokens, gen_kv_cache, tree_depths
+    batch, nodes, heads, ctx = ATTN_CASES[name]
+    shape, seed = TB.with_(n_q_heads=heads, vocab=600), 500 + len(name)
+    if nodes == 128:
+        parents = [np.arange(-1, nodes - 1, dtype=np.int32)]
+    else:
+        parents = [gen_tree(nodes, 8, 4, seed + b) if nodes > 1 else np.array([-1], dtype=np.int32) for b in range(batch)]
+    k, v = gen_kv_cache(shape, batch, max(ctx), seed, 0)
+    return Case(shape, seed, [k[b][None, :, :n].astype(np.float64) for b, n in enumerate(ctx)],
+                [v[b][None, :, :n].astype(np.float64) for b, n in enumerate(ctx)],
+                np.stack([gen_draft_tokens(p, shape.vocab, seed + b) for b, p in enumerate(parents)]),
+                np.stack(parents), np.stack([n + tree_depths(p) for n, p in zip(ctx, parents)]))
+
+
+@pytest.mark.parametrize("paged", [False, True], ids=["dense", "paged"])
+@pytest.mark.parametrize("name", list(ATTN_CASES))
+def test_attention_forms(name, paged):
+    full_check(attn_case(name), thresholds=(0.0, 0.5), paged=paged)
+
+
+@pytest.mark.parametrize("name", ["rows18_own_workgroups", "rows58_batch", "rows200_own_workgroups",
+                                  "rows128_unequal", "rows80_in_merge"])
+def test_infinite_values_stay_on_their_branch(name):
+    """A draft token whose embedding is not finite spoils its own subtree and nothing else.  Blocks of draft
+    nodes with such a value are added up node by node instead of by matrix instructions: at most 128 fp32
+    terms in another order, 128 * 2^-24 of an attention output of order 1, which the 16-bit high + low
+    operands of the matmuls after it (2^-17 each) and 2 layers carry into logits of up to about 10: the
+    2e-3 of the other cases covers it."""
+    from gpu_helpers import device_model
+    case = attn_case(name)
+    model = device_model(case.shape, case.seed)
+    bad = case.shape.vocab - 1
+    case.tokens[case.tokens == bad] = 0
+    clean = case.run_gpu(0.0, model=model)["logits"].copy()
+    model.tensors["embed"][bad].fill_(float("inf"))
+    spoilt = np.zeros((case.batch, case.n_nodes), dtype=bool)
+    for b in range(case.batch):
+        hit = case.n_nodes // 2
+        case.tokens[b][hit] = bad
+        for i in range(case.n_nodes):
+            spoilt[b, i] = i == hit or (case.parents[b][i] >= 0 and spoilt[b, case.parents[b][i]])
+    got = case.run_gpu(0.0, model=model)["logits"]
+    assert np.isfinite(clean).all() and not np.isfinite(got[spoilt]).all(axis=-1).any()
+    assert np.abs(got[~spoilt] - clean[~spoilt]).max() <= 2e-3
