@@ -277,22 +277,36 @@ void launch_reduce_swiglu(hipStream_t st, int dtype, const float *part, int n_sp
 }
 
 // ------------------------------------------------------------------ fp32 reference-precision matmul
-// One wavefront per (output column, group of 8 rows); lanes stride the reduction.
+// One wavefront per (output column, group of 8 rows); lanes stride the reduction.  Memory round trips
+// set its time, so the loads of 8 steps (512 reduction elements) are requested together, without a
+// branch around any of them; the additions stay in their order (256 x 512 over 9 rows: 18.6 -> 4.9 us).
 __global__ __launch_bounds__(64) void k_gemm_f32(GemmArgs a) {
   const int col = blockIdx.x;
   const int r0 = blockIdx.y * 8;
   int s = 0;
   while (s + 1 < a.n_seg && col >= a.seg[s + 1].col0) ++s;
   const float *w = (const float *)a.seg[s].w + (size_t)(col - a.seg[s].col0) * a.k;
-  const float *x = (const float *)a.x;
+  const float *x[8];   // rows past the end repeat the last one; their sums are not stored
+#pragma unroll
+  for (int j = 0; j < 8; ++j) x[j] = (const float *)a.x + (size_t)min(r0 + j, a.rows - 1) * a.k;
   float acc[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-  for (int k = threadIdx.x; k < a.k; k += 64) {
-    const float wv = w[k];
+  constexpr int U = 8;
+  for (int k0 = threadIdx.x; k0 < a.k; k0 += 64 * U) {
+    float wv[U], xv[U][8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (r0 + j < a.rows) acc[j] += x[(size_t)(r0 + j) * a.k + k] * wv;
+    for (int u = 0; u < U; ++u) {
+      const int k = min(k0 + 64 * u, a.k - 1);
+      wv[u] = w[k];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) xv[u][j] = x[j][k];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k0 + 64 * u < a.k)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] += xv[u][j] * wv[u];
   }
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
