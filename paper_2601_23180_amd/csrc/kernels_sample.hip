@@ -20,7 +20,8 @@ namespace ts {
 
 namespace {
 
-constexpr int kStatThreads = 1024;
+constexpr int kStatThreads = 256;
+constexpr int kWalkThreads = 1024;                      // a wavefront per node
 constexpr int kDrawThreads = 1024;
 constexpr int kPerThread = 4;                           // consecutive tokens per thread inside a chunk
 constexpr int kChunk = kDrawThreads * kPerThread;       // tokens per chunk (== kSampleChunk)
@@ -68,22 +69,27 @@ __device__ __forceinline__ double block_scan(double v, double *s_w, double *tota
 }
 
 // grid (chunks, rows): max / second max / lowest argmax of one chunk of a row, and the chunk's
-// partition sum relative to ITS maximum, sum exp((l - max_chunk) / T)
+// partition sum relative to ITS maximum, sum exp((l - max_chunk) / T).  16 tokens a thread, requested at
+// once: with 4 the exchanges between lanes outweighed the scan (36 rows x 151936: 62 -> 11 us).
 __global__ __launch_bounds__(kStatThreads) void k_sample_chunkstats(SampleArgs a) {
+  constexpr int PER = kChunk / kStatThreads;
   __shared__ Max2 s_m[kStatThreads / 64];
   __shared__ double s_w[kStatThreads / 64];
   const int chunk = blockIdx.x, r = blockIdx.y, tid = threadIdx.x, V = a.vocab;
   // status word of the whole call: cleared by the first kernel, bits are OR-ed in by the later ones
   if (chunk == 0 && r == 0 && tid == 0 && a.out.status) *a.out.status = 0;
   const float *row = a.logits + (size_t)r * V;
-  const int c0 = chunk * kChunk + tid * kPerThread;
-  float v[kPerThread];
+  const int c0 = chunk * kChunk + tid;
+  float v[PER];
   Max2 m;
   m.l1 = -INFINITY; m.l2 = -INFINITY; m.idx = 0x7fffffff;
 #pragma unroll
-  for (int e = 0; e < kPerThread; ++e) {       // ascending: the lowest index of equal maxima stays
-    v[e] = (c0 + e < V) ? row[c0 + e] : -INFINITY;
-    if (v[e] > m.l1) { m.l2 = m.l1; m.l1 = v[e]; m.idx = c0 + e; }
+  for (int e = 0; e < PER; ++e) v[e] = row[min(c0 + e * kStatThreads, V - 1)];
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {       // ascending: the lowest index of equal maxima stays
+    const int c = c0 + e * kStatThreads;
+    if (c >= V) v[e] = -INFINITY;
+    if (v[e] > m.l1) { m.l2 = m.l1; m.l1 = v[e]; m.idx = c; }
     else m.l2 = fmaxf(m.l2, v[e]);
   }
 #pragma unroll
@@ -99,8 +105,8 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_chunkstats(SampleArgs a
   for (int w = 1; w < kStatThreads / 64; ++w) m = max2_merge(m, s_m[w]);
   double z = 0.0;
 #pragma unroll
-  for (int e = 0; e < kPerThread; ++e)
-    if (c0 + e < V) z += (double)expf((v[e] - m.l1) * a.inv_temp);
+  for (int e = 0; e < PER; ++e)
+    if (c0 + e * kStatThreads < V) z += (double)expf((v[e] - m.l1) * a.inv_temp);
   double zt;
   (void)block_scan<kStatThreads>(z, s_w, &zt);
   if (tid != 0) return;
@@ -108,17 +114,19 @@ __global__ __launch_bounds__(kStatThreads) void k_sample_chunkstats(SampleArgs a
   a.cs_l1[o] = m.l1; a.cs_l2[o] = m.l2; a.cs_idx[o] = m.idx; a.cs_z[o] = zt;
 }
 
-__global__ __launch_bounds__(64) void k_sample_walk(SampleArgs a) {
+// One workgroup per sequence; its 16 wavefronts take a node each, in parallel (one after the other in a
+// single wavefront, 9 nodes took 20 us; now 5.4), then the first one decides.
+__global__ __launch_bounds__(kWalkThreads) void k_sample_walk(SampleArgs a) {
   __shared__ float s_conf[kMaxNodes], s_margin[kMaxNodes];
   __shared__ float s_pv[kMaxNodes], s_q[kMaxNodes];
-  const int b = blockIdx.x, i = threadIdx.x, M = a.n_nodes, V = a.vocab;
+  const int b = blockIdx.x, lane = threadIdx.x & 63, M = a.n_nodes, V = a.vocab;
   int bad = 0;
-  for (int n = 0; n < M; ++n) {
+  for (int n = threadIdx.x >> 6; n < M; n += kWalkThreads / 64) {
     // merge node n's chunk statistics: lanes stride the chunks, then a fixed butterfly
     const size_t o = (size_t)(b * M + n) * a.n_chunks;
     Max2 m;
     m.l1 = -INFINITY; m.l2 = -INFINITY; m.idx = 0x7fffffff;
-    for (int c = i; c < a.n_chunks; c += 64) {
+    for (int c = lane; c < a.n_chunks; c += 64) {
       Max2 t;
       t.l1 = a.cs_l1[o + c]; t.l2 = a.cs_l2[o + c]; t.idx = a.cs_idx[o + c];
       m = max2_merge(m, t);
@@ -130,11 +138,11 @@ __global__ __launch_bounds__(64) void k_sample_walk(SampleArgs a) {
       m = max2_merge(m, t);
     }
     double z = 0.0;
-    for (int c = i; c < a.n_chunks; c += 64)
+    for (int c = lane; c < a.n_chunks; c += 64)
       z += a.cs_z[o + c] * (double)expf((a.cs_l1[o + c] - m.l1) * a.inv_temp);
 #pragma unroll
     for (int w = 1; w < 64; w <<= 1) z += __shfl_xor(z, w, 64);
-    if (i == n) {   // lane n keeps node n
+    if (lane == 0) {
       const int r = b * M + n;
       a.row_l1[r] = m.l1; a.row_l2[r] = m.l2; a.row_idx[r] = m.idx; a.row_z[r] = z;
       // Eq. 6 operands of the NEXT chain node's token, judged by this node's distribution
@@ -150,27 +158,26 @@ __global__ __launch_bounds__(64) void k_sample_walk(SampleArgs a) {
         }
       }
       s_pv[n] = pv; s_q[n] = q;
+      const float conf = (float)(1.0 / z);
+      const float p2 = (float)((double)expf((m.l2 - m.l1) * a.inv_temp) / z);   // 0 for a one-token vocabulary
+      s_conf[n] = conf;
+      s_margin[n] = conf - p2;
+      if (a.out.argmax) a.out.argmax[r] = m.idx;
+      if (a.out.confidence) a.out.confidence[r] = conf;
+      if (a.out.margin) a.out.margin[r] = s_margin[n];
     }
   }
   bad = __syncthreads_or(bad);
+  const int i = threadIdx.x;
+  if (i >= 64) return;   // the path is one wavefront's work (no barrier below)
   if (i == 0) {
     a.seq_bad[b] = bad;
     if (bad && a.out.status) atomicOr(a.out.status, 1);
   }
-  if (i < M) {
-    const int r = b * M + i;
-    const double z = a.row_z[r];
-    const float conf = (float)(1.0 / z);
-    const float p2 = (float)((double)expf((a.row_l2[r] - a.row_l1[r]) * a.inv_temp) / z);   // 0 for a one-token vocabulary
-    s_conf[i] = conf;
-    s_margin[i] = conf - p2;
-    if (a.out.argmax) a.out.argmax[r] = a.row_idx[r];
-    if (a.out.confidence) a.out.confidence[r] = conf;
-    if (a.out.margin) a.out.margin[r] = s_margin[i];
-  }
   if (a.out.path)
     for (int j = i; j < TRISPEC_PATH_STRIDE; j += 64) a.out.path[b * TRISPEC_PATH_STRIDE + j] = -1;
-  __syncthreads();
+  __builtin_amdgcn_s_waitcnt(0);   // lane 0's entries come after the fill
+  __builtin_amdgcn_wave_barrier();
   if (i != 0) return;
   int cur = a.n_forced - 1, acc = 0, esc = 0, row = -1, mode = 0;   // mode: 0 none, 1 direct, 2 residual
   if (a.out.path) a.out.path[b * TRISPEC_PATH_STRIDE] = cur;
@@ -325,7 +332,7 @@ __global__ __launch_bounds__(kDrawThreads) void k_sample_pick(SampleArgs a) {
 
 void launch_sample_decide(hipStream_t st, const SampleArgs &a) {
   hipLaunchKernelGGL(k_sample_chunkstats, dim3(a.n_chunks, a.batch * a.n_nodes), dim3(kStatThreads), 0, st, a);
-  hipLaunchKernelGGL(k_sample_walk, dim3(a.batch), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(k_sample_walk, dim3(a.batch), dim3(kWalkThreads), 0, st, a);
   hipLaunchKernelGGL(k_sample_chunksum, dim3(a.n_chunks, a.batch), dim3(kDrawThreads), 0, st, a);
   hipLaunchKernelGGL(k_sample_pick, dim3(a.batch), dim3(kDrawThreads), 0, st, a);
 }
