@@ -719,16 +719,35 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
   };
 
   (void)hipGetLastError();
-  launch_setup(st, tab, rows, n_nodes, (AncMask *)(ws + L.anc), (int32_t *)(ws + L.parent), status,
-               (int32_t *)(ws + L.counters), L.n_zero);
-  launch_rope_table(st, positions, rows, c.head_dim, c.rope_base, cos_t, sin_t);
+  {
+    BeginArgs g;
+    memset(&g, 0, sizeof(g));
+    g.tab = tab;
+    g.rows = rows; g.n_nodes = n_nodes;
+    g.anc = (AncMask *)(ws + L.anc);
+    g.parent = (int32_t *)(ws + L.parent);
+    g.status = status;
+    g.zero = (int32_t *)(ws + L.counters);
+    g.n_zero = L.n_zero;
+    g.positions = positions;
+    g.head_dim = c.head_dim;
+    g.rope_base = c.rope_base;
+    g.cos_t = cos_t; g.sin_t = sin_t;
+    g.tokens = draft_tokens;
+    g.embed = m->embed; g.norm_w = m->norm_attn[0];
+    g.hidden = c.hidden; g.vocab = c.vocab;
+    g.eps = c.rms_eps;
+    g.x = x;
+    g.h = ws + L.h;
+    g.h_panel = f32 ? 0 : (size_t)(rp / 32);
+    g.ss_out = f32 ? nullptr : (float *)(ws + L.ss_part);
+    launch_begin_pass(st, c.dtype, g);
+  }
 
   if (f32) {
     // ---------------- fp32 models: plain kernels, one per step
     float *h = (float *)(ws + L.h), *q = (float *)(ws + L.q);
     at.q = q;
-    launch_embed_norm(st, c.dtype, draft_tokens, m->embed, m->norm_attn[0], rows, c.hidden, c.vocab,
-                      c.rms_eps, x, h, 0, nullptr, status);
     auto gemm = [&](const float *xin, int k, int n_seg, const void *w0, int n0, const void *w1, int n1,
                     const void *w2, int n2, float *out) {
       GemmArgs g;
@@ -797,8 +816,6 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
     at.q_panel = pan_q;
     // ss[0]: written by the embedding (1 tile) and by every down projection; ss[1]: by every O projection
     float *ss0 = (float *)(ws + L.ss_part), *ss1 = ss0 + (size_t)ss_tiles_of(c.hidden, 32) * rp;
-    launch_embed_norm(st, c.dtype, draft_tokens, m->embed, m->norm_attn[0], rows, c.hidden, c.vocab, c.rms_eps,
-                      x, h, (size_t)(rp / 32), ss0, status);
     int o_tiles = tiles_of(c.hidden), dn_tiles = o_tiles;   // sums of squares per row that the O / down projections leave
     auto base = [&](int epi, const void *xin, size_t xpanel, const float *ss_in, int ss_tiles, int k,
                     int n_total, const SplitPlan &p) {
@@ -1021,7 +1038,7 @@ int trispec_decide(trispec_model *m, int32_t batch, const int32_t *draft_tokens,
   (void)hipGetLastError();
   // the tree of THIS call (it may differ from the last verify's, e.g. after pruning): parents into
   // the workspace, the status word and the counters left alone
-  launch_setup(st, tab, batch * n_nodes, n_nodes, (AncMask *)(ws + L.anc), (int32_t *)(ws + L.parent), nullptr, nullptr, 0);
+  launch_setup(st, tab, batch * n_nodes, n_nodes, (AncMask *)(ws + L.anc), (int32_t *)(ws + L.parent));
   DecideArgs d = make_decide(L, ws, draft_tokens, batch, n_nodes, threshold, opts, out);
   launch_decide(st, d);
   return hipGetLastError() == hipSuccess ? TRISPEC_OK : TRISPEC_ELAUNCH;

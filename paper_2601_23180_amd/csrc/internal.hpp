@@ -237,13 +237,30 @@ struct DecideArgs {
 
 // ---- launchers (one per kernel family); all enqueue on `st` and return nothing:
 // the caller checks hipGetLastError once at the end of the pass.
-void launch_setup(hipStream_t st, const NodeTable &tab, int rows, int n_nodes, AncMask *anc, int32_t *parent,
-                  int32_t *status, int32_t *zero, int n_zero);
-void launch_rope_table(hipStream_t st, const int32_t *positions, int rows, int head_dim, float base,
-                       float *cos_t, float *sin_t);
-void launch_embed_norm(hipStream_t st, int dtype, const int32_t *tokens, const void *embed,
-                       const void *norm_w, int rows, int hidden, int vocab, float eps, float *x,
-                       void *h, size_t h_panel, float *ss_out, int32_t *status);
+void launch_setup(hipStream_t st, const NodeTable &tab, int rows, int n_nodes, AncMask *anc, int32_t *parent);
+// What a pass does before its first matmul
+struct BeginArgs {
+  NodeTable tab;
+  int32_t rows, n_nodes;
+  AncMask *anc;
+  int32_t *parent;
+  int32_t *status;     // 1: a token id is outside the vocabulary
+  int32_t *zero;       // n_zero counters to clear
+  int32_t n_zero;
+  const int32_t *positions;
+  int32_t head_dim;
+  float rope_base;
+  float *cos_t, *sin_t;
+  const int32_t *tokens;
+  const void *embed, *norm_w;
+  int32_t hidden, vocab;
+  float eps;
+  float *x;            // residual stream
+  void *h;             // fp32 models: the normalised rows; bf16 models: operand panels of the first matmul
+  size_t h_panel;
+  float *ss_out;       // bf16 models: sum of squares per row
+};
+void launch_begin_pass(hipStream_t st, int dtype, const BeginArgs &a);
 // nodes / counts of a commit, by value
 struct CommitTable {
   uint8_t node[kMaxBatch][kMaxNodes];

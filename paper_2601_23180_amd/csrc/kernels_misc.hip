@@ -9,8 +9,7 @@ namespace ts {
 // ------------------------------------------------------------------ set-up
 // Also clears `zero[0 .. n_zero)`: the tile counters of the split-K matmuls and the barrier
 // counters / abort word of the layer kernels, which must be zero when the pass starts.
-__global__ void k_setup(NodeTable tab, int rows, int n_nodes, AncMask *anc, int32_t *parent, int32_t *status,
-                        int32_t *zero, int n_zero) {
+__device__ __forceinline__ void setup_nodes(const NodeTable &tab, int rows, int n_nodes, AncMask *anc, int32_t *parent) {
   const int i = threadIdx.x;
   if (i < rows) {
     // root path of node i: walk up the parents (validated on the host: parent < node, root = -1)
@@ -24,13 +23,14 @@ __global__ void k_setup(NodeTable tab, int rows, int n_nodes, AncMask *anc, int3
     anc[i] = m;
     parent[i] = tab.parent[i];
   }
-  if (i == 0 && status != nullptr) *status = 0;
-  for (int j = i; j < n_zero; j += kMaxRows) zero[j] = 0;
 }
 
-void launch_setup(hipStream_t st, const NodeTable &tab, int rows, int n_nodes, AncMask *anc, int32_t *parent,
-                  int32_t *status, int32_t *zero, int n_zero) {
-  hipLaunchKernelGGL(k_setup, dim3(1), dim3(kMaxRows), 0, st, tab, rows, n_nodes, anc, parent, status, zero, n_zero);
+__global__ void k_setup(NodeTable tab, int rows, int n_nodes, AncMask *anc, int32_t *parent) {
+  setup_nodes(tab, rows, n_nodes, anc, parent);
+}
+
+void launch_setup(hipStream_t st, const NodeTable &tab, int rows, int n_nodes, AncMask *anc, int32_t *parent) {
+  hipLaunchKernelGGL(k_setup, dim3(1), dim3(kMaxRows), 0, st, tab, rows, n_nodes, anc, parent);
 }
 
 __global__ void k_wait_probe(int32_t *counter, int expect, unsigned long long limit, int32_t *abort_word,
@@ -45,9 +45,9 @@ void launch_wait_probe(hipStream_t st, int32_t *counter, int expect, unsigned lo
 
 // angle[r][j] = position_r * base^(-2j/d), evaluated in fp64 so that large positions keep
 // their phase; the table holds fp32 cos / sin.
-__global__ void k_rope_table(const int32_t *positions, int head_dim, float base, float *cos_t,
-                             float *sin_t) {
-  const int r = blockIdx.x, j = threadIdx.x;
+__device__ __forceinline__ void rope_row(int r, const int32_t *positions, int head_dim, float base, float *cos_t,
+                                         float *sin_t) {
+  const int j = threadIdx.x;
   const int half = head_dim >> 1;
   if (j >= half) return;
   const double inv = pow((double)base, -2.0 * (double)j / (double)head_dim);
@@ -56,28 +56,16 @@ __global__ void k_rope_table(const int32_t *positions, int head_dim, float base,
   sin_t[r * half + j] = (float)sin(ang);
 }
 
-void launch_rope_table(hipStream_t st, const int32_t *positions, int rows, int head_dim, float base,
-                       float *cos_t, float *sin_t) {
-  hipLaunchKernelGGL(k_rope_table, dim3(rows), dim3(head_dim / 2), 0, st, positions, head_dim, base,
-                     cos_t, sin_t);
-}
-
 // ------------------------------------------------------------------ embedding + first RMSNorm
 // x[r] = E[token_r] (fp32 residual stream).  fp32 models: h[r] = x * rstd * w.  bf16 models: the
 // first matmul's operand panels h = x * w as bf16 hi + lo, and the row's sum of squares (that
 // matmul's epilogue turns it into 1/rms).
 template <typename AT>
-__global__ __launch_bounds__(256) void k_embed_norm(const int32_t *tokens, const AT *embed,
-                                                    const AT *norm_w, int hidden, int vocab, float eps,
-                                                    float *x, void *h, size_t h_panel, float *ss_out,
-                                                    int32_t *status) {
+__device__ __forceinline__ void embed_row(int r, const int32_t *tokens, const AT *embed, const AT *norm_w, int hidden,
+                                          int vocab, float eps, float *x, void *h, size_t h_panel, float *ss_out) {
   __shared__ float red[4];
-  const int r = blockIdx.x;
   int tok = tokens[r];
-  if (tok < 0 || tok >= vocab) {
-    if (threadIdx.x == 0) atomicOr(status, 1);
-    tok = 0;
-  }
+  if (tok < 0 || tok >= vocab) tok = 0;   // reported by the workgroup that sets the pass up
   const AT *e = embed + (size_t)tok * hidden;
   float *xr = x + (size_t)r * hidden;
   if constexpr (sizeof(AT) == 2) {
@@ -136,15 +124,30 @@ __global__ __launch_bounds__(256) void k_embed_norm(const int32_t *tokens, const
   }
 }
 
-void launch_embed_norm(hipStream_t st, int dtype, const int32_t *tokens, const void *embed,
-                       const void *norm_w, int rows, int hidden, int vocab, float eps, float *x,
-                       void *h, size_t h_panel, float *ss_out, int32_t *status) {
-  if (dtype == TRISPEC_F32)
-    hipLaunchKernelGGL(k_embed_norm<float>, dim3(rows), dim3(256), 0, st, tokens, (const float *)embed,
-                       (const float *)norm_w, hidden, vocab, eps, x, h, h_panel, (float *)nullptr, status);
-  else
-    hipLaunchKernelGGL(k_embed_norm<bf16>, dim3(rows), dim3(256), 0, st, tokens, (const bf16 *)embed,
-                       (const bf16 *)norm_w, hidden, vocab, eps, x, h, h_panel, ss_out, status);
+// Everything before the first matmul in one launch: workgroups 0 .. rows - 1 an embedding row each, rows ..
+// 2 rows - 1 a row of the rotary table, the last one root paths, status word and counters.  Three
+// launches took 14 us of a pass, nearly all of it launch and first memory round trip.
+template <typename AT>
+__global__ __launch_bounds__(256) void k_begin_pass(BeginArgs a) {
+  static_assert(kMaxRows == 256, "a thread of the set-up workgroup per row");
+  const int wg = blockIdx.x, i = threadIdx.x;
+  if (wg < a.rows) {
+    embed_row<AT>(wg, a.tokens, (const AT *)a.embed, (const AT *)a.norm_w, a.hidden, a.vocab, a.eps, a.x, a.h, a.h_panel,
+                  a.ss_out);
+  } else if (wg < 2 * a.rows) {
+    rope_row(wg - a.rows, a.positions, a.head_dim, a.rope_base, a.cos_t, a.sin_t);
+  } else {
+    setup_nodes(a.tab, a.rows, a.n_nodes, a.anc, a.parent);
+    const int bad = __syncthreads_or(i < a.rows && (a.tokens[i] < 0 || a.tokens[i] >= a.vocab));
+    if (i == 0) *a.status = bad ? 1 : 0;
+    for (int j = i; j < a.n_zero; j += 256) a.zero[j] = 0;
+  }
+}
+
+void launch_begin_pass(hipStream_t st, int dtype, const BeginArgs &a) {
+  const dim3 grid(2 * a.rows + 1);
+  if (dtype == TRISPEC_F32) hipLaunchKernelGGL(k_begin_pass<float>, grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(k_begin_pass<bf16>, grid, dim3(256), 0, st, a);
 }
 
 __global__ void k_zero_counters(int32_t *counters, int n_counters) {
