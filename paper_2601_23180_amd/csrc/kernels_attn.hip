@@ -10,6 +10,8 @@
 // copies for later rounds, but the pass itself never reads them back.  Where they are evaluated is up to
 // the host (AttnArgs::draft_mode): in blocks of 32 by workgroups of the same launch, or by the merge
 // kernel, which combines all partials of a row in ascending order.
+#include <float.h>
+
 #include "device_util.hpp"
 
 namespace ts {
@@ -99,6 +101,11 @@ struct AttnLds {
   static constexpr int kBytesV = D * kStrideV;
   static constexpr int kBuf = kBytesK + kBytesV;  // one stage
 };
+
+// Maximum, in natural-log units, that a partial is stored with.  -inf marks a partial without keys, which the
+// merge skips without reading it; one whose scores are all NaN (fmaxf drops them) or all -inf has to be
+// added up all the same, so that the NaN in its sums reaches the row: it is stored with the lowest finite value.
+__device__ __forceinline__ float stored_max(float m_log2) { return fmaxf(m_log2 * 0.693147180559945f, -FLT_MAX); }
 
 // Softmax partial of 32 query rows (one wavefront) over the draft nodes 32 kb .. 32 kb + 31: S^T = K Q^T
 // and O^T = V^T P^T with fp32 matrix instructions (32x32x2), operands straight from the projections.
@@ -202,7 +209,7 @@ __device__ void draft_partial(const AttnArgs &a, int kb, int kvh, int b, int row
   }
   if (prow >= p_rows) return;
   if (g == 0) {
-    a.part_m[pi] = m * 0.693147180559945f;
+    a.part_m[pi] = mine != 0 ? stored_max(m) : -INFINITY;
     a.part_l[pi] = l;
   }
   float *out = a.part_o + pi * D;
@@ -473,7 +480,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
     if (p >= p_rows) continue;
     const float l_tot = l_run[i] + __shfl_xor(l_run[i], 32, 64);
     if (g == 0) {
-      a.part_m[part_base * p_rows + p] = m_run[i] * 0.693147180559945f;   // back to natural-log units
+      a.part_m[part_base * p_rows + p] = stored_max(m_run[i]);
       a.part_l[part_base * p_rows + p] = l_tot;
     }
     float *o = a.part_o + (part_base * p_rows + p) * D;
@@ -644,7 +651,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_few(AttnArgs a) {
   }
   const size_t pi = part_base * p_rows + prow;
   if (kg == 0 && g == 0) {
-    a.part_m[pi] = m * 0.693147180559945f;   // back to natural-log units
+    a.part_m[pi] = stored_max(m);
     a.part_l[pi] = l;
   }
   const int f0 = (kg * 2 + g) * FW;
