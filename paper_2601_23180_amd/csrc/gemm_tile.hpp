@@ -270,8 +270,11 @@ struct TileEpilogue {
 };
 
 // e^x for x <= 0: hardware exp2 with the rounding error of x * log2(e) put back (within 2 ulp, where
-// exp2(x * log2(e)) alone would be off by |x| / 2 ulp).
+// exp2(x * log2(e)) alone would be off by |x| / 2 ulp).  Below -104 the result is 0; from -2.4e38 on x * log2(e)
+// would overflow and its rounding error be a NaN.  A NaN stays one.  Confidences against fp64 on the same logits
+// (2400 nodes, 151936 columns): 1.07e-7 rms relative, as with expf and a running maximum.
 __device__ __forceinline__ float exp_neg(float x) {
+  x = x < -104.f ? -104.f : x;
   const float L = 1.44269504088896341f, Llo = 1.92596299112661e-8f;
   const float t = x * L;
   const float r = __builtin_fmaf(x, Llo, __builtin_fmaf(x, L, -t));

@@ -1,8 +1,11 @@
-"""Values that are not finite: a NaN that a row may see reaches its results whichever kernel adds the row up."""
+"""Values that are not finite, and logits near the end of the fp32 range: a NaN that a row may see reaches its
+results whichever kernel adds the row up, and no statistic makes a NaN of numbers or a number of a NaN."""
 import numpy as np
 import pytest
 
-from workloads import SHAPES, gen_draft_tokens, gen_kv_cache, gen_tree, tree_depths
+from paper_2601_23180_amd import model_from_arrays
+from workloads import SHAPES, WeightSource, gen_draft_tokens, gen_kv_cache, gen_tree, tree_depths
+from workloads.gen import bf16_bits
 from gpu_helpers import Case, device_model
 
 pytestmark = pytest.mark.gpu
@@ -87,3 +90,71 @@ def test_a_stretch_of_spoilt_context_is_not_skipped(name, paged):
         k[:, :, :spoilt] = np.nan
     got = case.run_gpu(0.0, paged=paged)["logits"]
     assert not np.isfinite(got).any()
+
+
+# ------------------------------------------------------------------ logit statistics
+# the kernels that end in the LM head's statistics: (batch, nodes, hidden)
+HEADS = {"chunks": (1, 40, 256), "ragged_k": (1, 40, 192), "wide": (3, 40, 256)}
+
+
+def head_case(name):
+    batch, nodes, hidden = HEADS[name]
+    shape = TB.with_(hidden=hidden, lm_head_std=0.3)
+    return synthetic_case(shape, 900 + len(name), (20,) * batch, [gen_tree(nodes, 8, 4, 5 + b) for b in range(batch)])
+
+
+def with_head_row(case, col, row):
+    ws = WeightSource(case.shape, case.seed)
+
+    def get(name, layer):
+        bits = ws.bits(name, layer)
+        if name == "lm_head":
+            bits[col] = bf16_bits(row)
+        return bits
+    return model_from_arrays(case.shape, get)
+
+
+def statistics(logits):
+    """fp64; one +inf logit takes all of the probability."""
+    x = logits.astype(np.float64)
+    top = x.max(axis=-1, keepdims=True)
+    with np.errstate(invalid="ignore"):
+        d = np.where(x == top, 0.0, x - top)
+    e = np.exp(d)
+    s = e.sum(axis=-1)
+    second = np.sort(e, axis=-1)[:, -2]
+    ent = np.log(s) - np.where(e > 0, e * np.where(e > 0, d, 0.0), 0.0).sum(axis=-1) / s
+    return x.argmax(axis=-1), 1.0 / s, (1.0 - second) / s, ent
+
+
+def check_statistics(gpu):
+    logits = gpu["logits"].reshape(-1, gpu["logits"].shape[-1])
+    arg, conf, margin, ent = statistics(logits)
+    assert np.array_equal(gpu["argmax"].reshape(-1), arg)
+    # 600 fp32 terms; exp of a distance d carries its rounding, |d| 2^-24: far below 1e-5
+    assert np.abs(gpu["confidence"].reshape(-1) - conf).max() <= 1e-5
+    assert np.abs(gpu["margin"].reshape(-1) - margin).max() <= 1e-5
+    near = np.abs(logits[:, 301]) < 1e30         # beyond, the entropy's sum of p * distance may overflow
+    assert np.abs(gpu["entropy"].reshape(-1) - ent)[near].max(initial=0.0) <= 1e-4
+
+
+def spiked(name, target):
+    """One vocabulary entry reads one feature only, with a weight that takes its logit to `target` at the node
+    where that feature is largest and to everything between -|target| and |target| at the others."""
+    case = head_case(name)
+    clean = case.run_gpu(0.0, export_hidden=True)["hidden"].reshape(-1, case.shape.hidden)
+    feat = int(np.abs(clean).max(axis=0).argmax())
+    peak = clean[np.abs(clean[:, feat]).argmax(), feat]
+    row = np.zeros(case.shape.hidden, dtype=np.float32)
+    row[feat] = target / float(peak)
+    return case.run_gpu(0.0, model=with_head_row(case, 301, row))
+
+
+@pytest.mark.parametrize("target", [3.1e38, -3.1e38])
+@pytest.mark.parametrize("name", list(HEADS))
+def test_statistics_of_logits_near_the_end_of_the_range(name, target):
+    """exp of a distance beyond 2.4e38 is 0, not a NaN."""
+    got = spiked(name, target)
+    x = got["logits"][..., 301]
+    assert np.isfinite(x).all() and (np.sign(target) * x).max() > 2.5e38
+    check_statistics(got)
