@@ -319,12 +319,13 @@ __device__ __forceinline__ void head_rows(const GemmArgs &a, const float *tl, co
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
           const float x = v[c >> 2][c & 3], dd = x - t.l1;
-          if (x != -INFINITY) {
+          if (x != -INFINITY && cbase + c != t.idx) {
             const float e = exp_neg(dd);
             t.s += e;
             t.t = __builtin_fmaf(e, dd, t.t);
           }
         }
+        t.s += 1.f;   // the largest itself: x - l1 would be a NaN for +inf.  Last: the small terms add up first
       }
     }
 #pragma unroll

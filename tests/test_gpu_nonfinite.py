@@ -158,3 +158,14 @@ def test_statistics_of_logits_near_the_end_of_the_range(name, target):
     x = got["logits"][..., 301]
     assert np.isfinite(x).all() and (np.sign(target) * x).max() > 2.5e38
     check_statistics(got)
+
+
+@pytest.mark.parametrize("name", list(HEADS))
+def test_statistics_of_one_infinite_logit(name):
+    """It takes all of the probability: confidence and margin 1."""
+    got = spiked(name, 8e38)
+    x = got["logits"][..., 301].reshape(-1)
+    top = x == np.inf
+    assert top.any()
+    check_statistics(got)
+    assert np.all(got["confidence"].reshape(-1)[top] == 1.0) and np.all(got["margin"].reshape(-1)[top] == 1.0)
