@@ -311,7 +311,7 @@ __device__ __forceinline__ void head_rows(const GemmArgs &a, const float *tl, co
         const float x = cbase + c < a.n_total ? v[c >> 2][c & 3] * rsc : -INFINITY;
         v[c >> 2][c & 3] = x;
         const bool up = x > t.l1;
-        t.l2 = fmaxf(t.l2, fminf(x, t.l1));
+        t.l2 = up ? t.l1 : fmaxf(t.l2, x);   // a NaN is neither
         t.idx = up ? cbase + c : t.idx;
         t.l1 = up ? x : t.l1;
       }

@@ -2,6 +2,7 @@
 results whichever kernel adds the row up, and no statistic makes a NaN of numbers or a number of a NaN."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2601_23180_amd import model_from_arrays
 from workloads import SHAPES, WeightSource, gen_draft_tokens, gen_kv_cache, gen_tree, tree_depths
@@ -109,7 +110,7 @@ def with_head_row(case, col, row):
     def get(name, layer):
         bits = ws.bits(name, layer)
         if name == "lm_head":
-            bits[col] = bf16_bits(row)
+            bits[col] = np.where(np.isnan(row), np.uint16(0x7FC0), bf16_bits(row))
         return bits
     return model_from_arrays(case.shape, get)
 
@@ -169,3 +170,17 @@ def test_statistics_of_one_infinite_logit(name):
     assert top.any()
     check_statistics(got)
     assert np.all(got["confidence"].reshape(-1)[top] == 1.0) and np.all(got["margin"].reshape(-1)[top] == 1.0)
+
+
+@pytest.mark.parametrize("name", list(HEADS))
+def test_a_nan_logit_does_not_stand_for_the_second_largest(name):
+    case = head_case(name)
+    top = case.run_gpu(0.0)["argmax"].reshape(-1)
+    col = next(int(c) + 1 for c in top if c % 16 < 15 and c + 1 not in top)   # the same thread's, after a largest
+    got = case.run_gpu(0.0, model=with_head_row(case, col, np.full(case.shape.hidden, np.nan)))
+    x = got["logits"].reshape(-1, case.shape.vocab)
+    assert np.isnan(x[:, col]).all()
+    rest = np.sort(np.delete(x, col, axis=1), axis=1)
+    l1, l2 = (got["_ver"].region(r).view(torch.float32)[:len(x)].cpu().numpy() for r in ("node_l1", "node_l2"))
+    assert np.array_equal(l1, rest[:, -1]) and np.array_equal(l2, rest[:, -2])
+    assert np.isnan(got["confidence"]).all()
