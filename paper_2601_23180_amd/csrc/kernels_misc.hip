@@ -428,7 +428,8 @@ __global__ __launch_bounds__(kMaxNodes) void k_decide(DecideArgs a) {
   const int b = blockIdx.x, i = threadIdx.x, M = a.n_nodes;
   if (i < M) {
     const int r = b * M + i;
-    const float s = a.node_sum[r];
+    // no logit above -inf (a row of NaN): the sum is empty, and 1 / 0 would pass every threshold
+    const float s = a.node_l1[r] == -INFINITY ? NAN : a.node_sum[r];
     const float conf = 1.0f / s;                                   // exp(l1 - l1) / sum
     const float p2 = expf(a.node_l2[r] - a.node_l1[r]) / s;        // 0 when there is no second entry
     s_conf[i] = conf;

@@ -1,9 +1,11 @@
 """Values that are not finite, and logits near the end of the fp32 range: a NaN that a row may see reaches its
-results whichever kernel adds the row up, and no statistic makes a NaN of numbers or a number of a NaN."""
+results whichever kernel adds the row up, no statistic makes a NaN of numbers or a number of a NaN, and a node
+whose statistic is a NaN is never trusted."""
 import numpy as np
 import pytest
 import torch
 
+from oracle import CRIT_TOP1
 from paper_2601_23180_amd import model_from_arrays
 from workloads import SHAPES, WeightSource, gen_draft_tokens, gen_kv_cache, gen_tree, tree_depths
 from workloads.gen import bf16_bits
@@ -184,3 +186,19 @@ def test_a_nan_logit_does_not_stand_for_the_second_largest(name):
     l1, l2 = (got["_ver"].region(r).view(torch.float32)[:len(x)].cpu().numpy() for r in ("node_l1", "node_l2"))
     assert np.array_equal(l1, rest[:, -1]) and np.array_equal(l2, rest[:, -2])
     assert np.isnan(got["confidence"]).all()
+
+
+@pytest.mark.parametrize("name", list(HEADS) + ["fp32"])
+def test_a_row_of_nan_logits_is_not_trusted(name):
+    if name == "fp32":
+        case = synthetic_case(SHAPES["tiny"].with_(n_layers=1, vocab=600), 950, (20,), [gen_tree(40, 8, 4, 5)])
+    else:
+        case = head_case(name)
+    model = device_model(case.shape, case.seed)
+    bad = case.shape.vocab - 1
+    model.tensors["embed"][bad].fill_(float("nan"))
+    case.tokens[:, 0] = bad                      # the root: every row
+    got = case.run_gpu(0.0, CRIT_TOP1, model=model)
+    assert np.isnan(got["logits"]).all()
+    assert np.isnan(got["confidence"]).all() and np.isnan(got["margin"]).all() and np.isnan(got["entropy"]).all()
+    assert np.all(got["escalate"] == 1) and np.all(got["token"] == -1) and np.all(got["accepted_len"] == 0)
