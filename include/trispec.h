@@ -219,7 +219,8 @@ int trispec_kv_create_paged(const trispec_model *m, void *k_pool_dev, void *v_po
 int trispec_kv_get_len(const trispec_kv *kv, int32_t *ctx_len_host);
 
 /* Device scratch needed by trispec_verify for up to `batch` sequences of up to
- * `max_nodes` nodes (256-byte aligned buffer).  Errors: TRISPEC_ENULL, TRISPEC_ENODES. */
+ * `max_nodes` nodes, or any other batch and node count of no more than batch * max_nodes rows
+ * (256-byte aligned buffer).  Errors: TRISPEC_ENULL, TRISPEC_ENODES. */
 int trispec_workspace_bytes(const trispec_model *m, int32_t batch, int32_t max_nodes,
                             size_t *bytes);
 

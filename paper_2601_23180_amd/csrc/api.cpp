@@ -249,7 +249,9 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
   // sums of squares per (tile, row): two buffers, a matmul reads its producer's while writing its own
   L.ss_part = take(2 * sizeof(float) * (size_t)ss_tiles_of(c.hidden, 32) * rp);   // sized for the narrowest tile
   const int group = c.n_q_heads / c.n_kv_heads;
-  const size_t prow = f32 ? 0 : (size_t)batch * c.n_kv_heads * (kMaxAttnSplits + (max_nodes + 31) / 32) * group * max_nodes;
+  // context splits and draft blocks of every row: the blocks of the longest tree, so that the size depends on
+  // batch * max_nodes alone and a workspace serves every other division of as many rows
+  const size_t prow = f32 ? 0 : (size_t)rows * c.n_kv_heads * (kMaxAttnSplits + (kMaxNodes + 31) / 32) * group;
   L.attn_o = take(sizeof(float) * prow * c.head_dim);
   L.attn_m = take(sizeof(float) * prow);
   L.attn_l = take(sizeof(float) * prow);

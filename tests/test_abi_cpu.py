@@ -97,6 +97,26 @@ def test_kv_and_workspace_sizes():
     lib.trispec_model_destroy(m)
 
 
+@pytest.mark.parametrize("kw", [dict(), dict(dtype=B.TRISPEC_BF16), dict(dtype=B.TRISPEC_BF16, hidden=1472, ffn=4032,
+                                                                          n_kv_heads=1)], ids=["f32", "bf16", "odd"])
+def test_a_workspace_serves_every_pass_of_no_more_rows(kw):
+    """2 x 30 nodes is as good as 1 x 60: the size grows with batch * nodes alone."""
+    lib = B.lib()
+    rc, m, keep = _model(**kw)
+    n = C.c_size_t()
+    sizes = []
+    for batch in range(1, 9):
+        for nodes in range(1, min(128, 256 // batch) + 1):
+            assert lib.trispec_workspace_bytes(m, batch, nodes, C.byref(n)) == 0
+            sizes.append((batch * nodes, n.value))
+    by_rows = {}
+    for rows, size in sizes:
+        assert by_rows.setdefault(rows, size) == size, rows
+    order = [by_rows[r] for r in sorted(by_rows)]
+    assert order == sorted(order)
+    lib.trispec_model_destroy(m)
+
+
 def _verify_rc(m, kv, parents, n_nodes, *, threshold=0.5, criterion=0, n_forced=1, ws=0x10000,
                ws_bytes=1 << 40, tokens=0x2000, positions=0x3000):
     o = B.VerifyOpts(criterion, n_forced, ws, ws_bytes, None, None, None)
