@@ -223,9 +223,7 @@ __device__ void draft_partial(const AttnArgs &a, int kb, int kvh, int b, int row
 // NW waves, each owning RBW blocks of 32 query rows: a workgroup covers 32 * NW * RBW rows.
 // <KT 128, NW 4>: one workgroup per CU.  <KT 64, NW 8>: 256 rows share every staged K/V tile
 // (trees of more than 128 rows read the cache once, not twice) and two waves per SIMD overlap
-// one another's softmax arithmetic and matrix work: the one in its products goes first (s_setprio),
-// so that the two drift apart instead of taking turns instruction by instruction (four sequences of 60
-// nodes, 32 heads, 16384 keys: 130 -> 124 us; one of 8192 keys 28.2 -> 26.2).
+// one another's softmax arithmetic and matrix work.
 // DRAFT: some workgroups (splits from n_splits on) take a block of draft nodes each instead.
 // PAGED: the cache is in pages of kKvPage slots (a multiple of KT, and every split starts at a
 // multiple of KT, so a tile never straddles two pages): one scalar page lookup per tile.
@@ -389,7 +387,6 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
       for (int ks = 0; ks < KT / 32; ++ks)
 #pragma unroll
         for (int e = 0; e < 16; ++e) s[ks][e] = 0.f;
-      if (NW == 8) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int tt = 0; tt < D / 16; ++tt) {
         bf16x8 kf[KT / 32];
@@ -403,7 +400,6 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
         for (int ks = 0; ks < KT / 32; ++ks)
           s[ks] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], ql[i][tt], s[ks], 0, 0, 0);
       }
-      if (NW == 8) __builtin_amdgcn_s_setprio(0);
       // mask (only the tile in which the context or the split ends: a scalar branch), tile max;
       // the scores arrive scaled: q was pre-multiplied by log2(e) / sqrt(d).  The vector ALU, not
       // the matrix cores, sets the pace of a tile step, so every instruction saved here counts.
@@ -447,7 +443,6 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
 #pragma unroll
           for (int e = 0; e < 16; ++e) oacc[i][db][e] *= alpha;
       }
-      if (NW == 8) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int u = 0; u < KT / 16; ++u) {
         bf16x8 vf[D / 32];
@@ -468,7 +463,6 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
           oacc[i][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], plo[u], oacc[i][db], 0, 0, 0);
       }
     }
-    if (NW == 8) __builtin_amdgcn_s_setprio(0);
     if (t + 1 < n_tiles) store_tile(buf ^ 1, k0 + KT);
     __syncthreads();
   }
