@@ -4,8 +4,10 @@ row counts at both ends of every panel size, reductions of 1, 2, 3 and more 64-d
 test_gpu_parity.py (logits 2e-3 absolute, decisions exact outside flagged ties)."""
 import numpy as np
 import pytest
+import torch
 
 from workloads import SHAPES, gen_tree
+from oracle import adapter
 from test_gpu_parity import full_check, make_case
 
 pytestmark = pytest.mark.gpu
@@ -42,6 +44,41 @@ def test_tile_edges(name, batch, nodes, shape):
     full_check(make_case(shape, seed, [20 + 17 * b for b in range(batch)], parents), thresholds=(0.0, 0.5))
 
 
+# The adapter's plain product: (batch, nodes, hidden, adapter width).  Up to 64 rows k splits that need more tile
+# counters than the layers do (one split instead); more rows: one split in 128- and in 256-column tiles, k splits
+# finished by the second launch, panels of 128 and 256 rows; widths that end inside a tile.
+ADAPTERS = {
+    "rows23_splits": (1, 23, 1472, 132),
+    "rows64_no_counters": (1, 64, 2048, 3204),
+    "rows100_one_split": (1, 100, 256, 200),
+    "rows100_splits_ragged_k": (1, 100, 1472, 132),
+    "rows250_splits": (5, 50, 1024, 260),
+    "rows130_wide_tiles": (2, 65, 64, 16500),
+}
+
+
+@pytest.mark.parametrize("name", list(ADAPTERS))
+def test_adapter_edges(name):
+    batch, nodes, hidden, dim = ADAPTERS[name]
+    shape, seed = TB.with_(hidden=hidden, ffn=256, vocab=300, lm_head_std=0.2), 600 + len(name)
+    case = make_case(shape, seed, [20 + 3 * b for b in range(batch)], [gen_tree(nodes, 9, 4, seed + b) for b in range(batch)])
+    want = case.run_oracle()
+    gpu = case.run_gpu(0.5)
+    rng = np.random.default_rng(seed)
+    w = torch.from_numpy((rng.standard_normal((dim, hidden)) * 0.05).astype(np.float32)).cuda().to(torch.bfloat16)
+    bias = rng.standard_normal(dim).astype(np.float32)
+    ver = gpu["_ver"]
+    out = ver.set_adapter(w, torch.from_numpy(bias).cuda())
+    out.fill_(float("nan"))
+    ver.verify(gpu["_kv"], gpu["_tok"], case.parents, torch.from_numpy(case.positions).cuda(), 0.5)
+    torch.cuda.synchronize()
+    y = out.cpu().numpy().reshape(batch, nodes, dim)
+    for b in range(batch):
+        ref = adapter(want[b]["final_hidden"], w.float().cpu().numpy(), bias)
+        err = np.abs(y[b] - ref).max(axis=1) / np.abs(ref).max(axis=1)
+        assert err.max() <= 3e-4, (b, err.max())     # bf16 hi + lo operands, as test_feature_layers_and_adapter
+
+
 # Who evaluates the draft nodes of an attention call, and with how many rows a workgroup:
 # (batch, nodes, query heads over 2 kv heads, contexts)
 ATTN_CASES = {
@@ -52,7 +89,8 @@ ATTN_CASES = {
     "rows200_own_workgroups": (1, 100, 4, (300,)),
     "rows512_chain_blocks": (1, 128, 8, (65,)),
     "rows128_unequal": (8, 32, 8, (13000, 300, 64, 0, 77, 12999, 500, 9)),
-    "rows80_in_merge": (4, 40, 4, (13000, 128, 0, 5000)),
+    # 32 splits of 512 keys fill the chip, paged or not: the draft nodes stay with the merge
+    "rows80_in_merge": (4, 40, 4, (16380, 128, 0, 5000)),
 }
 
 
@@ -84,8 +122,9 @@ def test_infinite_values_stay_on_their_branch(name):
     """A draft token whose embedding is not finite spoils its own subtree and nothing else.  Blocks of draft
     nodes with such a value are added up node by node instead of by matrix instructions: at most 128 fp32
     terms in another order, 128 * 2^-24 of an attention output of order 1, which the 16-bit high + low
-    operands of the matmuls after it (2^-17 each) and 2 layers carry into logits of up to about 10: the
-    2e-3 of the other cases covers it."""
+    operands of the matmuls after it (2^-17 each) in this one layer carry into logits of up to about 10: the
+    2e-3 of the other cases covers it.  (test_gpu_nonfinite.py has the nodes that are a row's only ancestor in
+    their block.)"""
     from gpu_helpers import device_model
     case = attn_case(name)
     model = device_model(case.shape, case.seed)
