@@ -74,12 +74,13 @@ unsigned long long g_spin_limit = 200000000ull;
 // wavefronts through LDS and has the better stream; it needs reductions of whole chunk pairs.  In the
 // streaming kernel (kernels_gemm_stream.hip) the wavefronts share out the reduction, which allows
 // narrow tiles: less of a partial tile to publish and to add up at the end, where a short matmul spends
-// half its time, against an activation panel read once per 32 or 64 columns.  Measured, 60 rows:
-// 2048 x 6144 22.6 us (128 columns) / 15.7 us (32), 2048 x 2048 14.6 / 10.2, QKV 4096 x 2048 19.0 /
-// 15.0 (64), 6144 x 4096 25.0 / 24.1; gate + up 24576 x 4096 44.2 / 48.1, 6144 x 1024 over 9 rows
-// 8.9 / 9.8; QKV over 32 rows and less: 10.3 / 10.4 and 16.8 / 18.7.  So the two residual products and
-// QKV over more than 32 rows take the streaming kernel, as does whatever the other one cannot: k not a
-// multiple of its chunk pair.  A head of 128 with its own norm needs all of its columns in one tile.
+// half its time, against an activation panel read once per 32 or 64 columns.  Measured, us, 128-column
+// kernel / streaming kernel.  QKV, 64 columns, over 60 rows: 4096 x 1024 18.4 / 14.1, 4096 x 2048 19.5 / 15.2, 6144 x
+// 4096 25.4 / 25.2; over 9 rows: 10.2 / 10.1, 11.2 / 12.3, 17.5 / 20.0; over 30: 12.3 / 10.5, 13.1 / 12.6,
+// 19.9 / 20.0.  Gate + up 24576 x 4096 over 60 rows 44.2 / 48.1, 6144 x 1024 over 9 8.9 / 9.8.  So QKV over
+// more than 32 rows and those residual products that gain (below) take the streaming kernel, as does
+// whatever the other one cannot: k not a multiple of its chunk pair, the adapter's plain product.  A head
+// of 128 with its own norm needs all of its columns in one tile.
 constexpr int kTargetWgs = 192;   // 128-column kernel; swept 128 .. 384 at the 8B shape: 192 - 224 is the flat optimum
 SplitPlan plan_gemm(int epi, int n_cols, int k, int rows_pad, int head_dim, bool qk_norm) {
   const int kb = k / 64, mb = rows_pad / 32;
@@ -105,11 +106,17 @@ SplitPlan plan_gemm(int epi, int n_cols, int k, int rows_pad, int head_dim, bool
   if (epi == EPI_HEAD) return p;
   // The smallest estimated time over tile widths and splits whose workgroups run all at once (one per
   // CU): a workgroup draws weights and activations at about 65 GB/s, needs 4 - 9 us beside that
-  // (growing with its tile) and another 3.5 us to meet the other splits.  A residual product
-  // stays with 128 columns where nothing is gained: over more than 32 rows where 64 columns would win over
-  // 32 (4096 x 12288: 37.0 us for 32, 32.3 - 33.7 for 64, 31.8 for 128), over fewer where 32 would (1024 x
-  // 2048 and 1024 x 3072 over 9 rows: 9.0 us either way, and 32 columns leave the reader four times the
-  // sums of squares; 2048 x 6144, 64 columns: 14.7 -> 12.2).
+  // (growing with its tile) and another 3.5 us to meet the other splits.
+  //
+  // A residual product stays with 128 columns where nothing is gained.  The estimate knows the streaming
+  // kernel only; its preferred width tells the two cases apart.  Measured, us for 128 / 32 / 64 columns.
+  // Over 60 rows 32 is preferred and wins at 1024 x 2048 13.7 / 10.0 / 14.2, 1024 x 3072 14.6 / 10.5 / 15.2,
+  // 2048 x 2048 14.3 / 10.5 / 12.6, 2048 x 6144 22.5 / 15.9 / 17.2, 4096 x 4096 18.6 / 17.5 / 19.4; 64 is at 4096 x
+  // 12288 33.9 / 38.3 / 34.4 and 4096 x 14336 39.4 / 44.5 / 39.6, where the weights outweigh the rest: 128.
+  // Over up to 32 rows 64 is preferred and wins at 2048 x 6144 14.6 / 12.0 / 12.6 (9 rows), 4096 x 4096 14.3 /
+  // 14.8 / 12.5, 4096 x 14336 28.4 / 34.2 / 27.8, and is even at 4096 x 12288 24.8 / 29.4 / 24.8 - 26.2; 32 is at
+  // 1024 x 2048 8.4 / 8.8 / 11.0, 1024 x 3072 8.9 / 9.1 / 11.7, 2048 x 2048 9.4 / 9.7 / 10.1: 128, although over
+  // 30 rows 32 columns take 0.7 us less at those three (9.9 / 9.2, 10.2 / 9.5, 10.0 / 9.2).
   const bool resid = epi == EPI_RESID || epi == EPI_PLAIN;   // the results of any 32 columns stand for themselves
   double best_us = 1e30;
   for (int tn = whole_head ? 128 : (resid ? 32 : 64); tn <= (whole_head ? 128 : 64); tn *= 2) {
@@ -673,8 +680,8 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
     // long context takes 256-row workgroups (eight waves, 64-key tiles), which stage every K/V
     // tile once instead of once per 128-row group; on shorter contexts the two 128-row groups,
     // each with its own CU, finish sooner.  At most 32 (64) rows over up to 128 (64) keys a CU take
-    // k_attn_few (9 nodes, 16 heads on 8: 1000 keys 11.4 -> 7.7 us, 4096 keys 12.3 -> 10.2; 30 nodes, 2048
-    // keys 12.8 -> 12.0); over more its scattered reads cost more than staging (8192 keys: 15.2 / 15.1 us
+    // k_attn_few (9 nodes, 16 heads on 8: 1000 keys 11.4 -> 7.6 us, 4096 keys 12.6 -> 10.6; 30 nodes, 2048
+    // keys 12.7 -> 12.1); over more its scattered reads cost more than staging (8192 keys: 15.2 / 15.1 us
     // for 9 nodes, 17.3 / 23.8 for 30; four sequences of 2048 keys 14.6 / 17.1).
     const int group = c.n_q_heads / c.n_kv_heads;
     const int p_rows = group * n_nodes;

@@ -1,7 +1,9 @@
 // Element-wise half of the matmul epilogues, on a block of RB rows x TN columns of the reduced fp32
 // product: rotary embedding + KV append, residual + next operand + norm statistics, SiLU * up, plain
-// store, LM-head statistics.  Shared by every kernel that finishes a tile (the streaming kernels
-// themselves and k_gemm_finish, which adds up split-K partial tiles).
+// store, LM-head statistics.  Used by k_gemm_stream, k_gemm_wide and k_gemm_finish (which adds up split-K
+// partial tiles).  The 128-column kernel and the layer kernel finish their tiles in gemm_epilogue.hpp, with
+// the same arithmetic written for their layout: a change here belongs there too.  The LM-head statistics
+// (head_rows) are the same code for all.
 #pragma once
 
 #include <type_traits>
@@ -58,9 +60,7 @@ constexpr int ss_width() { return TN < 128 ? TN : 128; }
 // next norm weight), so that they travel together with whatever the caller still waits for; apply()
 // reads the product through red(local row, local column) -> 4 consecutive columns.  rs[lr] is 1/rms
 // of row row0 + lr of the matmul's input.
-// WT: results that a later PHASE of the same launch reads are written through to memory.  MBC: 32-row
-// blocks of the panel where the kernel knows them.
-template <int EPI, int TN, int NT, int RB, bool WT = false, int MBC = 0>
+template <int EPI, int TN, int NT, int RB>
 struct TileEpilogue {
   static constexpr int QG = TN / 8;                          // threads per row: 4 rotation pairs each
   static constexpr int QKV_PASSES = (RB * QG + NT - 1) / NT;
@@ -106,7 +106,7 @@ struct TileEpilogue {
   template <class Red>
   __device__ __forceinline__ void apply(const GemmArgs &a, Red red, const float *rs, int tile, int row0) {
     const int tid = threadIdx.x;
-    const int mb_count = MBC ? MBC : a.rows_pad >> 5;
+    const int mb_count = a.rows_pad >> 5;
     if constexpr (EPI == EPI_QKV) {
       // a tile holds whole heads; thread = (row, 4 rotation pairs)
       const int d = a.head_dim, half = d >> 1;
@@ -200,8 +200,8 @@ struct TileEpilogue {
           lo[e] = (bf16)(o - (float)hi[e]);
         }
         bf16 *dst = (bf16 *)a.act_out;   // operand layout of the down projection (K = ffn)
-        store_bf16x4<WT>(dst + ol_offset(r, feat, 0, mb_count), hi);
-        store_bf16x4<WT>(dst + ol_offset(r, feat, 1, mb_count), lo);
+        *(bf16x4 *)(dst + ol_offset(r, feat, 0, mb_count)) = hi;
+        *(bf16x4 *)(dst + ol_offset(r, feat, 1, mb_count)) = lo;
       }
     } else if constexpr (EPI == EPI_PLAIN) {
       // ---- y = (x W^T) / rms + bias, written as it is (the adapter on the exported features)
@@ -239,7 +239,7 @@ struct TileEpilogue {
           ss[u] = 0.f;
           if (lr < RB && r < a.rows && col_ok) {
             const f32x4 v = xv[u] + red(lr, c);
-            store_f32x4<WT>(a.x_resid_out + (size_t)r * a.n_total + col, v);
+            *(f32x4 *)(a.x_resid_out + (size_t)r * a.n_total + col) = v;
             ss[u] = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
             // operand of the next matmul: x * (next RMSNorm weight), as bf16 hi + lo
             bf16x4 hi, lo;
@@ -250,8 +250,8 @@ struct TileEpilogue {
               lo[e] = (bf16)(o - (float)hi[e]);
             }
             bf16 *dst = (bf16 *)a.xw_out;   // operand layout of the next matmul (K = hidden)
-            store_bf16x4<WT>(dst + ol_offset(r, col, 0, mb_count), hi);
-            store_bf16x4<WT>(dst + ol_offset(r, col, 1, mb_count), lo);
+            *(bf16x4 *)(dst + ol_offset(r, col, 0, mb_count)) = hi;
+            *(bf16x4 *)(dst + ol_offset(r, col, 1, mb_count)) = lo;
           }
         }
         // the UB row sums are reduced side by side, so the exchanges of one hide behind the others'
@@ -262,7 +262,7 @@ struct TileEpilogue {
 #pragma unroll
         for (int u = 0; u < UB; ++u) {
           const int lr = r0 + (ub + u) * RPP, r = row0 + lr;
-          if (tid % SSL == 0 && lr < RB && r < a.rows && col_ok) store_f32<WT>(ssp + r, ss[u]);   // read by the next matmul
+          if (tid % SSL == 0 && lr < RB && r < a.rows && col_ok) ssp[r] = ss[u];   // read by the next matmul
         }
       }
     }

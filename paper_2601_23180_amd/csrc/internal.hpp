@@ -116,11 +116,12 @@ struct GemmArgs {
   int32_t n_splits;
   int32_t n_tiles;
   int32_t stream;      // up to 64 rows: 1 = kernels_gemm_stream.hip, 0 = kernels_gemm.hip
-  int32_t tile_n;      // output columns per workgroup (128 or, more than 64 rows, 256)
+  int32_t tile_n;      // output columns per workgroup: 128; stream 32, 64 or 128; more than 64 rows 128 or 256
   int32_t epi;
   float *out;          // fp32 path, and the PLAIN epilogue: [rows][n_total] fp32
   const float *bias;   // PLAIN epilogue / fp32 path: [n_total] added to every row, or nullptr
-  float *part;         // [n_splits][n_tiles][rows_pad][128] split-K partial tiles
+  float *part;         // [n_splits][n_tiles][rows_pad * tile_n] split-K partial tiles: rows of columns, stream in
+                       // accumulator fragments; more than 64 rows always in 128-column tiles
   int32_t *counters;   // [n_tiles + 1], zero between launches
   // QKV epilogue
   const float *cos_t, *sin_t;
@@ -137,7 +138,7 @@ struct GemmArgs {
   float *x_resid_out;  // the same after it (may be x_resid itself: every element is read and written by one thread)
   void *xw_out;        // bf16 hi/lo panels [rows_pad][n_total]: x * next norm weight
   const void *next_norm_w;  // bf16 [n_total]
-  float *ss_part;      // [n_tiles][rows_pad] sums of squares of the updated rows, per tile
+  float *ss_part;      // [entries][rows_pad] sums of squares of the updated rows, one entry per min(tile_n, 128) columns
   float eps;
   size_t out_panel;    // panel stride (elements) of xw_out / act_out
   // SWIGLU epilogue
@@ -274,7 +275,6 @@ void launch_copy_probe(hipStream_t st, void *dst, const void *src, size_t bytes)
 // (ss == nullptr: x is already normalised and weighted, plain copy)
 void launch_export_hidden(hipStream_t st, int dtype, const float *x, const void *norm_w, const float *ss,
                           int ss_tiles, int rows, int rows_pad, int hidden, float eps, float *out);
-void launch_zero_counters(hipStream_t st, int32_t *counters, int n_counters);
 void launch_qkv_epilogue(hipStream_t st, int dtype, const float *part, int n_splits, int rows,
                          int rows_pad, int n_q_heads, int n_kv_heads, int head_dim,
                          const float *cos_t, const float *sin_t, int n_nodes, CtxLens ctx,

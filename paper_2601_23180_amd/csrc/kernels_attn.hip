@@ -496,7 +496,8 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
 // operands straight from the cache to registers (a wavefront's keys are its own, so LDS would save
 // nothing); the groups' partials are merged through LDS at the end.  A tile's registers are requested
 // again as soon as it has been used.  What bounds it is one chain of memory round trips: rows and first
-// keys, partials out.  FEWFIG
+// keys, partials out.  Over the kernel above: 9 nodes, 16 heads on 8, 1000 keys 11.4 -> 7.6 us, 4096 keys
+// 12.6 -> 10.6; 30 nodes, 2048 keys 12.7 -> 12.1; one node, 32 heads on 8, 1500 keys 11.2 -> 7.4.
 template <int D, int RB, bool PAGED>
 __global__ __launch_bounds__(256, 2) void k_attn_few(AttnArgs a) {
   constexpr int KG = 4 / RB, LD = 33, FW = D / KG / 2;   // key groups; LDS row; features per thread of the merge
@@ -721,14 +722,15 @@ __global__ __launch_bounds__(512) void k_attn_merge(AttnArgs a) {
   d1[0] = (bf16)(o0 - (float)h0); d1[1] = (bf16)(o1 - (float)h1);
 }
 
-// The other merge, where the draft nodes have no workgroups of their own: combine the context splits of one (row, kv head) — all `group` query heads that share the kv
-// head — in ascending split order, with the draft-node part: for every ancestor-or-self j of the
+// The other merge, where the draft nodes have no workgroups of their own: combine the context splits of
+// one (row, kv head) — all `group` query heads that share the kv head — in ascending split order, with
+// the draft-node part: for every ancestor-or-self j of the
 // node, score = q . k_j / sqrt(d) and value v_j, all taken in fp32 from this pass's projections
 // (a.qkv: [row][(nq + 2 nkv) * d], q and k already rotated).
 // Memory round trips, not arithmetic, set this kernel's time: the ancestor mask (one word, quick
 // to arrive) is fetched alone, then everything else — query rows, the first 16 split partials,
 // the ancestors' keys and the first ancestors' values — in ONE round trip.  Block = group * d / 2 threads, two adjacent output features each;
-// the ancestor list (at most 64 nodes) is scored by (slot x quarter of the features) threads.
+// the ancestor list (at most 128 nodes) is scored by (slot x quarter of the features) threads.
 constexpr int kMergePreV = 8;    // ancestors whose values are fetched ahead of the scores
 template <int D>
 __global__ __launch_bounds__(512) void k_attn_merge_tree(AttnArgs a) {

@@ -9,11 +9,11 @@
 // Both come through one ring of equal depth, because loads return in order: a wait for the panel is a
 // wait for every weight requested before it.
 //
-// What bounds it: the panel is read once per 32 or 64 columns, so a CU draws two to three bytes per byte
-// of weights, at 60 - 70 GB/s; below 200 KB a workgroup the chain first data (2.2 us) - sum of the
+// What bounds it: the panel is read once per 32 or 64 columns, so a CU draws 3 or 2 bytes per byte of weights
+// over 32 rows, 5 or 3 over 64 ((2 * columns + 4 * rows) / (2 * columns)), at 60 - 70 GB/s; below 200 KB a workgroup the chain first data (2.2 us) - sum of the
 // wavefronts (1 - 2) - publish and count (1 - 1.8) - read the splits (1.2 - 2.1) - epilogue (0.6 - 1.8).
-// Over 60 rows, 128-column kernel -> this one: 2048 x 6144 22.6 -> 15.5 us, 2048 x 2048 14.6 -> 10.2,
-// 4096 x 2048 (QKV) 19.0 -> 15.1, 4096 x 4096 18.2 -> 17.3; 1472-wide layers (23 blocks of 64) over 46
+// Over 60 rows, 128-column kernel -> this one: 2048 x 6144 22.5 -> 15.8 us, 2048 x 2048 14.3 -> 10.5,
+// 4096 x 2048 (QKV) 19.5 -> 15.2, 4096 x 4096 18.6 -> 17.6; 1472-wide layers (23 blocks of 64) over 46
 // rows: QKV 18.6 -> 14.6, down 17.1 -> 10.9, gate + up 16.3 -> 15.9.
 //
 // The accumulators are added up in fragment order (16-byte LDS accesses); partial tiles go to memory in
@@ -209,7 +209,7 @@ static void dispatch_stream(hipStream_t st, const GemmArgs &a) {
     if (a.rows_pad == 32) hipLaunchKernelGGL((k_gemm_stream<1, NB_, D1_, EPI>), grid, block, 0, st, a); \
     else hipLaunchKernelGGL((k_gemm_stream<2, NB_, D2_, EPI>), grid, block, 0, st, a);        \
   } while (0)
-  if constexpr (EPI != EPI_RESID && EPI != EPI_PLAIN) {
+  if constexpr (EPI == EPI_QKV || EPI == EPI_HEAD) {
     if (a.tile_n == 128) { TS_LAUNCH(4, 6, 3); return; }
   }
   if constexpr (EPI != EPI_HEAD) {

@@ -150,15 +150,6 @@ void launch_begin_pass(hipStream_t st, int dtype, const BeginArgs &a) {
   else hipLaunchKernelGGL(k_begin_pass<bf16>, grid, dim3(256), 0, st, a);
 }
 
-__global__ void k_zero_counters(int32_t *counters, int n_counters) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n_counters) counters[i] = 0;
-}
-
-void launch_zero_counters(hipStream_t st, int32_t *counters, int n_counters) {
-  hipLaunchKernelGGL(k_zero_counters, dim3((n_counters + 255) / 256), dim3(256), 0, st, counters, n_counters);
-}
-
 // Sum of the split-K partials of one output element, ascending split order.
 __device__ __forceinline__ float sum_splits(const float *part, int n_splits, size_t slice, size_t off) {
   float v = part[off];
