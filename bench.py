@@ -348,7 +348,7 @@ def main():
             traffic_note = "profiles/ summary was measured on other kernel sources: not quoted"
 
     g = kernels["gemm"]
-    roofline = {"bound": "hbm", "kernel": "k_gemm_bf16 (weight-streaming projection / FFN matmul)",
+    roofline = {"bound": "hbm", "kernel": "k_gemm_stream (weight-streaming projection / FFN matmul)",
                 "achieved": g["achieved_GBs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": g["achieved_GBs"] / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_note,
                 "avg_launch_us": g["avg_us"], "bytes_per_launch": g["bytes_per_launch"],

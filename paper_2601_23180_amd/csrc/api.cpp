@@ -68,74 +68,87 @@ constexpr int kLayerSplitCap = 8;    // k splits of one matmul inside the layer 
 // magnitude above a whole pass).  trispec_debug_set_spin_limit changes it (tests of the expiry path).
 unsigned long long g_spin_limit = 200000000ull;
 
-// Decomposition of one matmul over at most 64 rows into (column tile, k split) workgroups.
+inline int tiles_of(int n) { return (n + kGemmTileN - 1) / kGemmTileN; }
+// 16-row blocks that the streaming kernel multiplies for a panel of up to 128 rows: 1 to 4, or 8.
+inline int row_blocks(int rows) { return rows <= 64 ? (rows + 15) / 16 : 8; }
+
+// Decomposition of one matmul over at most 128 rows into (column tile, k split) workgroups of the streaming
+// kernel (gemm_stream.hpp): the tile width and the number of splits with the smallest estimated time.
 //
-// Two kernels.  The 128-column kernel (kernels_gemm.hip) shares the activation panel among its four
-// wavefronts through LDS and has the better stream; it needs reductions of whole chunk pairs.  In the
-// streaming kernel (kernels_gemm_stream.hip) the wavefronts share out the reduction, which allows
-// narrow tiles: less of a partial tile to publish and to add up at the end, where a short matmul spends
-// half its time, against an activation panel read once per 32 or 64 columns.  Measured, us, 128-column
-// kernel / streaming kernel.  QKV, 64 columns, over 60 rows: 4096 x 1024 18.4 / 14.1, 4096 x 2048 19.5 / 15.2, 6144 x
-// 4096 25.4 / 25.2; over 9 rows: 10.2 / 10.1, 11.2 / 12.3, 17.5 / 20.0; over 30: 12.3 / 10.5, 13.1 / 12.6,
-// 19.9 / 20.0.  Gate + up 24576 x 4096 over 60 rows 44.2 / 48.1, 6144 x 1024 over 9 8.9 / 9.8.  So QKV over
-// more than 32 rows and those residual products that gain (below) take the streaming kernel, as does
-// whatever the other one cannot: k not a multiple of its chunk pair, the adapter's plain product.  A head
-// of 128 with its own norm needs all of its columns in one tile.
-constexpr int kTargetWgs = 192;   // 128-column kernel; swept 128 .. 384 at the 8B shape: 192 - 224 is the flat optimum
-SplitPlan plan_gemm(int epi, int n_cols, int k, int rows_pad, int head_dim, bool qk_norm) {
-  const int kb = k / 64, mb = rows_pad / 32;
-  const bool whole_head = epi == EPI_QKV && qk_norm && head_dim == 128;
-  SplitPlan wide;   // the 128-column kernel: k splits of whole 512-deep (256-deep) steps, at least 512 deep
-  wide.tile_n = kGemmTileN;
-  wide.n_tiles = (n_cols + kGemmTileN - 1) / kGemmTileN;
-  wide.n_splits = 1;
-  wide.k_per_split = k;
-  const bool chunks = k % (256 * (3 - mb)) == 0;
-  if (epi != EPI_HEAD && chunks) {
-    int s = (kTargetWgs + wide.n_tiles / 2) / wide.n_tiles;
-    if (s > k / 512) s = k / 512;
-    if (s < 1) s = 1;
-    const int per = (k + s - 1) / s;
-    wide.k_per_split = (int)align_up((size_t)per, k % 512 == 0 && (mb == 1 || per >= 1024) ? 512 : 256);
-    wide.n_splits = (k + wide.k_per_split - 1) / wide.k_per_split;
+// A workgroup (one runs per CU) takes 3 us to its first data.  It then draws its weights and its share of the
+// activation panel, 2 bytes a column and 64 a row block and k step, at 45 (one row block) to 60 GB/s; the chip draws no
+// more than 6.3 TB/s of weights.  Meeting the other splits costs 0.8 us and, a row block and column, 0.012 us
+// and 0.002 a split: publish the partial tile, count, read all of them.  So wide tiles draw less of the panel and narrow ones meet
+// sooner.  Estimated / measured, us: 4096 x 4096 over 60 rows 32 columns x 2 splits 17.3 / 16.9, 64 x 4 15.4 / 16.7,
+// 128 x 8 19.3 / 18.8, 16 x 1 22.6 / 19.9; 4096 x 12288 64 x 4 28.6 / 32.6, 32 x 2 39.2 / 38.4; 2048 x 6144 32 x 4 14.6 / 14.3,
+// 64 x 8 16.1 / 15.8; over 9 rows 1024 x 2048 16 x 4 5.5 / 6.5, 16 x 1 7.4 / 6.6, 32 x 2 7.6 / 7.4; over 111 rows
+// 2048 x 6144 32 x 4 19.9 / 19.9, 64 x 8 23.4 / 21.2.
+SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim, bool qk_norm) {
+  const int steps = k / 32;
+  SplitPlan best;
+  best.stream = 1;
+  best.k_per_split = k;
+  best.n_splits = 1;
+  best.tile_n = kGemmTileN;
+  if (epi == EPI_HEAD) {   // widths that the 128-column kernel does not take
+    best.n_tiles = tiles_of(n_cols);
+    return best;
   }
-  if (chunks && (epi == EPI_HEAD || epi == EPI_SWIGLU || (epi == EPI_QKV && (whole_head || mb == 1)))) return wide;
-  SplitPlan p = wide;
-  p.stream = 1;
-  p.k_per_split = k;
-  if (epi == EPI_HEAD) return p;
-  // The smallest estimated time over tile widths and splits whose workgroups run all at once (one per
-  // CU): a workgroup draws weights and activations at about 65 GB/s, needs 4 - 9 us beside that
-  // (growing with its tile) and another 3.5 us to meet the other splits.
-  //
-  // A residual product stays with 128 columns where nothing is gained.  The estimate knows the streaming
-  // kernel only; its preferred width tells the two cases apart.  Measured, us for 128 / 32 / 64 columns.
-  // Over 60 rows 32 is preferred and wins at 1024 x 2048 13.7 / 10.0 / 14.2, 1024 x 3072 14.6 / 10.5 / 15.2,
-  // 2048 x 2048 14.3 / 10.5 / 12.6, 2048 x 6144 22.5 / 15.9 / 17.2, 4096 x 4096 18.6 / 17.5 / 19.4; 64 is at 4096 x
-  // 12288 33.9 / 38.3 / 34.4 and 4096 x 14336 39.4 / 44.5 / 39.6, where the weights outweigh the rest: 128.
-  // Over up to 32 rows 64 is preferred and wins at 2048 x 6144 14.6 / 12.0 / 12.6 (9 rows), 4096 x 4096 14.3 /
-  // 14.8 / 12.5, 4096 x 14336 28.4 / 34.2 / 27.8, and is even at 4096 x 12288 24.8 / 29.4 / 24.8 - 26.2; 32 is at
-  // 1024 x 2048 8.4 / 8.8 / 11.0, 1024 x 3072 8.9 / 9.1 / 11.7, 2048 x 2048 9.4 / 9.7 / 10.1: 128, although over
-  // 30 rows 32 columns take 0.7 us less at those three (9.9 / 9.2, 10.2 / 9.5, 10.0 / 9.2).
-  const bool resid = epi == EPI_RESID || epi == EPI_PLAIN;   // the results of any 32 columns stand for themselves
+  // Widths.  QKV: whole rotation pairs; where q and k have a norm of their own, whole heads (over more than 64
+  // rows in two groups of 64: the accumulators of 128 would not fit).  Residual products: the sums of squares of any
+  // 16 columns stand for themselves.  The adapter's plain product is built in one width.
+  const int widths[] = {16, 32, 48, 64, 96, 112, 128};
   double best_us = 1e30;
-  for (int tn = whole_head ? 128 : (resid ? 32 : 64); tn <= (whole_head ? 128 : 64); tn *= 2) {
+  for (int tn : widths) {
+    int rb = row_blocks(rows), groups = 1;
+    if (epi == EPI_PLAIN) {
+      if (tn != 32) continue;
+    } else if (epi == EPI_SWIGLU) {
+      if (tn == 16 || tn == 128 || (tn == 112 && rb > 4)) continue;
+    } else if (epi == EPI_QKV) {
+      if (tn == 48 || tn == 112 || (qk_norm && tn < head_dim) || (tn == 96 && (qk_norm || head_dim != 128 || rb > 4))) continue;
+      if (tn == 128 && rb > 4) { rb = 4; groups = 2; }
+    } else if (tn == 48 || tn == 96 || tn == 112 || (tn == 128 && rb > 4)) {
+      continue;
+    }
     const int tiles = (n_cols + tn - 1) / tn;
-    const double fixed = tn == 32 ? 4.0 : (mb == 1 ? 5.2 : 9.0);
-    for (int s = 1; s <= 16 && s <= kb && (s == 1 || tiles * s <= 256); ++s) {
-      const double bytes = (double)((kb + s - 1) / s) * 64.0 * (2.0 * tn + 4.0 * rows_pad);
-      const double us = ((tiles * s + 255) / 256) * (bytes / 65e3 + fixed) + (s > 1 ? 3.5 : 0.0);
+    const double rate = rb == 1 ? 45e3 : 60e3, chip_us = 2.0 * n_cols * k / 6.3e6;
+    for (int sp = 1; sp <= 16 && sp <= steps && (sp == 1 || tiles * groups * sp <= 256); ++sp) {
+      const int rounds = (tiles * groups * sp + 255) / 256;
+      const double own_us = rounds * ((steps + sp - 1) / sp) * 32.0 * (2.0 * tn + 64.0 * rb) / rate;
+      double us = 3.0 * rounds + (own_us > chip_us ? own_us : chip_us);
+      if (sp > 1) us += 0.8 + (0.012 + 0.002 * sp) * rb * tn;
       if (us < best_us) {
         best_us = us;
-        p.tile_n = tn;
-        p.n_tiles = tiles;
-        p.n_splits = s;
+        best.tile_n = tn;
+        best.n_tiles = tiles;
+        best.n_splits = sp;
       }
+      if (epi == EPI_SWIGLU) break;   // tiles enough: the kernel has no splits for it
     }
   }
-  return chunks && epi == EPI_RESID && p.tile_n == (mb == 2 ? 64 : 32) ? wide : p;
+  return best;
 }
-inline int tiles_of(int n) { return (n + kGemmTileN - 1) / kGemmTileN; }
+// Tiles that meet at a counter, of one plan: row groups have their own
+inline int counted_tiles(int epi, const SplitPlan &p, int rows) {
+  return p.n_tiles * (epi == EPI_QKV && p.tile_n == 128 && rows > 64 ? 2 : 1);
+}
+// Floats of its partial tiles
+inline size_t stream_part_floats(int epi, const SplitPlan &p, int rows) {
+  const int rb = row_blocks(rows);
+  return p.n_splits < 2 ? 0 : (size_t)p.n_splits * p.n_tiles * p.tile_n * rb * 16;
+}
+// LM head over at most 64 rows: the 128-column kernel (kernels_gemm.hip) shares the activation panel among its
+// wavefronts through LDS; it needs reductions of whole chunk pairs.
+SplitPlan plan_head(int n_cols, int k, int rows, int rows_pad) {
+  if (k % (256 * (3 - rows_pad / 32)) != 0) return plan_stream(EPI_HEAD, n_cols, k, rows, 0, false);
+  SplitPlan p;
+  p.tile_n = kGemmTileN;
+  p.n_tiles = tiles_of(n_cols);
+  p.n_splits = 1;
+  p.k_per_split = k;
+  return p;
+}
 // entries per row of the sums of squares that a matmul with tiles of tile_n columns leaves
 inline int ss_tiles_of(int n, int tile_n) { return tile_n < kGemmTileN ? (n + tile_n - 1) / tile_n : tiles_of(n); }
 
@@ -172,6 +185,13 @@ SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_part_fl
   return best;
 }
 constexpr size_t kWidePartFloats = (size_t)12 << 20;   // partial tiles of one wide matmul: at most 48 MB
+
+SplitPlan plan_any(int epi, int n_cols, int k, int rows, int head_dim, bool qk_norm) {
+  const int rp = rows_pad_for(rows);
+  if (epi == EPI_HEAD && rp <= 64) return plan_head(n_cols, k, rows, rp);
+  if (epi == EPI_HEAD || rp > 128) return plan_wide(epi, n_cols, k, rp, kWidePartFloats);
+  return plan_stream(epi, n_cols, k, rows, head_dim, qk_norm);
+}
 
 // Decomposition of one matmul inside the layer kernel: at most max_items (tile, split) items, every
 // split the same whole number of `unit`-deep steps (unit = ring depth x chunk depth of the kernel
@@ -236,11 +256,12 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
     const int nc[4] = {nqkv, c.hidden, 2 * c.ffn, c.hidden};
     const int ks[4] = {c.hidden, qd, c.hidden, c.ffn};
     size_t floats = (size_t)kLayerPhases * kLayerMaxGrid * kGemmTileN * rp;
+    const int rows_of[] = {16, 32, 48, 64, 128, 256};   // one of every kind of panel
     for (int i = 0; i < 4; ++i)
-      for (int r = 32; r <= 256; r *= 2) {
-        const SplitPlan p = r <= 64 ? plan_gemm(ep[i], nc[i], ks[i], r, c.head_dim, c.qk_norm != 0) : plan_wide(ep[i], nc[i], ks[i], r, kWidePartFloats);
-        if (r <= 64 && p.n_tiles > L.max_tiles) L.max_tiles = p.n_tiles;
-        const size_t f = (size_t)p.n_splits * (r <= 64 ? p.n_tiles * p.tile_n : tiles_of(nc[i]) * kGemmTileN) * r;
+      for (int r : rows_of) {
+        const SplitPlan p = plan_any(ep[i], nc[i], ks[i], r, c.head_dim, c.qk_norm != 0);
+        if (p.stream && counted_tiles(ep[i], p, r) > L.max_tiles) L.max_tiles = counted_tiles(ep[i], p, r);
+        const size_t f = p.stream ? stream_part_floats(ep[i], p, r) : (size_t)p.n_splits * tiles_of(nc[i]) * kGemmTileN * r;
         if (r <= rp && f > floats) floats = f;
       }
     // the layer kernel runs at most kLayerMaxGrid (tile, split) items per matmul and gives each
@@ -254,7 +275,7 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
   L.n_zero = L.abort_index + 1;
   L.counters = take(sizeof(int32_t) * L.n_zero);
   // sums of squares per (tile, row): two buffers, a matmul reads its producer's while writing its own
-  L.ss_part = take(2 * sizeof(float) * (size_t)ss_tiles_of(c.hidden, 32) * rp);   // sized for the narrowest tile
+  L.ss_part = take(2 * sizeof(float) * (size_t)ss_tiles_of(c.hidden, 16) * rp);   // sized for the narrowest tile
   const int group = c.n_q_heads / c.n_kv_heads;
   // context splits and draft blocks of every row: the blocks of the longest tree, so that the size depends on
   // batch * max_nodes alone and a workspace serves every other division of as many rows
@@ -824,7 +845,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
     at.q = ws + L.q;
     at.q_panel = pan_q;
     // ss[0]: written by the embedding (1 tile) and by every down projection; ss[1]: by every O projection
-    float *ss0 = (float *)(ws + L.ss_part), *ss1 = ss0 + (size_t)ss_tiles_of(c.hidden, 32) * rp;
+    float *ss0 = (float *)(ws + L.ss_part), *ss1 = ss0 + (size_t)ss_tiles_of(c.hidden, 16) * rp;
     int o_tiles = tiles_of(c.hidden), dn_tiles = o_tiles;   // sums of squares per row that the O / down projections leave
     auto base = [&](int epi, const void *xin, size_t xpanel, const float *ss_in, int ss_tiles, int k,
                     int n_total, const SplitPlan &p) {
@@ -892,10 +913,10 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
     };
     const bool wide = rp > 64;
     auto plan = [&](int epi, int n_cols, int k) {
-      return wide ? plan_wide(epi, n_cols, k, rp, kWidePartFloats) : plan_gemm(epi, n_cols, k, rp, c.head_dim, c.qk_norm != 0);
+      return plan_any(epi, n_cols, k, rows, c.head_dim, c.qk_norm != 0);
     };
     auto launch_gemm = [&](const GemmArgs &g) {
-      if (wide) launch_gemm_wide(st, g); else if (g.stream) launch_gemm_stream(st, g); else launch_gemm_bf16(st, g);
+      if (g.stream) launch_gemm_stream(st, g); else if (wide) launch_gemm_wide(st, g); else launch_gemm_head(st, g);
     };
     const SplitPlan pq = plan(EPI_QKV, nqkv, c.hidden), po = plan(EPI_RESID, c.hidden, qd);
     const SplitPlan pg = plan(EPI_SWIGLU, 2 * c.ffn, c.hidden), pd = plan(EPI_RESID, c.hidden, c.ffn);
@@ -1004,9 +1025,9 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
     if (opts->adapter_w) {
       // the adapter on the final-norm features: the LM head's operand panels and 1/rms again, another
       // matrix, a plain fp32 result (+ bias)
-      SplitPlan pa = wide ? plan_wide(EPI_PLAIN, opts->adapter_dim, c.hidden, rp, L.part_floats)
-                          : plan_gemm(EPI_PLAIN, opts->adapter_dim, c.hidden, rp, c.head_dim, c.qk_norm != 0);
-      if (!wide && (pa.n_tiles > L.max_tiles || (size_t)pa.n_splits * pa.n_tiles * pa.tile_n * rp > L.part_floats))
+      SplitPlan pa = rp > 128 ? plan_wide(EPI_PLAIN, opts->adapter_dim, c.hidden, rp, L.part_floats)
+                              : plan_stream(EPI_PLAIN, opts->adapter_dim, c.hidden, rows, c.head_dim, c.qk_norm != 0);
+      if (pa.stream && (pa.n_tiles > L.max_tiles || stream_part_floats(EPI_PLAIN, pa, rows) > L.part_floats))
         pa.n_splits = 1;   // no counters for that many tiles, or no room
       GemmArgs g = base(EPI_PLAIN, h, pan_h, ss0, dn_tiles, c.hidden, opts->adapter_dim, pa);
       g.seg[0] = {opts->adapter_w, opts->adapter_dim, 0};

@@ -68,6 +68,19 @@ __device__ __forceinline__ void store_f32x4(float *p, f32x4 v) {
     *(f32x4 *)p = v;
   }
 }
+// 16 bytes a lane, written through to memory, at byte offset `off` of the `bytes` long buffer at `base` (the same
+// in every lane); past its end nothing is written.  A wavefront then writes whole 128-byte lines; as two 8-byte
+// atomic stores (store_f32x4<true>) every line goes out in two halves.
+struct ThroughBuffer {
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ __forceinline__ ThroughBuffer(float *base, uint32_t bytes)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00027000)) {}
+  __device__ __forceinline__ void store(uint32_t off, f32x4 v) const {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int kAgentScope = 16;   // sc1: through the L2, as an agent-scope atomic store
+    __builtin_amdgcn_raw_buffer_store_b128(*(u32x4 *)&v, rsrc, off, 0, kAgentScope);
+  }
+};
 template <bool WT>
 __device__ __forceinline__ void store_bf16x4(bf16 *p, bf16x4 v) {
   if constexpr (WT) {

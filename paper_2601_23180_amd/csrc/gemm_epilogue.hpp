@@ -1,4 +1,4 @@
-// Epilogue of the weight-streaming matmul kernel (see kernels_gemm.hip), written for any number
+// Epilogue of the layer kernel's matmuls (kernels_layer.hip), written for any number
 // of wavefronts per workgroup and of 32-column sub-tiles per wavefront.
 #pragma once
 
@@ -72,22 +72,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, f32x16 (&acc)[N
   static_assert(MB % MG == 0, "row groups must tile the rows");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ln = lane & 31, g = lane >> 5;
-  if (EPI == EPI_HEAD) {
-    // ---- per row, reduce this tile's TN logits to (l1, column, l2, sum exp)
-    float *tl = (float *)lds;
-    __syncthreads();
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          tl[(mb * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * (TN + 4) + (wave * NB + nb) * 32 + ln] = acc[nb][mb][e];
-    __syncthreads();
-    head_rows<TN, NT, MB * 32, TN + 4>(a, tl, s_rs, tile, 0);
-    return;
-  }
-
   // ---- hand the tile to the epilogue, as an fp32 tile in LDS.  One split: straight from the
   // accumulators.  Several splits: write-through partial tiles part[split][tile][row][TN] + a
   // counter per tile; only the last workgroup to arrive goes on.

@@ -28,17 +28,19 @@ struct RowScale {
 #pragma unroll
     for (int u = 0; u < PRE; ++u) x[u] = a.ss_in[(size_t)min(q + Q * u, a.ss_tiles - 1) * a.rows_pad + r];
   }
-  __device__ __forceinline__ void finish(const GemmArgs &a, int row0, float *s_tmp, float *s_rs) {
-    const int tid = threadIdx.x;
-    if (a.ss_in != nullptr) {
-      const int r = min(row0 + tid % ROWS, a.rows_pad - 1), q = tid / ROWS;
-      float v = 0.f;
+  // partial(): this thread's entries; total(), after a barrier: the threads of a row.  The caller synchronises
+  // the workgroup before s_rs is read.
+  __device__ __forceinline__ void partial(const GemmArgs &a, int row0, float *s_tmp) {
+    if (a.ss_in == nullptr) return;
+    const int tid = threadIdx.x, r = min(row0 + tid % ROWS, a.rows_pad - 1), q = tid / ROWS;
+    float v = 0.f;
 #pragma unroll
-      for (int u = 0; u < PRE; ++u) v += (q + Q * u < a.ss_tiles) ? x[u] : 0.f;
-      for (int t = q + Q * PRE; t < a.ss_tiles; t += Q) v += a.ss_in[(size_t)t * a.rows_pad + r];
-      s_tmp[tid] = v;
-    }
-    __syncthreads();
+    for (int u = 0; u < PRE; ++u) v += (q + Q * u < a.ss_tiles) ? x[u] : 0.f;
+    for (int t = q + Q * PRE; t < a.ss_tiles; t += Q) v += a.ss_in[(size_t)t * a.rows_pad + r];
+    s_tmp[tid] = v;
+  }
+  __device__ __forceinline__ void total(const GemmArgs &a, const float *s_tmp, float *s_rs) {
+    const int tid = threadIdx.x;
     if (tid < ROWS) {
       float ss = 0.f;
       if (a.ss_in != nullptr) {
@@ -47,6 +49,11 @@ struct RowScale {
       }
       s_rs[tid] = a.ss_in != nullptr ? 1.0f / sqrtf(ss / (float)a.k + a.eps) : 1.0f;
     }
+  }
+  __device__ __forceinline__ void finish(const GemmArgs &a, int row0, float *s_tmp, float *s_rs) {
+    partial(a, row0, s_tmp);
+    __syncthreads();
+    total(a, s_tmp, s_rs);
     __syncthreads();
   }
 };
@@ -54,6 +61,17 @@ struct RowScale {
 // Columns that one entry of the per-(tile, row) sums of squares covers.
 template <int TN>
 constexpr int ss_width() { return TN < 128 ? TN : 128; }
+
+// Column of the concatenated q, k, v projections that local column c of a QKV tile holds.  A tile of up to d
+// columns takes TN / 2 consecutive rotation pairs of one head: their low features, then their high ones; a
+// wider one whole heads.
+template <int TN>
+__device__ __forceinline__ int qkv_column(int tile, int c, int d) {
+  const int half = d >> 1;
+  if (TN / 2 > half) return tile * TN + c;
+  const int up = c >= TN / 2, p = tile * (TN / 2) + (up ? c - TN / 2 : c), head = p / half;
+  return head * d + p - head * half + (up ? half : 0);
+}
 
 // NT threads work on rows row0 .. row0 + RB - 1 and on columns tile * TN .. + TN of the product.
 // preload() issues the loads that do not depend on the product (rotary tables; residual rows and the
@@ -72,15 +90,12 @@ struct TileEpilogue {
   bf16x4 pre_nw;
 
   // Where 4 rotation pairs sit: columns c_lo .. and c_lo + off .. of the tile, features j .. and
-  // j + d/2 .. of head `head` of the concatenated q, k, v heads.  A 64-column tile holds a head of 64,
-  // or one half of the pairs of a head of 128 (features 32p .. 32p + 31 and 64 + 32p ..).
+  // j + d/2 .. of head `head` of the concatenated q, k, v heads.
   struct Pair { int c_lo, off, j, head; };
   static __device__ __forceinline__ Pair qkv_pair(int tile, int qi, int d) {
-    if constexpr (TN == 64) {
-      if (d == 128) return {qi * 4, 32, 32 * (tile & 1) + qi * 4, tile >> 1};
-    }
-    const int half = d >> 1, hl = (qi * 4) / half, j = qi * 4 - hl * half;
-    return {hl * d + j, half, j, (tile * TN + hl * d) / d};
+    const int half = d >> 1, p = tile * (TN / 2) + qi * 4, head = p / half, j = p - head * half;
+    if (TN / 2 <= half) return {qi * 4, TN / 2, j, head};
+    return {(head * d - tile * TN) + j, half, j, head};
   }
 
   __device__ __forceinline__ void preload(const GemmArgs &a, int tile, int row0) {

@@ -112,16 +112,16 @@ struct GemmArgs {
   int32_t k;           // reduction length
   int32_t rows;        // valid rows
   int32_t rows_pad;    // 32, 64, 128 or 256
-  int32_t k_per_split; // multiple of 64 (up to 64 rows; wider panels: the 64-deep blocks of k shared out evenly)
+  int32_t k_per_split; // of the layer kernel; the other kernels share k out evenly
   int32_t n_splits;
   int32_t n_tiles;
-  int32_t stream;      // up to 64 rows: 1 = kernels_gemm_stream.hip, 0 = kernels_gemm.hip
-  int32_t tile_n;      // output columns per workgroup: 128; stream 32, 64 or 128; more than 64 rows 128 or 256
+  int32_t stream;      // 1 = gemm_stream.hpp
+  int32_t tile_n;      // output columns per workgroup: 128; stream 16 .. 128; more than 128 rows 128 or 256
   int32_t epi;
   float *out;          // fp32 path, and the PLAIN epilogue: [rows][n_total] fp32
   const float *bias;   // PLAIN epilogue / fp32 path: [n_total] added to every row, or nullptr
-  float *part;         // [n_splits][n_tiles][rows_pad * tile_n] split-K partial tiles: rows of columns, stream in
-                       // accumulator fragments; more than 64 rows always in 128-column tiles
+  float *part;         // [n_splits][n_tiles][rows * tile_n] split-K partial tiles: rows of columns, stream in
+                       // accumulator fragments; more than 128 rows always in 128-column tiles
   int32_t *counters;   // [n_tiles + 1], zero between launches
   // QKV epilogue
   const float *cos_t, *sin_t;
@@ -288,8 +288,8 @@ void launch_reduce_swiglu(hipStream_t st, int dtype, const float *part, int n_sp
 void launch_gemm_f32(hipStream_t st, const GemmArgs &a);
 size_t packed_weight_bytes(int n_rows, int k);
 void launch_pack_weights(hipStream_t st, const void *w, int n_rows, int k, void *out);
-void launch_gemm_bf16(hipStream_t st, const GemmArgs &a);   // up to 64 rows: 4 wavefronts, 128-column tiles
-void launch_gemm_stream(hipStream_t st, const GemmArgs &a);   // up to 64 rows: 8 wavefronts share the reduction, tile_n = 32, 64 or 128
+void launch_gemm_head(hipStream_t st, const GemmArgs &a);   // LM head, up to 64 rows: 4 wavefronts, 128-column tiles
+void launch_gemm_stream(hipStream_t st, const GemmArgs &a);   // up to 128 rows: wavefronts share the reduction, tile_n = 16 .. 128
 void launch_gemm_wide(hipStream_t st, const GemmArgs &a);   // more rows: tile_n = 256 or 128 columns, k splits of whole 64-deep blocks
 void launch_stats_from_logits(hipStream_t st, const float *logits, int rows, int vocab,
                               const HeadStats &hs);

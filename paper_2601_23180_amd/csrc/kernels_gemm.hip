@@ -1,5 +1,5 @@
-// Weight-streaming small-M matmul on the matrix cores (bf16 weights, fp32 accumulate) with the
-// surrounding element-wise work fused in.
+// LM head over at most 64 rows: weight-streaming small-M matmul on the matrix cores (bf16 weights, fp32
+// accumulate) with the vocabulary statistics fused in, and the one-time repack of the weights.
 //
 //   y[r][n] = rstd[r] * sum_k X[r][k] * W[n][k]        r < rows_pad <= 64
 //
@@ -29,23 +29,14 @@
 // index inside a 64 block is permuted (lane half g owns k = 32g + 8j + 0..7 at MFMA step j)
 // identically for both operands.
 //
-// Work = (tile of 128 output columns) x (k split).  Every workgroup stores its fp32 partial tile;
-// the LAST workgroup to finish a tile (an atomic counter per tile) sums the splits in ascending
-// order — so the result does not depend on scheduling — and applies the tile's epilogue:
-//   QKV    rotary embedding, fp32 q/k/v for the attention kernels, bf16 K and V^T cache append
-//   RESID  residual add into the fp32 stream, operand panels (x * next norm weight, hi/lo) for
-//          the next matmul, per-row sum of squares of the tile (the consumer turns the tile sums
-//          into 1/rms — a second chip-wide counter here costs more than re-adding 32 numbers)
-//   SWIGLU SiLU(gate) * up as operand panels (a tile holds 64 gate columns and the matching 64
-//          up columns)
-//   HEAD   (LM head, no k split) per-row (largest logit, its column, second largest, sum of exp)
-//          of the tile's 128 logits — the probabilities are never materialised.
-#include "gemm_epilogue.hpp"
+// A workgroup takes 128 output columns over the whole reduction and leaves, per row, (largest logit, its column,
+// second largest, sum of exp) of them; the probabilities are never materialised.
+#include "gemm_tile.hpp"
 
 namespace ts {
 
-template <int MB, int KC, int EPI, int DEPTH>
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
+template <int MB, int KC, int DEPTH>
+__global__ __launch_bounds__(256) void k_gemm_head(GemmArgs a) {
   constexpr int KB = KC / 64;                 // 64-deep k blocks per chunk
   constexpr int FRAGS = KB * 4 * MB * 2;      // 1 KB operand fragments per chunk (operand layout)
   constexpr int BUF = FRAGS * 1024;           // one LDS stage
@@ -53,7 +44,6 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
   constexpr int EPI_BYTES = MB * 32 * (kGemmTileN + 4) * 4;   // the epilogue's fp32 tile reuses the stages
   constexpr int LDS_BYTES = 2 * BUF > EPI_BYTES ? 2 * BUF : EPI_BYTES;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
-  __shared__ int s_last;
   __shared__ float s_rs[kMaxRows];   // 1/rms of the rows of the matmul's input
   __shared__ float s_tmp[4 * kMaxRows];
 
@@ -62,56 +52,28 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
   // loads from the kernel arguments, not with a vector load that the first weight request waits for
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, g = lane >> 5;
-  const int tile = blockIdx.x, split = blockIdx.y;
-  const int k_begin = split * a.k_per_split;
-  const int klen = min(a.k, k_begin + a.k_per_split) - k_begin;
-  const int n_chunks = (klen + KC - 1) / KC;
+  const int tile = blockIdx.x;
+  const int n_chunks = (a.k + KC - 1) / KC;
   // Workgroups that run side by side start at different depths of their k range (and wrap
   // around), so that they do not all walk the memory channels in lockstep.  The order of the
-  // additions is still a fixed function of (tile, split).
-  const int rot = (int)((blockIdx.x * 11u + blockIdx.y * 5u) % (unsigned)n_chunks);
+  // additions is still a fixed function of the tile.
+  const int rot = (int)((blockIdx.x * 11u) % (unsigned)n_chunks);
   auto rc = [&](int c) { const int cc = c + rot; return cc >= n_chunks ? cc - n_chunks : cc; };
 
-  // ---- this wavefront's packed sub-tile.  Plain tiles: 4 consecutive sub-tiles of the
-  // concatenated segments.  SWIGLU tiles: waves 0,1 -> gate sub-tiles 2t, 2t+1; waves 2,3 -> the
-  // same sub-tiles of the up projection.
-  int sidx, sub;
-  if (EPI == EPI_SWIGLU) {
-    sidx = wave >> 1;
-    sub = 2 * tile + (wave & 1);
-  } else {
-    const int n0 = tile * kGemmTileN + wave * 32;
-    sidx = 0;
-    if (a.n_seg > 1 && n0 >= a.seg[1].col0) sidx = 1;
-    if (a.n_seg > 2 && n0 >= a.seg[2].col0) sidx = 2;
-    const int col0 = sidx == 0 ? a.seg[0].col0 : (sidx == 1 ? a.seg[1].col0 : a.seg[2].col0);
-    sub = (n0 - col0) >> 5;
-  }
-  const bf16 *wseg = (const bf16 *)(sidx == 0 ? a.seg[0].w : (sidx == 1 ? a.seg[1].w : a.seg[2].w));
-  const int seg_rows = sidx == 0 ? a.seg[0].n_rows : (sidx == 1 ? a.seg[1].n_rows : a.seg[2].n_rows);
-  // clamped to the segment's last sub-tile: always valid memory (idle wavefronts of a ragged last
-  // tile compute on it and their columns are never stored)
-  sub = min(max(sub, 0), ((seg_rows + 31) >> 5) - 1);
-  const bf16 *wrow = wseg + ((size_t)sub * (a.k >> 6) + (k_begin >> 6)) * 2048 + lane * 8;
+  // ---- this wavefront's packed sub-tile, clamped to the last one: always valid memory (idle wavefronts of a
+  // ragged last tile compute on it and their columns are never stored)
+  const int sub = min(tile * 4 + wave, ((a.seg[0].n_rows + 31) >> 5) - 1);
+  const bf16 *wrow = (const bf16 *)a.seg[0].w + (size_t)sub * (a.k >> 6) * 2048 + lane * 8;
 
   // ---- X staging: the chunk is a contiguous run of FRAGS fragments in operand layout; this
   // wavefront copies fragments wave*XV .. wave*XV + XV-1, 16 bytes per lane each
-  const bf16 *xg = (const bf16 *)a.x + ((size_t)(k_begin >> 6) * 4 * MB * 2 + wave * XV) * 512 + lane * 8;
+  const bf16 *xg = (const bf16 *)a.x + (size_t)wave * XV * 512 + lane * 8;
 
-  // 1/rms of every row of the matmul's INPUT (used by the epilogue).  With the deep ring, requested ahead
-  // of everything else and finished with the prologue: up to 128 entries a row come in one round trip (a
-  // residual product in 32-column tiles leaves one per 32 columns); fetched after the stream they cost
-  // 4 us.  With the shallow one, for short reductions over few columns, requested here and finished after
-  // the stream: the barrier in the prologue would cost them 0.5 us each.
-  constexpr bool EARLY = DEPTH > 2;
+  // 1/rms of every row of the matmul's INPUT, requested ahead of everything else and finished with the
+  // prologue: up to 128 entries a row come in one round trip; fetched after the stream they cost 4 us.
   RowScale<256, MB * 32, 16 * MB> scale;
-  float rs_in[(MB + 1) / 2][8];
-  if constexpr (EARLY) {
-    scale.issue(a, 0);
-    __builtin_amdgcn_sched_barrier(0);
-  } else {
-    rstd_load<256, MB>(a, rs_in);
-  }
+  scale.issue(a, 0);
+  __builtin_amdgcn_sched_barrier(0);
 
   f32x16 acc[MB];
 #pragma unroll
@@ -205,8 +167,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) load_w_block(d, d, kb);
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (EARLY) scale.finish(a, 0, s_tmp, s_rs);   // ends with a barrier
-  else __syncthreads();
+  scale.finish(a, 0, s_tmp, s_rs);   // ends with a barrier
   int c0 = 0;
   for (; c0 + DEPTH < n_chunks; c0 += DEPTH) {
 #pragma unroll
@@ -228,9 +189,15 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs a) {
     if (d + 1 < DEPTH) __syncthreads();
   }
 
-  if constexpr (!EARLY) rstd_finish<256, MB>(a, rs_in, s_tmp, s_rs);
+  // ---- per row, this tile's 128 logits to (l1, column, l2, sum exp)
+  float *tl = (float *)lds;
   __syncthreads();   // every wavefront is done reading the last X stage
-  gemm_epilogue<MB, EPI, 4>(a, reinterpret_cast<f32x16(&)[1][MB]>(acc), lds, &s_last, s_rs, tile, split);
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) tl[(mb * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * (kGemmTileN + 4) + wave * 32 + ln] = acc[mb][e];
+  __syncthreads();
+  head_rows<kGemmTileN, 256, MB * 32, kGemmTileN + 4>(a, tl, s_rs, tile, 0);
 }
 
 // One-time repack of a row-major [n_rows, k] bf16 matrix into the layout above.  One thread per
@@ -259,30 +226,16 @@ void launch_pack_weights(hipStream_t st, const void *w, int n_rows, int k, void 
                      (const bf16 *)w, n_rows, k, (uint4 *)out, n_pieces);
 }
 
-template <int EPI>
-static void dispatch(hipStream_t st, const GemmArgs &a) {
-  dim3 grid(a.n_tiles, a.n_splits), block(256);
+void launch_gemm_head(hipStream_t st, const GemmArgs &a) {
+  const dim3 grid(a.n_tiles), block(256);
 #define TS_LAUNCH(MB_, KC_)                                                                   \
   do {                                                                                        \
-    if (a.k_per_split % (4 * KC_) == 0 && a.k % (4 * KC_) == 0)                               \
-      hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, 4>), grid, block, 0, st, a);             \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_gemm_bf16<MB_, KC_, EPI, 2>), grid, block, 0, st, a);             \
+    if (a.k % (4 * KC_) == 0) hipLaunchKernelGGL((k_gemm_head<MB_, KC_, 4>), grid, block, 0, st, a); \
+    else hipLaunchKernelGGL((k_gemm_head<MB_, KC_, 2>), grid, block, 0, st, a);               \
   } while (0)
-  switch (a.rows_pad) {
-    case 32: TS_LAUNCH(1, 256); break;
-    default: TS_LAUNCH(2, 128); break;   // 64; larger panels: kernels_gemm_wide.hip
-  }
+  if (a.rows_pad == 32) TS_LAUNCH(1, 256);
+  else TS_LAUNCH(2, 128);   // 64; larger panels: kernels_gemm_wide.hip
 #undef TS_LAUNCH
-}
-
-void launch_gemm_bf16(hipStream_t st, const GemmArgs &a) {
-  switch (a.epi) {
-    case EPI_QKV: dispatch<EPI_QKV>(st, a); break;
-    case EPI_RESID: dispatch<EPI_RESID>(st, a); break;
-    case EPI_SWIGLU: dispatch<EPI_SWIGLU>(st, a); break;
-    default: dispatch<EPI_HEAD>(st, a); break;
-  }
 }
 
 }  // namespace ts

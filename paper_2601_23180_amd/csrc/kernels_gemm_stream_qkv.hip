@@ -1,0 +1,8 @@
+// Streaming kernel (gemm_stream.hpp): QKV projections.
+#include "gemm_stream.hpp"
+
+namespace ts {
+
+void launch_gemm_stream_qkv(hipStream_t st, const GemmArgs &a) { dispatch_rows<EPI_QKV>(st, a); }
+
+}  // namespace ts

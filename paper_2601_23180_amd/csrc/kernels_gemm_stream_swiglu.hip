@@ -1,0 +1,8 @@
+// Streaming kernel (gemm_stream.hpp): gate + up products.
+#include "gemm_stream.hpp"
+
+namespace ts {
+
+void launch_gemm_stream_swiglu(hipStream_t st, const GemmArgs &a) { dispatch_rows<EPI_SWIGLU>(st, a); }
+
+}  // namespace ts

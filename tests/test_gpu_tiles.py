@@ -26,7 +26,15 @@ CASES = [
     ("rows64_whole_heads", 1, 64, TB.with_(hidden=1344, ffn=1024, n_q_heads=8, qk_norm=True, vocab=129,
                                            lm_head_std=0.2)),
     ("rows64_chunks", 4, 16, TB.with_(hidden=2048, ffn=2560, n_q_heads=16, n_kv_heads=8, lm_head_std=0.15)),
+    # every tile width: gate + up 48, 96 and 112 columns, QKV 96, runs that are no whole number of rounds, 8 wavefronts and 4
+    ("rows60_qkv96_gate_up48", 1, 60, TB.with_(hidden=4096, ffn=6144, n_q_heads=32, n_kv_heads=8, lm_head_std=0.1)),
+    ("rows16_gate_up112_odd_head64", 1, 16, TB.with_(hidden=448, ffn=14336, head_dim=64, n_q_heads=7, n_kv_heads=7,
+                                                     lm_head_std=0.3)),
+    ("rows48_gate_up96_ragged", 3, 16, TB.with_(hidden=576, ffn=12352, n_q_heads=4, lm_head_std=0.3)),
+    ("rows17_wide_down", 1, 17, TB.with_(hidden=4096, ffn=4096, n_q_heads=2, lm_head_std=0.1)),
     # more than 64 rows
+    ("rows100_gate_up96", 1, 100, TB.with_(hidden=512, ffn=12288, lm_head_std=0.3)),
+    ("rows111_whole_heads", 3, 37, TB.with_(hidden=1024, ffn=6144, n_q_heads=16, n_kv_heads=8, qk_norm=True, lm_head_std=0.2)),
     ("rows65_one_block", 1, 65, TB.with_(hidden=64, ffn=64, head_dim=64, n_q_heads=1, n_kv_heads=1, lm_head_std=0.8)),
     ("rows96_two_blocks", 3, 32, TB.with_(hidden=128, ffn=128, lm_head_std=0.6)),
     ("rows128_three_blocks_ragged", 2, 64, TB.with_(hidden=192, ffn=320, head_dim=64, n_q_heads=6, n_kv_heads=3,
