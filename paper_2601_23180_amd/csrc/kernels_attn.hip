@@ -102,6 +102,18 @@ struct AttnLds {
   static constexpr int kBuf = kBytesK + kBytesV;  // one stage
 };
 
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+// Elements e and e + 1 of the high and the low part of a probability operand: one conversion for two values.
+__device__ __forceinline__ void split_pair(f32x2 p, bf16x8 &hi, bf16x8 &lo, int e) {
+  const bf16x2 h = __builtin_convertvector(p, bf16x2);
+  const f32x2 rest = {p[0] - (float)h[0], p[1] - (float)h[1]};
+  const bf16x2 l = __builtin_convertvector(rest, bf16x2);
+  hi[e] = h[0]; hi[e + 1] = h[1];
+  lo[e] = l[0]; lo[e + 1] = l[1];
+}
+constexpr float kAttnSlack = 8.f;   // log2 units that a score may exceed the running reference by
+
 // Maximum, in natural-log units, that a partial is stored with.  -inf marks a partial without keys, which the
 // merge skips without reading it; one whose scores are all NaN (fmaxf drops them) or all -inf has to be
 // added up all the same, so that the NaN in its sums reaches the row: it is stored with the lowest finite value.
@@ -367,6 +379,9 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
     }
   }
   store_tile(0, k_begin);
+  // Long loops: the query rows have arrived before them.  A wait for them inside the loop could not tell them from the
+  // next tile's loads, which may or may not have been issued since, and would drain those in every step.
+  if (NW == 8) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
   __syncthreads();
 
   for (int t = 0; t < n_tiles; ++t) {
@@ -418,31 +433,61 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, s[ks][e]);
       tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-      const float m_new = fmaxf(m_run[i], tmax);
-      const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(m_run[i] - m_safe);   // exp2(-inf) = 0 on the first tile
-      m_run[i] = m_new;
-      float psum = 0.f;
+      float alpha = 1.f, psum = 0.f;
       bf16x8 phi[KT / 16], plo[KT / 16];
+      if constexpr (NW == 8) {
+        // Long loops, two wavefronts a SIMD: what the vector ALU does adds to the products' time.  So the reference
+        // that exponents are taken against moves only when some row of the wavefront outgrows it by 2^8 (probabilities
+        // up to 256 lose nothing: high and low part are relative, the sums are fp32), which makes the 64
+        // multiplications of the accumulators rare, and two probabilities are converted at a time: 131 -> 125 us
+        // for 4 x 60 nodes over 16384 keys.  (With four wavefronts and two or three tiles neither pays: 17.6 -> 17.9.)
+        if (__builtin_amdgcn_ballot_w64(tmax > m_run[i] + kAttnSlack) != 0) {   // also from -inf, on the first keys
+          const float m_new = fmaxf(m_run[i], tmax);
+          alpha = __builtin_amdgcn_exp2f(m_run[i] - (m_new == -INFINITY ? 0.f : m_new));   // exp2(-inf) = 0
+          m_run[i] = m_new;
+          if (t > 0) {
 #pragma unroll
-      for (int ks = 0; ks < KT / 32; ++ks)
+            for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float p = __builtin_amdgcn_exp2f(s[ks][e] - m_safe);   // exp2(-inf) = 0 for masked keys
-          psum += p;
-          const bf16 hi = (bf16)p;
-          const bf16 lo = (bf16)(p - (float)hi);
-          phi[ks * 2 + (e >> 3)][e & 7] = hi;
-          plo[ks * 2 + (e >> 3)][e & 7] = lo;
+              for (int e = 0; e < 16; ++e) oacc[i][db][e] *= alpha;
+          }
         }
-      l_run[i] = l_run[i] * alpha + psum;
-      // O^T[feature][row] = alpha * O^T + V^T P^T, the feature blocks interleaved for the same reason
-      if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // the running maximum of some row moved
+        const float m_safe = (m_run[i] == -INFINITY) ? 0.f : m_run[i];
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db)
+        for (int ks = 0; ks < KT / 32; ++ks)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) oacc[i][db][e] *= alpha;
+          for (int e = 0; e < 16; e += 2) {
+            const f32x2 p = {__builtin_amdgcn_exp2f(s[ks][e] - m_safe), __builtin_amdgcn_exp2f(s[ks][e + 1] - m_safe)};   // exp2(-inf) = 0 for masked keys
+            psum += p[0];
+            psum += p[1];
+            split_pair(p, phi[ks * 2 + (e >> 3)], plo[ks * 2 + (e >> 3)], e & 7);
+          }
+        l_run[i] = l_run[i] * alpha + psum;
+      } else {
+        const float m_new = fmaxf(m_run[i], tmax);
+        const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+        alpha = __builtin_amdgcn_exp2f(m_run[i] - m_safe);   // exp2(-inf) = 0 on the first tile
+        m_run[i] = m_new;
+#pragma unroll
+        for (int ks = 0; ks < KT / 32; ++ks)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const float p = __builtin_amdgcn_exp2f(s[ks][e] - m_safe);   // exp2(-inf) = 0 for masked keys
+            psum += p;
+            const bf16 hi = (bf16)p;
+            const bf16 lo = (bf16)(p - (float)hi);
+            phi[ks * 2 + (e >> 3)][e & 7] = hi;
+            plo[ks * 2 + (e >> 3)][e & 7] = lo;
+          }
+        l_run[i] = l_run[i] * alpha + psum;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // the running maximum of some row moved
+#pragma unroll
+          for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) oacc[i][db][e] *= alpha;
+        }
       }
+      // O^T[feature][row] = alpha * O^T + V^T P^T, the feature blocks interleaved for the same reason
 #pragma unroll
       for (int u = 0; u < KT / 16; ++u) {
         bf16x8 vf[D / 32];
@@ -728,8 +773,9 @@ __global__ __launch_bounds__(512) void k_attn_merge(AttnArgs a) {
 // node, score = q . k_j / sqrt(d) and value v_j, all taken in fp32 from this pass's projections
 // (a.qkv: [row][(nq + 2 nkv) * d], q and k already rotated).
 // Memory round trips, not arithmetic, set this kernel's time: the ancestor mask (one word, quick
-// to arrive) is fetched alone, then everything else — query rows, the first 16 split partials,
-// the ancestors' keys and the first ancestors' values — in ONE round trip.  Block = group * d / 2 threads, two adjacent output features each;
+// to arrive) is requested first, the query rows and the first 16 split partials right behind it, and the
+// ancestors' keys and the first ancestors' values, whose addresses need the mask, while those are on their way
+// (60 nodes, 32 heads: 10.3 us with the partials behind the mask's arrival, 9.7 now; 9 x 4 nodes 6.9 -> 6.1).  Block = group * d / 2 threads, two adjacent output features each;
 // the ancestor list (at most 128 nodes) is scored by (slot x quarter of the features) threads.
 constexpr int kMergePreV = 8;    // ancestors whose values are fetched ahead of the scores
 template <int D>
@@ -750,14 +796,7 @@ __global__ __launch_bounds__(512) void k_attn_merge_tree(AttnArgs a) {
   // ---- the ancestor list first: one word per workgroup arrives quickly, and every address of
   // the second group of loads depends on it
   const AncMask mask = a.anc[r];           // bit j: node j is on the root path of this node (self included)
-  const int n_anc = mask.count();          // >= 1
-  for (int j = tid; j < kMaxNodes; j += nt)
-    if (mask.has(j)) s_anc[mask.rank(j)] = j;
-  __syncthreads();
-
-  // ---- one round trip for everything else: the query rows, the
-  // first 16 split partials of this thread's outputs, the values of the first ancestors and the
-  // keys of the first batch of ancestors
+  // what does not depend on it follows at once: the query rows and the first 16 split partials of this thread's outputs
   const float2 q2 = *(const float2 *)(a.qkv + (size_t)r * n_total + (size_t)(kvh * group + al) * D + f);
   float pm[16], pl[16];
   float2 po[16];
@@ -768,6 +807,13 @@ __global__ __launch_bounds__(512) void k_attn_merge_tree(AttnArgs a) {
     pl[i] = a.part_l[idx];
     po[i] = *(const float2 *)(a.part_o + idx * D + f);
   }
+  __builtin_amdgcn_sched_barrier(0);
+  const int n_anc = mask.count();          // >= 1
+  for (int j = tid; j < kMaxNodes; j += nt)
+    if (mask.has(j)) s_anc[mask.rank(j)] = j;
+  __syncthreads();
+
+  // ---- the values of the first ancestors and the keys of the first batch of ancestors
   const float *vbase = a.qkv + (size_t)(a.n_q_heads + a.n_kv_heads + kvh) * D + f;
   float2 vpre[kMergePreV];
 #pragma unroll
