@@ -139,14 +139,22 @@ inline size_t stream_part_floats(int epi, const SplitPlan &p, int rows) {
   return p.n_splits < 2 ? 0 : (size_t)p.n_splits * p.n_tiles * p.tile_n * rb * 16;
 }
 // LM head over at most 64 rows: the 128-column kernel (kernels_gemm.hip) shares the activation panel among its
-// wavefronts through LDS; it needs reductions of whole chunk pairs.
+// wavefronts through LDS; it needs reductions of whole chunk pairs.  n_splits is the number of passes of a
+// workgroup, n_tiles the entries that all of them leave: one pass each, but for more than 512 tiles (two workgroups a CU)
+// over at most 32 rows, where 512 workgroups share the sub-tiles of 32 out.
+constexpr int kHeadPlaces = 512;
+inline int head_places(int n_cols) { return tiles_of(n_cols) < kHeadPlaces ? tiles_of(n_cols) : kHeadPlaces; }
+inline int head_passes(int n_cols) {
+  const int n_sub = (n_cols + 31) / 32, places = head_places(n_cols);
+  return ((n_sub + places - 1) / places + 3) / 4;
+}
 SplitPlan plan_head(int n_cols, int k, int rows, int rows_pad) {
   if (k % (256 * (3 - rows_pad / 32)) != 0) return plan_stream(EPI_HEAD, n_cols, k, rows, 0, false);
   SplitPlan p;
   p.tile_n = kGemmTileN;
-  p.n_tiles = tiles_of(n_cols);
-  p.n_splits = 1;
   p.k_per_split = k;
+  p.n_splits = rows_pad == 32 ? head_passes(n_cols) : 1;
+  p.n_tiles = rows_pad == 32 ? head_places(n_cols) * p.n_splits : tiles_of(n_cols);
   return p;
 }
 // entries per row of the sums of squares that a matmul with tiles of tile_n columns leaves
@@ -227,7 +235,9 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
   const int nqkv = qd + 2 * kvd;
   L.rows_max = rows;
   L.rows_pad_max = rp;
-  L.head_tiles = f32 ? 1 : tiles_of(c.vocab);   // 128-column tiles; wide panels use half as many
+  // entries per row: 128-column tiles (wide panels use half as many), or the passes of the 128-column kernel
+  const int head_entries = head_places(c.vocab) * head_passes(c.vocab);
+  L.head_tiles = f32 ? 1 : (tiles_of(c.vocab) > head_entries ? tiles_of(c.vocab) : head_entries);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   L.anc = take(sizeof(AncMask) * kMaxRows);

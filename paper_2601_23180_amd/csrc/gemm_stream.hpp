@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
     }
   __syncthreads();
   if constexpr (EPI == EPI_HEAD)
-    head_rows<TN, NT, ROWS, LD>(a, tl, s_rs, tile, row0);
+    head_rows<TN, NT, ROWS, LD>(a, tl, s_rs, tile * TN, min((tile + 1) * TN, a.n_total), tile, row0);
   else
     epi.apply(a, [&](int lr, int c) { return *(const f32x4 *)(tl + lr * LD + c); }, s_rs, tile, row0);
 }

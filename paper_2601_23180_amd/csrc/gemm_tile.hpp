@@ -297,17 +297,18 @@ __device__ __forceinline__ float exp_neg(float x) {
   return __builtin_fmaf(e, r * 0.693147180559945f, e);
 }
 
-// LM head: rows row0 .. row0 + RB - 1 of a tile's TN logits, in LDS as tl[lr * LD + column], to
-// (largest logit, its column, second largest, sum of exp, sum of exp * distance) per row; TN / 16
-// threads scan a row, 16 columns each.  rs[lr]: 1/rms of the row's input.
+// LM head: rows row0 .. row0 + RB - 1 of the logits of columns col0 .. col_end - 1 (TN at most), in LDS as
+// tl[lr * LD + column], to (largest logit, its column, second largest, sum of exp, sum of exp * distance) per
+// row, entry `entry` of it; TN / 16 threads scan a row, 16 columns each.  rs[lr]: 1/rms of the row's input.
 template <int TN, int NT, int RB, int LD>
-__device__ __forceinline__ void head_rows(const GemmArgs &a, const float *tl, const float *rs, int tile, int row0) {
+__device__ __forceinline__ void head_rows(const GemmArgs &a, const float *tl, const float *rs, int col0, int col_end,
+                                          int entry, int row0) {
   constexpr int PARTS = TN / 16, RP = NT / PARTS;
   const int tid = threadIdx.x, srow = tid / PARTS, part = tid % PARTS;
   if (a.debug_logits != nullptr) {   // materialised logits: consecutive threads write consecutive columns
     for (int i = tid; i < RB * TN; i += NT) {
-      const int lr = i / TN, c = i % TN, r = row0 + lr, col = tile * TN + c;
-      if (r < a.rows && col < a.n_total) a.debug_logits[(size_t)r * a.n_total + col] = tl[lr * LD + c] * rs[lr];
+      const int lr = i / TN, c = i % TN, r = row0 + lr, col = col0 + c;
+      if (r < a.rows && col < col_end) a.debug_logits[(size_t)r * a.n_total + col] = tl[lr * LD + c] * rs[lr];
     }
   }
 #pragma unroll
@@ -315,7 +316,7 @@ __device__ __forceinline__ void head_rows(const GemmArgs &a, const float *tl, co
     const int lr = rp + srow, r = row0 + lr;
     const bool in = lr < RB;
     const float rsc = in && r < a.rows ? rs[lr] : 1.0f;
-    const int cbase = tile * TN + part * 16;
+    const int cbase = col0 + part * 16;
     Top2 t = top2_empty();
     if (in) {
       f32x4 v[4];
@@ -323,7 +324,7 @@ __device__ __forceinline__ void head_rows(const GemmArgs &a, const float *tl, co
       for (int q = 0; q < 4; ++q) v[q] = *(const f32x4 *)(tl + lr * LD + part * 16 + 4 * q);
 #pragma unroll
       for (int c = 0; c < 16; ++c) {   // ascending: the lowest column of equal maxima stays
-        const float x = cbase + c < a.n_total ? v[c >> 2][c & 3] * rsc : -INFINITY;
+        const float x = cbase + c < col_end ? v[c >> 2][c & 3] * rsc : -INFINITY;
         v[c >> 2][c & 3] = x;
         const bool up = x > t.l1;
         t.l2 = up ? t.l1 : fmaxf(t.l2, x);   // a NaN is neither
@@ -346,7 +347,7 @@ __device__ __forceinline__ void head_rows(const GemmArgs &a, const float *tl, co
 #pragma unroll
     for (int o = 1; o < PARTS; o <<= 1) t = top2_merge(t, top2_shfl_xor(t, o));
     if (part == 0 && in && r < a.rows) {
-      const size_t o = (size_t)r * a.hs.n_tiles + tile;
+      const size_t o = (size_t)r * a.hs.n_tiles + entry;
       a.hs.l1[o] = t.l1; a.hs.l2[o] = t.l2; a.hs.sumexp[o] = t.s; a.hs.ent[o] = t.t; a.hs.idx[o] = t.idx;
     }
   }

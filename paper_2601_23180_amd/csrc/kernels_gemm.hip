@@ -29,14 +29,20 @@
 // index inside a 64 block is permuted (lane half g owns k = 32g + 8j + 0..7 at MFMA step j)
 // identically for both operands.
 //
-// A workgroup takes 128 output columns over the whole reduction and leaves, per row, (largest logit, its column,
-// second largest, sum of exp) of them; the probabilities are never materialised.
+// A workgroup takes up to 128 output columns at a time over the whole reduction and leaves, per row, (largest
+// logit, its column, second largest, sum of exp) of them; the probabilities are never materialised.
+//
+// Two workgroups run per CU (at most 256 registers a lane).  Over at most 32 rows a vocabulary of more tiles than that is
+// shared out evenly in sub-tiles of 32: every workgroup makes the same number of passes over runs of neighbouring
+// sub-tiles, and the chip has no last wave that is a third full (1187 tiles on 512 places).  151936 columns over 9
+// rows of 1024 83 -> 66 us (one workgroup a CU and a tile each before), over one row of 4096 211 -> 206.  Over 60 rows the
+// panel, drawn once per pass, outweighs that (256 -> 295 us): a tile each.
 #include "gemm_tile.hpp"
 
 namespace ts {
 
 template <int MB, int KC, int DEPTH>
-__global__ __launch_bounds__(256) void k_gemm_head(GemmArgs a) {
+__global__ __launch_bounds__(256, MB == 1 ? 2 : 1) void k_gemm_head(GemmArgs a) {
   constexpr int KB = KC / 64;                 // 64-deep k blocks per chunk
   constexpr int FRAGS = KB * 4 * MB * 2;      // 1 KB operand fragments per chunk (operand layout)
   constexpr int BUF = FRAGS * 1024;           // one LDS stage
@@ -52,34 +58,29 @@ __global__ __launch_bounds__(256) void k_gemm_head(GemmArgs a) {
   // loads from the kernel arguments, not with a vector load that the first weight request waits for
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, g = lane >> 5;
-  const int tile = blockIdx.x;
   const int n_chunks = (a.k + KC - 1) / KC;
   // Workgroups that run side by side start at different depths of their k range (and wrap
   // around), so that they do not all walk the memory channels in lockstep.  The order of the
-  // additions is still a fixed function of the tile.
+  // additions is still a fixed function of the workgroup.
   const int rot = (int)((blockIdx.x * 11u) % (unsigned)n_chunks);
   auto rc = [&](int c) { const int cc = c + rot; return cc >= n_chunks ? cc - n_chunks : cc; };
 
-  // ---- this wavefront's packed sub-tile, clamped to the last one: always valid memory (idle wavefronts of a
-  // ragged last tile compute on it and their columns are never stored)
-  const int sub = min(tile * 4 + wave, ((a.seg[0].n_rows + 31) >> 5) - 1);
-  const bf16 *wrow = (const bf16 *)a.seg[0].w + (size_t)sub * (a.k >> 6) * 2048 + lane * 8;
+  // ---- this workgroup's sub-tiles, and its passes over at most four of them
+  const int n_sub = (a.seg[0].n_rows + 31) >> 5, n_pass = MB == 1 ? a.n_splits : 1;
+  const int s_begin = (int)((long long)n_sub * blockIdx.x / gridDim.x), s_count = (int)((long long)n_sub * (blockIdx.x + 1) / gridDim.x) - s_begin;
 
   // ---- X staging: the chunk is a contiguous run of FRAGS fragments in operand layout; this
   // wavefront copies fragments wave*XV .. wave*XV + XV-1, 16 bytes per lane each
   const bf16 *xg = (const bf16 *)a.x + (size_t)wave * XV * 512 + lane * 8;
 
   // 1/rms of every row of the matmul's INPUT, requested ahead of everything else and finished with the
-  // prologue: up to 128 entries a row come in one round trip; fetched after the stream they cost 4 us.
-  RowScale<256, MB * 32, 16 * MB> scale;
+  // prologue: 64 or 128 entries a row come in one round trip; fetched after the stream they cost 4 us.
+  RowScale<256, MB * 32> scale;
   scale.issue(a, 0);
   __builtin_amdgcn_sched_barrier(0);
 
   f32x16 acc[MB];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[mb][e] = 0.f;
+  const bf16 *wrow;   // this wavefront's packed sub-tile
 
   // The streaming loop is kept free of branches around loads: a load behind a branch makes the
   // wait-count analysis assume it may not have been issued, which turns every wait into "drain
@@ -152,52 +153,64 @@ __global__ __launch_bounds__(256) void k_gemm_head(GemmArgs a) {
     }
   };
 
-  // n_chunks is a multiple of DEPTH (DEPTH even).  The prologue issues its loads in the order
-  // the steady state does (X of a chunk before the W refill of the same step), so the wait
-  // counts merged at the loop head are the steady-state ones.
-  load_x(0);
+  for (int pass = 0; pass < n_pass; ++pass) {
+    const int s0 = s_begin + s_count * pass / n_pass, s1 = s_begin + s_count * (pass + 1) / n_pass;
+    // wavefronts beyond the run take its last sub-tile again (its lines are on their way already); their columns
+    // are not looked at.  A run may be empty: its entries say so.
+    wrow = (const bf16 *)a.seg[0].w + (size_t)min(min(s0 + wave, max(s1 - 1, s0)), n_sub - 1) * (a.k >> 6) * 2048 + lane * 8;
 #pragma unroll
-  for (int kb = 0; kb < KB; ++kb) load_w_block(0, 0, kb);
-  __builtin_amdgcn_sched_barrier(0);
-  store_x(0);
-  load_x(1);
-  __builtin_amdgcn_sched_barrier(0);
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-  for (int d = 1; d < DEPTH; ++d)
+      for (int e = 0; e < 16; ++e) acc[mb][e] = 0.f;
+    if (pass > 0) __syncthreads();   // the previous pass has read its logits
+    // n_chunks is a multiple of DEPTH (DEPTH even).  The prologue issues its loads in the order
+    // the steady state does (X of a chunk before the W refill of the same step), so the wait
+    // counts merged at the loop head are the steady-state ones.
+    load_x(0);
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) load_w_block(d, d, kb);
-  __builtin_amdgcn_sched_barrier(0);
-  scale.finish(a, 0, s_tmp, s_rs);   // ends with a barrier
-  int c0 = 0;
-  for (; c0 + DEPTH < n_chunks; c0 += DEPTH) {
+    for (int kb = 0; kb < KB; ++kb) load_w_block(0, 0, kb);
+    __builtin_amdgcn_sched_barrier(0);
+    store_x(0);
+    load_x(1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int d = 1; d < DEPTH; ++d)
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) load_w_block(d, d, kb);
+    __builtin_amdgcn_sched_barrier(0);
+    if (pass == 0) scale.finish(a, 0, s_tmp, s_rs);   // ends with a barrier
+    else __syncthreads();
+    int c0 = 0;
+    for (; c0 + DEPTH < n_chunks; c0 += DEPTH) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        store_x((d + 1) & 1);                                    // chunk c0+d+1
+        load_x(min(c0 + d + 2, n_chunks - 1));   // clamped, never a branch
+        __builtin_amdgcn_sched_barrier(0);
+        compute_chunk(d, d & 1, c0 + d + DEPTH, true);
+        __syncthreads();
+      }
+    }
+    // last DEPTH chunks: nothing left to fetch from W
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
-      store_x((d + 1) & 1);                                    // chunk c0+d+1
-      load_x(min(c0 + d + 2, n_chunks - 1));   // clamped, never a branch
+      if (d + 1 < DEPTH) store_x((d + 1) & 1);
+      if (d + 2 < DEPTH) load_x(c0 + d + 2);
       __builtin_amdgcn_sched_barrier(0);
-      compute_chunk(d, d & 1, c0 + d + DEPTH, true);
-      __syncthreads();
+      compute_chunk(d, d & 1, 0, false);
+      if (d + 1 < DEPTH) __syncthreads();
     }
-  }
-  // last DEPTH chunks: nothing left to fetch from W
-#pragma unroll
-  for (int d = 0; d < DEPTH; ++d) {
-    if (d + 1 < DEPTH) store_x((d + 1) & 1);
-    if (d + 2 < DEPTH) load_x(c0 + d + 2);
-    __builtin_amdgcn_sched_barrier(0);
-    compute_chunk(d, d & 1, 0, false);
-    if (d + 1 < DEPTH) __syncthreads();
-  }
 
-  // ---- per row, this tile's 128 logits to (l1, column, l2, sum exp)
-  float *tl = (float *)lds;
-  __syncthreads();   // every wavefront is done reading the last X stage
+    // ---- per row, this tile's 128 logits to (l1, column, l2, sum exp)
+    float *tl = (float *)lds;
+    __syncthreads();   // every wavefront is done reading the last X stage
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) tl[(mb * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * (kGemmTileN + 4) + wave * 32 + ln] = acc[mb][e];
-  __syncthreads();
-  head_rows<kGemmTileN, 256, MB * 32, kGemmTileN + 4>(a, tl, s_rs, tile, 0);
+      for (int e = 0; e < 16; ++e) tl[(mb * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * (kGemmTileN + 4) + wave * 32 + ln] = acc[mb][e];
+    __syncthreads();
+    head_rows<kGemmTileN, 256, MB * 32, kGemmTileN + 4>(a, tl, s_rs, s0 * 32, min(s1 * 32, a.n_total), (int)blockIdx.x * n_pass + pass, 0);
+  }
 }
 
 // One-time repack of a row-major [n_rows, k] bf16 matrix into the layout above.  One thread per
@@ -227,15 +240,10 @@ void launch_pack_weights(hipStream_t st, const void *w, int n_rows, int k, void 
 }
 
 void launch_gemm_head(hipStream_t st, const GemmArgs &a) {
-  const dim3 grid(a.n_tiles), block(256);
-#define TS_LAUNCH(MB_, KC_)                                                                   \
-  do {                                                                                        \
-    if (a.k % (4 * KC_) == 0) hipLaunchKernelGGL((k_gemm_head<MB_, KC_, 4>), grid, block, 0, st, a); \
-    else hipLaunchKernelGGL((k_gemm_head<MB_, KC_, 2>), grid, block, 0, st, a);               \
-  } while (0)
-  if (a.rows_pad == 32) TS_LAUNCH(1, 256);
-  else TS_LAUNCH(2, 128);   // 64; larger panels: kernels_gemm_wide.hip
-#undef TS_LAUNCH
+  const dim3 grid(a.n_tiles / a.n_splits), block(256);
+  if (a.rows_pad == 32) hipLaunchKernelGGL((k_gemm_head<1, 128, 4>), grid, block, 0, st, a);
+  else if (a.k % 512 == 0) hipLaunchKernelGGL((k_gemm_head<2, 128, 4>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_gemm_head<2, 128, 2>), grid, block, 0, st, a);   // 64; larger panels: kernels_gemm_wide.hip
 }
 
 }  // namespace ts

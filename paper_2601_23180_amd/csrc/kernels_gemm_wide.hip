@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256) void k_gemm_wide(GemmArgs a) {
     }
     __syncthreads();
     if constexpr (EPI == EPI_HEAD)
-      head_rows<TN, 256, 32, LD>(a, tl, s_rs + mb * 32, tile, row0);
+      head_rows<TN, 256, 32, LD>(a, tl, s_rs + mb * 32, tile * TN, min((tile + 1) * TN, a.n_total), tile, row0);
     else
       epi.apply(a, [&](int lr, int cc) { return *(const f32x4 *)(tl + lr * LD + cc); }, s_rs + mb * 32, tile, row0);
   }

@@ -32,6 +32,9 @@ CASES = [
                                                      lm_head_std=0.3)),
     ("rows48_gate_up96_ragged", 3, 16, TB.with_(hidden=576, ffn=12352, n_q_heads=4, lm_head_std=0.3)),
     ("rows17_wide_down", 1, 17, TB.with_(hidden=4096, ffn=4096, n_q_heads=2, lm_head_std=0.1)),
+    # LM head: more tiles than places over at most 32 rows (two passes of two or three sub-tiles, a ragged last one)
+    ("rows9_vocab_passes", 1, 9, TB.with_(hidden=512, ffn=256, vocab=70001, lm_head_std=0.3)),
+    ("rows32_vocab_passes", 4, 8, TB.with_(hidden=512, ffn=256, vocab=132000, lm_head_std=0.3)),
     # more than 64 rows
     ("rows100_gate_up96", 1, 100, TB.with_(hidden=512, ffn=12288, lm_head_std=0.3)),
     ("rows111_whole_heads", 3, 37, TB.with_(hidden=1024, ffn=6144, n_q_heads=16, n_kv_heads=8, qk_norm=True, lm_head_std=0.2)),
