@@ -708,13 +708,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_few(AttnArgs a) {
 
 // Combine the partials of one (row, kv head) — all `group` query heads that share the kv head: context
 // splits, then draft blocks, in ascending order.  Memory round trips, not arithmetic, set its time: up to
-// kMergeBatch partials of a thread are requested at once.  Block = group * d / 2 threads, two adjacent
-// output features each.
+// NB partials of a thread are requested at once, the smallest of 6, 12 and 20 that holds them all (a request beyond the
+// last partial would fetch it again, and its registers cost wavefronts in flight: 128 nodes, 12 partials, 8.0 us
+// with 20 requested, 6.8 with 12).  Block = group * d / 2 threads, two adjacent output features each.
 constexpr int kMergeBatch = 20;   // 16 context splits and the draft blocks of 128 nodes
 // e^x through the hardware exp2 (about 1e-7 |x| relative error; the arguments here are <= 0)
 __device__ __forceinline__ float fast_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
 
-template <int D>
+template <int D, int NB>
 __global__ __launch_bounds__(512) void k_attn_merge(AttnArgs a) {
   const int r = blockIdx.x, kvh = blockIdx.y, tid = threadIdx.x;
   const int M = a.n_nodes, group = a.n_q_heads / a.n_kv_heads;
@@ -724,11 +725,11 @@ __global__ __launch_bounds__(512) void k_attn_merge(AttnArgs a) {
   const int al = tid / (D / 2), f = (tid - al * (D / 2)) * 2;   // head, first feature
   if (al >= group) return;
   const int p = al * M + node;
-  float pm[kMergeBatch], pl[kMergeBatch];
-  float2 po[kMergeBatch];
+  float pm[NB], pl[NB];
+  float2 po[NB];
   auto request = [&](int s0) {
 #pragma unroll
-    for (int i = 0; i < kMergeBatch; ++i) {
+    for (int i = 0; i < NB; ++i) {
       const size_t idx = (base + min(s0 + i, n - 1)) * p_rows + p;
       pm[i] = a.part_m[idx];
       pl[i] = a.part_l[idx];
@@ -738,8 +739,8 @@ __global__ __launch_bounds__(512) void k_attn_merge(AttnArgs a) {
   request(0);
   float m_tot = -INFINITY;
 #pragma unroll
-  for (int i = 0; i < kMergeBatch; ++i) m_tot = fmaxf(m_tot, i < n ? pm[i] : -INFINITY);
-  for (int s0 = kMergeBatch; s0 < n; s0 += 16) {   // long contexts only
+  for (int i = 0; i < NB; ++i) m_tot = fmaxf(m_tot, i < n ? pm[i] : -INFINITY);
+  for (int s0 = NB; s0 < n; s0 += 16) {   // long contexts only
     float t[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) t[i] = a.part_m[(base + min(s0 + i, n - 1)) * p_rows + p];
@@ -747,10 +748,10 @@ __global__ __launch_bounds__(512) void k_attn_merge(AttnArgs a) {
     for (int i = 0; i < 16; ++i) m_tot = fmaxf(m_tot, t[i]);
   }
   float num0 = 0.f, num1 = 0.f, den = 0.f;
-  for (int s0 = 0; s0 < n; s0 += kMergeBatch) {
+  for (int s0 = 0; s0 < n; s0 += NB) {
     if (s0 > 0) request(s0);
 #pragma unroll
-    for (int i = 0; i < kMergeBatch; ++i) {
+    for (int i = 0; i < NB; ++i) {
       if (s0 + i >= n || pm[i] == -INFINITY) continue;   // no key in it: its o was never written
       const float w = fast_exp(pm[i] - m_tot);
       num0 += po[i].x * w;
@@ -773,12 +774,14 @@ __global__ __launch_bounds__(512) void k_attn_merge(AttnArgs a) {
 // node, score = q . k_j / sqrt(d) and value v_j, all taken in fp32 from this pass's projections
 // (a.qkv: [row][(nq + 2 nkv) * d], q and k already rotated).
 // Memory round trips, not arithmetic, set this kernel's time: the ancestor mask (one word, quick
-// to arrive) is requested first, the query rows and the first 16 split partials right behind it, and the
+// to arrive) is requested first, the query rows and the first NB split partials right behind it, and the
 // ancestors' keys and the first ancestors' values, whose addresses need the mask, while those are on their way
-// (60 nodes, 32 heads: 10.3 us with the partials behind the mask's arrival, 9.7 now; 9 x 4 nodes 6.9 -> 6.1).  Block = group * d / 2 threads, two adjacent output features each;
+// (60 nodes, 32 heads: 10.3 us with the partials behind the mask's arrival, 9.7 now; 9 x 4 nodes 6.9 -> 6.1).
+// NB: 8 where that holds every split, else 16 (4 x 60 nodes, 8 splits: 26.4 us with 16 requested, 21.7 with 8; 9 x 4 nodes
+// 6.1 -> 5.4).  Block = group * d / 2 threads, two adjacent output features each;
 // the ancestor list (at most 128 nodes) is scored by (slot x quarter of the features) threads.
 constexpr int kMergePreV = 8;    // ancestors whose values are fetched ahead of the scores
-template <int D>
+template <int D, int NB>
 __global__ __launch_bounds__(512) void k_attn_merge_tree(AttnArgs a) {
   __shared__ float s_q[kMaxGroup][D];
   __shared__ float s_sc[kMaxGroup][kMaxNodes];
@@ -796,12 +799,12 @@ __global__ __launch_bounds__(512) void k_attn_merge_tree(AttnArgs a) {
   // ---- the ancestor list first: one word per workgroup arrives quickly, and every address of
   // the second group of loads depends on it
   const AncMask mask = a.anc[r];           // bit j: node j is on the root path of this node (self included)
-  // what does not depend on it follows at once: the query rows and the first 16 split partials of this thread's outputs
+  // what does not depend on it follows at once: the query rows and the first NB split partials of this thread's outputs
   const float2 q2 = *(const float2 *)(a.qkv + (size_t)r * n_total + (size_t)(kvh * group + al) * D + f);
-  float pm[16], pl[16];
-  float2 po[16];
+  float pm[NB], pl[NB];
+  float2 po[NB];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
+  for (int i = 0; i < NB; ++i) {
     const size_t idx = (base + min(i, a.n_splits - 1)) * p_rows + p;
     pm[i] = a.part_m[idx];
     pl[i] = a.part_l[idx];
@@ -857,19 +860,19 @@ __global__ __launch_bounds__(512) void k_attn_merge_tree(AttnArgs a) {
   float m_tot = -INFINITY;
   for (int i = 0; i < n_anc; ++i) m_tot = fmaxf(m_tot, s_sc[al][i]);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) m_tot = fmaxf(m_tot, (i < a.n_splits) ? pm[i] : -INFINITY);
-  for (int s0 = 16; s0 < a.n_splits; s0 += 16) {   // long contexts only
-    float t[16];
+  for (int i = 0; i < NB; ++i) m_tot = fmaxf(m_tot, (i < a.n_splits) ? pm[i] : -INFINITY);
+  for (int s0 = NB; s0 < a.n_splits; s0 += NB) {   // long contexts only
+    float t[NB];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) t[i] = (s0 + i < a.n_splits) ? a.part_m[(base + s0 + i) * p_rows + p] : -INFINITY;
+    for (int i = 0; i < NB; ++i) t[i] = (s0 + i < a.n_splits) ? a.part_m[(base + s0 + i) * p_rows + p] : -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) m_tot = fmaxf(m_tot, t[i]);
+    for (int i = 0; i < NB; ++i) m_tot = fmaxf(m_tot, t[i]);
   }
   float num0 = 0.f, num1 = 0.f, den = 0.f;
-  for (int s0 = 0; s0 < a.n_splits; s0 += 16) {    // ascending split order
+  for (int s0 = 0; s0 < a.n_splits; s0 += NB) {    // ascending split order
     if (s0 > 0) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
+      for (int i = 0; i < NB; ++i) {
         const size_t idx = (base + min(s0 + i, a.n_splits - 1)) * p_rows + p;
         pm[i] = a.part_m[idx];
         pl[i] = a.part_l[idx];
@@ -877,7 +880,7 @@ __global__ __launch_bounds__(512) void k_attn_merge_tree(AttnArgs a) {
       }
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < NB; ++i) {
       if (s0 + i >= a.n_splits || pm[i] == -INFINITY) continue;   // empty split: its o / l were never written
       const float w = fast_exp(pm[i] - m_tot);
       num0 += po[i].x * w;
@@ -943,10 +946,18 @@ static void launch_attn_bf16_d(hipStream_t st, const AttnArgs &a) {
 #undef TS_ATTN
   const int group = a.n_q_heads / a.n_kv_heads;
   const int merge_threads = group * D / 2 < 64 ? 64 : group * D / 2;   // <= 512 (group <= 8, d <= 128)
-  if (a.draft_mode == kDraftInMerge)
-    hipLaunchKernelGGL(k_attn_merge_tree<D>, dim3(a.batch * a.n_nodes, a.n_kv_heads), dim3(merge_threads), 0, st, a);
-  else
-    hipLaunchKernelGGL(k_attn_merge<D>, dim3(a.batch * a.n_nodes, a.n_kv_heads), dim3(merge_threads), 0, st, a);
+  const dim3 mgrid(a.batch * a.n_nodes, a.n_kv_heads), mblock(merge_threads);
+  const int n = a.n_splits + a.n_draft;
+  if (a.draft_mode == kDraftInMerge) {
+    if (n <= 8) hipLaunchKernelGGL((k_attn_merge_tree<D, 8>), mgrid, mblock, 0, st, a);
+    else hipLaunchKernelGGL((k_attn_merge_tree<D, 16>), mgrid, mblock, 0, st, a);
+  } else if (n <= 6) {
+    hipLaunchKernelGGL((k_attn_merge<D, 6>), mgrid, mblock, 0, st, a);
+  } else if (n <= 12) {
+    hipLaunchKernelGGL((k_attn_merge<D, 12>), mgrid, mblock, 0, st, a);
+  } else {
+    hipLaunchKernelGGL((k_attn_merge<D, kMergeBatch>), mgrid, mblock, 0, st, a);
+  }
 }
 
 void launch_attn_bf16(hipStream_t st, const AttnArgs &a) {
