@@ -232,23 +232,27 @@ __device__ void draft_partial(const AttnArgs &a, int kb, int kvh, int b, int row
       *(f32x4 *)(out + db * 32 + 8 * q + 4 * g) = f32x4{o[db][4 * q], o[db][4 * q + 1], o[db][4 * q + 2], o[db][4 * q + 3]};
 }
 
-// NW waves, each owning RBW blocks of 32 query rows: a workgroup covers 32 * NW * RBW rows.
-// <KT 128, NW 4>: one workgroup per CU.  <KT 64, NW 8>: 256 rows share every staged K/V tile
+// NW wavefronts; KG groups of them take KT / KG keys of every tile each, the NW / KG wavefronts of a group a
+// block of 32 query rows each; the groups' sums meet in LDS at the end.
+// <KT 128, NW 4, KG 1>: 128 rows, one workgroup per CU.  <KT 64, NW 8, KG 1>: 256 rows share every staged K/V tile
 // (trees of more than 128 rows read the cache once, not twice) and two waves per SIMD overlap
 // one another's softmax arithmetic and matrix work.
+// <KT 128, KG 2 or 4>: 128 rows, of which a quarter and more are missing: wavefronts that would have none take
+// keys instead (launch_attn_bf16_d).
 // DRAFT: some workgroups (splits from n_splits on) take a block of draft nodes each instead.
 // PAGED: the cache is in pages of kKvPage slots (a multiple of KT, and every split starts at a
 // multiple of KT, so a tile never straddles two pages): one scalar page lookup per tile.
-template <int D, int RBW, int KT, int NW, bool PAGED, bool DRAFT>
+template <int D, int KT, int NW, int KG, bool PAGED, bool DRAFT>
 __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
   using L = AttnLds<D, KT>;
-  constexpr int NT = 64 * NW;
+  constexpr int NT = 64 * NW, RB = NW / KG, KW = KT / KG;   // row blocks; keys of a tile that a wavefront takes
+  constexpr bool LONG = KT == 64, SPARE = LONG || KG > 1;   // 256-row workgroups; two wavefronts a SIMD or few rows
   __shared__ __attribute__((aligned(16))) unsigned char lds[2 * L::kBuf];
   const int split = blockIdx.x, kvh = blockIdx.y;
   const int b = blockIdx.z / a.n_row_groups, rg = blockIdx.z - b * a.n_row_groups;   // sequence, group of query rows
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: branches on it are wave-uniform
-  const int ln = lane & 31, g = lane >> 5;
+  const int ln = lane & 31, g = lane >> 5, rb = wave % RB, kg = wave / RB;
   const int M = a.n_nodes, group = a.n_q_heads / a.n_kv_heads;
   const int p_rows = group * M;
   const int ctx = a.ctx.v[b];
@@ -258,26 +262,20 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
   const size_t part_base = ((size_t)b * a.n_kv_heads + kvh) * (a.n_splits + a.n_draft) + split;
   if constexpr (DRAFT) {
     if (split >= a.n_splits) {
-#pragma unroll
-      for (int i = 0; i < RBW; ++i)
-        draft_partial<D>(a, split - a.n_splits, kvh, b, rg * NW * RBW + wave + NW * i, part_base, (float *)lds + wave * 1024);
+      if (kg == 0) draft_partial<D>(a, split - a.n_splits, kvh, b, rg * RB + rb, part_base, (float *)lds + wave * 1024);
       return;
     }
   }
 
-  // ---- this lane's query rows
-  int prow[RBW];
-#pragma unroll
-  for (int i = 0; i < RBW; ++i) prow[i] = (rg * NW * RBW + wave + NW * i) * 32 + ln;
+  const int prow = (rg * RB + rb) * 32 + ln;   // this lane's query row
+  const bool rows_here = (rg * RB + rb) * 32 < p_rows;   // wave-uniform
 
   if (k_begin >= k_end) {   // empty split: neutral partial
-#pragma unroll
-    for (int i = 0; i < RBW; ++i)
-      if (prow[i] < p_rows && g == 0) {
-        a.part_m[part_base * p_rows + prow[i]] = -INFINITY;
-        a.part_l[part_base * p_rows + prow[i]] = 0.f;
-      }
-      return;
+    if (prow < p_rows && g == 0 && kg == 0) {
+      a.part_m[part_base * p_rows + prow] = -INFINITY;
+      a.part_l[part_base * p_rows + prow] = 0.f;
+    }
+    return;
   }
 
   static_assert(kKvPage % KT == 0, "a tile must not straddle pages");
@@ -346,18 +344,13 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
     }
   };
 
-  // ---- running state per row block: one query row per lane (both lane halves hold the same row)
-  float m_run[RBW], l_run[RBW];
-  f32x16 oacc[RBW][D / 32];
+  // ---- running state: one query row per lane (both lane halves hold the same row)
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 oacc[D / 32];
 #pragma unroll
-  for (int i = 0; i < RBW; ++i) {
-    m_run[i] = -INFINITY;
-    l_run[i] = 0.f;
+  for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) oacc[i][db][e] = 0.f;
-  }
+    for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
 
   const int n_tiles = (k_end - k_begin + KT - 1) / KT;
   load_tile(k_begin);
@@ -365,23 +358,22 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
   // whose wait then does not include them, and without a branch (a row past the end reads the
   // last row: every lane's row is independent and such lanes store nothing).
   // rotated query as bf16 high part + bf16 low part (written by the QKV epilogue)
-  bf16x8 qf[RBW][D / 16], ql[RBW][D / 16];
-#pragma unroll
-  for (int i = 0; i < RBW; ++i) {
-    const int pc = min(prow[i], p_rows - 1);
+  bf16x8 qf[D / 16], ql[D / 16];
+  {
+    const int pc = min(prow, p_rows - 1);
     const int al = pc / M, node = pc - al * M;
     const int r = b * M + node;
     const bf16 *q = (const bf16 *)a.q + (size_t)r * a.n_q_heads * D + (size_t)(kvh * group + al) * D;
 #pragma unroll
     for (int t = 0; t < D / 16; ++t) {
-      qf[i][t] = *(const bf16x8 *)(q + 16 * t + 8 * g);
-      ql[i][t] = *(const bf16x8 *)(q + a.q_panel + 16 * t + 8 * g);
+      qf[t] = *(const bf16x8 *)(q + 16 * t + 8 * g);
+      ql[t] = *(const bf16x8 *)(q + a.q_panel + 16 * t + 8 * g);
     }
   }
   store_tile(0, k_begin);
   // Long loops: the query rows have arrived before them.  A wait for them inside the loop could not tell them from the
   // next tile's loads, which may or may not have been issued since, and would drain those in every step.
-  if (NW == 8) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+  if (SPARE) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
   __syncthreads();
 
   for (int t = 0; t < n_tiles; ++t) {
@@ -390,71 +382,70 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
     if (t + 1 < n_tiles) load_tile(k0 + KT);
     const unsigned char *kb = lds + buf * L::kBuf;
     const unsigned char *vb = kb + L::kBytesK;
-    const bool need_mask = (k0 + KT > k_end);   // ragged end of the context or of this split
+    const int kw = kg * KW;                          // this wavefront's keys of the tile
+    const bool need_mask = (k0 + kw + KW > k_end);   // ragged end of the context or of this split
 
-#pragma unroll
-    for (int i = 0; i < RBW; ++i) {
-      if ((rg * NW * RBW + wave + NW * i) * 32 >= p_rows) continue;   // wave-uniform
+    if (rows_here) {
       // S^T[key][row] for the 32-key sub-tiles.  Consecutive matrix instructions go to different
       // accumulators: one that adds to the result of the instruction before it has to wait for it.
-      f32x16 s[KT / 32];
+      f32x16 s[KW / 32];
 #pragma unroll
-      for (int ks = 0; ks < KT / 32; ++ks)
+      for (int ks = 0; ks < KW / 32; ++ks)
 #pragma unroll
         for (int e = 0; e < 16; ++e) s[ks][e] = 0.f;
 #pragma unroll
       for (int tt = 0; tt < D / 16; ++tt) {
-        bf16x8 kf[KT / 32];
+        bf16x8 kf[KW / 32];
 #pragma unroll
-        for (int ks = 0; ks < KT / 32; ++ks)
-          kf[ks] = *(const bf16x8 *)(kb + (ks * 32 + ln) * L::kStrideK + (16 * tt + 8 * g) * 2);
+        for (int ks = 0; ks < KW / 32; ++ks)
+          kf[ks] = *(const bf16x8 *)(kb + (kw + ks * 32 + ln) * L::kStrideK + (16 * tt + 8 * g) * 2);
 #pragma unroll
-        for (int ks = 0; ks < KT / 32; ++ks)
-          s[ks] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[i][tt], s[ks], 0, 0, 0);
+        for (int ks = 0; ks < KW / 32; ++ks)
+          s[ks] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[tt], s[ks], 0, 0, 0);
 #pragma unroll
-        for (int ks = 0; ks < KT / 32; ++ks)
-          s[ks] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], ql[i][tt], s[ks], 0, 0, 0);
+        for (int ks = 0; ks < KW / 32; ++ks)
+          s[ks] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], ql[tt], s[ks], 0, 0, 0);
       }
       // mask (only the tile in which the context or the split ends: a scalar branch), tile max;
       // the scores arrive scaled: q was pre-multiplied by log2(e) / sqrt(d).  The vector ALU, not
       // the matrix cores, sets the pace of a tile step, so every instruction saved here counts.
       if (need_mask) {
 #pragma unroll
-        for (int ks = 0; ks < KT / 32; ++ks)
+        for (int ks = 0; ks < KW / 32; ++ks)
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
-            const int key = k0 + ks * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
+            const int key = k0 + kw + ks * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
             s[ks][e] = (key < k_end) ? s[ks][e] : -INFINITY;
           }
       }
       float tmax = -INFINITY;
 #pragma unroll
-      for (int ks = 0; ks < KT / 32; ++ks)
+      for (int ks = 0; ks < KW / 32; ++ks)
 #pragma unroll
         for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, s[ks][e]);
       tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
       float alpha = 1.f, psum = 0.f;
-      bf16x8 phi[KT / 16], plo[KT / 16];
-      if constexpr (NW == 8) {
+      bf16x8 phi[KW / 16], plo[KW / 16];
+      if constexpr (SPARE) {
         // Long loops, two wavefronts a SIMD: what the vector ALU does adds to the products' time.  So the reference
         // that exponents are taken against moves only when some row of the wavefront outgrows it by 2^8 (probabilities
         // up to 256 lose nothing: high and low part are relative, the sums are fp32), which makes the 64
         // multiplications of the accumulators rare, and two probabilities are converted at a time: 131 -> 125 us
-        // for 4 x 60 nodes over 16384 keys.  (With four wavefronts and two or three tiles neither pays: 17.6 -> 17.9.)
-        if (__builtin_amdgcn_ballot_w64(tmax > m_run[i] + kAttnSlack) != 0) {   // also from -inf, on the first keys
-          const float m_new = fmaxf(m_run[i], tmax);
-          alpha = __builtin_amdgcn_exp2f(m_run[i] - (m_new == -INFINITY ? 0.f : m_new));   // exp2(-inf) = 0
-          m_run[i] = m_new;
+        // for 4 x 60 nodes over 16384 keys.  (One group of four wavefronts and two or three tiles: neither pays, 17.6 -> 17.9.)
+        if (__builtin_amdgcn_ballot_w64(tmax > m_run + kAttnSlack) != 0) {   // also from -inf, on the first keys
+          const float m_new = fmaxf(m_run, tmax);
+          alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));   // exp2(-inf) = 0
+          m_run = m_new;
           if (t > 0) {
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-              for (int e = 0; e < 16; ++e) oacc[i][db][e] *= alpha;
+              for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
           }
         }
-        const float m_safe = (m_run[i] == -INFINITY) ? 0.f : m_run[i];
+        const float m_safe = (m_run == -INFINITY) ? 0.f : m_run;
 #pragma unroll
-        for (int ks = 0; ks < KT / 32; ++ks)
+        for (int ks = 0; ks < KW / 32; ++ks)
 #pragma unroll
           for (int e = 0; e < 16; e += 2) {
             const f32x2 p = {__builtin_amdgcn_exp2f(s[ks][e] - m_safe), __builtin_amdgcn_exp2f(s[ks][e + 1] - m_safe)};   // exp2(-inf) = 0 for masked keys
@@ -462,14 +453,14 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
             psum += p[1];
             split_pair(p, phi[ks * 2 + (e >> 3)], plo[ks * 2 + (e >> 3)], e & 7);
           }
-        l_run[i] = l_run[i] * alpha + psum;
+        l_run = l_run * alpha + psum;
       } else {
-        const float m_new = fmaxf(m_run[i], tmax);
+        const float m_new = fmaxf(m_run, tmax);
         const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-        alpha = __builtin_amdgcn_exp2f(m_run[i] - m_safe);   // exp2(-inf) = 0 on the first tile
-        m_run[i] = m_new;
+        alpha = __builtin_amdgcn_exp2f(m_run - m_safe);   // exp2(-inf) = 0 on the first tile
+        m_run = m_new;
 #pragma unroll
-        for (int ks = 0; ks < KT / 32; ++ks)
+        for (int ks = 0; ks < KW / 32; ++ks)
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
             const float p = __builtin_amdgcn_exp2f(s[ks][e] - m_safe);   // exp2(-inf) = 0 for masked keys
@@ -479,22 +470,22 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
             phi[ks * 2 + (e >> 3)][e & 7] = hi;
             plo[ks * 2 + (e >> 3)][e & 7] = lo;
           }
-        l_run[i] = l_run[i] * alpha + psum;
+        l_run = l_run * alpha + psum;
         if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // the running maximum of some row moved
 #pragma unroll
           for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) oacc[i][db][e] *= alpha;
+            for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
         }
       }
       // O^T[feature][row] = alpha * O^T + V^T P^T, the feature blocks interleaved for the same reason
 #pragma unroll
-      for (int u = 0; u < KT / 16; ++u) {
+      for (int u = 0; u < KW / 16; ++u) {
         bf16x8 vf[D / 32];
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) {
           // key slots of lane half g at step u: 16u + 4g + {0..3} and 16u + 8 + 4g + {0..3}
-          const unsigned char *vp = vb + (db * 32 + ln) * L::kStrideV + (16 * u + 4 * g) * 2;
+          const unsigned char *vp = vb + (db * 32 + ln) * L::kStrideV + (kw + 16 * u + 4 * g) * 2;
           const u32x2 v0 = *(const u32x2 *)vp;
           const u32x2 v1 = *(const u32x2 *)(vp + 16);
           const u32x4 vv = u32x4{v0.x, v0.y, v1.x, v1.y};
@@ -502,37 +493,74 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
         }
 #pragma unroll
         for (int db = 0; db < D / 32; ++db)
-          oacc[i][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], phi[u], oacc[i][db], 0, 0, 0);
+          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], phi[u], oacc[db], 0, 0, 0);
 #pragma unroll
         for (int db = 0; db < D / 32; ++db)
-          oacc[i][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], plo[u], oacc[i][db], 0, 0, 0);
+          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], plo[u], oacc[db], 0, 0, 0);
       }
     }
     if (t + 1 < n_tiles) store_tile(buf ^ 1, k0 + KT);
     __syncthreads();
   }
 
-  // ---- write the split's partial: O[row][feature] unnormalised, m, l
+  l_run += __shfl_xor(l_run, 32, 64);
+  if constexpr (KG > 1) {
+    // ---- the key groups of a row block: all but the first hand their sums over through LDS (the last barrier of
+    // the loop has freed it), 16 bytes a lane, no conflicts
+    constexpr int kSums = (KG - 1) * RB;
+    static_assert(kSums * ((D / 8) * 1024 + 256) <= 2 * L::kBuf, "the sums fit where the tiles were");
+    f32x4 (*so)[D / 8][64] = (f32x4(*)[D / 8][64])lds;
+    float *sm = (float *)(lds + kSums * (D / 8) * 1024), *sl = sm + kSums * 32;
+    if (kg > 0) {
+      const int o = (kg - 1) * RB + rb;
 #pragma unroll
-  for (int i = 0; i < RBW; ++i) {
-    const int p = prow[i];
-    if (p >= p_rows) continue;
-    const float l_tot = l_run[i] + __shfl_xor(l_run[i], 32, 64);
-    if (g == 0) {
-      a.part_m[part_base * p_rows + p] = stored_max(m_run[i]);
-      a.part_l[part_base * p_rows + p] = l_tot;
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          so[o][db * 4 + q][lane] = f32x4{oacc[db][4 * q], oacc[db][4 * q + 1], oacc[db][4 * q + 2], oacc[db][4 * q + 3]};
+      if (g == 0) { sm[o * 32 + ln] = m_run; sl[o * 32 + ln] = l_run; }
     }
-    float *o = a.part_o + (part_base * p_rows + p) * D;
+    __syncthreads();
+    if (kg > 0) return;
+    float m = m_run;
+#pragma unroll
+    for (int i = 1; i < KG; ++i) m = fmaxf(m, sm[((i - 1) * RB + rb) * 32 + ln]);
+    const float m_safe = m == -INFINITY ? 0.f : m;
+    const float w0 = __builtin_amdgcn_exp2f(m_run - m_safe);   // 0 without keys
+    m_run = m;
+    l_run *= w0;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        f32x4 v;
-        v[0] = oacc[i][db][4 * q4 + 0]; v[1] = oacc[i][db][4 * q4 + 1];
-        v[2] = oacc[i][db][4 * q4 + 2]; v[3] = oacc[i][db][4 * q4 + 3];
-        *(f32x4 *)(o + db * 32 + 8 * q4 + 4 * g) = v;
-      }
+      for (int e = 0; e < 16; ++e) oacc[db][e] *= w0;
+#pragma unroll 1
+    for (int i = 1; i < KG; ++i) {   // in ascending order
+      const int o = (i - 1) * RB + rb;
+      const float w = __builtin_amdgcn_exp2f(sm[o * 32 + ln] - m_safe);
+      l_run += sl[o * 32 + ln] * w;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 o1 = so[o][db * 4 + q][lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) oacc[db][4 * q + e] += o1[e] * w;
+        }
+    }
   }
+
+  // ---- write the split's partial: O[row][feature] unnormalised, m, l
+  if (prow >= p_rows) return;
+  if (g == 0) {
+    a.part_m[part_base * p_rows + prow] = stored_max(m_run);
+    a.part_l[part_base * p_rows + prow] = l_run;
+  }
+  float *o = a.part_o + (part_base * p_rows + prow) * D;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4)
+      *(f32x4 *)(o + db * 32 + 8 * q4 + 4 * g) = f32x4{oacc[db][4 * q4], oacc[db][4 * q4 + 1], oacc[db][4 * q4 + 2], oacc[db][4 * q4 + 3]};
 }
 
 // Context (and draft blocks) for at most 64 query rows per kv head: chains, short trees, single tokens.
@@ -923,12 +951,12 @@ template <int D>
 static void launch_attn_bf16_d(hipStream_t st, const AttnArgs &a) {
   dim3 grid(a.n_splits + (a.draft_mode == kDraftOwnGroups ? a.n_draft : 0), a.n_kv_heads, a.batch * a.n_row_groups);
   const bool paged = a.kv.page_table != nullptr;
-#define TS_ATTN(KT_, NW_, PAGED_, NT_)                                                                                       \
+#define TS_ATTN(KT_, NW_, KG_, PAGED_)                                                                                       \
   do {                                                                                                                       \
     if (a.draft_mode == kDraftOwnGroups)                                                                                     \
-      hipLaunchKernelGGL((k_attn_bf16<D, 1, KT_, NW_, PAGED_, true>), grid, dim3(NT_), 0, st, a);                            \
+      hipLaunchKernelGGL((k_attn_bf16<D, KT_, NW_, KG_, PAGED_, true>), grid, dim3(64 * NW_), 0, st, a);                            \
     else                                                                                                                     \
-      hipLaunchKernelGGL((k_attn_bf16<D, 1, KT_, NW_, PAGED_, false>), grid, dim3(NT_), 0, st, a);                           \
+      hipLaunchKernelGGL((k_attn_bf16<D, KT_, NW_, KG_, PAGED_, false>), grid, dim3(64 * NW_), 0, st, a);                           \
   } while (0)
   if (a.rows_per_wg == 32) {
     if (paged) hipLaunchKernelGGL((k_attn_few<D, 1, true>), grid, dim3(256), 0, st, a);
@@ -937,11 +965,27 @@ static void launch_attn_bf16_d(hipStream_t st, const AttnArgs &a) {
     if (paged) hipLaunchKernelGGL((k_attn_few<D, 2, true>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((k_attn_few<D, 2, false>), grid, dim3(256), 0, st, a);
   } else if (a.rows_per_wg == 256) {
-    if (paged) TS_ATTN(64, 8, true, 512);
-    else TS_ATTN(64, 8, false, 512);
+    if (paged) TS_ATTN(64, 8, 1, true);
+    else TS_ATTN(64, 8, 1, false);
   } else {
-    if (paged) TS_ATTN(128, 4, true, 256);
-    else TS_ATTN(128, 4, false, 256);
+    // 128 rows; fewer: the wavefronts that would have none share the keys of a tile out.  us, one group -> KG: 18 rows
+    // (8192 keys, KG 4 of 4 wavefronts) 15.4 -> 13.5, 32 rows (4 x 4096) 25.3 -> 19.7, 52 rows (12000, 4 of 8) 21.2 -> 17.9, 56 rows
+    // (8192) 16.6 -> 15.9, 74 rows (3 x 3001, 2 of 8) 20.9 -> 19.3, 88 rows (8192) 18.4 -> 17.7.  With all four
+    // row blocks it does not pay: 17.4 -> 19 for 120 rows over 256 keys a workgroup.
+    const int p_rows = a.n_q_heads / a.n_kv_heads * a.n_nodes;
+    if (p_rows <= 32) {
+      if (paged) TS_ATTN(128, 4, 4, true);
+      else TS_ATTN(128, 4, 4, false);
+    } else if (p_rows <= 64) {
+      if (paged) TS_ATTN(128, 8, 4, true);
+      else TS_ATTN(128, 8, 4, false);
+    } else if (p_rows <= 96) {
+      if (paged) TS_ATTN(128, 8, 2, true);
+      else TS_ATTN(128, 8, 2, false);
+    } else {
+      if (paged) TS_ATTN(128, 4, 1, true);
+      else TS_ATTN(128, 4, 1, false);
+    }
   }
 #undef TS_ATTN
   const int group = a.n_q_heads / a.n_kv_heads;

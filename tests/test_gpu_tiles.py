@@ -100,6 +100,10 @@ ATTN_CASES = {
     "rows200_own_workgroups": (1, 100, 4, (300,)),
     "rows512_chain_blocks": (1, 128, 8, (65,)),
     "rows128_unequal": (8, 32, 8, (13000, 300, 64, 0, 77, 12999, 500, 9)),
+    # few rows over many keys: the wavefronts share the keys of a tile out (four, four of eight, two of eight)
+    "rows18_shared_keys": (2, 9, 4, (16500, 300)),
+    "rows52_shared_keys": (2, 26, 4, (9000, 8001)),
+    "rows74_shared_keys": (3, 37, 4, (3001, 0, 130)),
     # 32 splits of 512 keys fill the chip, paged or not: the draft nodes stay with the merge
     "rows80_in_merge": (4, 40, 4, (16380, 128, 0, 5000)),
 }
