@@ -138,7 +138,7 @@ inline size_t stream_part_floats(int epi, const SplitPlan &p, int rows) {
   const int rb = row_blocks(rows);
   return p.n_splits < 2 ? 0 : (size_t)p.n_splits * p.n_tiles * p.tile_n * rb * 16;
 }
-// LM head over at most 64 rows: the 128-column kernel (kernels_gemm.hip) shares the activation panel among its
+// LM head over at most 128 rows: the 128-column kernel (kernels_gemm.hip) shares the activation panel among its
 // wavefronts through LDS; it needs reductions of whole chunk pairs.  n_splits is the number of passes of a
 // workgroup, n_tiles the entries that all of them leave: one pass each, but for more than 512 tiles (two workgroups a CU)
 // over at most 32 rows, where 512 workgroups share the sub-tiles of 32 out.
@@ -149,7 +149,7 @@ inline int head_passes(int n_cols) {
   return ((n_sub + places - 1) / places + 3) / 4;
 }
 SplitPlan plan_head(int n_cols, int k, int rows, int rows_pad) {
-  if (k % (256 * (3 - rows_pad / 32)) != 0) return plan_stream(EPI_HEAD, n_cols, k, rows, 0, false);
+  if (k % (rows_pad == 32 ? 512 : 256) != 0) return plan_stream(EPI_HEAD, n_cols, k, rows, 0, false);
   SplitPlan p;
   p.tile_n = kGemmTileN;
   p.k_per_split = k;
@@ -196,7 +196,7 @@ constexpr size_t kWidePartFloats = (size_t)12 << 20;   // partial tiles of one w
 
 SplitPlan plan_any(int epi, int n_cols, int k, int rows, int head_dim, bool qk_norm) {
   const int rp = rows_pad_for(rows);
-  if (epi == EPI_HEAD && rp <= 64) return plan_head(n_cols, k, rows, rp);
+  if (epi == EPI_HEAD && (rp <= 64 || (rp == 128 && k % 256 == 0))) return plan_head(n_cols, k, rows, rp);
   if (epi == EPI_HEAD || rp > 128) return plan_wide(epi, n_cols, k, rp, kWidePartFloats);
   return plan_stream(epi, n_cols, k, rows, head_dim, qk_norm);
 }
@@ -921,12 +921,11 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       g.next_norm_w = (l + 1 < c.n_layers) ? m->norm_attn[l + 1] : m->final_norm; g.ss_part = ss0;
       return g;
     };
-    const bool wide = rp > 64;
     auto plan = [&](int epi, int n_cols, int k) {
       return plan_any(epi, n_cols, k, rows, c.head_dim, c.qk_norm != 0);
     };
     auto launch_gemm = [&](const GemmArgs &g) {
-      if (g.stream) launch_gemm_stream(st, g); else if (wide) launch_gemm_wide(st, g); else launch_gemm_head(st, g);
+      if (g.stream) launch_gemm_stream(st, g); else if (g.epi == EPI_HEAD && g.tile_n == kGemmTileN) launch_gemm_head(st, g); else launch_gemm_wide(st, g);
     };
     const SplitPlan pq = plan(EPI_QKV, nqkv, c.hidden), po = plan(EPI_RESID, c.hidden, qd);
     const SplitPlan pg = plan(EPI_SWIGLU, 2 * c.ffn, c.hidden), pd = plan(EPI_RESID, c.hidden, c.ffn);

@@ -1,7 +1,7 @@
-// LM head over at most 64 rows: weight-streaming small-M matmul on the matrix cores (bf16 weights, fp32
+// LM head over at most 128 rows: weight-streaming small-M matmul on the matrix cores (bf16 weights, fp32
 // accumulate) with the vocabulary statistics fused in, and the one-time repack of the weights.
 //
-//   y[r][n] = rstd[r] * sum_k X[r][k] * W[n][k]        r < rows_pad <= 64
+//   y[r][n] = rstd[r] * sum_k X[r][k] * W[n][k]        r < rows_pad <= 128
 //
 // At these row counts the product is bound by streaming W from HBM once, so the layout serves
 // the W stream.  W is read from the PACKED copy made once by k_pack_weights: for every 32-row
@@ -12,7 +12,7 @@
 // passes through LDS and is never re-read.  (Reading row-major W with the same operand layout
 // touches 32 rows x 32 bytes per instruction and reaches ~75 % of the contiguous rate.)
 //
-// The activation panel X (at most 64 rows; more rows: kernels_gemm_wide.hip) is what the four wavefronts of a workgroup share.
+// The activation panel X (at most 128 rows; more rows: kernels_gemm_wide.hip) is what the four wavefronts of a workgroup share.
 // It arrives as two bf16 panels, a high part and a low part (hi = round(v), lo = round(v - hi),
 // written once by whichever kernel produced the activation — splitting it here would repeat the
 // conversion in every one of the hundreds of workgroups and costs more issue slots than the
@@ -36,13 +36,15 @@
 // shared out evenly in sub-tiles of 32: every workgroup makes the same number of passes over runs of neighbouring
 // sub-tiles, and the chip has no last wave that is a third full (1187 tiles on 512 places).  151936 columns over 9
 // rows of 1024 83 -> 66 us (one workgroup a CU and a tile each before), over one row of 4096 211 -> 206.  Over 60 rows the
-// panel, drawn once per pass, outweighs that (256 -> 295 us): a tile each.
+// panel, drawn once per pass, outweighs that (256 -> 295 us): a tile each.  Over 65 to 128 rows the LDS delivers all it can (an
+// operand fragment feeds one matrix instruction), and two workgroups a CU still beat the wide kernel's 256-column tiles, of
+// which 594 leave a last wave a third full: 151936 x 2048 247 -> 215 us, 151936 x 4096 383 -> 367.
 #include "gemm_tile.hpp"
 
 namespace ts {
 
 template <int MB, int KC, int DEPTH>
-__global__ __launch_bounds__(256, MB == 1 ? 2 : 1) void k_gemm_head(GemmArgs a) {
+__global__ __launch_bounds__(256, MB == 2 ? 1 : 2) void k_gemm_head(GemmArgs a) {
   constexpr int KB = KC / 64;                 // 64-deep k blocks per chunk
   constexpr int FRAGS = KB * 4 * MB * 2;      // 1 KB operand fragments per chunk (operand layout)
   constexpr int BUF = FRAGS * 1024;           // one LDS stage
@@ -241,9 +243,10 @@ void launch_pack_weights(hipStream_t st, const void *w, int n_rows, int k, void 
 
 void launch_gemm_head(hipStream_t st, const GemmArgs &a) {
   const dim3 grid(a.n_tiles / a.n_splits), block(256);
-  if (a.rows_pad == 32) hipLaunchKernelGGL((k_gemm_head<1, 128, 4>), grid, block, 0, st, a);
+  if (a.rows_pad == 128) hipLaunchKernelGGL((k_gemm_head<4, 64, 4>), grid, block, 0, st, a);
+  else if (a.rows_pad == 32) hipLaunchKernelGGL((k_gemm_head<1, 128, 4>), grid, block, 0, st, a);
   else if (a.k % 512 == 0) hipLaunchKernelGGL((k_gemm_head<2, 128, 4>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_gemm_head<2, 128, 2>), grid, block, 0, st, a);   // 64; larger panels: kernels_gemm_wide.hip
+  else hipLaunchKernelGGL((k_gemm_head<2, 128, 2>), grid, block, 0, st, a); 
 }
 
 }  // namespace ts
