@@ -77,8 +77,8 @@ inline int row_blocks(int rows) { return rows <= 64 ? (rows + 15) / 16 : 8; }
 //
 // A workgroup (one runs per CU) takes 3 us to its first data.  It then draws its weights and its share of the
 // activation panel, 2 bytes a column and 64 a row block and k step, at 45 (one row block) to 60 GB/s; the chip draws no
-// more than 6.3 TB/s of weights.  Meeting the other splits costs 0.8 us and, a row block and column, 0.012 us
-// and 0.002 a split: publish the partial tile, count, read all of them.  So wide tiles draw less of the panel and narrow ones meet
+// more than 6.3 TB/s of weights.  Finishing a tile takes 0.012 us a row block and
+// column, meeting the other splits 0.8 us more and 0.002 a split: publish the partial tile, count, read all of them.  So wide tiles draw less of the panel and narrow ones meet
 // sooner.  Estimated / measured, us: 4096 x 4096 over 60 rows 32 columns x 2 splits 17.3 / 16.9, 64 x 4 15.4 / 16.7,
 // 128 x 8 19.3 / 18.8, 16 x 1 22.6 / 19.9; 4096 x 12288 64 x 4 28.6 / 32.6, 32 x 2 39.2 / 38.4; 2048 x 6144 32 x 4 14.6 / 14.3,
 // 64 x 8 16.1 / 15.8; over 9 rows 1024 x 2048 16 x 4 5.5 / 6.5, 16 x 1 7.4 / 6.6, 32 x 2 7.6 / 7.4; over 111 rows
@@ -116,8 +116,8 @@ SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim, bool q
     for (int sp = 1; sp <= 16 && sp <= steps && (sp == 1 || tiles * groups * sp <= 256); ++sp) {
       const int rounds = (tiles * groups * sp + 255) / 256;
       const double own_us = rounds * ((steps + sp - 1) / sp) * 32.0 * (2.0 * tn + 64.0 * rb) / rate;
-      double us = 3.0 * rounds + (own_us > chip_us ? own_us : chip_us);
-      if (sp > 1) us += 0.8 + (0.012 + 0.002 * sp) * rb * tn;
+      double us = 3.0 * rounds + (own_us > chip_us ? own_us : chip_us) + 0.012 * rb * tn;
+      if (sp > 1) us += 0.8 + 0.002 * sp * rb * tn;
       if (us < best_us) {
         best_us = us;
         best.tile_n = tn;
