@@ -69,17 +69,17 @@ constexpr int kLayerSplitCap = 8;    // k splits of one matmul inside the layer 
 unsigned long long g_spin_limit = 200000000ull;
 
 inline int tiles_of(int n) { return (n + kGemmTileN - 1) / kGemmTileN; }
-// 16-row blocks that the streaming kernel multiplies for a panel of up to 128 rows: 1 to 4, or 8.
-inline int row_blocks(int rows) { return rows <= 64 ? (rows + 15) / 16 : 8; }
+// 16-row blocks that the streaming kernel multiplies for a panel of up to 128 rows: 1 to 4, 6 or 8.
+inline int row_blocks(int rows) { return rows <= 64 ? (rows + 15) / 16 : (rows <= 96 ? 6 : 8); }
 
 // Decomposition of one matmul over at most 128 rows into (column tile, k split) workgroups of the streaming
 // kernel (gemm_stream.hpp): the tile width and the number of splits with the smallest estimated time.
 //
 // A workgroup (one runs per CU) takes 3 us to its first data.  It then draws its weights and its share of the
 // activation panel, 2 bytes a column and 64 a row block and k step, at 45 (one row block) to 60 GB/s; the chip draws no
-// more than 6.3 TB/s of weights.  Finishing a tile takes 0.012 us a row block and
-// column, meeting the other splits 0.8 us more and 0.002 a split: publish the partial tile, count, read all of them.  So wide tiles draw less of the panel and narrow ones meet
-// sooner.  Estimated / measured, us: 4096 x 4096 over 60 rows 32 columns x 2 splits 17.3 / 16.9, 64 x 4 15.4 / 16.7,
+// more than 6.3 TB/s of weights.  Finishing a tile takes 0.012 us a row block and column,
+// meeting the other splits 0.8 us more and 0.002 a split: publish the partial tile, count, read all of them.  So wide
+// tiles draw less of the panel and narrow ones meet sooner.  Estimated / measured, us: 4096 x 4096 over 60 rows 32 columns x 2 splits 17.3 / 16.9, 64 x 4 15.4 / 16.7,
 // 128 x 8 19.3 / 18.8, 16 x 1 22.6 / 19.9; 4096 x 12288 64 x 4 28.6 / 32.6, 32 x 2 39.2 / 38.4; 2048 x 6144 32 x 4 14.6 / 14.3,
 // 64 x 8 16.1 / 15.8; over 9 rows 1024 x 2048 16 x 4 5.5 / 6.5, 16 x 1 7.4 / 6.6, 32 x 2 7.6 / 7.4; over 111 rows
 // 2048 x 6144 32 x 4 19.9 / 19.9, 64 x 8 23.4 / 21.2.
@@ -160,7 +160,7 @@ SplitPlan plan_head(int n_cols, int k, int rows, int rows_pad) {
 // entries per row of the sums of squares that a matmul with tiles of tile_n columns leaves
 inline int ss_tiles_of(int n, int tile_n) { return tile_n < kGemmTileN ? (n + tile_n - 1) / tile_n : tiles_of(n); }
 
-// Decomposition of one matmul over a panel of 128 or 256 rows (kernels_gemm_wide.hip): the tile width
+// Decomposition of one matmul over a panel of 256 rows, LM head also 128 (kernels_gemm_wide.hip): the tile width
 // and the number of k splits with the smallest estimated time.  Measured on the 28672 x 4096 and
 // 4096 x 14336 products: a 64-deep chunk takes a workgroup 1.65 us on a 128 x 256 tile and 1.12 us on
 // a 128 x 128 tile, a workgroup about 6 us beside its chunks, one workgroup runs per CU; splitting
@@ -266,7 +266,7 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
     const int nc[4] = {nqkv, c.hidden, 2 * c.ffn, c.hidden};
     const int ks[4] = {c.hidden, qd, c.hidden, c.ffn};
     size_t floats = (size_t)kLayerPhases * kLayerMaxGrid * kGemmTileN * rp;
-    const int rows_of[] = {16, 32, 48, 64, 128, 256};   // one of every kind of panel
+    const int rows_of[] = {16, 32, 48, 64, 96, 128, 256};   // one of every kind of panel
     for (int i = 0; i < 4; ++i)
       for (int r : rows_of) {
         const SplitPlan p = plan_any(ep[i], nc[i], ks[i], r, c.head_dim, c.qk_norm != 0);

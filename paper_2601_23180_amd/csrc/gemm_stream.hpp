@@ -49,7 +49,7 @@ template <int RB, int CB, int NW, int D, int EPI>
 __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
   constexpr int NT = 64 * NW, ROWS = RB * 16, TN = CB * 16, LD = TN + 4;
   // 32-row blocks of the activation panel: as many as the rows need, or the four of two row groups
-  const int MBT = RB <= 2 ? 1 : (RB == 3 ? 2 : (RB == 8 ? 4 : a.rows_pad >> 5));
+  const int MBT = RB <= 2 ? 1 : (RB == 3 ? 2 : (RB > 4 ? 4 : a.rows_pad >> 5));
   constexpr int MG = StreamShape<RB, CB>::MG;                      // row blocks that go through LDS at a time
   constexpr int NQ = CB * MG;                                      // 1 KB accumulator fragments of those
   constexpr int QW = (NQ + NW - 1) / NW;                           // fragments that a wavefront adds up
@@ -295,6 +295,7 @@ void dispatch_rows(hipStream_t st, const GemmArgs &a) {
     case 4: dispatch_cols<4, EPI>(st, a); break;
     default:   // up to 128 rows; a head of 128 that stays whole: two groups of 64
       if (EPI == EPI_QKV && a.tile_n == 128) dispatch_cols<4, EPI>(st, a);
+      else if (a.rows <= 96) dispatch_cols<6, EPI>(st, a);
       else dispatch_cols<8, EPI>(st, a);
       break;
   }

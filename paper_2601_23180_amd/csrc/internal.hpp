@@ -63,7 +63,7 @@ struct HeadStats {
   int32_t n_tiles;
 };
 
-// One weight-streaming matmul  y[r][col] = sum_k X[r][k] * W[col][k]  (see kernels_gemm.hip).
+// One weight-streaming matmul  y[r][col] = sum_k X[r][k] * W[col][k]  (see gemm_stream.hpp).
 // Where the slots of a sequence live inside ONE layer of the cache.  Contiguous cache:
 // K [B][nkv][capacity][d], V^T [B][nkv][d][capacity].  Paged cache: pages of kKvPage slots,
 // K [n_pages][nkv][kKvPage][d], V^T [n_pages][nkv][d][kKvPage]; slot s of sequence b is slot
@@ -288,7 +288,7 @@ void launch_reduce_swiglu(hipStream_t st, int dtype, const float *part, int n_sp
 void launch_gemm_f32(hipStream_t st, const GemmArgs &a);
 size_t packed_weight_bytes(int n_rows, int k);
 void launch_pack_weights(hipStream_t st, const void *w, int n_rows, int k, void *out);
-void launch_gemm_head(hipStream_t st, const GemmArgs &a);   // LM head, up to 64 rows: 4 wavefronts, 128-column tiles
+void launch_gemm_head(hipStream_t st, const GemmArgs &a);   // LM head, up to 128 rows: 4 wavefronts, 128-column tiles
 void launch_gemm_stream(hipStream_t st, const GemmArgs &a);   // up to 128 rows: wavefronts share the reduction, tile_n = 16 .. 128
 void launch_gemm_wide(hipStream_t st, const GemmArgs &a);   // more rows: tile_n = 256 or 128 columns, k splits of whole 64-deep blocks
 void launch_stats_from_logits(hipStream_t st, const float *logits, int rows, int vocab,

@@ -1,4 +1,5 @@
-// Matmul for panels of more than 64 activation rows (several sequences, prompt chains), where the
+// Matmul for panels of more than 128 activation rows (several sequences; for the LM head of a width that
+// kernels_gemm.hip does not take, more than 64), where the
 // matrix cores and not the weight stream set the time: 4 * rows * N * K flops for the high and low
 // parts against 2 * N * K bytes cross at about 140 rows of one pass.
 //

@@ -9,8 +9,8 @@
 // arrived at the barrier, so HBM keeps streaming weights while the last workgroups of the phase
 // reduce their tiles, while the barrier settles and while the next activation panel is fetched.
 //
-// The phases are the matmul of kernels_gemm.hip (same packed weights, same operand layout, same
-// MFMA schedule, same epilogues) restricted to its fast path: every workgroup's k range is a whole
+// The phases are a matmul of 128-column tiles like that of kernels_gemm.hip (same packed weights, same operand
+// layout, same MFMA schedule) with the epilogues of gemm_epilogue.hpp, restricted to its fast path: every workgroup's k range is a whole
 // number of DEPTH chunks.  Work item of workgroup g in a phase: tile g % n_tiles, split
 // g / n_tiles (idle if g >= n_tiles * n_splits); a fixed function of g, so results do not depend
 // on scheduling.
@@ -37,7 +37,7 @@ struct Item {
   const bf16 *wrow;   // this wavefront's packed run at k_begin, lane offset included
 };
 
-// This wavefront's packed sub-tile for (tile, split) of matmul `a` — as in k_gemm_bf16.
+// This wavefront's packed sub-tile for (tile, split) of matmul `a` — as in k_gemm_head.
 template <int KC>
 __device__ __forceinline__ Item item_of(const GemmArgs &a, int epi, int wg, int wave, int lane) {
   Item it;
