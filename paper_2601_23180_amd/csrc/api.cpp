@@ -161,10 +161,11 @@ SplitPlan plan_head(int n_cols, int k, int rows, int rows_pad) {
 inline int ss_tiles_of(int n, int tile_n) { return tile_n < kGemmTileN ? (n + tile_n - 1) / tile_n : tiles_of(n); }
 
 // Decomposition of one matmul over a panel of 256 rows, LM head also 128 (kernels_gemm_wide.hip): the tile width
-// and the number of k splits with the smallest estimated time.  Measured on the 28672 x 4096 and
-// 4096 x 14336 products: a 64-deep chunk takes a workgroup 1.65 us on a 128 x 256 tile and 1.12 us on
-// a 128 x 128 tile, a workgroup about 6 us beside its chunks, one workgroup runs per CU; splitting
-// costs a second launch (about 5 us) and the partial tiles, written and read back at about 5 TB/s.
+// and the number of k splits with the smallest estimated time.  Fitted to products of 1024 to 4096 wide models: a 64-deep
+// chunk takes a workgroup 1.65 us on a 128 x 256 tile and 1.0 us on a 128 x 128 tile, a workgroup about 6 us beside its
+// chunks, one workgroup runs per CU; splitting costs 1.5 us (a second launch, but no epilogue in the first) and the
+// partial tiles, written and read back at about 6.5 TB/s.  Estimated / measured, us, 240 rows: 6144 x 1024 in one split 22.0 / 21.7,
+// two 19.4 / 18.8; 2048 x 6144 in four 34.8 / 33.6, eight 24.7 / 25.0; 4096 x 14336 (256 columns) in eight 64.0 / 65.2.
 SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_part_floats) {
   const int kb = k / 64, n_rg = rows_pad / 128;
   SplitPlan best;
@@ -180,8 +181,8 @@ SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_part_fl
       const size_t floats = (size_t)s * tiles_of(n_cols) * kGemmTileN * rows_pad;
       if (s > 1 && floats > max_part_floats) break;
       const int rounds = (tiles * n_rg * s + 255) / 256, chunks = (kb + s - 1) / s;
-      const double us = rounds * (chunks * (tile_n == 256 ? 1.65 : 1.12) + 6.0) +
-                        (s > 1 ? 5.0 + (double)floats * 8.0 / 5e6 : 0.0);
+      const double us = rounds * (chunks * (tile_n == 256 ? 1.65 : 1.0) + 6.0) +
+                        (s > 1 ? 1.5 + (double)floats * 8.0 / 6.5e6 : 0.0);
       if (us < best_us) {
         best_us = us;
         best.tile_n = tile_n;

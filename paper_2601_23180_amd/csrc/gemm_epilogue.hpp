@@ -10,8 +10,7 @@ namespace ts {
 // rstd_load only ISSUES loads (wavefront q of the workgroup takes tiles q, q+Q, ...; a lane takes
 // rows lane, lane+64, ...) and is called before the weight stream starts, so that nothing waits
 // for them; rstd_finish, called after the stream, adds them up (plus the entries beyond the first
-// 8*Q, 32 with four wavefronts: more than 4096 columns in entries of 128, more than 1024 in entries of 32,
-// which a residual product in 32-column tiles leaves) and combines the wavefronts' sums through LDS.  The
+// 8*Q, 32 with four wavefronts: more than 4096 columns in entries of 128) and combines the wavefronts' sums through LDS.  The
 // order of the additions is fixed, so the result does not depend on scheduling.
 template <int NT, int MB>
 __device__ __forceinline__ void rstd_load(const GemmArgs &a, float (&x)[(MB + 1) / 2][8]) {

@@ -1,9 +1,8 @@
 // Element-wise half of the matmul epilogues, on a block of RB rows x TN columns of the reduced fp32
 // product: rotary embedding + KV append, residual + next operand + norm statistics, SiLU * up, plain
 // store, LM-head statistics.  Used by k_gemm_stream, k_gemm_wide and k_gemm_finish (which adds up split-K
-// partial tiles).  The 128-column kernel and the layer kernel finish their tiles in gemm_epilogue.hpp, with
-// the same arithmetic written for their layout: a change here belongs there too.  The LM-head statistics
-// (head_rows) are the same code for all.
+// partial tiles); the LM-head statistics (head_rows) by k_gemm_head too.  The layer kernel finishes its tiles in
+// gemm_epilogue.hpp, with the same arithmetic written for its layout: a change here belongs there too.
 #pragma once
 
 #include <type_traits>

@@ -3,11 +3,16 @@
 // matrix cores and not the weight stream set the time: 4 * rows * N * K flops for the high and low
 // parts against 2 * N * K bytes cross at about 140 rows of one pass.
 //
-// A workgroup owns 128 rows x 256 columns (or 128 x 128) of the product over one k split.  Four
-// wavefronts; each holds 128 x 64 (64 x 64) accumulators, so that a weight fragment is multiplied
-// with eight activation fragments and an activation fragment with two weight fragments: the LDS
-// then delivers 64 bytes a clock at the full matrix rate, half of what it can.  (One wavefront per
-// 32 columns and all 256 rows, the split of the narrow kernel, asks for 128 bytes a clock.)
+// A workgroup owns 128 rows x 256 columns or 128 x 128 of the product over one k split.  256 columns: four
+// wavefronts with 128 x 64 accumulators, so that a weight fragment is multiplied with eight activation
+// fragments and an activation fragment with two weight fragments: the LDS then delivers 64 bytes a
+// clock at the full matrix rate, half of what it can.  128 columns: these tiles serve the smaller products, whose time
+// is first data, waits and hand-over rather than matrix rate, so eight wavefronts of 64 x 32, two a SIMD, of which one works
+// while the other waits; both rows of wavefronts read the same weights, the second out of the L1, hence without the
+// non-temporal hint (40.3 -> 39.2, hinted 4096 x 14336 in 4 splits 77.7, plain 75.0).  Four wavefronts of 64 x 64 -> eight, 240 rows,
+// us with the finishing launch: 1472 wide QKV 20.6 -> 18.6, O 15.5 -> 13.1, gate + up 28.3 -> 25.5, down 22.4 -> 20.0; 2048 wide 25.1 -> 24.0,
+// 18.4 -> 17.0, 41.3 -> 40.1, 26.7 -> 25.3; 1024 wide 19.4 -> 18.6, 15.8 -> 14.5, 24.0 -> 21.7, 18.2 -> 16.6.  The 256-column tile with eight wavefronts
+// of 64 x 64 is slower (28672 x 4096: 108 -> 120, 130 with the hint).
 // Activations go global -> registers -> LDS in 64-deep chunks, double buffered; weights go straight
 // to registers, two chunks ahead.
 //
@@ -33,16 +38,17 @@ constexpr int kWideRows = 128;      // rows per workgroup
 }  // namespace
 
 template <int WR, int WC, int MBW, int NBW, int EPI>
-__global__ __launch_bounds__(256) void k_gemm_wide(GemmArgs a) {
-  static_assert(WR * WC == 4 && WR * MBW * 32 == kWideRows, "four wavefronts on 128 rows");
+__global__ __launch_bounds__(WR * WC * 64) void k_gemm_wide(GemmArgs a) {
+  static_assert(WR * MBW * 32 == kWideRows, "the wavefronts cover 128 rows");
+  constexpr int NW = WR * WC, NT = NW * 64;
   constexpr int MB = WR * MBW;                   // 32-row blocks of the workgroup
   constexpr int TN = WC * NBW * 32;              // columns of the workgroup
-  constexpr int FR = 4 * MB * 2, XV = FR / 4;    // 1 KB activation fragments per chunk, per wavefront
+  constexpr int FR = 4 * MB * 2, XV = FR / NW;    // 1 KB activation fragments per chunk, per wavefront
   constexpr int BUF = FR * 1024;
   constexpr int LD = TN + 4;                     // floats per row of the epilogue's LDS tile
   constexpr int EPI_BYTES = 32 * LD * 4, LDS_BYTES = 2 * BUF > EPI_BYTES ? 2 * BUF : EPI_BYTES;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
-  __shared__ float s_tmp[256], s_rs[kWideRows];
+  __shared__ float s_tmp[NT], s_rs[kWideRows];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -74,11 +80,12 @@ __global__ __launch_bounds__(256) void k_gemm_wide(GemmArgs a) {
     const bf16 *wseg = (const bf16 *)(sidx == 0 ? a.seg[0].w : (sidx == 1 ? a.seg[1].w : a.seg[2].w));
     const int seg_rows = sidx == 0 ? a.seg[0].n_rows : (sidx == 1 ? a.seg[1].n_rows : a.seg[2].n_rows);
     sub = min(max(sub, 0), ((seg_rows + 31) >> 5) - 1);
-    wp[i] = wseg + ((size_t)sub * kb_total + b0) * 2048 + lane * 8;
+    wp[i] = wseg + ((size_t)sub * kb_total + b0) * 2048;
   }
-  const bf16 *xg = (const bf16 *)a.x + ((size_t)b0 * 4 * mbt + (size_t)rg * MB) * 1024 + lane * 8;
+  const bf16 *xg = (const bf16 *)a.x + ((size_t)b0 * 4 * mbt + (size_t)rg * MB) * 1024;
+  const unsigned lane_off = lane * 16;   // bases are scalar
 
-  RowScale<256, kWideRows> scale;
+  RowScale<NT, kWideRows> scale;
   if (a.n_splits == 1) scale.issue(a, rg * kWideRows);
 
   f32x16 acc[NBW][MBW];
@@ -94,11 +101,13 @@ __global__ __launch_bounds__(256) void k_gemm_wide(GemmArgs a) {
   u32x4 xr[XV];
   auto load_x1 = [&](int i, int c) {   // fragment i of this wavefront's share of chunk c
     const int f = wave * XV + i, j = f / (MB * 2), r = f % (MB * 2);
-    xr[i] = *(const u32x4 *)(xg + ((size_t)(c * 4 + j) * mbt * 2 + r) * 512);
+    xr[i] = *(const u32x4 *)((const char *)(xg + ((size_t)(c * 4 + j) * mbt * 2 + r) * 512) + lane_off);
   };
   auto store_x1 = [&](int i, int buf) { *(u32x4 *)(lds + buf * BUF + (wave * XV + i) * 1024 + lane * 16) = xr[i]; };
+  constexpr bool SHARED_W = WR > 1;              // several wavefronts read the same weights
   auto load_w1 = [&](int set, int t, int i, int c) {
-    w[set][t][i] = __builtin_nontemporal_load((const bf16x8 *)(wp[i] + (size_t)c * 2048 + 512 * t));
+    const bf16x8 *p = (const bf16x8 *)((const char *)(wp[i] + (size_t)c * 2048 + 512 * t) + lane_off);
+    w[set][t][i] = SHARED_W ? *p : __builtin_nontemporal_load(p);
   };
   auto read_x1 = [&](int slot, int t, int buf, int m) {
     xf[slot][m] = *(const bf16x8 *)(lds + buf * BUF + (t * MB * 2 + wr * MBW * 2 + m) * 1024 + lane * 16);
@@ -120,17 +129,18 @@ __global__ __launch_bounds__(256) void k_gemm_wide(GemmArgs a) {
         for (int i = q * XV / NG; i < (q + 1) * XV / NG; ++i) store_x1(i, set ^ 1);
       if (LX)
 #pragma unroll
-        for (int i = q * XV / NG; i < (q + 1) * XV / NG; ++i) load_x1(i, cx);
+        for (int i = q * XV / NG; i < (q + 1) * XV / NG; ++i) load_x1(i, min(cx, n - 1));
 #pragma unroll
       for (int u = 0; u < 2; ++u) {   // consecutive instructions go to different accumulators
         const int e = q * 2 + u, p = e / (MBW * NBW), i = (e / MBW) % NBW, m = e % MBW;
         acc[i][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[t & 1][2 * m + p], w[set][t][i], acc[i][m], 0, 0, 0);
       }
-      if (LW && q >= NG - NBW) load_w1(set, t, q - (NG - NBW), cw);
+      if (LW && q >= NG - NBW) load_w1(set, t, q - (NG - NBW), min(cw, n - 1));
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // One chunk in LDS buffer / weight set `set`.  MORE: another chunk follows (in xr); FAR: chunk c + 2 exists.
+  // One chunk in LDS buffer / weight set `set`.  MORE: the next chunk (in xr) goes to the other buffer; FAR: chunk
+  // c + 2 is requested.
   auto chunk = [&](auto set_c, int c, auto more_c, auto far_c) {
     constexpr bool MORE = decltype(more_c)::value, FAR = decltype(far_c)::value;
     constexpr int set = decltype(set_c)::value;
@@ -167,16 +177,12 @@ __global__ __launch_bounds__(256) void k_gemm_wide(GemmArgs a) {
     chunk(IC<0>{}, c, IC<1>{}, IC<1>{});
     chunk(IC<1>{}, c + 1, IC<1>{}, IC<1>{});
   }
-  if (n - c == 3) {
-    chunk(IC<0>{}, c, IC<1>{}, IC<1>{});
-    chunk(IC<1>{}, c + 1, IC<1>{}, IC<0>{});
-    chunk(IC<0>{}, c + 2, IC<0>{}, IC<0>{});
-  } else if (n - c == 2) {
-    chunk(IC<0>{}, c, IC<1>{}, IC<0>{});
-    chunk(IC<1>{}, c + 1, IC<0>{}, IC<0>{});
-  } else {
-    chunk(IC<0>{}, c, IC<0>{}, IC<0>{});
-  }
+  // 1 to 3 chunks are left; surplus requests repeat the last one, into registers and an LDS buffer that nothing reads.  (As
+  // three-way code without surplus the accumulators were in different registers on each way: 504 registers and
+  // copies between them, now 338; 120 for eight wavefronts.)
+  chunk(IC<0>{}, c, IC<1>{}, IC<1>{});
+  if (c + 1 < n) chunk(IC<1>{}, c + 1, IC<1>{}, IC<0>{});
+  if (c + 2 < n) chunk(IC<0>{}, c + 2, IC<0>{}, IC<0>{});
 
   if (a.n_splits > 1) {
     // partial tiles [split][128-column tile][row][128]; k_gemm_finish adds them up
@@ -199,7 +205,7 @@ __global__ __launch_bounds__(256) void k_gemm_wide(GemmArgs a) {
 
   // one split: the epilogue, 32 rows at a time through LDS
   float *tl = (float *)lds;
-  TileEpilogue<EPI == EPI_HEAD ? EPI_PLAIN : EPI, TN, 256, 32> epi;
+  TileEpilogue<EPI == EPI_HEAD ? EPI_PLAIN : EPI, TN, NT, 32> epi;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     const int row0 = rg * kWideRows + mb * 32;
@@ -215,7 +221,7 @@ __global__ __launch_bounds__(256) void k_gemm_wide(GemmArgs a) {
     }
     __syncthreads();
     if constexpr (EPI == EPI_HEAD)
-      head_rows<TN, 256, 32, LD>(a, tl, s_rs + mb * 32, tile * TN, min((tile + 1) * TN, a.n_total), tile, row0);
+      head_rows<TN, NT, 32, LD>(a, tl, s_rs + mb * 32, tile * TN, min((tile + 1) * TN, a.n_total), tile, row0);
     else
       epi.apply(a, [&](int lr, int cc) { return *(const f32x4 *)(tl + lr * LD + cc); }, s_rs + mb * 32, tile, row0);
   }
@@ -271,7 +277,7 @@ static void dispatch_wide(hipStream_t st, const GemmArgs &a) {
   const int n_rg = (a.rows + kWideRows - 1) / kWideRows;
   const dim3 grid((a.n_total + a.tile_n - 1) / a.tile_n, n_rg, a.n_splits);
   if (a.tile_n == 256) hipLaunchKernelGGL((k_gemm_wide<1, 4, 4, 2, EPI>), grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((k_gemm_wide<2, 2, 2, 2, EPI>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((k_gemm_wide<2, 4, 2, 1, EPI>), grid, dim3(512), 0, st, a);
   if constexpr (EPI != EPI_HEAD) {
     if (a.n_splits > 1)
       hipLaunchKernelGGL(k_gemm_finish<EPI>, dim3((a.n_total + 127) / 128, (a.rows + 31) / 32), dim3(256), 0, st, a);

@@ -45,6 +45,7 @@ CASES = [
     ("rows129_five_blocks", 3, 43, TB.with_(hidden=320, ffn=192, vocab=513, lm_head_std=0.4)),
     ("rows256_splits", 4, 64, TB.with_(hidden=1024, ffn=1472, n_q_heads=8, vocab=1024, lm_head_std=0.2)),
     ("rows250_many_splits_qk_norm", 5, 50, TB.with_(hidden=256, ffn=4096, qk_norm=True, lm_head_std=0.4)),
+    ("rows129_odd_chunks", 3, 43, TB.with_(hidden=320, ffn=448, lm_head_std=0.4)),
 ]
 
 
