@@ -112,7 +112,6 @@ __device__ __forceinline__ void split_pair(f32x2 p, bf16x8 &hi, bf16x8 &lo, int 
   hi[e] = h[0]; hi[e + 1] = h[1];
   lo[e] = l[0]; lo[e + 1] = l[1];
 }
-constexpr float kAttnSlack = 8.f;   // log2 units that a score may exceed the running reference by
 
 // Maximum, in natural-log units, that a partial is stored with.  -inf marks a partial without keys, which the
 // merge skips without reading it; one whose scores are all NaN (fmaxf drops them) or all -inf has to be
@@ -427,12 +426,13 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a) {
       float alpha = 1.f, psum = 0.f;
       bf16x8 phi[KW / 16], plo[KW / 16];
       if constexpr (SPARE) {
-        // Long loops, two wavefronts a SIMD: what the vector ALU does adds to the products' time.  So the reference
-        // that exponents are taken against moves only when some row of the wavefront outgrows it by 2^8 (probabilities
-        // up to 256 lose nothing: high and low part are relative, the sums are fp32), which makes the 64
-        // multiplications of the accumulators rare, and two probabilities are converted at a time: 131 -> 125 us
-        // for 4 x 60 nodes over 16384 keys.  (One group of four wavefronts and two or three tiles: neither pays, 17.6 -> 17.9.)
-        if (__builtin_amdgcn_ballot_w64(tmax > m_run + kAttnSlack) != 0) {   // also from -inf, on the first keys
+        // Long loops, two wavefronts a SIMD: what the vector ALU does adds to the products' time, so two probabilities are
+        // converted at a time.  (One group of four wavefronts and two or three tiles: it does not pay, 17.6 -> 17.9 us.)
+        // The reference is the running maximum of each row, whatever the other rows do.  One that moves only when a
+        // score outgrows it by 2^8 saves most of the multiplications below (4 x 60 nodes over 16384 keys 13.07 -> 12.98 ms
+        // a pass), but the largest probability is then no longer exactly 1, high part 1 and low part 0: logits are off by up to
+        // 4 % more on rows with few large probabilities, and a probability of 2^8 takes values beyond 1e36 out of range.
+        if (__builtin_amdgcn_ballot_w64(tmax > m_run) != 0) {
           const float m_new = fmaxf(m_run, tmax);
           alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));   // exp2(-inf) = 0
           m_run = m_new;
