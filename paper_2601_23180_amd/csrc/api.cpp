@@ -39,13 +39,6 @@ struct TimedLaunch {
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline size_t esize(int dtype) { return dtype == TRISPEC_F32 ? 4 : 2; }
 
-int rows_pad_for(int rows) {
-  if (rows <= 32) return 32;
-  if (rows <= 64) return 64;
-  if (rows <= 128) return 128;
-  return 256;
-}
-
 // Workspace regions, in order.  Offsets are a pure function of (model, batch, n_nodes).
 struct Layout {
   size_t anc, parent, status, cos_t, sin_t, x, x2, h, h2, q, qkv_f32, attn_out, act, part, counters, ss_part, attn_o, attn_m, attn_l, head_l1, head_l2, head_sum, head_ent, head_idx, node_l1, node_l2, node_sum,
@@ -58,175 +51,15 @@ struct Layout {
   size_t part_floats;  // floats of the whole partial region
 };
 
-struct SplitPlan {
-  int tile_n, n_tiles, n_splits, k_per_split;
-  int stream = 0;
-};
 constexpr int kLayerMaxGrid = 256;   // workgroups of the layer kernel (one per CU)
 constexpr int kLayerSplitCap = 8;    // k splits of one matmul inside the layer kernel
 // Longest wait at a device-side barrier, in ticks of the 100 MHz wall clock (2 s: three orders of
 // magnitude above a whole pass).  trispec_debug_set_spin_limit changes it (tests of the expiry path).
 unsigned long long g_spin_limit = 200000000ull;
 
-inline int tiles_of(int n) { return (n + kGemmTileN - 1) / kGemmTileN; }
-// 16-row blocks that the streaming kernel multiplies for a panel of up to 128 rows: 1 to 4, 6 or 8.
-inline int row_blocks(int rows) { return rows <= 64 ? (rows + 15) / 16 : (rows <= 96 ? 6 : 8); }
-
-// Decomposition of one matmul over at most 128 rows into (column tile, k split) workgroups of the streaming
-// kernel (gemm_stream.hpp): the tile width and the number of splits with the smallest estimated time.
-//
-// A workgroup (one runs per CU) takes 3 us to its first data.  It then draws its weights and its share of the
-// activation panel, 2 bytes a column and 64 a row block and k step, at 45 (one row block) to 60 GB/s; the chip draws no
-// more than 6.3 TB/s of weights.  Finishing a tile takes 0.012 us a row block and column,
-// meeting the other splits 0.8 us more and 0.002 a split: publish the partial tile, count, read all of them.  So wide
-// tiles draw less of the panel and narrow ones meet sooner.  Estimated / measured, us: 4096 x 4096 over 60 rows 32 columns x 2 splits 17.3 / 16.9, 64 x 4 15.4 / 16.7,
-// 128 x 8 19.3 / 18.8, 16 x 1 22.6 / 19.9; 4096 x 12288 64 x 4 28.6 / 32.6, 32 x 2 39.2 / 38.4; 2048 x 6144 32 x 4 14.6 / 14.3,
-// 64 x 8 16.1 / 15.8; over 9 rows 1024 x 2048 16 x 4 5.5 / 6.5, 16 x 1 7.4 / 6.6, 32 x 2 7.6 / 7.4; over 111 rows
-// 2048 x 6144 32 x 4 19.9 / 19.9, 64 x 8 23.4 / 21.2.
-SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim, bool qk_norm) {
-  const int steps = k / 32;
-  SplitPlan best;
-  best.stream = 1;
-  best.k_per_split = k;
-  best.n_splits = 1;
-  best.tile_n = kGemmTileN;
-  if (epi == EPI_HEAD) {   // widths that the 128-column kernel does not take
-    best.n_tiles = tiles_of(n_cols);
-    return best;
-  }
-  // Widths.  QKV: whole rotation pairs; where q and k have a norm of their own, whole heads (over more than 64
-  // rows in two groups of 64: the accumulators of 128 would not fit).  Residual products: the sums of squares of any
-  // 16 columns stand for themselves.  The adapter's plain product is built in one width.
-  const int widths[] = {16, 32, 48, 64, 96, 112, 128};
-  double best_us = 1e30;
-  for (int tn : widths) {
-    int rb = row_blocks(rows), groups = 1;
-    if (epi == EPI_PLAIN) {
-      if (tn != 32) continue;
-    } else if (epi == EPI_SWIGLU) {
-      if (tn == 16 || tn == 128 || (tn == 112 && rb > 4)) continue;
-    } else if (epi == EPI_QKV) {
-      if (tn == 48 || tn == 112 || (qk_norm && tn < head_dim) || (tn == 96 && (qk_norm || head_dim != 128 || rb > 4))) continue;
-      if (tn == 128 && rb > 4) { rb = 4; groups = 2; }
-    } else if (tn == 48 || tn == 96 || tn == 112 || (tn == 128 && rb > 4)) {
-      continue;
-    }
-    const int tiles = (n_cols + tn - 1) / tn;
-    const double rate = rb == 1 ? 45e3 : 60e3, chip_us = 2.0 * n_cols * k / 6.3e6;
-    for (int sp = 1; sp <= 16 && sp <= steps && (sp == 1 || tiles * groups * sp <= 256); ++sp) {
-      const int rounds = (tiles * groups * sp + 255) / 256;
-      const double own_us = rounds * ((steps + sp - 1) / sp) * 32.0 * (2.0 * tn + 64.0 * rb) / rate;
-      double us = 3.0 * rounds + (own_us > chip_us ? own_us : chip_us) + 0.012 * rb * tn;
-      if (sp > 1) us += 0.8 + 0.002 * sp * rb * tn;
-      if (us < best_us) {
-        best_us = us;
-        best.tile_n = tn;
-        best.n_tiles = tiles;
-        best.n_splits = sp;
-      }
-      if (epi == EPI_SWIGLU) break;   // tiles enough: the kernel has no splits for it
-    }
-  }
-  return best;
-}
-// Tiles that meet at a counter, of one plan: row groups have their own
-inline int counted_tiles(int epi, const SplitPlan &p, int rows) {
-  return p.n_tiles * (epi == EPI_QKV && p.tile_n == 128 && rows > 64 ? 2 : 1);
-}
-// Floats of its partial tiles
-inline size_t stream_part_floats(int epi, const SplitPlan &p, int rows) {
-  const int rb = row_blocks(rows);
-  return p.n_splits < 2 ? 0 : (size_t)p.n_splits * p.n_tiles * p.tile_n * rb * 16;
-}
-// LM head over at most 128 rows: the 128-column kernel (kernels_gemm.hip) shares the activation panel among its
-// wavefronts through LDS; it needs reductions of whole chunk pairs.  n_splits is the number of passes of a
-// workgroup, n_tiles the entries that all of them leave: one pass each, but for more than 512 tiles (two workgroups a CU)
-// over at most 32 rows, where 512 workgroups share the sub-tiles of 32 out.
-constexpr int kHeadPlaces = 512;
-inline int head_places(int n_cols) { return tiles_of(n_cols) < kHeadPlaces ? tiles_of(n_cols) : kHeadPlaces; }
-inline int head_passes(int n_cols) {
-  const int n_sub = (n_cols + 31) / 32, places = head_places(n_cols);
-  return ((n_sub + places - 1) / places + 3) / 4;
-}
-SplitPlan plan_head(int n_cols, int k, int rows, int rows_pad) {
-  if (k % (rows_pad == 32 ? 512 : 256) != 0) return plan_stream(EPI_HEAD, n_cols, k, rows, 0, false);
-  SplitPlan p;
-  p.tile_n = kGemmTileN;
-  p.k_per_split = k;
-  p.n_splits = rows_pad == 32 ? head_passes(n_cols) : 1;
-  p.n_tiles = rows_pad == 32 ? head_places(n_cols) * p.n_splits : tiles_of(n_cols);
-  return p;
-}
-// entries per row of the sums of squares that a matmul with tiles of tile_n columns leaves
-inline int ss_tiles_of(int n, int tile_n) { return tile_n < kGemmTileN ? (n + tile_n - 1) / tile_n : tiles_of(n); }
-
-// Decomposition of one matmul over a panel of 256 rows, LM head also 128 (kernels_gemm_wide.hip): the tile width
-// and the number of k splits with the smallest estimated time.  Fitted to products of 1024 to 4096 wide models: a 64-deep
-// chunk takes a workgroup 1.65 us on a 128 x 256 tile and 1.0 us on a 128 x 128 tile, a workgroup about 6 us beside its
-// chunks, one workgroup runs per CU; splitting costs 1.5 us (a second launch, but no epilogue in the first) and the
-// partial tiles, written and read back at about 6.5 TB/s.  Estimated / measured, us, 240 rows: 6144 x 1024 in one split 22.0 / 21.7,
-// two 19.4 / 18.8; 2048 x 6144 in four 34.8 / 33.6, eight 24.7 / 25.0; 4096 x 14336 (256 columns) in eight 64.0 / 65.2.
-SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_part_floats) {
-  const int kb = k / 64, n_rg = rows_pad / 128;
-  SplitPlan best;
-  best.tile_n = 256;
-  best.n_tiles = (n_cols + 255) / 256;
-  best.n_splits = 1;
-  best.k_per_split = k;
-  if (epi == EPI_HEAD) return best;
-  double best_us = 1e30;
-  for (int tile_n = 256; tile_n >= 128; tile_n -= 128) {
-    const int tiles = (n_cols + tile_n - 1) / tile_n;
-    for (int s = 1; s <= 16 && s <= kb; ++s) {
-      const size_t floats = (size_t)s * tiles_of(n_cols) * kGemmTileN * rows_pad;
-      if (s > 1 && floats > max_part_floats) break;
-      const int rounds = (tiles * n_rg * s + 255) / 256, chunks = (kb + s - 1) / s;
-      const double us = rounds * (chunks * (tile_n == 256 ? 1.65 : 1.0) + 6.0) +
-                        (s > 1 ? 1.5 + (double)floats * 8.0 / 6.5e6 : 0.0);
-      if (us < best_us) {
-        best_us = us;
-        best.tile_n = tile_n;
-        best.n_tiles = tiles;
-        best.n_splits = s;
-      }
-    }
-  }
-  return best;
-}
-constexpr size_t kWidePartFloats = (size_t)12 << 20;   // partial tiles of one wide matmul: at most 48 MB
-
-SplitPlan plan_any(int epi, int n_cols, int k, int rows, int head_dim, bool qk_norm) {
-  const int rp = rows_pad_for(rows);
-  if (epi == EPI_HEAD && (rp <= 64 || (rp == 128 && k % 256 == 0))) return plan_head(n_cols, k, rows, rp);
-  if (epi == EPI_HEAD || rp > 128) return plan_wide(epi, n_cols, k, rp, kWidePartFloats);
-  return plan_stream(epi, n_cols, k, rows, head_dim, qk_norm);
-}
-
-// Decomposition of one matmul inside the layer kernel: at most max_items (tile, split) items, every
-// split the same whole number of `unit`-deep steps (unit = ring depth x chunk depth of the kernel
-// for this row count).  n_splits = 0: not possible for this shape.
-SplitPlan plan_layer(int n_cols, int k, int unit, int max_items, int split_cap) {
-  SplitPlan p;
-  p.tile_n = kGemmTileN;
-  p.n_tiles = (n_cols + p.tile_n - 1) / p.tile_n;
-  p.n_splits = 0;
-  p.k_per_split = 0;
-  if (p.n_tiles > max_items || k % unit != 0) return p;
-  int smax = max_items / p.n_tiles;
-  if (smax > kMaxSplitK) smax = kMaxSplitK;
-  if (smax > k / unit) smax = k / unit;
-  if (smax > split_cap) smax = split_cap;
-  for (int s = smax; s >= 1; --s)
-    if (k % s == 0 && (k / s) % unit == 0) {
-      p.n_splits = s;
-      p.k_per_split = k / s;
-      break;
-    }
-  return p;
-}
-
-
-Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
+// Only arithmetic: the matmuls' plans are the model's.  Every call of verify and decide comes through here.
+Layout make_layout(const trispec_model &m, int batch, int max_nodes) {
+  const trispec_model_config &c = m.cfg;
   Layout L;
   memset(&L, 0, sizeof(L));
   const int rows = batch * max_nodes;
@@ -261,20 +94,11 @@ Layout make_layout(const trispec_model_config &c, int batch, int max_nodes) {
     if (2 * c.ffn > m) m = 2 * c.ffn;
     L.part = take(sizeof(float) * (size_t)rp * m);
   } else {
-    // split-K partial tiles: the largest of splits x tiles x tile width x rows over the matmuls of a
-    // layer and over the panels up to this one (a workspace also serves passes of fewer rows)
-    const int ep[4] = {EPI_QKV, EPI_RESID, EPI_SWIGLU, EPI_RESID};
-    const int nc[4] = {nqkv, c.hidden, 2 * c.ffn, c.hidden};
-    const int ks[4] = {c.hidden, qd, c.hidden, c.ffn};
+    // split-K partial tiles of one matmul, over the panels up to this one (a workspace also serves passes of fewer rows)
     size_t floats = (size_t)kLayerPhases * kLayerMaxGrid * kGemmTileN * rp;
-    const int rows_of[] = {16, 32, 48, 64, 96, 128, 256};   // one of every kind of panel
-    for (int i = 0; i < 4; ++i)
-      for (int r : rows_of) {
-        const SplitPlan p = plan_any(ep[i], nc[i], ks[i], r, c.head_dim, c.qk_norm != 0);
-        if (p.stream && counted_tiles(ep[i], p, r) > L.max_tiles) L.max_tiles = counted_tiles(ep[i], p, r);
-        const size_t f = p.stream ? stream_part_floats(ep[i], p, r) : (size_t)p.n_splits * tiles_of(nc[i]) * kGemmTileN * r;
-        if (r <= rp && f > floats) floats = f;
-      }
+    const size_t planned = m.plans.part_floats[panel_kind(rp)];
+    if (planned > floats) floats = planned;
+    L.max_tiles = m.plans.max_tiles;
     // the layer kernel runs at most kLayerMaxGrid (tile, split) items per matmul and gives each
     // of its matmuls a partial region of its own
     L.part_phase = (size_t)kLayerMaxGrid * kGemmTileN * rp;
@@ -400,6 +224,7 @@ int trispec_model_create(const trispec_model_config *cfg, const trispec_weights 
   trispec_model *m = new (std::nothrow) trispec_model;
   if (!m) return TRISPEC_EARG;
   m->cfg = *cfg;
+  if (cfg->dtype == TRISPEC_BF16) m->plans = make_plans(*cfg);
   m->embed = w->embed;
   m->lm_head = w->lm_head;
   m->final_norm = w->final_norm;
@@ -586,7 +411,7 @@ int trispec_workspace_bytes(const trispec_model *m, int32_t batch, int32_t max_n
   if (batch < 1 || batch > kMaxBatch || max_nodes < 1 || max_nodes > kMaxNodes ||
       batch * max_nodes > kMaxRows)
     return TRISPEC_ENODES;
-  *bytes = make_layout(m->cfg, batch, max_nodes).total;
+  *bytes = make_layout(*m, batch, max_nodes).total;
   return TRISPEC_OK;
 }
 
@@ -597,7 +422,7 @@ int trispec_workspace_region(const trispec_model *m, int32_t batch, int32_t max_
   if (batch < 1 || batch > kMaxBatch || max_nodes < 1 || max_nodes > kMaxNodes ||
       batch * max_nodes > kMaxRows)
     return TRISPEC_ENODES;
-  const Layout L = make_layout(m->cfg, batch, max_nodes);
+  const Layout L = make_layout(*m, batch, max_nodes);
   const trispec_model_config &c = m->cfg;
   const size_t rp = L.rows_pad_max;
   struct { const char *n; size_t o, b; } tab[] = {
@@ -658,7 +483,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
   memset(&tab, 0, sizeof(tab));
   rc = build_nodes(tree_parents, B, n_nodes, opts->n_forced, tab);
   if (rc) return rc;
-  const Layout L = make_layout(c, B, n_nodes);
+  const Layout L = make_layout(*m, B, n_nodes);
   if (opts->workspace_bytes < L.total) return TRISPEC_EWORKSPACE;
   for (int i = 0; i < opts->n_feature_layers; ++i)
     if (opts->feature_layers[i] < 0 || opts->feature_layers[i] >= c.n_layers ||
@@ -922,14 +747,11 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       g.next_norm_w = (l + 1 < c.n_layers) ? m->norm_attn[l + 1] : m->final_norm; g.ss_part = ss0;
       return g;
     };
-    auto plan = [&](int epi, int n_cols, int k) {
-      return plan_any(epi, n_cols, k, rows, c.head_dim, c.qk_norm != 0);
-    };
     auto launch_gemm = [&](const GemmArgs &g) {
       if (g.stream) launch_gemm_stream(st, g); else if (g.epi == EPI_HEAD && g.tile_n == kGemmTileN) launch_gemm_head(st, g); else launch_gemm_wide(st, g);
     };
-    const SplitPlan pq = plan(EPI_QKV, nqkv, c.hidden), po = plan(EPI_RESID, c.hidden, qd);
-    const SplitPlan pg = plan(EPI_SWIGLU, 2 * c.ffn, c.hidden), pd = plan(EPI_RESID, c.hidden, c.ffn);
+    const int kind = panel_kind(rows);
+    const SplitPlan &pq = m->plans.qkv[kind], &po = m->plans.o[kind], &pg = m->plans.gate_up[kind], &pd = m->plans.down[kind];
     auto timed_gemm = [&](const GemmArgs &g, double bytes) {
       TimedLaunch tl(opts->timer, TRISPEC_K_GEMM, st, bytes);
       launch_gemm(g);
@@ -1023,7 +845,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       }
     }
     {
-      GemmArgs g = base(EPI_HEAD, h, pan_h, ss0, dn_tiles, c.hidden, c.vocab, plan(EPI_HEAD, c.vocab, c.hidden));
+      GemmArgs g = base(EPI_HEAD, h, pan_h, ss0, dn_tiles, c.hidden, c.vocab, m->plans.head[kind]);
       g.seg[0] = {m->p_lm_head, c.vocab, 0};
       g.n_seg = 1;
       hs.n_tiles = g.n_tiles;
@@ -1071,7 +893,7 @@ int trispec_decide(trispec_model *m, int32_t batch, const int32_t *draft_tokens,
   memset(&tab, 0, sizeof(tab));
   rc = build_nodes(tree_parents, batch, n_nodes, opts->n_forced, tab);
   if (rc) return rc;
-  const Layout L = make_layout(m->cfg, batch, n_nodes);
+  const Layout L = make_layout(*m, batch, n_nodes);
   if (opts->workspace_bytes < L.total) return TRISPEC_EWORKSPACE;
   hipStream_t st = (hipStream_t)opts->stream;
   char *ws = (char *)opts->workspace;

@@ -14,7 +14,7 @@
 // for weights; it draws both together at 45 - 60 GB/s, 2 bytes a column and 64 a row block and k step.  Meeting
 // the splits is bound by the size of the partial tile: it is written through to memory (32 KB a workgroup 1.7
 // us; as 8-byte stores, which leave half lines, 3.3), counted, and read back by one CU.  Without the stream's 3 us, meeting costs
-// 3.5 us at 32 columns x 64 rows and 11 at 128.  The host weighs one against the other (plan_stream in api.cpp).
+// 3.5 us at 32 columns x 64 rows and 11 at 128.  The host weighs one against the other (plan_stream in plan.hpp).
 // Measured, us, before (128-column kernel, or tiles of 32 and 64 columns in 32-row blocks) -> now.  9 rows: 4096 x 1024 (QKV) 10.5 -> 6.3,
 // 1024 x 2048 8.9 -> 6.3, 6144 x 1024 (gate + up) 9.0 -> 6.5, 1024 x 3072 9.0 -> 6.8.  One row: 6144 x 4096 17.2 -> 15.9, 4096 x
 // 4096 12.0 -> 10.6, 24576 x 4096 38.4 -> 33.1, 4096 x 12288 23.7 -> 20.1.  36 rows: 13.6 -> 8.1, 10.4 -> 7.4, 13.2 -> 8.4, 10.4 -> 8.5 at the

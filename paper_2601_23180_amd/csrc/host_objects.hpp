@@ -3,9 +3,11 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "plan.hpp"
 
 struct trispec_model {
   trispec_model_config cfg;
+  ts::ModelPlans plans = {};   // bf16 models; not changed after creation
   const void *embed, *lm_head, *final_norm;
   std::vector<const void *> wq, wk, wv, wo, w_gate, w_up, w_down, norm_attn, norm_ffn, q_norm, k_norm;
   // bf16 models: packed copies of the matrices (device, inside the caller's pack buffer)

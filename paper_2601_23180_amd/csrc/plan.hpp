@@ -1,0 +1,215 @@
+// How the matmuls of a pass are divided into workgroups: pure functions of the shape and of the number of rows.
+#pragma once
+
+#include "internal.hpp"
+
+namespace ts {
+
+inline int rows_pad_for(int rows) {
+  if (rows <= 32) return 32;
+  if (rows <= 64) return 64;
+  if (rows <= 128) return 128;
+  return 256;
+}
+
+struct SplitPlan {
+  int tile_n, n_tiles, n_splits, k_per_split;
+  int stream = 0;
+};
+
+inline int tiles_of(int n) { return (n + kGemmTileN - 1) / kGemmTileN; }
+// 16-row blocks that the streaming kernel multiplies for a panel of up to 128 rows: 1 to 4, 6 or 8.
+inline int row_blocks(int rows) { return rows <= 64 ? (rows + 15) / 16 : (rows <= 96 ? 6 : 8); }
+
+// Decomposition of one matmul over at most 128 rows into (column tile, k split) workgroups of the streaming
+// kernel (gemm_stream.hpp): the tile width and the number of splits with the smallest estimated time.
+//
+// A workgroup (one runs per CU) takes 3 us to its first data.  It then draws its weights and its share of the
+// activation panel, 2 bytes a column and 64 a row block and k step, at 45 (one row block) to 60 GB/s; the chip draws no
+// more than 6.3 TB/s of weights.  Finishing a tile takes 0.012 us a row block and column,
+// meeting the other splits 0.8 us more and 0.002 a split: publish the partial tile, count, read all of them.  So wide
+// tiles draw less of the panel and narrow ones meet sooner.  Estimated / measured, us: 4096 x 4096 over 60 rows 32 columns x 2 splits 17.3 / 16.9, 64 x 4 15.4 / 16.7,
+// 128 x 8 19.3 / 18.8, 16 x 1 22.6 / 19.9; 4096 x 12288 64 x 4 28.6 / 32.6, 32 x 2 39.2 / 38.4; 2048 x 6144 32 x 4 14.6 / 14.3,
+// 64 x 8 16.1 / 15.8; over 9 rows 1024 x 2048 16 x 4 5.5 / 6.5, 16 x 1 7.4 / 6.6, 32 x 2 7.6 / 7.4; over 111 rows
+// 2048 x 6144 32 x 4 19.9 / 19.9, 64 x 8 23.4 / 21.2.
+inline SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim, bool qk_norm) {
+  const int steps = k / 32;
+  SplitPlan best;
+  best.stream = 1;
+  best.k_per_split = k;
+  best.n_splits = 1;
+  best.tile_n = kGemmTileN;
+  if (epi == EPI_HEAD) {   // widths that the 128-column kernel does not take
+    best.n_tiles = tiles_of(n_cols);
+    return best;
+  }
+  // Widths.  QKV: whole rotation pairs; where q and k have a norm of their own, whole heads (over more than 64
+  // rows in two groups of 64: the accumulators of 128 would not fit).  Residual products: the sums of squares of any
+  // 16 columns stand for themselves.  The adapter's plain product is built in one width.
+  const int widths[] = {16, 32, 48, 64, 96, 112, 128};
+  double best_us = 1e30;
+  for (int tn : widths) {
+    int rb = row_blocks(rows), groups = 1;
+    if (epi == EPI_PLAIN) {
+      if (tn != 32) continue;
+    } else if (epi == EPI_SWIGLU) {
+      if (tn == 16 || tn == 128 || (tn == 112 && rb > 4)) continue;
+    } else if (epi == EPI_QKV) {
+      if (tn == 48 || tn == 112 || (qk_norm && tn < head_dim) || (tn == 96 && (qk_norm || head_dim != 128 || rb > 4))) continue;
+      if (tn == 128 && rb > 4) { rb = 4; groups = 2; }
+    } else if (tn == 48 || tn == 96 || tn == 112 || (tn == 128 && rb > 4)) {
+      continue;
+    }
+    const int tiles = (n_cols + tn - 1) / tn;
+    const double rate = rb == 1 ? 45e3 : 60e3, chip_us = 2.0 * n_cols * k / 6.3e6;
+    for (int sp = 1; sp <= 16 && sp <= steps && (sp == 1 || tiles * groups * sp <= 256); ++sp) {
+      const int rounds = (tiles * groups * sp + 255) / 256;
+      const double own_us = rounds * ((steps + sp - 1) / sp) * 32.0 * (2.0 * tn + 64.0 * rb) / rate;
+      double us = 3.0 * rounds + (own_us > chip_us ? own_us : chip_us) + 0.012 * rb * tn;
+      if (sp > 1) us += 0.8 + 0.002 * sp * rb * tn;
+      if (us < best_us) {
+        best_us = us;
+        best.tile_n = tn;
+        best.n_tiles = tiles;
+        best.n_splits = sp;
+      }
+      if (epi == EPI_SWIGLU) break;   // tiles enough: the kernel has no splits for it
+    }
+  }
+  return best;
+}
+// Tiles that meet at a counter, of one plan: row groups have their own
+inline int counted_tiles(int epi, const SplitPlan &p, int rows) {
+  return p.n_tiles * (epi == EPI_QKV && p.tile_n == 128 && rows > 64 ? 2 : 1);
+}
+// Floats of its partial tiles
+inline size_t stream_part_floats(int epi, const SplitPlan &p, int rows) {
+  const int rb = row_blocks(rows);
+  return p.n_splits < 2 ? 0 : (size_t)p.n_splits * p.n_tiles * p.tile_n * rb * 16;
+}
+// LM head over at most 128 rows: the 128-column kernel (kernels_gemm.hip) shares the activation panel among its
+// wavefronts through LDS; it needs reductions of whole chunk pairs.  n_splits is the number of passes of a
+// workgroup, n_tiles the entries that all of them leave: one pass each, but for more than 512 tiles (two workgroups a CU)
+// over at most 32 rows, where 512 workgroups share the sub-tiles of 32 out.
+constexpr int kHeadPlaces = 512;
+inline int head_places(int n_cols) { return tiles_of(n_cols) < kHeadPlaces ? tiles_of(n_cols) : kHeadPlaces; }
+inline int head_passes(int n_cols) {
+  const int n_sub = (n_cols + 31) / 32, places = head_places(n_cols);
+  return ((n_sub + places - 1) / places + 3) / 4;
+}
+inline SplitPlan plan_head(int n_cols, int k, int rows, int rows_pad) {
+  if (k % (rows_pad == 32 ? 512 : 256) != 0) return plan_stream(EPI_HEAD, n_cols, k, rows, 0, false);
+  SplitPlan p;
+  p.tile_n = kGemmTileN;
+  p.k_per_split = k;
+  p.n_splits = rows_pad == 32 ? head_passes(n_cols) : 1;
+  p.n_tiles = rows_pad == 32 ? head_places(n_cols) * p.n_splits : tiles_of(n_cols);
+  return p;
+}
+// entries per row of the sums of squares that a matmul with tiles of tile_n columns leaves
+inline int ss_tiles_of(int n, int tile_n) { return tile_n < kGemmTileN ? (n + tile_n - 1) / tile_n : tiles_of(n); }
+
+// Decomposition of one matmul over a panel of 256 rows, LM head also 128 (kernels_gemm_wide.hip): the tile width
+// and the number of k splits with the smallest estimated time.  Fitted to products of 1024 to 4096 wide models: a 64-deep
+// chunk takes a workgroup 1.65 us on a 128 x 256 tile and 1.0 us on a 128 x 128 tile, a workgroup about 6 us beside its
+// chunks, one workgroup runs per CU; splitting costs 1.5 us (a second launch, but no epilogue in the first) and the
+// partial tiles, written and read back at about 6.5 TB/s.  Estimated / measured, us, 240 rows: 6144 x 1024 in one split 22.0 / 21.7,
+// two 19.4 / 18.8; 2048 x 6144 in four 34.8 / 33.6, eight 24.7 / 25.0; 4096 x 14336 (256 columns) in eight 64.0 / 65.2.
+inline SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_part_floats) {
+  const int kb = k / 64, n_rg = rows_pad / 128;
+  SplitPlan best;
+  best.tile_n = 256;
+  best.n_tiles = (n_cols + 255) / 256;
+  best.n_splits = 1;
+  best.k_per_split = k;
+  if (epi == EPI_HEAD) return best;
+  double best_us = 1e30;
+  for (int tile_n = 256; tile_n >= 128; tile_n -= 128) {
+    const int tiles = (n_cols + tile_n - 1) / tile_n;
+    for (int s = 1; s <= 16 && s <= kb; ++s) {
+      const size_t floats = (size_t)s * tiles_of(n_cols) * kGemmTileN * rows_pad;
+      if (s > 1 && floats > max_part_floats) break;
+      const int rounds = (tiles * n_rg * s + 255) / 256, chunks = (kb + s - 1) / s;
+      const double us = rounds * (chunks * (tile_n == 256 ? 1.65 : 1.0) + 6.0) +
+                        (s > 1 ? 1.5 + (double)floats * 8.0 / 6.5e6 : 0.0);
+      if (us < best_us) {
+        best_us = us;
+        best.tile_n = tile_n;
+        best.n_tiles = tiles;
+        best.n_splits = s;
+      }
+    }
+  }
+  return best;
+}
+constexpr size_t kWidePartFloats = (size_t)12 << 20;   // partial tiles of one wide matmul: at most 48 MB
+
+inline SplitPlan plan_any(int epi, int n_cols, int k, int rows, int head_dim, bool qk_norm) {
+  const int rp = rows_pad_for(rows);
+  if (epi == EPI_HEAD && (rp <= 64 || (rp == 128 && k % 256 == 0))) return plan_head(n_cols, k, rows, rp);
+  if (epi == EPI_HEAD || rp > 128) return plan_wide(epi, n_cols, k, rp, kWidePartFloats);
+  return plan_stream(epi, n_cols, k, rows, head_dim, qk_norm);
+}
+
+// Decomposition of one matmul inside the layer kernel: at most max_items (tile, split) items, every
+// split the same whole number of `unit`-deep steps (unit = ring depth x chunk depth of the kernel
+// for this row count).  n_splits = 0: not possible for this shape.
+inline SplitPlan plan_layer(int n_cols, int k, int unit, int max_items, int split_cap) {
+  SplitPlan p;
+  p.tile_n = kGemmTileN;
+  p.n_tiles = (n_cols + p.tile_n - 1) / p.tile_n;
+  p.n_splits = 0;
+  p.k_per_split = 0;
+  if (p.n_tiles > max_items || k % unit != 0) return p;
+  int smax = max_items / p.n_tiles;
+  if (smax > kMaxSplitK) smax = kMaxSplitK;
+  if (smax > k / unit) smax = k / unit;
+  if (smax > split_cap) smax = split_cap;
+  for (int s = smax; s >= 1; --s)
+    if (k % s == 0 && (k / s) % unit == 0) {
+      p.n_splits = s;
+      p.k_per_split = k / s;
+      break;
+    }
+  return p;
+}
+
+// ---- the plans of one model, made once: the matmuls of a pass depend on its rows only through the kind of panel
+
+// kinds of panels: 1 to 4 row blocks of 16, 6, 8, more than 128 rows
+constexpr int kPanelKinds = 7;
+constexpr int kPanelRows[kPanelKinds] = {16, 32, 48, 64, 96, 128, 256};   // the most rows of each
+inline int panel_kind(int rows) {
+  int i = 0;
+  while (i + 1 < kPanelKinds && rows > kPanelRows[i]) ++i;
+  return i;
+}
+struct ModelPlans {
+  SplitPlan qkv[kPanelKinds], o[kPanelKinds], gate_up[kPanelKinds], down[kPanelKinds], head[kPanelKinds];
+  int max_tiles;                     // tile counters that the streaming kernel needs, over all panels
+  size_t part_floats[kPanelKinds];   // partial tiles of one matmul over panels of this and the smaller kinds
+};
+inline ModelPlans make_plans(const trispec_model_config &c) {   // bf16 models
+  ModelPlans m = {};
+  const int qd = c.n_q_heads * c.head_dim, nqkv = qd + 2 * c.n_kv_heads * c.head_dim;
+  for (int i = 0; i < kPanelKinds; ++i) {
+    const int r = kPanelRows[i];
+    m.part_floats[i] = i > 0 ? m.part_floats[i - 1] : 0;
+    auto plan = [&](int epi, int n_cols, int k) {
+      const SplitPlan p = plan_any(epi, n_cols, k, r, c.head_dim, c.qk_norm != 0);
+      if (epi == EPI_HEAD) return p;
+      if (p.stream && counted_tiles(epi, p, r) > m.max_tiles) m.max_tiles = counted_tiles(epi, p, r);
+      const size_t f = p.stream ? stream_part_floats(epi, p, r) : (size_t)p.n_splits * tiles_of(n_cols) * kGemmTileN * r;
+      if (f > m.part_floats[i]) m.part_floats[i] = f;
+      return p;
+    };
+    m.qkv[i] = plan(EPI_QKV, nqkv, c.hidden);
+    m.o[i] = plan(EPI_RESID, c.hidden, qd);
+    m.gate_up[i] = plan(EPI_SWIGLU, 2 * c.ffn, c.hidden);
+    m.down[i] = plan(EPI_RESID, c.hidden, c.ffn);
+    m.head[i] = plan(EPI_HEAD, c.vocab, c.hidden);
+  }
+  return m;
+}
+
+}  // namespace ts

@@ -3,6 +3,7 @@ and the host-side validation returns the documented error codes without touching
 import ctypes as C
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -95,6 +96,29 @@ def test_kv_and_workspace_sizes():
     per_layer = 2 * 256 * 256 + 2 * 256 * 128 + 3 * 256 * 512 + 2 * 256
     assert d.value == (2 * per_layer + 4096 * 256 + 2 * 2 * (128 + 9) * 128) * 4
     lib.trispec_model_destroy(m)
+
+
+def test_the_layout_of_a_call_does_not_plan_the_matmuls():
+    """verify and decide lay the workspace out on every call; the plans of the matmuls (microseconds)
+    are made with the model.  Against a size query that plans nothing, with the same cost of the call itself."""
+    lib = B.lib()
+    rc, m, keep = _model(dtype=B.TRISPEC_BF16, hidden=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, ffn=12288, vocab=151936)
+    assert rc == 0
+    n = C.c_size_t()
+    p = C.byref(n)
+
+    def best_us(fn, *args):
+        best = 1e9
+        for _ in range(30):
+            t0 = time.perf_counter()
+            for _ in range(200):
+                fn(*args)
+            best = min(best, time.perf_counter() - t0)
+        return best / 200 * 1e6
+
+    plain, layout = best_us(lib.trispec_kv_bytes, m, 1, 4096, p), best_us(lib.trispec_workspace_bytes, m, 1, 60, p)
+    lib.trispec_model_destroy(m)
+    assert layout < 2 * plain, (plain, layout)
 
 
 @pytest.mark.parametrize("kw", [dict(), dict(dtype=B.TRISPEC_BF16), dict(dtype=B.TRISPEC_BF16, hidden=1472, ffn=4032,
