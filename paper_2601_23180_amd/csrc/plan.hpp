@@ -78,14 +78,14 @@ inline SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim,
   }
   return best;
 }
-// Tiles that meet at a counter, of one plan: row groups have their own
-inline int counted_tiles(int epi, const SplitPlan &p, int rows) {
-  return p.n_tiles * (epi == EPI_QKV && p.tile_n == 128 && rows > 64 ? 2 : 1);
-}
+// Row groups of one plan: a QKV tile of 128 columns over more than 64 rows takes them in two groups of 64
+inline int row_groups(int epi, const SplitPlan &p, int rows) { return epi == EPI_QKV && p.tile_n == 128 && rows > 64 ? 2 : 1; }
+// Tiles that meet at a counter: row groups have their own
+inline int counted_tiles(int epi, const SplitPlan &p, int rows) { return p.n_tiles * row_groups(epi, p, rows); }
 // Floats of its partial tiles
 inline size_t stream_part_floats(int epi, const SplitPlan &p, int rows) {
-  const int rb = row_blocks(rows);
-  return p.n_splits < 2 ? 0 : (size_t)p.n_splits * p.n_tiles * p.tile_n * rb * 16;
+  const int groups = row_groups(epi, p, rows), tile_rows = groups > 1 ? 64 : 16 * row_blocks(rows);
+  return p.n_splits < 2 ? 0 : (size_t)p.n_splits * p.n_tiles * groups * tile_rows * p.tile_n;
 }
 // LM head over at most 128 rows: the 128-column kernel (kernels_gemm.hip) shares the activation panel among its
 // wavefronts through LDS; it needs reductions of whole chunk pairs.  n_splits is the number of passes of a
