@@ -584,6 +584,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
     if (f32) launch_attn_f32(st, at); else launch_attn_bf16(st, at);
   };
 
+  bool launched = true;   // every matmul had a kernel for its plan
   (void)hipGetLastError();
   {
     BeginArgs g;
@@ -698,7 +699,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       g.rows = rows;
       g.rows_pad = rp;
       g.tile_n = p.tile_n;
-      g.stream = p.stream;
+      g.kernel = p.kernel;
       g.n_tiles = p.n_tiles;
       g.n_splits = p.n_splits;
       g.k_per_split = p.k_per_split;
@@ -748,7 +749,9 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       return g;
     };
     auto launch_gemm = [&](const GemmArgs &g) {
-      if (g.stream) launch_gemm_stream(st, g); else if (g.epi == EPI_HEAD && g.tile_n == kGemmTileN) launch_gemm_head(st, g); else launch_gemm_wide(st, g);
+      if (g.kernel == GEMM_STREAM) launched = launch_gemm_stream(st, g) && launched;
+      else if (g.kernel == GEMM_HEAD) launch_gemm_head(st, g);
+      else launch_gemm_wide(st, g);
     };
     const int kind = panel_kind(rows);
     const SplitPlan &pq = m->plans.qkv[kind], &po = m->plans.o[kind], &pg = m->plans.gate_up[kind], &pd = m->plans.down[kind];
@@ -859,7 +862,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       // matrix, a plain fp32 result (+ bias)
       SplitPlan pa = rp > 128 ? plan_wide(EPI_PLAIN, opts->adapter_dim, c.hidden, rp, L.part_floats)
                               : plan_stream(EPI_PLAIN, opts->adapter_dim, c.hidden, rows, c.head_dim, c.qk_norm != 0);
-      if (pa.stream && (pa.n_tiles > L.max_tiles || stream_part_floats(EPI_PLAIN, pa, rows) > L.part_floats))
+      if (pa.kernel == GEMM_STREAM && (pa.n_tiles > L.max_tiles || stream_part_floats(EPI_PLAIN, pa, rows) > L.part_floats))
         pa.n_splits = 1;   // no counters for that many tiles, or no room
       GemmArgs g = base(EPI_PLAIN, h, pan_h, ss0, dn_tiles, c.hidden, opts->adapter_dim, pa);
       g.seg[0] = {opts->adapter_w, opts->adapter_dim, 0};
@@ -877,7 +880,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
                       (float *)(ws + L.node_sum), (float *)(ws + L.node_ent), (int32_t *)(ws + L.node_idx));
   DecideArgs d = make_decide(L, ws, draft_tokens, B, n_nodes, threshold, opts, out);
   launch_decide(st, d);
-  return hipGetLastError() == hipSuccess ? TRISPEC_OK : TRISPEC_ELAUNCH;
+  return launched && hipGetLastError() == hipSuccess ? TRISPEC_OK : TRISPEC_ELAUNCH;
 }
 
 int trispec_decide(trispec_model *m, int32_t batch, const int32_t *draft_tokens, const int32_t *tree_parents,

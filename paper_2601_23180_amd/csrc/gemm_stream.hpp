@@ -27,6 +27,7 @@
 #pragma once
 
 #include "gemm_tile.hpp"
+#include "plan.hpp"
 
 namespace ts {
 
@@ -261,43 +262,36 @@ void launch_one(hipStream_t st, const GemmArgs &a) {
   hipLaunchKernelGGL((k_gemm_stream<RB, CB, S::NW, 2, EPI>), grid, block, 0, st, a);
 }
 
+// False, and nothing launched: not built
 template <int RB, int EPI>
-void dispatch_cols(hipStream_t st, const GemmArgs &a) {
-  if constexpr (EPI == EPI_HEAD) {
-    if constexpr (RB <= 4) launch_one<RB, 8, EPI>(st, a);
-  } else if constexpr (EPI == EPI_PLAIN) {
-    launch_one<RB, 2, EPI>(st, a);
-  } else if constexpr (EPI == EPI_SWIGLU) {
-    switch (a.tile_n) {
-      case 32: launch_one<RB, 2, EPI>(st, a); break;
-      case 48: launch_one<RB, 3, EPI>(st, a); break;
-      case 64: launch_one<RB, 4, EPI>(st, a); break;
-      case 96: launch_one<RB, 6, EPI>(st, a); break;
-      default: if constexpr (RB <= 4) launch_one<RB, 7, EPI>(st, a); break;   // 112
-    }
-  } else {
-    switch (a.tile_n) {
-      case 16: launch_one<RB, 1, EPI>(st, a); break;
-      case 32: launch_one<RB, 2, EPI>(st, a); break;
-      case 64: launch_one<RB, 4, EPI>(st, a); break;
-      case 96: if constexpr (EPI == EPI_QKV && RB <= 4) launch_one<RB, 6, EPI>(st, a); break;
-      default: if constexpr (RB <= 4) launch_one<RB, 8, EPI>(st, a); break;
-    }
+bool dispatch_cols(hipStream_t st, const GemmArgs &a) {
+  auto built = [&](auto cb) {
+    constexpr int CB = decltype(cb)::value;
+    if constexpr (stream_built(EPI, CB * 16, RB)) launch_one<RB, CB, EPI>(st, a);
+    return stream_built(EPI, CB * 16, RB);
+  };
+  switch (a.tile_n) {
+    case 16: return built(IC<1>{});
+    case 32: return built(IC<2>{});
+    case 48: return built(IC<3>{});
+    case 64: return built(IC<4>{});
+    case 96: return built(IC<6>{});
+    case 112: return built(IC<7>{});
+    case 128: return built(IC<8>{});
+    default: return false;
   }
 }
 
 template <int EPI>
-void dispatch_rows(hipStream_t st, const GemmArgs &a) {
-  switch ((a.rows + 15) / 16) {
-    case 1: dispatch_cols<1, EPI>(st, a); break;
-    case 2: dispatch_cols<2, EPI>(st, a); break;
-    case 3: dispatch_cols<3, EPI>(st, a); break;
-    case 4: dispatch_cols<4, EPI>(st, a); break;
+bool dispatch_rows(hipStream_t st, const GemmArgs &a) {
+  switch (row_blocks(a.rows)) {
+    case 1: return dispatch_cols<1, EPI>(st, a);
+    case 2: return dispatch_cols<2, EPI>(st, a);
+    case 3: return dispatch_cols<3, EPI>(st, a);
+    case 4: return dispatch_cols<4, EPI>(st, a);
     default:   // up to 128 rows; a head of 128 that stays whole: two groups of 64
-      if (EPI == EPI_QKV && a.tile_n == 128) dispatch_cols<4, EPI>(st, a);
-      else if (a.rows <= 96) dispatch_cols<6, EPI>(st, a);
-      else dispatch_cols<8, EPI>(st, a);
-      break;
+      if (EPI == EPI_QKV && a.tile_n == 128) return dispatch_cols<4, EPI>(st, a);
+      return row_blocks(a.rows) == 6 ? dispatch_cols<6, EPI>(st, a) : dispatch_cols<8, EPI>(st, a);
   }
 }
 

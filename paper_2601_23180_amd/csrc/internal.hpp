@@ -97,6 +97,8 @@ struct GemmSeg {
   int32_t col0;    // first output column of this segment
 };
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3, EPI_PLAIN = 4 };
+// gemm_stream.hpp, kernels_gemm.hip, kernels_gemm_wide.hip, kernels_layer.hip
+enum { GEMM_STREAM = 0, GEMM_HEAD = 1, GEMM_WIDE = 2, GEMM_LAYER = 3 };
 struct GemmArgs {
   // fp32 reference-precision path: x is [rows_pad, K] fp32, out is [rows][n_total].
   // bf16 path: x is the bf16 hi panel [rows_pad, K], the lo panel follows x_panel elements later.
@@ -115,7 +117,7 @@ struct GemmArgs {
   int32_t k_per_split; // of the layer kernel; the other kernels share k out evenly
   int32_t n_splits;
   int32_t n_tiles;
-  int32_t stream;      // 1 = gemm_stream.hpp
+  int32_t kernel;      // GEMM_*
   int32_t tile_n;      // output columns per workgroup: 128; stream 16 .. 128; more than 128 rows 128 or 256
   int32_t epi;
   float *out;          // fp32 path, and the PLAIN epilogue: [rows][n_total] fp32
@@ -289,7 +291,7 @@ void launch_gemm_f32(hipStream_t st, const GemmArgs &a);
 size_t packed_weight_bytes(int n_rows, int k);
 void launch_pack_weights(hipStream_t st, const void *w, int n_rows, int k, void *out);
 void launch_gemm_head(hipStream_t st, const GemmArgs &a);   // LM head, up to 128 rows: 4 wavefronts, 128-column tiles
-void launch_gemm_stream(hipStream_t st, const GemmArgs &a);   // up to 128 rows: wavefronts share the reduction, tile_n = 16 .. 128
+bool launch_gemm_stream(hipStream_t st, const GemmArgs &a);   // up to 128 rows: wavefronts share the reduction, tile_n = 16 .. 128; false: not built (stream_built in plan.hpp)
 void launch_gemm_wide(hipStream_t st, const GemmArgs &a);   // more rows: tile_n = 256 or 128 columns, k splits of whole 64-deep blocks
 void launch_stats_from_logits(hipStream_t st, const float *logits, int rows, int vocab,
                               const HeadStats &hs);

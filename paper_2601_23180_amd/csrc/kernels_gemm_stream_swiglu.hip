@@ -3,6 +3,6 @@
 
 namespace ts {
 
-void launch_gemm_stream_swiglu(hipStream_t st, const GemmArgs &a) { dispatch_rows<EPI_SWIGLU>(st, a); }
+bool launch_gemm_stream_swiglu(hipStream_t st, const GemmArgs &a) { return dispatch_rows<EPI_SWIGLU>(st, a); }
 
 }  // namespace ts

@@ -276,8 +276,11 @@ template <int EPI>
 static void dispatch_wide(hipStream_t st, const GemmArgs &a) {
   const int n_rg = (a.rows + kWideRows - 1) / kWideRows;
   const dim3 grid((a.n_total + a.tile_n - 1) / a.tile_n, n_rg, a.n_splits);
-  if (a.tile_n == 256) hipLaunchKernelGGL((k_gemm_wide<1, 4, 4, 2, EPI>), grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((k_gemm_wide<2, 4, 2, 1, EPI>), grid, dim3(512), 0, st, a);
+  if (EPI == EPI_HEAD || a.tile_n == 256) {   // the LM head is always in 256-column tiles
+    hipLaunchKernelGGL((k_gemm_wide<1, 4, 4, 2, EPI>), grid, dim3(256), 0, st, a);
+  } else if constexpr (EPI != EPI_HEAD) {
+    hipLaunchKernelGGL((k_gemm_wide<2, 4, 2, 1, EPI>), grid, dim3(512), 0, st, a);
+  }
   if constexpr (EPI != EPI_HEAD) {
     if (a.n_splits > 1)
       hipLaunchKernelGGL(k_gemm_finish<EPI>, dim3((a.n_total + 127) / 128, (a.rows + 31) / 32), dim3(256), 0, st, a);

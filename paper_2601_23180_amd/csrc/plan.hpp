@@ -13,13 +13,26 @@ inline int rows_pad_for(int rows) {
 }
 
 struct SplitPlan {
+  int kernel;   // GEMM_*
   int tile_n, n_tiles, n_splits, k_per_split;
-  int stream = 0;
 };
 
 inline int tiles_of(int n) { return (n + kGemmTileN - 1) / kGemmTileN; }
 // 16-row blocks that the streaming kernel multiplies for a panel of up to 128 rows: 1 to 4, 6 or 8.
 inline int row_blocks(int rows) { return rows <= 64 ? (rows + 15) / 16 : (rows <= 96 ? 6 : 8); }
+
+// Tile widths that the streaming kernel is built in, by 16-row blocks of its tile.  QKV: whole rotation pairs.  The sums of
+// squares of any 16 columns of a residual product stand for themselves.  The adapter's plain product: one width.  LM
+// head: widths that the 128-column kernel does not take.  Accumulators of 128 x 128, for QKV also 96 columns over more than
+// 64 rows, for gate + up 112, do not fit.
+constexpr bool stream_built(int epi, int tile_n, int rb) {
+  if (rb < 1 || rb > 8 || rb == 5 || rb == 7) return false;
+  if (epi == EPI_HEAD) return tile_n == 128 && rb <= 4;
+  if (epi == EPI_PLAIN) return tile_n == 32;
+  if (epi == EPI_SWIGLU) return tile_n == 32 || tile_n == 48 || tile_n == 64 || tile_n == 96 || (tile_n == 112 && rb <= 4);
+  if (tile_n == 96) return epi == EPI_QKV && rb <= 4;
+  return tile_n == 16 || tile_n == 32 || tile_n == 64 || (tile_n == 128 && rb <= 4);
+}
 
 // Decomposition of one matmul over at most 128 rows into (column tile, k split) workgroups of the streaming
 // kernel (gemm_stream.hpp): the tile width and the number of splits with the smallest estimated time.
@@ -35,7 +48,7 @@ inline int row_blocks(int rows) { return rows <= 64 ? (rows + 15) / 16 : (rows <
 inline SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim, bool qk_norm) {
   const int steps = k / 32;
   SplitPlan best;
-  best.stream = 1;
+  best.kernel = GEMM_STREAM;
   best.k_per_split = k;
   best.n_splits = 1;
   best.tile_n = kGemmTileN;
@@ -43,23 +56,17 @@ inline SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim,
     best.n_tiles = tiles_of(n_cols);
     return best;
   }
-  // Widths.  QKV: whole rotation pairs; where q and k have a norm of their own, whole heads (over more than 64
-  // rows in two groups of 64: the accumulators of 128 would not fit).  Residual products: the sums of squares of any
-  // 16 columns stand for themselves.  The adapter's plain product is built in one width.
+  // Where q and k have a norm of their own a tile holds whole heads, over more than 64 rows in two groups of 64; other heads
+  // of 128 are divided into rotation pairs by 96 columns too.
   const int widths[] = {16, 32, 48, 64, 96, 112, 128};
   double best_us = 1e30;
   for (int tn : widths) {
     int rb = row_blocks(rows), groups = 1;
-    if (epi == EPI_PLAIN) {
-      if (tn != 32) continue;
-    } else if (epi == EPI_SWIGLU) {
-      if (tn == 16 || tn == 128 || (tn == 112 && rb > 4)) continue;
-    } else if (epi == EPI_QKV) {
-      if (tn == 48 || tn == 112 || (qk_norm && tn < head_dim) || (tn == 96 && (qk_norm || head_dim != 128 || rb > 4))) continue;
+    if (epi == EPI_QKV) {
+      if ((qk_norm && tn < head_dim) || (tn == 96 && (qk_norm || head_dim != 128))) continue;
       if (tn == 128 && rb > 4) { rb = 4; groups = 2; }
-    } else if (tn == 48 || tn == 96 || tn == 112 || (tn == 128 && rb > 4)) {
-      continue;
     }
+    if (!stream_built(epi, tn, rb)) continue;
     const int tiles = (n_cols + tn - 1) / tn;
     const double rate = rb == 1 ? 45e3 : 60e3, chip_us = 2.0 * n_cols * k / 6.3e6;
     for (int sp = 1; sp <= 16 && sp <= steps && (sp == 1 || tiles * groups * sp <= 256); ++sp) {
@@ -100,6 +107,7 @@ inline int head_passes(int n_cols) {
 inline SplitPlan plan_head(int n_cols, int k, int rows, int rows_pad) {
   if (k % (rows_pad == 32 ? 512 : 256) != 0) return plan_stream(EPI_HEAD, n_cols, k, rows, 0, false);
   SplitPlan p;
+  p.kernel = GEMM_HEAD;
   p.tile_n = kGemmTileN;
   p.k_per_split = k;
   p.n_splits = rows_pad == 32 ? head_passes(n_cols) : 1;
@@ -118,6 +126,7 @@ inline int ss_tiles_of(int n, int tile_n) { return tile_n < kGemmTileN ? (n + ti
 inline SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_part_floats) {
   const int kb = k / 64, n_rg = rows_pad / 128;
   SplitPlan best;
+  best.kernel = GEMM_WIDE;
   best.tile_n = 256;
   best.n_tiles = (n_cols + 255) / 256;
   best.n_splits = 1;
@@ -156,6 +165,7 @@ inline SplitPlan plan_any(int epi, int n_cols, int k, int rows, int head_dim, bo
 // for this row count).  n_splits = 0: not possible for this shape.
 inline SplitPlan plan_layer(int n_cols, int k, int unit, int max_items, int split_cap) {
   SplitPlan p;
+  p.kernel = GEMM_LAYER;
   p.tile_n = kGemmTileN;
   p.n_tiles = (n_cols + p.tile_n - 1) / p.tile_n;
   p.n_splits = 0;
@@ -198,8 +208,9 @@ inline ModelPlans make_plans(const trispec_model_config &c) {   // bf16 models
     auto plan = [&](int epi, int n_cols, int k) {
       const SplitPlan p = plan_any(epi, n_cols, k, r, c.head_dim, c.qk_norm != 0);
       if (epi == EPI_HEAD) return p;
-      if (p.stream && counted_tiles(epi, p, r) > m.max_tiles) m.max_tiles = counted_tiles(epi, p, r);
-      const size_t f = p.stream ? stream_part_floats(epi, p, r) : (size_t)p.n_splits * tiles_of(n_cols) * kGemmTileN * r;
+      const bool stream = p.kernel == GEMM_STREAM;
+      if (stream && counted_tiles(epi, p, r) > m.max_tiles) m.max_tiles = counted_tiles(epi, p, r);
+      const size_t f = stream ? stream_part_floats(epi, p, r) : (size_t)p.n_splits * tiles_of(n_cols) * kGemmTileN * r;
       if (f > m.part_floats[i]) m.part_floats[i] = f;
       return p;
     };
