@@ -26,11 +26,11 @@ CASES = [
     ("rows64_whole_heads", 1, 64, TB.with_(hidden=1344, ffn=1024, n_q_heads=8, qk_norm=True, vocab=129,
                                            lm_head_std=0.2)),
     ("rows64_chunks", 4, 16, TB.with_(hidden=2048, ffn=2560, n_q_heads=16, n_kv_heads=8, lm_head_std=0.15)),
-    # every tile width: gate + up 48, 96 and 112 columns, QKV 96, runs that are no whole number of rounds, 8 wavefronts and 4
+    # larger products: QKV in 96 columns, gate + up in 48 and 112, runs that are no whole number of rounds
     ("rows60_qkv96_gate_up48", 1, 60, TB.with_(hidden=4096, ffn=6144, n_q_heads=32, n_kv_heads=8, lm_head_std=0.1)),
     ("rows16_gate_up112_odd_head64", 1, 16, TB.with_(hidden=448, ffn=14336, head_dim=64, n_q_heads=7, n_kv_heads=7,
                                                      lm_head_std=0.3)),
-    ("rows48_gate_up96_ragged", 3, 16, TB.with_(hidden=576, ffn=12352, n_q_heads=4, lm_head_std=0.3)),
+    ("rows48_gate_up112_ragged", 3, 16, TB.with_(hidden=576, ffn=12352, n_q_heads=4, lm_head_std=0.3)),
     ("rows17_wide_down", 1, 17, TB.with_(hidden=4096, ffn=4096, n_q_heads=2, lm_head_std=0.1)),
     # LM head: more tiles than places over at most 32 rows (two passes of two or three sub-tiles, a ragged last one)
     ("rows9_vocab_passes", 1, 9, TB.with_(hidden=512, ffn=256, vocab=70001, lm_head_std=0.3)),
@@ -49,6 +49,34 @@ CASES = [
 ]
 
 
+# The streaming kernel in every tile width that a model of at most 30M weights a layer takes, over every number of row blocks,
+# in one k split and in several (test_plans.py looks the plans up): batch, nodes, hidden, query heads, kv heads,
+# head_dim, ffn, qk_norm
+WIDTHS = [
+    (1, 1, 64, 32, 4, 128, 8448, 0), (2, 4, 64, 10, 2, 64, 64, 1), (1, 8, 1536, 8, 1, 128, 64, 1),
+    (3, 3, 4160, 1, 1, 64, 64, 1), (1, 11, 16512, 1, 1, 64, 64, 1), (2, 6, 2816, 14, 2, 128, 128, 0),
+    (2, 7, 64, 8, 1, 64, 12352, 0), (5, 3, 64, 2, 1, 64, 6400, 0), (2, 8, 64, 2, 1, 128, 4224, 1),
+    (4, 4, 8576, 1, 1, 64, 64, 0), (1, 19, 64, 32, 4, 128, 18624, 0), (5, 4, 4160, 1, 1, 64, 64, 0),
+    (3, 8, 1472, 12, 2, 128, 64, 1), (1, 25, 64, 2, 1, 128, 6848, 1), (1, 26, 2624, 3, 3, 128, 64, 0),
+    (2, 14, 64, 1, 1, 64, 4224, 1), (7, 4, 16512, 1, 1, 64, 64, 0), (1, 29, 8320, 1, 1, 64, 64, 1),
+    (1, 29, 2816, 20, 4, 128, 192, 1), (4, 8, 64, 3, 1, 64, 12416, 0), (1, 33, 64, 2, 1, 64, 8448, 1),
+    (5, 7, 64, 4, 2, 64, 4160, 0), (2, 19, 64, 2, 2, 128, 6272, 1), (8, 5, 2816, 20, 4, 128, 128, 0),
+    (1, 41, 4160, 1, 1, 64, 64, 0), (1, 43, 2112, 8, 1, 128, 64, 1), (2, 23, 8384, 1, 1, 64, 64, 1),
+    (1, 46, 16448, 1, 1, 64, 64, 1), (3, 16, 64, 28, 4, 128, 13632, 0), (5, 10, 16832, 1, 1, 64, 64, 1),
+    (1, 51, 64, 1, 1, 128, 6272, 1), (3, 17, 8320, 1, 1, 64, 64, 0), (1, 53, 64, 1, 1, 64, 12352, 1),
+    (5, 11, 64, 1, 1, 128, 4160, 0), (3, 19, 2304, 7, 1, 128, 64, 1), (3, 19, 2816, 24, 4, 128, 64, 0),
+    (1, 59, 4160, 1, 1, 64, 64, 1), (4, 16, 64, 28, 4, 128, 8384, 0), (6, 11, 2304, 6, 1, 128, 64, 1),
+    (3, 23, 64, 3, 1, 64, 4224, 1), (2, 37, 2752, 24, 3, 128, 64, 0), (3, 25, 8448, 1, 1, 64, 64, 0),
+    (2, 42, 64, 5, 1, 64, 64, 0), (7, 13, 64, 1, 1, 128, 6784, 1), (7, 13, 128, 28, 4, 128, 8768, 0),
+    (3, 32, 4160, 1, 1, 64, 64, 1), (3, 33, 64, 32, 4, 128, 6720, 0), (2, 53, 2752, 24, 4, 128, 64, 1),
+    (6, 18, 8320, 1, 1, 64, 64, 1), (2, 55, 64, 5, 1, 64, 64, 1), (1, 123, 4160, 1, 1, 64, 64, 0),
+    (4, 31, 2688, 7, 1, 128, 64, 0), (1, 125, 64, 1, 1, 64, 18496, 0), (4, 32, 64, 5, 1, 64, 4160, 0),
+]
+CASES += [("widths_rows%d_%d" % (w[0] * w[1], i), w[0], w[1],
+           TB.with_(hidden=w[2], n_q_heads=w[3], n_kv_heads=w[4], head_dim=w[5], ffn=w[6], qk_norm=bool(w[7]), vocab=200,
+                    lm_head_std=3 / w[2] ** 0.5)) for i, w in enumerate(WIDTHS)]
+
+
 @pytest.mark.parametrize("name,batch,nodes,shape", CASES, ids=[c[0] for c in CASES])
 def test_tile_edges(name, batch, nodes, shape):
     seed = 300 + len(name)
@@ -56,15 +84,16 @@ def test_tile_edges(name, batch, nodes, shape):
     full_check(make_case(shape, seed, [20 + 17 * b for b in range(batch)], parents), thresholds=(0.0, 0.5))
 
 
-# The adapter's plain product: (batch, nodes, hidden, adapter width).  Up to 64 rows k splits that need more tile
-# counters than the layers do (one split instead); more rows: one split in 128- and in 256-column tiles, k splits
-# finished by the second launch, panels of 128 and 256 rows; widths that end inside a tile.
+# The adapter's plain product: (batch, nodes, hidden, adapter width).  Up to 128 rows, the streaming kernel: one split,
+# several, several that need more tile counters than the layers do (one split instead); more rows: one split in 128- and
+# in 256-column tiles, k splits finished by the second launch; widths that end inside a tile.
 ADAPTERS = {
     "rows23_splits": (1, 23, 1472, 132),
-    "rows64_no_counters": (1, 64, 2048, 3204),
+    "rows64_no_counters": (1, 64, 1024, 2052),
     "rows100_one_split": (1, 100, 256, 200),
     "rows100_splits_ragged_k": (1, 100, 1472, 132),
     "rows250_splits": (5, 50, 1024, 260),
+    "rows130_one_split": (2, 65, 64, 200),
     "rows130_wide_tiles": (2, 65, 64, 16500),
 }
 

@@ -78,3 +78,46 @@ def test_every_plan_has_a_kernel(plans):
             assert epi == HEAD and k % (512 if rows <= 32 else 256) == 0, (s, p)
         else:
             assert p.kernel == WIDE and epi == HEAD and rows > 64 and p.width == 256, (s, p)
+
+
+def layer_products(batch, nodes, s):
+    rows, qd = batch * nodes, s.n_q_heads * s.head_dim
+    return [(QKV, qd + 2 * s.n_kv_heads * s.head_dim, s.hidden, rows, s.head_dim, s.qk_norm),
+            (RESID, s.hidden, qd, rows, s.head_dim, 0), (SWIGLU, 2 * s.ffn, s.hidden, rows, s.head_dim, 0),
+            (RESID, s.hidden, s.ffn, rows, s.head_dim, 0)]
+
+
+def test_the_gpu_cases_reach_every_width(plans):
+    """test_gpu_tiles.py: (product, width, row blocks, several splits) of the streaming kernel."""
+    from test_gpu_tiles import CASES
+    shapes = [p for _, batch, nodes, shape in CASES for p in layer_products(batch, nodes, shape)]
+    got = set()
+    for s, p in zip(shapes, plans(shapes)):
+        if p.kernel == STREAM:
+            got.add((s[0], p.width, rows_laid_out(RESID, p, s[3]) // 16, p.splits > 1))
+    every = (1, 2, 3, 4, 6, 8)
+    want = {(SWIGLU, w, rb, False) for w in (32, 48, 64, 96, 112) for rb in every if w < 112 or rb <= 4}
+    want |= {(RESID, w, rb, sp) for w in (16, 32, 64) for rb in every for sp in (False, True)}
+    want |= {(RESID, 128, rb, False) for rb in (1, 2, 3, 4)}      # in splits: products of more than 100M weights
+    # 64 columns over 8 row blocks lose to two groups of 4 in 128, but for layers of 17 and more kv heads
+    want |= {(QKV, w, rb, sp) for w in (16, 32, 64, 128) for rb in every for sp in (False, True) if (w, rb) != (64, 8)}
+    want |= {(QKV, 96, 4, True)}                                  # others: products of more than 40M weights
+    assert not want - got, sorted(want - got)
+
+
+def test_the_gpu_cases_of_the_adapter(plans):
+    """What the cases of test_gpu_tiles.py are named for."""
+    from test_gpu_tiles import ADAPTERS, TB
+    planned = {n: plans([(PLAIN, dim, hidden, batch * nodes, 128, 0)])[0]
+               for n, (batch, nodes, hidden, dim) in ADAPTERS.items()}
+    layers = layer_products(1, 1, TB.with_(hidden=ADAPTERS["rows64_no_counters"][2], ffn=256))
+    counters = max(p.counters for rows in (16, 32, 48, 64, 96, 128)
+                   for p in plans([(s[0], s[1], s[2], rows, s[4], s[5]) for s in layers]) if p.kernel == STREAM)
+    p = planned["rows64_no_counters"]
+    assert p.kernel == STREAM and p.splits > 1 and p.tiles > counters
+    for name in ("rows23_splits", "rows100_splits_ragged_k"):
+        assert planned[name].kernel == STREAM and 1 < planned[name].splits
+    assert planned["rows100_one_split"][:2] == (STREAM, 32) and planned["rows100_one_split"].splits == 1
+    assert planned["rows250_splits"].kernel == WIDE and planned["rows250_splits"].splits > 1
+    assert planned["rows130_one_split"][:2] == (WIDE, 128) and planned["rows130_one_split"].splits == 1
+    assert planned["rows130_wide_tiles"][:2] == (WIDE, 256) and planned["rows130_wide_tiles"].splits == 1
