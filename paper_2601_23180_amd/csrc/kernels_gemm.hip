@@ -56,11 +56,10 @@ __global__ __launch_bounds__(256, MB == 2 ? 1 : 2) void k_gemm_head(GemmArgs a) 
   __shared__ float s_tmp[4 * kMaxRows];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  // scalar: what is selected by it (this wavefront's weight segment) is then fetched with scalar
-  // loads from the kernel arguments, not with a vector load that the first weight request waits for
+  // scalar: the address of this wavefront's packed run stays in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, g = lane >> 5;
-  const int n_chunks = (a.k + KC - 1) / KC;
+  const int n_chunks = a.k / KC;   // whole, and a multiple of DEPTH (plan_head, launch_gemm_head)
   // Workgroups that run side by side start at different depths of their k range (and wrap
   // around), so that they do not all walk the memory channels in lockstep.  The order of the
   // additions is still a fixed function of the workgroup.
@@ -88,7 +87,7 @@ __global__ __launch_bounds__(256, MB == 2 ? 1 : 2) void k_gemm_head(GemmArgs a) 
   // wait-count analysis assume it may not have been issued, which turns every wait into "drain
   // everything" and serialises the stream.
   //
-  // Fast variant (every k split is a whole multiple of DEPTH chunks of KC), per chunk c:
+  // Per chunk c:
   //   1. X registers (chunk c+1, fetched during chunk c-1) -> LDS stage (c+1)&1
   //   2. issue the X loads of chunk c+2
   //   3. per 64-deep block: 4 x MB x 2 MFMAs on W set c % DEPTH, then refill that block of the
@@ -101,8 +100,7 @@ __global__ __launch_bounds__(256, MB == 2 ? 1 : 2) void k_gemm_head(GemmArgs a) 
   bf16x8 w[DEPTH][KB][4];
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // native vector: stays in registers
   // One register stage of the panel.  Loads come back in order, so the wait for it is also one for every
-  // weight load before it; a second stage (a chunk more of weights in flight) is slower all the same:
-  // 44.2 -> 48.9 us on the 24576 x 4096 product over 60 rows, 16.8 -> 18.6 on 6144 x 4096 over one.
+  // weight load before it.
   u32x4 xr[XV];
 
   auto load_w_block = [&](int set, int c, int kb) {
@@ -157,15 +155,15 @@ __global__ __launch_bounds__(256, MB == 2 ? 1 : 2) void k_gemm_head(GemmArgs a) 
 
   for (int pass = 0; pass < n_pass; ++pass) {
     const int s0 = s_begin + s_count * pass / n_pass, s1 = s_begin + s_count * (pass + 1) / n_pass;
-    // wavefronts beyond the run take its last sub-tile again (its lines are on their way already); their columns
-    // are not looked at.  A run may be empty: its entries say so.
-    wrow = (const bf16 *)a.seg[0].w + (size_t)min(min(s0 + wave, max(s1 - 1, s0)), n_sub - 1) * (a.k >> 6) * 2048 + lane * 8;
+    // one to four sub-tiles (head_passes in plan.hpp); wavefronts beyond them take the last one again (its lines are
+    // on their way already), and their columns are not looked at
+    wrow = (const bf16 *)a.seg[0].w + (size_t)min(s0 + wave, s1 - 1) * (a.k >> 6) * 2048 + lane * 8;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[mb][e] = 0.f;
     if (pass > 0) __syncthreads();   // the previous pass has read its logits
-    // n_chunks is a multiple of DEPTH (DEPTH even).  The prologue issues its loads in the order
+    // The prologue issues its loads in the order
     // the steady state does (X of a chunk before the W refill of the same step), so the wait
     // counts merged at the loop head are the steady-state ones.
     load_x(0);
@@ -246,7 +244,7 @@ void launch_gemm_head(hipStream_t st, const GemmArgs &a) {
   if (a.rows_pad == 128) hipLaunchKernelGGL((k_gemm_head<4, 64, 4>), grid, block, 0, st, a);
   else if (a.rows_pad == 32) hipLaunchKernelGGL((k_gemm_head<1, 128, 4>), grid, block, 0, st, a);
   else if (a.k % 512 == 0) hipLaunchKernelGGL((k_gemm_head<2, 128, 4>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_gemm_head<2, 128, 2>), grid, block, 0, st, a); 
+  else hipLaunchKernelGGL((k_gemm_head<2, 128, 2>), grid, block, 0, st, a);
 }
 
 }  // namespace ts

@@ -80,6 +80,18 @@ def test_every_plan_has_a_kernel(plans):
             assert p.kernel == WIDE and epi == HEAD and rows > 64 and p.width == 256, (s, p)
 
 
+def test_every_pass_of_the_head_kernel_has_sub_tiles(plans):
+    """Over at most 32 rows its workgroups share the sub-tiles of 32 columns out as evenly as integers go, then their
+    passes those of a workgroup: one to four sub-tiles each."""
+    cols = [*range(1, 2000, 13), 65504, 65505, 65536, 65537, 98304, 98305, 131072, 131073, 151936, 262144, 999999]
+    for n, p in zip(cols, plans([(HEAD, n, 512, 9, 128, 0) for n in cols])):
+        places, sub, passes = p.tiles // p.splits, (n + 31) // 32, p.splits
+        assert p.kernel == HEADK and places * passes == p.tiles
+        runs = [sub * (w + 1) // places - sub * w // places for w in range(places)]
+        sizes = [r * (i + 1) // passes - r * i // passes for r in set(runs) for i in range(passes)]
+        assert sum(runs) == sub and min(sizes) >= 1 and max(sizes) <= 4, (n, p)
+
+
 def layer_products(batch, nodes, s):
     rows, qd = batch * nodes, s.n_q_heads * s.head_dim
     return [(QKV, qd + 2 * s.n_kv_heads * s.head_dim, s.hidden, rows, s.head_dim, s.qk_norm),
