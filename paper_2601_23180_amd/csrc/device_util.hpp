@@ -54,23 +54,20 @@ __device__ __forceinline__ f32x4 ld_agent_f32x4(const float *p) {
   t.u[1] = ld_agent_u64(p + 2);
   return t.v;
 }
-// Stores of a kernel's results.  WT = false: plain stores (the end of the kernel makes them
-// visible).  WT = true: write-through, for results that another workgroup of the SAME launch reads
-// after a device-side barrier.
-template <bool WT>
-__device__ __forceinline__ void store_f32x4(float *p, f32x4 v) {
-  if constexpr (WT) {
-    union { uint64_t u[2]; f32x4 v; } t;
-    t.v = v;
-    st_agent_u64(p, t.u[0]);
-    st_agent_u64(p + 2, t.u[1]);
-  } else {
-    *(f32x4 *)p = v;
-  }
+__device__ __forceinline__ void st_agent_f32x4(float *p, f32x4 v) {
+  union { uint64_t u[2]; f32x4 v; } t;
+  t.v = v;
+  st_agent_u64(p, t.u[0]);
+  st_agent_u64(p + 2, t.u[1]);
+}
+__device__ __forceinline__ void st_agent_bf16x4(bf16 *p, bf16x4 v) {
+  union { uint64_t u; bf16x4 v; } t;
+  t.v = v;
+  st_agent_u64(p, t.u);
 }
 // 16 bytes a lane, written through to memory, at byte offset `off` of the `bytes` long buffer at `base` (the same
 // in every lane); past its end nothing is written.  A wavefront then writes whole 128-byte lines; as two 8-byte
-// atomic stores (store_f32x4<true>) every line goes out in two halves.
+// atomic stores (st_agent_f32x4) every line goes out in two halves.
 struct ThroughBuffer {
   __amdgpu_buffer_rsrc_t rsrc;
   __device__ __forceinline__ ThroughBuffer(float *base, uint32_t bytes)
@@ -81,21 +78,6 @@ struct ThroughBuffer {
     __builtin_amdgcn_raw_buffer_store_b128(*(u32x4 *)&v, rsrc, off, 0, kAgentScope);
   }
 };
-template <bool WT>
-__device__ __forceinline__ void store_bf16x4(bf16 *p, bf16x4 v) {
-  if constexpr (WT) {
-    union { uint64_t u; bf16x4 v; } t;
-    t.v = v;
-    st_agent_u64(p, t.u);
-  } else {
-    *(bf16x4 *)p = v;
-  }
-}
-template <bool WT>
-__device__ __forceinline__ void store_f32(float *p, float v) {
-  if constexpr (WT) st_agent(p, v);
-  else *p = v;
-}
 
 // Device-side barrier between the phases of one launch (every workgroup of the grid is resident:
 // the host checks that before it chooses such a kernel).  bar_arrive: called by every thread after

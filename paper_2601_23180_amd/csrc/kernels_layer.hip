@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256) void k_layer_bf16(LayerArgs la) {
       auto rc = [&](int c) { const int cc = c + rot; return cc >= n_chunks ? cc - n_chunks : cc; };
       const bf16 *xg = (const bf16 *)a.x + ((size_t)(it.k_begin >> 6) * 4 * MB * 2 + wave * XV) * 512 + lane * 8;
       float rs_in[(MB + 1) / 2][8];
-      rstd_load<256, MB>(a, rs_in);
+      rstd_load<MB>(a, rs_in);
       f32x16 acc[MB];
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
@@ -219,10 +219,9 @@ __global__ __launch_bounds__(256) void k_layer_bf16(LayerArgs la) {
         if (d + 1 < DEPTH) __syncthreads();
       }
       stamp(2 + 3 * p);
-      rstd_finish<256, MB>(a, rs_in, s_rsp, s_rs);
+      rstd_finish<MB>(a, rs_in, s_rsp, s_rs);
       __syncthreads();
-      gemm_epilogue<MB, EPI, 4, 1, MB, true>(a, reinterpret_cast<f32x16(&)[1][MB]>(acc), lds, &s_last, s_rs, it.tile,
-                                             it.split);
+      gemm_epilogue<MB, EPI>(a, acc, lds, &s_last, s_rs, it.tile, it.split);
     }
     bar_arrive(la.bar + p);
     stamp(3 + 3 * p);
