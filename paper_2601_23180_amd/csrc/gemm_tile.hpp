@@ -122,7 +122,8 @@ struct TileEpilogue {
     const int tid = threadIdx.x;
     const int mb_count = a.rows_pad >> 5;
     if constexpr (EPI == EPI_QKV) {
-      // a tile holds whole heads; thread = (row, 4 rotation pairs)
+      // thread = (row, 4 rotation pairs); a tile holds pairs of one or two heads, or whole heads (qkv_column), where
+      // q and k have a norm of their own always the latter
       const int d = a.head_dim, half = d >> 1;
       const int n_q = a.n_q_heads, n_kv = a.n_kv_heads;
       const bool paged = a.kv.page_table != nullptr;          // uniform: the contiguous cache's addresses stay plain arithmetic
