@@ -119,7 +119,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
 
   bf16x8 w[D][CB], x[D][2 * RB];
   // A run that is no whole number of rounds requests its last step again: no branch around any load, behind
-  // which a wait would drain everything.  The host picks D so that this is rare.
+  // which a wait would drain everything.  launch_one picks D so that this is one step at most.
   auto load = [&](int slot, int s_) {
     const int s = min(s_, last);
 #pragma unroll
@@ -250,7 +250,9 @@ template <int RB, int CB, int EPI>
 void launch_one(hipStream_t st, const GemmArgs &a) {
   using S = StreamShape<RB, CB>;
   const dim3 grid(a.n_tiles, a.n_splits, RB == 4 ? (a.rows + 63) / 64 : 1), block(64 * S::NW);
-  // the deepest ring that divides the steps of a wavefront; uneven runs: one step again at most
+  // The deepest ring that divides the steps of a wavefront, for a ring deeper than the run requests its last step again
+  // and again (2.5 us on a 6 us kernel).  Eight and four steps serve reductions that are powers of two, or three of them;
+  // most others share out unevenly and have two in flight, with one step again at most.
   const int steps = a.k / 32, each = steps / (S::NW * a.n_splits);
   const int even = steps % (S::NW * a.n_splits) == 0 ? each : 2;
   if constexpr (S::D == 8) {

@@ -24,7 +24,9 @@ inline int row_blocks(int rows) { return rows <= 64 ? (rows + 15) / 16 : (rows <
 // Tile widths that the streaming kernel is built in, by 16-row blocks of its tile.  QKV: whole rotation pairs.  The sums of
 // squares of any 16 columns of a residual product stand for themselves.  The adapter's plain product: one width.  LM
 // head: widths that the 128-column kernel does not take.  Accumulators of 128 x 128, for QKV also 96 columns over more than
-// 64 rows, for gate + up 112, do not fit.
+// 64 rows, for gate + up 112, do not fit.  Gate + up in 112 columns makes one tile a CU of 28672 (us over 9 / 30 / 60 rows,
+// 4096 deep): 112 columns 38.2 / 39.8 / 47.5, 96 51.9 / 57.0 / 70.9, 64 42.0 / 46.9 / 59.2, 48 48.5 / 58.0 / 77.7; of 24576 96 columns
+// do (60 rows 43.0, 112 53.2, 64 56.9).  80 columns, one tile a CU of 20480, are not built.
 constexpr bool stream_built(int epi, int tile_n, int rb) {
   if (rb < 1 || rb > 8 || rb == 5 || rb == 7) return false;
   if (epi == EPI_HEAD) return tile_n == 128 && rb <= 4;
@@ -37,14 +39,27 @@ constexpr bool stream_built(int epi, int tile_n, int rb) {
 // Decomposition of one matmul over at most 128 rows into (column tile, k split) workgroups of the streaming
 // kernel (gemm_stream.hpp): the tile width and the number of splits with the smallest estimated time.
 //
-// A workgroup (one runs per CU) takes 3 us to its first data.  It then draws its weights and its share of the
+// The estimate.  A workgroup takes 3 us to its first data.  It then draws its weights and its share of the
 // activation panel, 2 bytes a column and 64 a row block and k step, at 45 (one row block) to 60 GB/s; the chip draws no
-// more than 6.3 TB/s of weights.  Finishing a tile takes 0.012 us a row block and column,
-// meeting the other splits 0.8 us more and 0.002 a split: publish the partial tile, count, read all of them.  So wide
-// tiles draw less of the panel and narrow ones meet sooner.  Estimated / measured, us: 4096 x 4096 over 60 rows 32 columns x 2 splits 17.3 / 16.9, 64 x 4 15.4 / 16.7,
-// 128 x 8 19.3 / 18.8, 16 x 1 22.6 / 19.9; 4096 x 12288 64 x 4 28.6 / 32.6, 32 x 2 39.2 / 38.4; 2048 x 6144 32 x 4 14.6 / 14.3,
-// 64 x 8 16.1 / 15.8; over 9 rows 1024 x 2048 16 x 4 5.5 / 6.5, 16 x 1 7.4 / 6.6, 32 x 2 7.6 / 7.4; over 111 rows
-// 2048 x 6144 32 x 4 19.9 / 19.9, 64 x 8 23.4 / 21.2.
+// more than 6.3 TB/s of weights.  Finishing a tile takes 0.012 us a row block and column, meeting the other splits
+// 0.8 us more and 0.002 a split, row block and column: publish the partial tile, count, read all of them.  So wide tiles draw less of
+// the panel and narrow ones meet sooner.  256 workgroups at a time: one a CU, as most tiles fill it (16 and 32 columns
+// over at most 32 rows would fit one to four times, by ring depth).  What it does not know: the ring's depth (launch_one in
+// gemm_stream.hpp), and the epilogues apart (QKV in wide tiles takes 1 to 4 us more than estimated).  Eight and more splits
+// and more than 64 rows cost less than estimated.
+//
+// Estimated / measured, us (kernel times over cold weights; * chosen):
+//   4096 x 4096, 60 rows    32 x 2 16.8 / 17.0   64 x 4* 15.5 / 15.7   128 x 8 23.5 / 18.4   16 x 1 23.4 / 18.3   32 x 1 26.4 / 21.2
+//   4096 x 12288, 60 rows   64 x 4* 28.6 / 32.4   128 x 8 34.1 / 30.9   32 x 2 38.6 / 36.4   64 x 2 47.2 / 44.8   32 x 1 70.1 / 58.1
+//   6144 x 4096 (QKV), 60   96 x 4* 19.5 / 23.0   64 x 2 21.0 / 22.3   128 x 4 22.8 / 24.7   96 x 2 25.2 / 26.6   32 x 1 26.4 / 23.7
+//   24576 x 4096 (gate + up), 60   96* 39.6 / 43.0   112 41.1 / 53.2   48 56.4 / 56.5   64 61.5 / 56.9   32 76.1 / 67.0
+//   2048 x 2048, 60 rows    32 x 4* 9.1 / 9.0   16 x 2 9.7 / 9.7   32 x 2 11.3 / 10.8   64 x 8 12.6 / 10.8
+//   2048 x 6144, 60 rows    32 x 4* 14.6 / 13.8   64 x 8 15.9 / 15.2   16 x 2 19.6 / 17.1   32 x 2 22.2 / 19.7
+//   2048 x 2048, 111 rows   32 x 4* 13.8 / 11.7   16 x 2 15.1 / 12.7   32 x 2 17.7 / 14.3   64 x 4 19.5 / 15.6
+//   2048 x 6144, 111 rows   32 x 4* 23.7 / 19.7   64 x 8 26.3 / 20.6   64 x 4 30.4 / 24.3   16 x 2 33.7 / 25.7
+//   1024 x 2048, 9 rows     16 x 4* 5.2 / 6.4   32 x 4 5.9 / 6.6   16 x 2 6.2 / 6.6   32 x 2 7.2 / 7.3   16 x 1 7.6 / 6.5
+//   1024 x 3072, 9 rows     16 x 4* 5.8 / 6.8   32 x 4 6.6 / 7.4   16 x 2 7.3 / 7.4   32 x 2 8.7 / 8.4   16 x 1 9.7 / 8.2
+// Of the tilings measured the chosen one is the fastest or within 5 % of it.
 inline SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim, bool qk_norm) {
   const int steps = k / 32;
   SplitPlan best;
@@ -120,9 +135,9 @@ inline int ss_tiles_of(int n, int tile_n) { return tile_n < kGemmTileN ? (n + ti
 // Decomposition of one matmul over a panel of 256 rows, LM head also 128 (kernels_gemm_wide.hip): the tile width
 // and the number of k splits with the smallest estimated time.  Fitted to products of 1024 to 4096 wide models: a 64-deep
 // chunk takes a workgroup 1.65 us on a 128 x 256 tile and 1.0 us on a 128 x 128 tile, a workgroup about 6 us beside its
-// chunks, one workgroup runs per CU; splitting costs 1.5 us (a second launch, but no epilogue in the first) and the
+// chunks, one workgroup a CU (two of the 128-column tiles would fit); splitting costs 1.5 us (a second launch, but no epilogue in the first) and the
 // partial tiles, written and read back at about 6.5 TB/s.  Estimated / measured, us, 240 rows: 6144 x 1024 in one split 22.0 / 21.7,
-// two 19.4 / 18.8; 2048 x 6144 in four 34.8 / 33.6, eight 24.7 / 25.0; 4096 x 14336 (256 columns) in eight 64.0 / 65.2.
+// two 19.4 / 18.8; 2048 x 6144 in four 34.1 / 33.6, eight 24.7 / 25.0; 4096 x 14336 (256 columns) in eight 64.0 / 65.2.
 inline SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_part_floats) {
   const int kb = k / 64, n_rg = rows_pad / 128;
   SplitPlan best;
