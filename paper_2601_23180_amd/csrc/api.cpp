@@ -45,8 +45,9 @@ struct Layout {
       node_ent, node_idx, logits, total;
   int rows_max, rows_pad_max, head_tiles, max_tiles;
   // `counters` holds, in this order: max_tiles + 1 tile counters of the split-K matmuls, kLayerPhases
-  // barrier counters per layer, the abort word — n_zero ints that the set-up kernel clears
-  int bar_index, abort_index, n_zero;
+  // barrier counters per layer, the abort word, a counter of finished rows per sequence — n_zero ints that the set-up
+  // kernel clears
+  int bar_index, abort_index, done_index, n_zero;
   size_t part_phase;   // floats per partial region of one phase of the layer kernel
   size_t part_floats;  // floats of the whole partial region
 };
@@ -107,7 +108,8 @@ Layout make_layout(const trispec_model &m, int batch, int max_nodes) {
   }
   L.bar_index = L.max_tiles + 1;
   L.abort_index = L.bar_index + kLayerPhases * c.n_layers;
-  L.n_zero = L.abort_index + 1;
+  L.done_index = L.abort_index + 1;
+  L.n_zero = L.done_index + kMaxBatch;
   L.counters = take(sizeof(int32_t) * L.n_zero);
   // sums of squares per (tile, row): two buffers, a matmul reads its producer's while writing its own
   L.ss_part = take(2 * sizeof(float) * (size_t)ss_tiles_of(c.hidden, 16) * rp);   // sized for the narrowest tile
@@ -585,6 +587,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
   };
 
   bool launched = true;   // every matmul had a kernel for its plan
+  const float *row_logits = nullptr;   // fp32 models: the statistics come from the logits themselves
   (void)hipGetLastError();
   {
     BeginArgs g;
@@ -653,7 +656,7 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
     {
       TimedLaunch tl(opts->timer, TRISPEC_K_HEAD, st, (double)c.vocab * c.hidden * es);
       gemm(h, c.hidden, 1, m->lm_head, c.vocab, nullptr, 0, nullptr, 0, logits);
-      launch_stats_from_logits(st, logits, rows, c.vocab, hs);
+      row_logits = logits;
     }
     if (opts->hidden_out)
       launch_export_hidden(st, c.dtype, h, nullptr, nullptr, 0, rows, rp, c.hidden, c.rms_eps, opts->hidden_out);
@@ -876,10 +879,8 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
                            opts->hidden_out);
   }
 
-  launch_stats_reduce(st, hs, rows, (float *)(ws + L.node_l1), (float *)(ws + L.node_l2),
-                      (float *)(ws + L.node_sum), (float *)(ws + L.node_ent), (int32_t *)(ws + L.node_idx));
-  DecideArgs d = make_decide(L, ws, draft_tokens, B, n_nodes, threshold, opts, out);
-  launch_decide(st, d);
+  launch_stats_decide(st, hs, rows, row_logits, c.vocab, (int32_t *)(ws + L.counters) + L.done_index,
+                      make_decide(L, ws, draft_tokens, B, n_nodes, threshold, opts, out));
   return launched && hipGetLastError() == hipSuccess ? TRISPEC_OK : TRISPEC_ELAUNCH;
 }
 

@@ -183,24 +183,6 @@ __device__ __forceinline__ Top2 top2_merge(const Top2 &a, const Top2 &b) {
   }
   return r;
 }
-__device__ __forceinline__ void top2_push(Top2 &t, float v, int col) {
-  // columns arrive in ascending order
-  if (v > t.l1) {
-    if (t.l1 == -INFINITY) {
-      t.s = 1.f; t.t = 0.f;
-    } else {
-      const float d = t.l1 - v, e = expf(d);
-      t.t = (t.t + t.s * d) * e;                 // the new maximum itself adds e^0 * 0
-      t.s = t.s * e + 1.f;
-    }
-    t.l2 = t.l1; t.l1 = v; t.idx = col;
-  } else if (v != -INFINITY) {
-    const float d = v - t.l1, e = expf(d);
-    t.s += e;
-    t.t += e * d;
-    t.l2 = fmaxf(t.l2, v);
-  }
-}
 __device__ __forceinline__ Top2 top2_shfl_xor(const Top2 &t, int o) {
   Top2 r;
   r.l1 = __shfl_xor(t.l1, o, 64);

@@ -293,12 +293,10 @@ void launch_pack_weights(hipStream_t st, const void *w, int n_rows, int k, void 
 void launch_gemm_head(hipStream_t st, const GemmArgs &a);   // LM head, up to 128 rows: 4 wavefronts, 128-column tiles
 bool launch_gemm_stream(hipStream_t st, const GemmArgs &a);   // up to 128 rows: wavefronts share the reduction, tile_n = 16 .. 128; false: not built (stream_built in plan.hpp)
 void launch_gemm_wide(hipStream_t st, const GemmArgs &a);   // more rows: tile_n = 256 or 128 columns, k splits of whole 64-deep blocks
-void launch_stats_from_logits(hipStream_t st, const float *logits, int rows, int vocab,
-                              const HeadStats &hs);
 void launch_attn_f32(hipStream_t st, const AttnArgs &a);
 void launch_attn_bf16(hipStream_t st, const AttnArgs &a);
-void launch_stats_reduce(hipStream_t st, const HeadStats &hs, int rows, float *node_l1, float *node_l2,
-                         float *node_sum, float *node_ent, int32_t *node_idx);
+// per-tile statistics (logits != nullptr: rows of logits) to the rows' statistics, then every sequence's decision; done: a zero counter a sequence
+void launch_stats_decide(hipStream_t st, const HeadStats &hs, int rows, const float *logits, int vocab, int32_t *done, const DecideArgs &d);
 // rank[r] of node r > 0 of every sequence: vocabulary entries that precede tokens[r] in the logits of
 // its parent's row (larger, or equal with a lower id); -1 for roots and token ids outside the vocabulary
 void launch_draft_ranks(hipStream_t st, const float *logits, const int32_t *tokens, const NodeTable &tab,

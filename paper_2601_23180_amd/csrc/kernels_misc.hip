@@ -314,71 +314,6 @@ void launch_gemm_f32(hipStream_t st, const GemmArgs &a) {
   hipLaunchKernelGGL(k_gemm_f32, dim3(a.n_total, (a.rows + 7) / 8), dim3(64), 0, st, a);
 }
 
-// ------------------------------------------------------------------ vocabulary statistics
-// fp32 models: scan a row of materialised logits.  One workgroup per row, 256 threads, each
-// scanning a contiguous slab in ascending order.
-__global__ __launch_bounds__(256) void k_stats_from_logits(const float *logits, int vocab, HeadStats hs) {
-  __shared__ Top2 sm[4];
-  const int r = blockIdx.x;
-  const float *row = logits + (size_t)r * vocab;
-  const int per = (vocab + 255) / 256;
-  const int lo = threadIdx.x * per, hi = min(vocab, lo + per);
-  Top2 t = top2_empty();
-  for (int c = lo; c < hi; ++c) top2_push(t, row[c], c);
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) t = top2_merge(t, top2_shfl_xor(t, o));
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = t;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    Top2 a = sm[0];
-    for (int w = 1; w < 4; ++w) a = top2_merge(a, sm[w]);
-    hs.l1[r] = a.l1; hs.l2[r] = a.l2; hs.sumexp[r] = a.s; hs.ent[r] = a.t; hs.idx[r] = a.idx;
-  }
-}
-
-void launch_stats_from_logits(hipStream_t st, const float *logits, int rows, int vocab,
-                              const HeadStats &hs) {
-  hipLaunchKernelGGL(k_stats_from_logits, dim3(rows), dim3(256), 0, st, logits, vocab, hs);
-}
-
-// Merge the per-tile statistics of every row: one workgroup of 16 wavefronts per row, threads
-// stride the tiles (every load of a thread is requested before the first merge), then a fixed
-// butterfly per wavefront and the wavefronts in ascending order.
-constexpr int kStatsThreads = 1024;
-__global__ __launch_bounds__(kStatsThreads) void k_stats_reduce(HeadStats hs, float *node_l1, float *node_l2,
-                                                                float *node_sum, float *node_ent, int32_t *node_idx) {
-  __shared__ Top2 s_w[kStatsThreads / 64];
-  const int r = blockIdx.x, tid = threadIdx.x;
-  Top2 t = top2_empty();
-  for (int i0 = tid; i0 < hs.n_tiles; i0 += 4 * kStatsThreads) {
-    Top2 b[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u * kStatsThreads;
-      const size_t o = (size_t)r * hs.n_tiles + min(i, hs.n_tiles - 1);
-      b[u].l1 = hs.l1[o]; b[u].l2 = hs.l2[o]; b[u].s = hs.sumexp[o]; b[u].t = hs.ent[o]; b[u].idx = hs.idx[o];
-      if (i >= hs.n_tiles) b[u] = top2_empty();
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) t = top2_merge(t, b[u]);
-  }
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) t = top2_merge(t, top2_shfl_xor(t, o));
-  if ((tid & 63) == 0) s_w[tid >> 6] = t;
-  __syncthreads();
-  if (tid == 0) {
-    t = s_w[0];
-    for (int w = 1; w < kStatsThreads / 64; ++w) t = top2_merge(t, s_w[w]);
-    node_l1[r] = t.l1; node_l2[r] = t.l2; node_sum[r] = t.s; node_ent[r] = t.t; node_idx[r] = t.idx;
-  }
-}
-
-void launch_stats_reduce(hipStream_t st, const HeadStats &hs, int rows, float *node_l1, float *node_l2,
-                         float *node_sum, float *node_ent, int32_t *node_idx) {
-  hipLaunchKernelGGL(k_stats_reduce, dim3(rows), dim3(kStatsThreads), 0, st, hs, node_l1, node_l2, node_sum,
-                     node_ent, node_idx);
-}
-
 // One workgroup per node: count the vocabulary entries that precede the node's token in its
 // parent's row of logits (exact integer sum: any order gives the same count).
 __global__ __launch_bounds__(256) void k_draft_ranks(const float *logits, const int32_t *tokens, NodeTable tab,
@@ -410,60 +345,175 @@ void launch_draft_ranks(hipStream_t st, const float *logits, const int32_t *toke
 }
 
 // ------------------------------------------------------------------ decision
-// One workgroup per sequence.  Threads fill the per-node outputs; thread 0 then walks the tree:
-// at the current node test the trust predicate first (tau_a = tau_m is an escalation), then
-// follow the lowest-numbered child whose draft token equals the verifier's argmax.
-__global__ __launch_bounds__(kMaxNodes) void k_decide(DecideArgs a) {
-  __shared__ float s_conf[kMaxNodes], s_margin[kMaxNodes], s_ent[kMaxNodes];
-  __shared__ int s_arg[kMaxNodes], s_tok[kMaxNodes], s_par[kMaxNodes], s_rank[kMaxNodes];
-  const int b = blockIdx.x, i = threadIdx.x, M = a.n_nodes;
+// Outputs of sequence b's nodes and its walk, by one workgroup of at least kMaxNodes threads.  At the current node test the
+// trust predicate first (tau_a = tau_m is an escalation), then follow the lowest-numbered child whose draft token
+// equals the verifier's argmax: one wavefront, two nodes a lane, so that a step is two ballots and not a search of the
+// node table.
+// AGENT: the statistics were written by other workgroups of this launch.
+template <bool AGENT>
+__device__ void decide_sequence(const DecideArgs &a, int b) {
+  __shared__ int s_arg[kMaxNodes];
+  const int i = threadIdx.x, M = a.n_nodes;
+  auto ldf = [&](const float *p) { return AGENT ? ld_agent(p) : *p; };
+  bool trusted = false;
   if (i < M) {
     const int r = b * M + i;
+    const float l1 = ldf(a.node_l1 + r), l2 = ldf(a.node_l2 + r), sum = ldf(a.node_sum + r), ent = ldf(a.node_ent + r);
+    const int arg = AGENT ? __hip_atomic_load(a.node_idx + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : a.node_idx[r];
     // no logit above -inf (a row of NaN): the sum is empty, and 1 / 0 would pass every threshold
-    const float s = a.node_l1[r] == -INFINITY ? NAN : a.node_sum[r];
-    const float conf = 1.0f / s;                                   // exp(l1 - l1) / sum
-    const float p2 = expf(a.node_l2[r] - a.node_l1[r]) / s;        // 0 when there is no second entry
-    s_conf[i] = conf;
-    s_margin[i] = conf - p2;
-    s_ent[i] = logf(s) - a.node_ent[r] / s;                        // ln sum e^d - sum e^d d / sum e^d
-    s_rank[i] = a.draft_ranks != nullptr ? a.draft_ranks[r] : -1;
-    s_arg[i] = a.node_idx[r];
-    s_tok[i] = a.tokens[r];
-    s_par[i] = a.parent[r];
-    if (a.out.argmax) a.out.argmax[r] = s_arg[i];
+    const float s = l1 == -INFINITY ? NAN : sum;
+    const float conf = 1.0f / s;                    // exp(l1 - l1) / sum
+    const float margin = conf - expf(l2 - l1) / s;  // the second term is 0 when there is no second entry
+    const float h = logf(s) - ent / s;              // ln sum e^d - sum e^d d / sum e^d
+    s_arg[i] = arg;
+    if (a.out.argmax) a.out.argmax[r] = arg;
     if (a.out.confidence) a.out.confidence[r] = conf;
-    if (a.out.margin) a.out.margin[r] = s_margin[i];
-    if (a.out.entropy) a.out.entropy[r] = s_ent[i];
+    if (a.out.margin) a.out.margin[r] = margin;
+    if (a.out.entropy) a.out.entropy[r] = h;
+    // statistic on the right side of the threshold (a NaN statistic is never trusted)
+    trusted = a.criterion == TRISPEC_CRIT_ENTROPY ? h <= a.threshold : (a.criterion == TRISPEC_CRIT_MARGIN ? margin : conf) >= a.threshold;
   }
-  if (a.out.path) a.out.path[b * TRISPEC_PATH_STRIDE + i] = -1;
+  static_assert(kMaxNodes == 128, "the nodes are those of two wavefronts");
+  __shared__ unsigned long long s_trust[2];
+  const unsigned long long mine = __builtin_amdgcn_ballot_w64(trusted);
+  if (i < kMaxNodes && (i & 63) == 0) s_trust[i >> 6] = mine;
+  if (a.out.path && i < kMaxNodes) a.out.path[b * TRISPEC_PATH_STRIDE + i] = -1;
   __syncthreads();
-  if (i != 0) return;
-  int cur = a.n_forced - 1, acc = 0, token = -1, esc = 0;
-  if (a.out.path) a.out.path[b * TRISPEC_PATH_STRIDE] = cur;
+  if (i >= 64) return;
   const bool relaxed = a.accept_top_k > 1 && a.draft_ranks != nullptr;
-  for (int step = 0; step <= M; ++step) {
-    // trusted: statistic on the right side of the threshold (a NaN statistic is never trusted)
-    const bool trusted = a.criterion == TRISPEC_CRIT_ENTROPY
-                             ? (s_ent[cur] <= a.threshold)
-                             : ((a.criterion == TRISPEC_CRIT_MARGIN ? s_margin[cur] : s_conf[cur]) >= a.threshold);
-    if (!trusted) { esc = 1; token = -1; break; }
-    const int t = s_arg[cur];
-    int nxt = -1;
-    for (int c = cur + 1; c < M; ++c)
-      if (s_par[c] == cur && (relaxed ? (s_rank[c] >= 0 && s_rank[c] < a.accept_top_k) : s_tok[c] == t)) { nxt = c; break; }
-    if (nxt < 0) { token = t; break; }
-    cur = nxt;
-    ++acc;
-    if (a.out.path) a.out.path[b * TRISPEC_PATH_STRIDE + acc] = cur;
+  int par[2], tok[2], rank[2];
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    const int c = i + 64 * w, r = b * M + min(c, M - 1);
+    par[w] = c < M ? a.parent[r] : -2;
+    tok[w] = a.tokens[r];
+    rank[w] = relaxed ? a.draft_ranks[r] : -1;
   }
+  const unsigned long long trust0 = s_trust[0], trust1 = s_trust[1];
+  int cur = a.n_forced - 1, acc = 0, token = -1, esc = 0;
+  if (a.out.path && i == 0) a.out.path[b * TRISPEC_PATH_STRIDE] = cur;
+  for (int step = 0; step <= M; ++step) {
+    if (!(((cur < 64 ? trust0 : trust1) >> (cur & 63)) & 1ull)) { esc = 1; token = -1; break; }
+    const int t = s_arg[cur];
+    auto follows = [&](int w) { return par[w] == cur && (relaxed ? rank[w] >= 0 && rank[w] < a.accept_top_k : tok[w] == t); };
+    const unsigned long long c0 = __builtin_amdgcn_ballot_w64(follows(0)), c1 = __builtin_amdgcn_ballot_w64(follows(1));
+    if ((c0 | c1) == 0) { token = t; break; }
+    cur = c0 != 0 ? __ffsll(c0) - 1 : 64 + __ffsll(c1) - 1;
+    ++acc;
+    if (a.out.path && i == 0) a.out.path[b * TRISPEC_PATH_STRIDE + acc] = cur;
+  }
+  if (i != 0) return;
   if (b == 0 && a.out.status) *a.out.status = *a.status_src;
   if (a.out.accepted_len) a.out.accepted_len[b] = acc;
   if (a.out.token) a.out.token[b] = token;
   if (a.out.escalate) a.out.escalate[b] = esc;
 }
 
+__global__ __launch_bounds__(kMaxNodes) void k_decide(DecideArgs a) { decide_sequence<false>(a, blockIdx.x); }
+
 void launch_decide(hipStream_t st, const DecideArgs &a) {
   hipLaunchKernelGGL(k_decide, dim3(a.batch), dim3(kMaxNodes), 0, st, a);
+}
+
+// ------------------------------------------------------------------ vocabulary statistics
+// Largest logit (its column, the second largest) of two sets; the lowest column of equal maxima
+__device__ __forceinline__ void top2_win(float &l1, float &l2, int &idx, float ol1, float ol2, int oidx) {
+  const bool up = ol1 > l1 || (ol1 == l1 && ol1 != -INFINITY && oidx < idx);
+  l2 = up ? fmaxf(l1, ol2) : fmaxf(l2, ol1);
+  l1 = up ? ol1 : l1;
+  idx = up ? oidx : idx;
+}
+// The sums of a set whose largest logit is l1 at column idx, relative to the largest of all, m1 at column mi
+__device__ __forceinline__ void top2_rescale(float l1, int idx, float m1, int mi, float &s, float &t) {
+  if (idx == mi) return;   // the largest itself: l1 - m1 would be a NaN for +inf
+  const float d = l1 == -INFINITY ? 0.f : l1 - m1, f = l1 == -INFINITY ? 0.f : expf(d);
+  t = (t + s * d) * f;
+  s *= f;
+}
+template <int U>
+__device__ __forceinline__ void top2_absorb(Top2 &a, const Top2 (&b)[U]) {
+  const float l0 = a.l1;
+  const int i0 = a.idx;
+#pragma unroll
+  for (int u = 0; u < U; ++u) top2_win(a.l1, a.l2, a.idx, b[u].l1, b[u].l2, b[u].idx);
+  top2_rescale(l0, i0, a.l1, a.idx, a.s, a.t);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    float s = b[u].s, t = b[u].t;
+    top2_rescale(b[u].l1, b[u].idx, a.l1, a.idx, s, t);
+    a.s += s;
+    a.t += t;
+  }
+}
+
+// One workgroup per row: the per-tile statistics of the LM head (LOGITS: the row of logits itself, fp32 models) to the
+// row's; the last workgroup of a sequence to finish takes its decision.  Threads stride the tiles, everything a thread
+// reads is requested at once; then the largest of a wavefront is found first and every lane rescales its sums once, so that
+// no exponential is on the chain of exchanges.  Orders are fixed: results do not depend on scheduling.
+// Memory round trips set its time.  us, statistics (merged by pairs) and decision as launches of their own -> here: 1187 tiles,
+// 60 nodes 9.8 + 7.6 -> 7.7, a chain of 128 9.6 + 12.3 -> 7.8, 512 entries and 9 nodes 9.5 + 4.0 -> 8.0; 4096 logits and 9 nodes
+// 7.7 + 4.0 + 2.8 (three launches) -> 7.8.
+constexpr int kStatsThreads = 256;
+template <bool LOGITS>
+__global__ __launch_bounds__(kStatsThreads) void k_stats_decide(HeadStats hs, const float *logits, int vocab, int32_t *done, DecideArgs d) {
+  constexpr int NW = kStatsThreads / 64, U = LOGITS ? 16 : 5;
+  static_assert(kStatsThreads >= kMaxNodes, "the workgroup takes a sequence's decision");
+  __shared__ Top2 s_w[NW];
+  __shared__ int s_last;
+  const int r = blockIdx.x, tid = threadIdx.x, n = LOGITS ? vocab : hs.n_tiles;
+  Top2 a = top2_empty();
+  for (int i0 = tid; i0 < n; i0 += U * kStatsThreads) {
+    Top2 b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * kStatsThreads;
+      const size_t o = (size_t)r * n + min(i, n - 1);
+      if constexpr (LOGITS) {
+        const float v = logits[o];
+        b[u].l1 = v; b[u].l2 = -INFINITY; b[u].s = v == -INFINITY ? 0.f : 1.f; b[u].t = 0.f; b[u].idx = i;
+      } else {
+        b[u].l1 = hs.l1[o]; b[u].l2 = hs.l2[o]; b[u].s = hs.sumexp[o]; b[u].t = hs.ent[o]; b[u].idx = hs.idx[o];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * kStatsThreads >= n) b[u] = top2_empty();
+    top2_absorb(a, b);
+  }
+  {
+    const float l1 = a.l1;
+    const int idx = a.idx;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const float ol1 = __shfl_xor(a.l1, o, 64), ol2 = __shfl_xor(a.l2, o, 64);
+      const int oi = __shfl_xor(a.idx, o, 64);
+      top2_win(a.l1, a.l2, a.idx, ol1, ol2, oi);
+    }
+    top2_rescale(l1, idx, a.l1, a.idx, a.s, a.t);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      a.s += __shfl_xor(a.s, o, 64);
+      a.t += __shfl_xor(a.t, o, 64);
+    }
+  }
+  if ((tid & 63) == 0) s_w[tid >> 6] = a;
+  __syncthreads();
+  if (tid == 0) {
+    Top2 b[NW - 1];
+    a = s_w[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) b[w - 1] = s_w[w];
+    top2_absorb(a, b);
+    st_agent(d.node_l1 + r, a.l1); st_agent(d.node_l2 + r, a.l2); st_agent(d.node_sum + r, a.s); st_agent(d.node_ent + r, a.t);
+    __hip_atomic_store(d.node_idx + r, a.idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  const int b = r / d.n_nodes;
+  if (publish_then_count(done + b, d.n_nodes, &s_last)) decide_sequence<true>(d, b);
+}
+
+void launch_stats_decide(hipStream_t st, const HeadStats &hs, int rows, const float *logits, int vocab, int32_t *done, const DecideArgs &d) {
+  if (logits != nullptr) hipLaunchKernelGGL(k_stats_decide<true>, dim3(rows), dim3(kStatsThreads), 0, st, hs, logits, vocab, done, d);
+  else hipLaunchKernelGGL(k_stats_decide<false>, dim3(rows), dim3(kStatsThreads), 0, st, hs, logits, vocab, done, d);
 }
 
 // Plain streaming copy: grid-stride over blocks of 4 x 256 16-byte vectors, four independent
