@@ -82,18 +82,15 @@ Layout make_layout(const trispec_model &m, int batch, int max_nodes) {
   L.sin_t = take(sizeof(float) * rows * (c.head_dim / 2));
   L.x = take(sizeof(float) * (size_t)rp * c.hidden);
   L.x2 = take(f32 ? 0 : sizeof(float) * (size_t)rp * c.hidden);   // the layer kernel alternates two copies
-  // matmul operands: fp32 models one fp32 panel; bf16 models a bf16 hi panel + a bf16 lo panel
-  L.h = take(sizeof(float) * (size_t)rp * c.hidden);
+  // matmul operands: a bf16 hi panel + a bf16 lo panel (fp32 models read the residual stream)
+  L.h = take(f32 ? 0 : sizeof(float) * (size_t)rp * c.hidden);
   L.h2 = take(f32 ? 0 : sizeof(float) * (size_t)rp * c.hidden);
   L.q = take(sizeof(float) * (size_t)rp * qd);
   L.qkv_f32 = take(f32 ? 0 : sizeof(float) * (size_t)rp * nqkv);
   L.attn_out = take(sizeof(float) * (size_t)rp * qd);
   L.act = take(sizeof(float) * (size_t)rp * c.ffn);
   if (f32) {
-    int m = nqkv;
-    if (c.hidden > m) m = c.hidden;
-    if (2 * c.ffn > m) m = 2 * c.ffn;
-    L.part = take(sizeof(float) * (size_t)rp * m);
+    L.part = take(c.qk_norm ? sizeof(float) * (size_t)rp * nqkv : 0);   // q, k, v before their norms
   } else {
     // split-K partial tiles of one matmul, over the panels up to this one (a workspace also serves passes of fewer rows)
     size_t floats = (size_t)kLayerPhases * kLayerMaxGrid * kGemmTileN * rp;
@@ -615,62 +612,76 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
   }
 
   if (f32) {
-    // ---------------- fp32 models: plain kernels, one per step
-    float *h = (float *)(ws + L.h), *q = (float *)(ws + L.q);
+    // ---------------- fp32 models: per layer QKV, attention, O, gate/up, down; the consumers of x normalise it
+    float *q = (float *)(ws + L.q);
     at.q = q;
-    auto gemm = [&](const float *xin, int k, int n_seg, const void *w0, int n0, const void *w1, int n1,
-                    const void *w2, int n2, float *out) {
+    auto base = [&](int epi, const void *xin, const void *norm_w, int k, int n_total) {
       GemmArgs g;
       memset(&g, 0, sizeof(g));
+      g.epi = epi;
       g.x = xin;
-      g.seg[0] = {w0, n0, 0};
-      g.seg[1] = {w1, n1, n0};
-      g.seg[2] = {w2, n2, n0 + n1};
-      g.n_seg = n_seg;
-      g.n_total = n0 + n1 + n2;
+      g.norm_w = (const float *)norm_w;
+      g.eps = c.rms_eps;
       g.k = k;
+      g.n_total = n_total;
       g.rows = rows;
-      g.rows_pad = rp;
-      g.n_splits = 1;
-      g.out = out;
-      TimedLaunch tl(opts->timer, TRISPEC_K_GEMM, st, (double)g.n_total * k * es);
+      g.n_seg = 1;
+      g.ffn = c.ffn;
+      return g;
+    };
+    auto gemm = [&](const GemmArgs &g) {
+      TimedLaunch tl(opts->timer, TRISPEC_K_GEMM, st, (double)g.n_total * g.k * es);
       launch_gemm_f32(st, g);
     };
     for (int l = 0; l < c.n_layers; ++l) {
-      gemm(h, c.hidden, 3, m->wq[l], qd, m->wk[l], kvd, m->wv[l], kvd, part);
       char *kl = (char *)kv->k + (size_t)l * kv_layer, *vl = (char *)kv->v + (size_t)l * kv_layer;
-      launch_qkv_epilogue(st, c.dtype, part, 1, rows, rp, c.n_q_heads, c.n_kv_heads, c.head_dim, cos_t, sin_t,
-                          n_nodes, ctx, kv->map(), q, kl, vl, c.qk_norm ? (const float *)m->q_norm[l] : nullptr,
-                          c.qk_norm ? (const float *)m->k_norm[l] : nullptr, c.rms_eps);
+      GemmArgs g = base(c.qk_norm ? EPI_PLAIN : EPI_QKV, x, m->norm_attn[l], c.hidden, nqkv);
+      g.seg[0] = {m->wq[l], qd, 0};
+      g.seg[1] = {m->wk[l], kvd, qd};
+      g.seg[2] = {m->wv[l], kvd, qd + kvd};
+      g.n_seg = 3;
+      g.out = part;
+      g.cos_t = cos_t; g.sin_t = sin_t; g.ctx = ctx;
+      g.q_out = q; g.k_cache = kl; g.v_cache = vl;
+      g.n_nodes = n_nodes; g.n_q_heads = c.n_q_heads; g.n_kv_heads = c.n_kv_heads; g.head_dim = c.head_dim;
+      g.kv = kv->map();
+      gemm(g);
+      if (c.qk_norm) {   // a norm over whole heads: a launch of its own
+        g.q_norm_w = m->q_norm[l];
+        g.k_norm_w = m->k_norm[l];
+        launch_qkv_epilogue_f32(st, g, part);
+      }
       attention(kl, vl);
-      gemm((const float *)attn_out, qd, 1, m->wo[l], c.hidden, nullptr, 0, nullptr, 0, part);
-      launch_reduce_residual_norm(st, c.dtype, part, 1, rows, rp, c.hidden, m->norm_ffn[l], c.rms_eps, x, h);
-      gemm(h, c.hidden, 2, m->w_gate[l], c.ffn, m->w_up[l], c.ffn, nullptr, 0, part);
-      launch_reduce_swiglu(st, c.dtype, part, 1, rows, rp, c.ffn, act);
-      gemm((const float *)act, c.ffn, 1, m->w_down[l], c.hidden, nullptr, 0, nullptr, 0, part);
-      const void *next_norm = (l + 1 < c.n_layers) ? m->norm_attn[l + 1] : m->final_norm;
-      launch_reduce_residual_norm(st, c.dtype, part, 1, rows, rp, c.hidden, next_norm, c.rms_eps, x, h);
+      g = base(EPI_RESID, attn_out, nullptr, qd, c.hidden);
+      g.seg[0] = {m->wo[l], c.hidden, 0};
+      g.x_resid = x; g.x_resid_out = x;
+      gemm(g);
+      g = base(EPI_SWIGLU, x, m->norm_ffn[l], c.hidden, 2 * c.ffn);
+      g.seg[0] = {m->w_gate[l], c.ffn, 0};
+      g.seg[1] = {m->w_up[l], c.ffn, c.ffn};
+      g.n_seg = 2;
+      g.act_out = act;
+      gemm(g);
+      g = base(EPI_RESID, act, nullptr, c.ffn, c.hidden);
+      g.seg[0] = {m->w_down[l], c.hidden, 0};
+      g.x_resid = x; g.x_resid_out = x;
+      gemm(g);
       export_layer(l, x);
     }
     float *logits = opts->debug_logits ? opts->debug_logits : (float *)(ws + L.logits);
     {
+      GemmArgs g = base(EPI_PLAIN, x, m->final_norm, c.hidden, c.vocab);
+      g.seg[0] = {m->lm_head, c.vocab, 0};
+      g.out = logits;
       TimedLaunch tl(opts->timer, TRISPEC_K_HEAD, st, (double)c.vocab * c.hidden * es);
-      gemm(h, c.hidden, 1, m->lm_head, c.vocab, nullptr, 0, nullptr, 0, logits);
+      gemm(g);
       row_logits = logits;
     }
     if (opts->hidden_out)
-      launch_export_hidden(st, c.dtype, h, nullptr, nullptr, 0, rows, rp, c.hidden, c.rms_eps, opts->hidden_out);
-    if (opts->adapter_w) {   // y = f W^T + b on the final-norm features (h is already normalised here)
-      GemmArgs g;
-      memset(&g, 0, sizeof(g));
-      g.x = h;
+      launch_norm_rows_f32(st, x, (const float *)m->final_norm, rows, c.hidden, c.rms_eps, opts->hidden_out);
+    if (opts->adapter_w) {   // y = f W^T + b on the final-norm features
+      GemmArgs g = base(EPI_PLAIN, x, m->final_norm, c.hidden, opts->adapter_dim);
       g.seg[0] = {opts->adapter_w, opts->adapter_dim, 0};
-      g.n_seg = 1;
-      g.n_total = opts->adapter_dim;
-      g.k = c.hidden;
-      g.rows = rows;
-      g.rows_pad = rp;
-      g.n_splits = 1;
       g.out = opts->adapter_out;
       g.bias = opts->adapter_bias;
       launch_gemm_f32(st, g);

@@ -100,7 +100,7 @@ enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3, EPI_PLAIN = 4 }
 // gemm_stream.hpp, kernels_gemm.hip, kernels_gemm_wide.hip, kernels_layer.hip
 enum { GEMM_STREAM = 0, GEMM_HEAD = 1, GEMM_WIDE = 2, GEMM_LAYER = 3 };
 struct GemmArgs {
-  // fp32 reference-precision path: x is [rows_pad, K] fp32, out is [rows][n_total].
+  // fp32 path: x is [rows, K] fp32; matrices, outputs and residual stream are fp32, row by row.
   // bf16 path: x is the bf16 hi panel [rows_pad, K], the lo panel follows x_panel elements later.
   // ss_in (or nullptr): [ss_tiles][rows_pad] sums of squares of the rows of the un-normalised
   // input; the epilogue multiplies the reduced sums by 1/sqrt(sum/K + eps).
@@ -120,8 +120,9 @@ struct GemmArgs {
   int32_t kernel;      // GEMM_*
   int32_t tile_n;      // output columns per workgroup: 128; stream 16 .. 128; more than 128 rows 128 or 256
   int32_t epi;
-  float *out;          // fp32 path, and the PLAIN epilogue: [rows][n_total] fp32
-  const float *bias;   // PLAIN epilogue / fp32 path: [n_total] added to every row, or nullptr
+  const float *norm_w; // fp32 path: weight of the RMSNorm of x's rows, or nullptr: x as it is
+  float *out;          // PLAIN epilogue, fp32 path's LM head: [rows][n_total] fp32
+  const float *bias;   // PLAIN epilogue: [n_total] added to every row, or nullptr
   float *part;         // [n_splits][n_tiles][rows * tile_n] split-K partial tiles: rows of columns, stream in
                        // accumulator fragments; more than 128 rows always in 128-column tiles
   int32_t *counters;   // [n_tiles + 1], zero between launches
@@ -277,17 +278,12 @@ void launch_copy_probe(hipStream_t st, void *dst, const void *src, size_t bytes)
 // (ss == nullptr: x is already normalised and weighted, plain copy)
 void launch_export_hidden(hipStream_t st, int dtype, const float *x, const void *norm_w, const float *ss,
                           int ss_tiles, int rows, int rows_pad, int hidden, float eps, float *out);
-void launch_qkv_epilogue(hipStream_t st, int dtype, const float *part, int n_splits, int rows,
-                         int rows_pad, int n_q_heads, int n_kv_heads, int head_dim,
-                         const float *cos_t, const float *sin_t, int n_nodes, CtxLens ctx,
-                         const KvMap &kvm, void *q_out, void *k_cache, void *v_cache, const float *q_norm_w,
-                         const float *k_norm_w, float eps);
-void launch_reduce_residual_norm(hipStream_t st, int dtype, const float *part, int n_splits, int rows,
-                                 int rows_pad, int hidden, const void *norm_w, float eps, float *x,
-                                 void *h);
-void launch_reduce_swiglu(hipStream_t st, int dtype, const float *part, int n_splits, int rows,
-                          int rows_pad, int ffn, void *act);
+// fp32 models (kernels_f32.hip)
 void launch_gemm_f32(hipStream_t st, const GemmArgs &a);
+// rotation, per-head norms and KV append of the rows of q, k, v in `qkv`
+void launch_qkv_epilogue_f32(hipStream_t st, const GemmArgs &a, const float *qkv);
+// out[r][c] = x[r][c] * w[c] / rms(x[r])
+void launch_norm_rows_f32(hipStream_t st, const float *x, const float *w, int rows, int hidden, float eps, float *out);
 size_t packed_weight_bytes(int n_rows, int k);
 void launch_pack_weights(hipStream_t st, const void *w, int n_rows, int k, void *out);
 void launch_gemm_head(hipStream_t st, const GemmArgs &a);   // LM head, up to 128 rows: 4 wavefronts, 128-column tiles

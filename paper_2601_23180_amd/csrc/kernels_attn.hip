@@ -17,38 +17,59 @@
 namespace ts {
 
 // ------------------------------------------------------------------ fp32 path (small models)
-// One wavefront per (row, query head).  Scores of all allowed keys go to LDS, then a plain
-// two-pass softmax and the value sum with one lane per output feature.  Keys and values come in 16-byte
-// pieces, 16 of them requested at once; the sums run in the order of the features and keys (9 rows, 4
-// heads, 137 keys: 28.5 -> 8.2 us, most of which had been one memory round trip after another).
-constexpr int kAttnF32MaxKeys = 12288;
+// One workgroup per (row, query head).  Scores of all allowed keys go to LDS, a thread a key, then a plain
+// two-pass softmax and the value sum, a thread per output feature and share of the keys (whole runs of 64).  Keys and values
+// come in 16-byte pieces, 16 of them requested at once, the first ones with the query: memory round trips and the pieces'
+// scattered lines set its time (9 rows, 4 heads, 137 keys: 8.4 us with one wavefront -> 7.6).
+constexpr int kAttnF32MaxKeys = 12288, kAttnF32Threads = 256;
 
-__global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a) {
-  extern __shared__ float sc[];
-  const int r = blockIdx.x, head = blockIdx.y, lane = threadIdx.x;
-  const int d = a.head_dim, group = a.n_q_heads / a.n_kv_heads, kvh = head / group;
+__global__ __launch_bounds__(kAttnF32Threads) void k_attn_f32(AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float sc[];   // n_keys scores, then zeros up to a multiple of 64
+  constexpr int NT = kAttnF32Threads, NW = NT / 64;
+  __shared__ __attribute__((aligned(16))) float s_q[128], s_o[NT], s_red[NW];
+  const int r = blockIdx.x, head = blockIdx.y, tid = threadIdx.x;
+  const int d = a.head_dim, group = a.n_q_heads / a.n_kv_heads, kvh = head / group;   // d is 64 or 128
   const int b = r / a.n_nodes, node = r - b * a.n_nodes;
   const int ctx = a.ctx.v[b];
   const int n_keys = ctx + a.n_nodes;
   const AncMask mask = a.anc[r];
-  const float *q = (const float *)a.q + (size_t)r * a.n_q_heads * d + (size_t)head * d;
   const float *kc = (const float *)a.k_cache, *vc = (const float *)a.v_cache;   // slots through a.kv
+  const int j = tid % d, share = tid / d, shares = NT / d;   // output feature, share of the keys
+  const int per = ((n_keys + shares - 1) / shares + 63) / 64 * 64, k_begin = share * per, k_end = min(n_keys, k_begin + per);
+  const size_t vj = (size_t)j * a.kv.v_stride();
+  // the first key's first 64 features and the first 64 values are requested with the query and the mask
+  f32x4 k0[16], v0[16];
+  {
+    const float *kr = kc + a.kv.k_row(b, kvh, min(tid, n_keys - 1));
+    const f32x4 *vp = (const f32x4 *)(vc + a.kv.v_col(b, kvh, k_begin < k_end ? k_begin : 0) + vj);
+    const float q = tid < d ? ((const float *)a.q)[((size_t)r * a.n_q_heads + head) * d + tid] : 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) k0[i] = *(const f32x4 *)(kr + 4 * i);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v0[i] = vp[i];
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < d) s_q[tid] = q;
+  }
+  __syncthreads();
   const float scale = 1.0f / sqrtf((float)d);
   float mx = -INFINITY;
-  for (int k = lane; k < n_keys; k += 64) {
+  for (int k = tid; k < n_keys; k += NT) {
     const bool ok = (k < ctx) || mask.has(k - ctx);
     float s = -INFINITY;
     if (ok) {
       const float *kr = kc + a.kv.k_row(b, kvh, k);
       float acc = 0.f;
-      for (int j0 = 0; j0 < d; j0 += 64) {   // d is 64 or 128
-        f32x4 kv[16], qv[16];
+      for (int j0 = 0; j0 < d; j0 += 64) {
+        if (k >= NT || j0 > 0) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) { kv[j] = *(const f32x4 *)(kr + j0 + 4 * j); qv[j] = *(const f32x4 *)(q + j0 + 4 * j); }
+          for (int i = 0; i < 16; ++i) k0[i] = *(const f32x4 *)(kr + j0 + 4 * i);
+        }
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
+        for (int i = 0; i < 16; ++i) {
+          const f32x4 q4 = *(const f32x4 *)(s_q + j0 + 4 * i);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc += qv[j][e] * kv[j][e];
+          for (int e = 0; e < 4; ++e) acc += q4[e] * k0[i][e];
+        }
       }
       s = acc * scale;
     }
@@ -56,39 +77,44 @@ __global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a) {
     mx = fmaxf(mx, s);
   }
   mx = wave_max(mx);
+  if ((tid & 63) == 0) s_red[tid >> 6] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) mx = fmaxf(mx, s_red[w]);
   float sum = 0.f;
-  for (int k = lane; k < n_keys; k += 64) {
-    const float p = (sc[k] == -INFINITY) ? 0.f : expf(sc[k] - mx);
+  for (int k = tid; k < (n_keys + 63) / 64 * 64; k += NT) {
+    const float p = (k >= n_keys || sc[k] == -INFINITY) ? 0.f : expf(sc[k] - mx);
     sc[k] = p;
     sum += p;
   }
-  sum = wave_sum(sum);
-  __syncthreads();
-  float *o = (float *)a.out + (size_t)r * a.n_q_heads * d + (size_t)head * d;
-  for (int j = lane; j < d; j += 64) {
-    const size_t vj = (size_t)j * a.kv.v_stride();
-    float acc = 0.f;
-    int k = 0;
-    for (; k + 64 <= n_keys; k += 64) {   // 64 slots from a multiple of 64 lie side by side, paged or not
-      f32x4 v[16];
+  sum = block_sum<NW>(sum, s_red);   // its barriers also publish sc
+  float acc = 0.f;
+  for (int k = k_begin; k < k_end; k += 64) {   // 64 slots from a multiple of 64 lie side by side inside the cache, paged or not
+    if (k > k_begin) {
       const f32x4 *vp = (const f32x4 *)(vc + a.kv.v_col(b, kvh, k) + vj);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = vp[i];
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc += sc[k + 4 * i + e] * v[i][e];
+      for (int i = 0; i < 16; ++i) v0[i] = vp[i];
     }
-    for (; k < n_keys; ++k) acc += sc[k] * vc[a.kv.v_col(b, kvh, k) + vj];
-    o[j] = acc / sum;
+    const int left = n_keys - k;   // slots past the last key hold no value: their weight is 0, and a NaN is not to meet it
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const f32x4 p4 = *(const f32x4 *)(sc + k + 4 * i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc += p4[e] * (4 * i + e < left ? v0[i][e] : 0.f);
+    }
   }
+  s_o[tid] = acc;
+  __syncthreads();
+  if (tid >= d) return;
+  for (int s = 1; s < shares; ++s) acc += s_o[s * d + tid];
+  ((float *)a.out)[((size_t)r * a.n_q_heads + head) * d + tid] = acc / sum;
 }
 
 void launch_attn_f32(hipStream_t st, const AttnArgs &a) {
   int max_keys = 0;
   for (int b = 0; b < a.batch; ++b) max_keys = max(max_keys, a.ctx.v[b] + a.n_nodes);
-  hipLaunchKernelGGL(k_attn_f32, dim3(a.batch * a.n_nodes, a.n_q_heads), dim3(64),
-                     (size_t)max_keys * sizeof(float), st, a);
+  hipLaunchKernelGGL(k_attn_f32, dim3(a.batch * a.n_nodes, a.n_q_heads), dim3(kAttnF32Threads),
+                     (size_t)((max_keys + 63) / 64 * 64) * sizeof(float), st, a);
 }
 
 // ------------------------------------------------------------------ bf16 path

@@ -1,7 +1,5 @@
 // Small kernels of the verification pass: set-up, rotary table, embedding (+ first RMSNorm
-// statistic), vocabulary statistics reduction and the routing decision; plus the plain fp32
-// pipeline (matmul, rotary + KV append, residual + RMSNorm, SiLU*up as separate simple kernels)
-// that serves fp32 models, where reference precision matters and speed does not.
+// statistic), vocabulary statistics and the routing decision, feature export, commit of a path.
 #include "device_util.hpp"
 
 namespace ts {
@@ -57,7 +55,7 @@ __device__ __forceinline__ void rope_row(int r, const int32_t *positions, int he
 }
 
 // ------------------------------------------------------------------ embedding + first RMSNorm
-// x[r] = E[token_r] (fp32 residual stream).  fp32 models: h[r] = x * rstd * w.  bf16 models: the
+// x[r] = E[token_r] (fp32 residual stream).  bf16 models also: the
 // first matmul's operand panels h = x * w as bf16 hi + lo, and the row's sum of squares (that
 // matmul's epilogue turns it into 1/rms).
 template <typename AT>
@@ -110,17 +108,8 @@ __device__ __forceinline__ void embed_row(int r, const int32_t *tokens, const AT
     if (threadIdx.x == 0) ss_out[r] = ss;
     (void)eps;
   } else {
-    float ss = 0.f;
-    for (int i = threadIdx.x; i < hidden; i += 256) {
-      const float v = to_f32(e[i]);
-      xr[i] = v;
-      ss += v * v;
-    }
-    ss = block_sum<4>(ss, red);
-    const float rstd = 1.0f / sqrtf(ss / (float)hidden + eps);
-    float *hp = (float *)h + (size_t)r * hidden;
-    for (int i = threadIdx.x; i < hidden; i += 256) hp[i] = to_f32(e[i]) * rstd * to_f32(norm_w[i]);
-    (void)h_panel; (void)ss_out;
+    for (int i = threadIdx.x; i < hidden; i += 256) xr[i] = to_f32(e[i]);   // the consumers normalise
+    (void)eps; (void)h; (void)h_panel; (void)ss_out; (void)norm_w;
   }
 }
 
@@ -148,170 +137,6 @@ void launch_begin_pass(hipStream_t st, int dtype, const BeginArgs &a) {
   const dim3 grid(2 * a.rows + 1);
   if (dtype == TRISPEC_F32) hipLaunchKernelGGL(k_begin_pass<float>, grid, dim3(256), 0, st, a);
   else hipLaunchKernelGGL(k_begin_pass<bf16>, grid, dim3(256), 0, st, a);
-}
-
-// Sum of the split-K partials of one output element, ascending split order.
-__device__ __forceinline__ float sum_splits(const float *part, int n_splits, size_t slice, size_t off) {
-  float v = part[off];
-  for (int s = 1; s < n_splits; ++s) v += part[(size_t)s * slice + off];
-  return v;
-}
-
-// ------------------------------------------------------------------ fp32 pipeline: QKV epilogue
-// One workgroup per (row, head): rotary embedding of q and k heads (pair (j, j + d/2)), q to the
-// attention operand buffer, k and v to cache slot ctx_len + node (v transposed).
-__global__ void k_qkv_epilogue_f32(const float *part, int n_splits, int rows_pad, int n_q_heads,
-                                   int n_kv_heads, int head_dim, const float *cos_t, const float *sin_t,
-                                   int n_nodes, CtxLens ctx, KvMap kvm, float *q_out, float *k_cache,
-                                   float *v_cache, const float *q_norm_w, const float *k_norm_w, float eps) {
-  __shared__ float s_sq[64];
-  const int r = blockIdx.x, hh = blockIdx.y, j = threadIdx.x;   // head_dim / 2 threads
-  const int half = head_dim >> 1;
-  const int n_total = (n_q_heads + 2 * n_kv_heads) * head_dim;
-  const size_t slice = (size_t)rows_pad * n_total;
-  const size_t off = (size_t)r * n_total + (size_t)hh * head_dim + j;
-  float a = sum_splits(part, n_splits, slice, off);
-  float b = sum_splits(part, n_splits, slice, off + half);
-  if (q_norm_w != nullptr && hh < n_q_heads + n_kv_heads) {   // RMSNorm over the head (uniform branch)
-    s_sq[j] = a * a + b * b;
-    __syncthreads();
-    float ss = 0.f;
-    for (int i = 0; i < half; ++i) ss += s_sq[i];           // ascending: the same order in every thread
-    const float rn = 1.0f / sqrtf(ss / (float)head_dim + eps);
-    const float *nw = hh < n_q_heads ? q_norm_w : k_norm_w;
-    a *= rn * nw[j];
-    b *= rn * nw[j + half];
-  }
-  const int bidx = r / n_nodes, node = r - bidx * n_nodes;
-  const int slot = ctx.v[bidx] + node;
-  if (hh < n_q_heads + n_kv_heads) {
-    const float c = cos_t[r * half + j], s = sin_t[r * half + j];
-    const float ra = a * c - b * s;
-    const float rb = b * c + a * s;
-    a = ra; b = rb;
-  }
-  if (hh < n_q_heads) {
-    float *q = q_out + (size_t)r * n_q_heads * head_dim + (size_t)hh * head_dim;
-    q[j] = a;
-    q[j + half] = b;
-  } else if (hh < n_q_heads + n_kv_heads) {
-    const int kvh = hh - n_q_heads;
-    float *k = k_cache + kvm.k_row(bidx, kvh, slot);
-    k[j] = a;
-    k[j + half] = b;
-  } else {
-    const int kvh = hh - n_q_heads - n_kv_heads;
-    float *v = v_cache + kvm.v_col(bidx, kvh, slot);
-    v[(size_t)j * kvm.v_stride()] = a;
-    v[(size_t)(j + half) * kvm.v_stride()] = b;
-  }
-}
-
-void launch_qkv_epilogue(hipStream_t st, int dtype, const float *part, int n_splits, int rows,
-                         int rows_pad, int n_q_heads, int n_kv_heads, int head_dim,
-                         const float *cos_t, const float *sin_t, int n_nodes, CtxLens ctx,
-                         const KvMap &kvm, void *q_out, void *k_cache, void *v_cache, const float *q_norm_w,
-                         const float *k_norm_w, float eps) {
-  (void)dtype;
-  dim3 grid(rows, n_q_heads + 2 * n_kv_heads), block(head_dim / 2);
-  hipLaunchKernelGGL(k_qkv_epilogue_f32, grid, block, 0, st, part, n_splits, rows_pad, n_q_heads,
-                     n_kv_heads, head_dim, cos_t, sin_t, n_nodes, ctx, kvm, (float *)q_out,
-                     (float *)k_cache, (float *)v_cache, q_norm_w, k_norm_w, eps);
-}
-
-// ------------------------------------------------------------------ fp32 pipeline: residual + RMSNorm
-// x[r] += y[r]; h[r] = x[r] * rstd * w.  One workgroup per row.
-__global__ __launch_bounds__(256) void k_reduce_residual_norm_f32(const float *part, int n_splits,
-                                                                  int rows_pad, int hidden,
-                                                                  const float *norm_w, float eps, float *x,
-                                                                  float *h) {
-  __shared__ float red[4];
-  const int r = blockIdx.x;
-  const size_t slice = (size_t)rows_pad * hidden;
-  float *xr = x + (size_t)r * hidden;
-  float ss = 0.f;
-  for (int i = threadIdx.x; i < hidden; i += 256) {
-    const float v = xr[i] + sum_splits(part, n_splits, slice, (size_t)r * hidden + i);
-    xr[i] = v;
-    ss += v * v;
-  }
-  ss = block_sum<4>(ss, red);
-  const float rstd = 1.0f / sqrtf(ss / (float)hidden + eps);
-  for (int i = threadIdx.x; i < hidden; i += 256) h[(size_t)r * hidden + i] = xr[i] * rstd * norm_w[i];
-}
-
-void launch_reduce_residual_norm(hipStream_t st, int dtype, const float *part, int n_splits, int rows,
-                                 int rows_pad, int hidden, const void *norm_w, float eps, float *x,
-                                 void *h) {
-  (void)dtype;
-  hipLaunchKernelGGL(k_reduce_residual_norm_f32, dim3(rows), dim3(256), 0, st, part, n_splits, rows_pad,
-                     hidden, (const float *)norm_w, eps, x, (float *)h);
-}
-
-// ------------------------------------------------------------------ fp32 pipeline: SiLU(gate) * up
-// columns [0, F) of y are the gate projection, [F, 2F) the up projection.
-__global__ __launch_bounds__(256) void k_reduce_swiglu_f32(const float *part, int n_splits, int rows_pad,
-                                                           int ffn, float *act) {
-  const int r = blockIdx.y;
-  const int f = blockIdx.x * 256 + threadIdx.x;
-  if (f >= ffn) return;
-  const size_t slice = (size_t)rows_pad * 2 * ffn;
-  const size_t off = (size_t)r * 2 * ffn + f;
-  const float g = sum_splits(part, n_splits, slice, off);
-  const float u = sum_splits(part, n_splits, slice, off + ffn);
-  const float silu = g / (1.0f + expf(-g));
-  act[(size_t)r * ffn + f] = silu * u;
-}
-
-void launch_reduce_swiglu(hipStream_t st, int dtype, const float *part, int n_splits, int rows,
-                          int rows_pad, int ffn, void *act) {
-  (void)dtype;
-  dim3 grid((ffn + 255) / 256, rows);
-  hipLaunchKernelGGL(k_reduce_swiglu_f32, grid, dim3(256), 0, st, part, n_splits, rows_pad, ffn, (float *)act);
-}
-
-// ------------------------------------------------------------------ fp32 reference-precision matmul
-// One wavefront per (output column, group of 8 rows); lanes stride the reduction.  Memory round trips
-// set its time, so the loads of 8 steps (512 reduction elements) are requested together, without a
-// branch around any of them; the additions stay in their order (256 x 512 over 9 rows: 18.6 -> 4.9 us).
-__global__ __launch_bounds__(64) void k_gemm_f32(GemmArgs a) {
-  const int col = blockIdx.x;
-  const int r0 = blockIdx.y * 8;
-  int s = 0;
-  while (s + 1 < a.n_seg && col >= a.seg[s + 1].col0) ++s;
-  const float *w = (const float *)a.seg[s].w + (size_t)(col - a.seg[s].col0) * a.k;
-  const float *x[8];   // rows past the end repeat the last one; their sums are not stored
-#pragma unroll
-  for (int j = 0; j < 8; ++j) x[j] = (const float *)a.x + (size_t)min(r0 + j, a.rows - 1) * a.k;
-  float acc[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-  constexpr int U = 8;
-  for (int k0 = threadIdx.x; k0 < a.k; k0 += 64 * U) {
-    float wv[U], xv[U][8];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = min(k0 + 64 * u, a.k - 1);
-      wv[u] = w[k];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) xv[u][j] = x[j][k];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (k0 + 64 * u < a.k)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += xv[u][j] * wv[u];
-  }
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float v = wave_sum(acc[j]);
-    if (threadIdx.x == 0 && r0 + j < a.rows)
-      a.out[(size_t)(r0 + j) * a.n_total + col] = v + (a.bias != nullptr ? a.bias[col] : 0.f);
-  }
-}
-
-void launch_gemm_f32(hipStream_t st, const GemmArgs &a) {
-  hipLaunchKernelGGL(k_gemm_f32, dim3(a.n_total, (a.rows + 7) / 8), dim3(64), 0, st, a);
 }
 
 // One workgroup per node: count the vocabulary entries that precede the node's token in its
