@@ -162,6 +162,17 @@ int build_nodes(const int32_t *parents, int batch, int n_nodes, int n_forced, No
   return TRISPEC_OK;
 }
 
+// Nodes on the longest root path
+int tree_depth(const NodeTable &tab, int rows, int n_nodes) {
+  int longest = 0, depth[kMaxNodes];
+  for (int i = 0; i < rows; ++i) {
+    const int node = i % n_nodes;
+    depth[node] = node == 0 ? 1 : depth[tab.parent[i]] + 1;
+    if (depth[node] > longest) longest = depth[node];
+  }
+  return longest;
+}
+
 int check_opts(const trispec_verify_opts *o, float threshold) {
   if (!o) return TRISPEC_ENULL;
   if (o->criterion != TRISPEC_CRIT_MARGIN && o->criterion != TRISPEC_CRIT_TOP1 && o->criterion != TRISPEC_CRIT_ENTROPY)
@@ -528,46 +539,12 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
   at.ctx = ctx;
   at.batch = B; at.n_nodes = n_nodes; at.n_q_heads = c.n_q_heads; at.n_kv_heads = c.n_kv_heads;
   at.head_dim = c.head_dim; at.kv = kv->map();
-  {
-    // context split: aim at one workgroup per CU over (sequence, kv head, row group, split), at
-    // least 256 keys per workgroup, at most kMaxAttnSplits splits.  Long contexts and batches then
-    // take few, long splits — the fp32 partial outputs a split writes (rows x head_dim) would
-    // otherwise outweigh the K/V it reads.  A tree of more than 128 query rows per kv head over a
-    // long context takes 256-row workgroups (eight waves, 64-key tiles), which stage every K/V
-    // tile once instead of once per 128-row group; on shorter contexts the two 128-row groups,
-    // each with its own CU, finish sooner.  At most 32 (64) rows over up to 128 (64) keys a CU take
-    // k_attn_few (9 nodes, 16 heads on 8: 1000 keys 11.4 -> 7.6 us, 4096 keys 12.6 -> 10.6; 30 nodes, 2048
-    // keys 12.7 -> 12.1); over more its scattered reads cost more than staging (8192 keys: 15.2 / 15.1 us
-    // for 9 nodes, 17.3 / 23.8 for 30; four sequences of 2048 keys 14.6 / 17.1).
-    const int group = c.n_q_heads / c.n_kv_heads;
-    const int p_rows = group * n_nodes;
-    at.rows_per_wg = p_rows > 128 && max_keys >= kAttnWideMinKeys ? 256 : 128;
-    if (p_rows <= 32 ? B * c.n_kv_heads * max_keys <= 32768 : p_rows <= 64 && B * c.n_kv_heads * max_keys <= 16384)
-      at.rows_per_wg = p_rows <= 32 ? 32 : 64;
-    at.n_row_groups = (p_rows + at.rows_per_wg - 1) / at.rows_per_wg;
-    const int per_split = B * c.n_kv_heads * at.n_row_groups, n_draft = (n_nodes + 31) / 32;
-    int want = (256 + per_split - 1) / per_split, unit = kv->page_table ? 128 : 64, least = 256;
-    if (at.rows_per_wg <= 64) {
-      // 128 keys at least, two workgroups to a CU; up to 16 splits, which the merge fetches in one round
-      // trip, more only when a split would grow past 512 keys
-      unit = least = 128;
-      const int room = 512 / per_split - n_draft;
-      want = max_keys > 16 * 512 ? (max_keys + 511) / 512 : 16;
-      if (want > room) want = room;
-      if (want < 1) want = 1;
-    }
-    if (want > kMaxAttnSplits) want = kMaxAttnSplits;
-    // (a paged cache: every split starts at a multiple of the largest key tile, so that no tile straddles two pages)
-    int kps = (int)align_up((size_t)((max_keys + want - 1) / want), unit);
-    if (kps < least) kps = least;
-    at.keys_per_split = kps;
-    at.n_splits = (max_keys + kps - 1) / kps;
-    if (at.n_splits < 1) at.n_splits = 1;
-    // The draft nodes: by workgroups of their own where the context leaves CUs free, else in the merge
-    // kernel (60 nodes, 32 heads, 4096 keys, whose context takes every CU: 17.6 + 10.2 us; with a second
-    // round of workgroups 27.4 + 6.3, with fewer and longer splits no better).
-    at.draft_mode = at.rows_per_wg <= 64 || (at.n_splits + n_draft) * per_split <= 256 ? kDraftOwnGroups : kDraftInMerge;
-    at.n_draft = at.draft_mode == kDraftInMerge ? 0 : n_draft;
+  if (!f32) {
+    const AttnPlan p = plan_attn(B, c.n_kv_heads, group, c.head_dim, n_nodes, tree_depth(tab, rows, n_nodes), max_keys, kv->page_table != nullptr);
+    at.few = p.few;
+    at.rows_per_wg = p.rows_per_wg; at.n_row_groups = p.n_row_groups;
+    at.keys_per_split = p.keys_per_split; at.n_splits = p.n_splits;
+    at.draft_mode = p.draft_mode; at.n_draft = p.n_draft;
   }
   at.part_o = (float *)(ws + L.attn_o);
   at.part_m = (float *)(ws + L.attn_m);

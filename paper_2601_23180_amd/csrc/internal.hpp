@@ -23,7 +23,6 @@ constexpr int kMaxChain = 64;        // nodes of a chain in the sampling form (o
 constexpr int kMaxGroup = 8;         // query heads per kv head (bf16 attention)
 constexpr int kMaxSplitK = 32;       // k-splits of one matmul
 constexpr int kMaxAttnSplits = 64;   // context splits of one attention call
-constexpr int kAttnWideMinKeys = 6144;   // longest context from which trees of > 128 rows take 256-row workgroups
 constexpr int kGemmTileN = 128;      // output columns per workgroup (4 waves x 32)
 
 // Per-call node table, passed to the set-up kernel by value (1 KB of kernel arguments).
@@ -179,7 +178,8 @@ enum { kDraftInMerge = 0, kDraftOwnGroups = 1 };
 struct AttnArgs {
   const void *q;        // fp32 path: [rows_pad, nq*d] fp32 queries; bf16 path: bf16 hi panel, lo q_panel later
   size_t q_panel;
-  int32_t rows_per_wg;  // query rows (group * n_nodes of them per kv head) one workgroup covers: 32, 64 (k_attn_few), 128 or 256
+  int32_t rows_per_wg;  // query rows (group * n_nodes of them per kv head) one workgroup covers: 32, 64, 128 or 256
+  bool few;             // 32 or 64 rows by k_attn_few
   int32_t n_row_groups; // ceil(group * n_nodes / rows_per_wg)
   const void *k_cache;  // this layer's K and V^T, addressed through `kv`
   const void *v_cache;

@@ -984,12 +984,15 @@ static void launch_attn_bf16_d(hipStream_t st, const AttnArgs &a) {
     else                                                                                                                     \
       hipLaunchKernelGGL((k_attn_bf16<D, KT_, NW_, KG_, PAGED_, false>), grid, dim3(64 * NW_), 0, st, a);                           \
   } while (0)
-  if (a.rows_per_wg == 32) {
+  if (a.few && a.rows_per_wg == 32) {
     if (paged) hipLaunchKernelGGL((k_attn_few<D, 1, true>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((k_attn_few<D, 1, false>), grid, dim3(256), 0, st, a);
-  } else if (a.rows_per_wg == 64) {
+  } else if (a.few) {
     if (paged) hipLaunchKernelGGL((k_attn_few<D, 2, true>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((k_attn_few<D, 2, false>), grid, dim3(256), 0, st, a);
+  } else if (a.rows_per_wg == 64) {
+    if (paged) TS_ATTN(128, 8, 4, true);
+    else TS_ATTN(128, 8, 4, false);
   } else if (a.rows_per_wg == 256) {
     if (paged) TS_ATTN(64, 8, 1, true);
     else TS_ATTN(64, 8, 1, false);

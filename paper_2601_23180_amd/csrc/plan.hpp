@@ -199,6 +199,84 @@ inline SplitPlan plan_layer(int n_cols, int k, int unit, int max_items, int spli
   return p;
 }
 
+// ---- attention: how the query rows and the keys of a pass are divided into workgroups
+struct AttnPlan {
+  bool few;          // k_attn_few
+  int rows_per_wg, n_row_groups, keys_per_split, n_splits, draft_mode, n_draft;
+};
+
+// group * n_nodes query rows per kv head over up to max_keys keys; depth: nodes on the longest root path.
+//
+// At most 32 (64) rows over up to 128 (64) keys a CU take k_attn_few (9 nodes, 16 heads on 8: 1000 keys 11.4 -> 7.6 us, 4096
+// keys 12.6 -> 10.6; 30 nodes, 2048 keys 12.7 -> 12.1); over more its scattered reads cost more than staging (8192 keys:
+// 15.2 / 15.1 us for 9 nodes, 17.3 / 23.8 for 30; four sequences of 2048 keys 14.6 / 17.1).
+//
+// Else: workgroups of 64, 128 or 256 rows and a number of key splits, with the smallest estimated time of the context kernel
+// and the merge together.  A context kernel takes a fixed time (launch, queries and first tile, partials out) and a time per key
+// of its split; beyond 256 workgroups, one a CU, that comes again.  256 rows stage a key once for all rows of a tree;
+// 64 rows by eight wavefronts that share a tile's keys out are the fastest per row, two wavefronts a SIMD, and leave
+// half the partials of 128 rows, but every row group reads the keys again.  The draft nodes have workgroups of their own
+// where those fit beside the context, else they are the merge's, by the node: 0.24 us for every node that the longest
+// path goes beyond 8 (chains: 60 nodes over 4096 keys, 32 heads, 38.2 + 21.9 us in the merge, with fewer splits and own workgroups 20.2 + 6.0).
+// Fitted to 64-, 128- and 256-row forms in 1 to 32 splits, 57 shapes of 24 to 240 rows, 700 to 16384 keys, one to four sequences, head_dim 64
+// and 128: the chosen one is on average 1.6 % slower than the fastest, at worst 17 %.  Before (256 / (sequences * heads * row groups)
+// splits, rounded up, of 256 keys at least, so that three sequences left a second round of 8 workgroups) -> now, us, context + merge:
+//   120 rows   8192 keys 19.6 + 10.0 -> 19.9 + 7.0, 16384 30.8 + 10.0 -> 28.0 + 7.2, 1024 14.0 + 4.8 -> 12.6 + 4.1, three sequences of 8192 57.0 + 11.3 -> 40.8 + 9.6
+//   240 rows   8192 keys 25.1 + 13.2 -> 28.7 + 7.9, 4096 17.4 + 9.4 -> 19.8 + 8.0, 2048 16.3 + 8.9 -> 16.6 + 4.8
+inline AttnPlan plan_attn(int batch, int n_kv, int group, int head_dim, int n_nodes, int depth, int max_keys, bool paged) {
+  const int p_rows = group * n_nodes, n_draft = (n_nodes + 31) / 32;
+  AttnPlan best;
+  if (p_rows <= 32 ? batch * n_kv * max_keys <= 32768 : p_rows <= 64 && batch * n_kv * max_keys <= 16384) {
+    // 128 keys at least, two workgroups to a CU; up to 16 splits, which the merge fetches in one round
+    // trip, more only when a split would grow past 512 keys
+    int want = max_keys > 16 * 512 ? (max_keys + 511) / 512 : 16;
+    const int room = 512 / (batch * n_kv) - n_draft;
+    if (want > room) want = room;
+    if (want < 1) want = 1;
+    if (want > kMaxAttnSplits) want = kMaxAttnSplits;
+    int kps = ((max_keys + want - 1) / want + 127) / 128 * 128;
+    if (kps < 128) kps = 128;
+    best.few = true;
+    best.rows_per_wg = p_rows <= 32 ? 32 : 64;
+    best.n_row_groups = 1;
+    best.keys_per_split = kps;
+    best.n_splits = max_keys > kps ? (max_keys + kps - 1) / kps : 1;
+    best.draft_mode = kDraftOwnGroups;
+    best.n_draft = n_draft;
+    return best;
+  }
+  best.few = false;
+  double best_us = 1e30;
+  for (int rows = 64; rows <= 256; rows *= 2) {
+    if ((rows == 64 && p_rows <= 64) || (rows == 256 && p_rows <= 128)) continue;   // 128 rows with at most 64 are the 64-row form
+    const int groups = (p_rows + rows - 1) / rows, per_split = batch * n_kv * groups;
+    const double fixed = (rows == 256 ? 13.5 : (rows == 64 ? 9.3 : 8.9)) * (head_dim < 128 ? 0.67 : 1.0);
+    const double per_key = (rows == 256 || (rows == 128 && p_rows > 96) ? 0.033 : (rows == 128 && p_rows > 64 ? 0.021 : 0.018)) * (head_dim < 128 ? 0.58 : 1.0);
+    // every split starts at a multiple of the kernel's key tile, in a paged cache of the largest
+    const int unit = rows == 256 && !paged ? 64 : 128;
+    for (int s = 1; s <= kMaxAttnSplits; ++s) {
+      int kps = ((max_keys + s - 1) / s + unit - 1) / unit * unit;
+      if (kps < 128) kps = 128;
+      const int n = max_keys > kps ? (max_keys + kps - 1) / kps : 1;
+      if (n != s) continue;
+      const bool own = (n + n_draft) * per_split <= 256;
+      const int rounds = (n * per_split + 255) / 256;
+      const double mb = (double)(n + (own ? n_draft : 0)) * p_rows * batch * n_kv * (head_dim + 2) * 4e-6;   // partials
+      const double us = fixed + per_key * kps * rounds + (own ? 3.0 + 0.30 * mb : 7.0 + 0.36 * mb + 0.24 * (depth > 8 ? depth - 8 : 0));
+      if (us < best_us) {
+        best_us = us;
+        best.rows_per_wg = rows;
+        best.n_row_groups = groups;
+        best.keys_per_split = kps;
+        best.n_splits = n;
+        best.draft_mode = own ? kDraftOwnGroups : kDraftInMerge;
+        best.n_draft = own ? n_draft : 0;
+      }
+    }
+  }
+  return best;
+}
+
 // ---- the plans of one model, made once: the matmuls of a pass depend on its rows only through the kind of panel
 
 // kinds of panels: 1 to 4 row blocks of 16, 6, 8, more than 128 rows
