@@ -880,9 +880,9 @@ __global__ __launch_bounds__(512) void k_attn_merge_tree(AttnArgs a) {
   f32x4 kv4[D / 16];
   {
     const int j = s_anc[min(tid >> 2, n_anc - 1)];
-    const float *kp = a.qkv + (size_t)(b * M + j) * n_total + (size_t)(a.n_q_heads + kvh) * D + qq * (D / 4);
+    const float *kp = a.qkv + (size_t)(b * M + j) * n_total + (size_t)(a.n_q_heads + kvh) * D + qq * 4;   // four lanes: 64 bytes side by side
 #pragma unroll
-    for (int i = 0; i < D / 16; ++i) kv4[i] = *(const f32x4 *)(kp + 4 * i);
+    for (int i = 0; i < D / 16; ++i) kv4[i] = *(const f32x4 *)(kp + 16 * i);
   }
   if (active) { s_q[al][f] = q2.x; s_q[al][f + 1] = q2.y; }
   __syncthreads();
@@ -893,16 +893,16 @@ __global__ __launch_bounds__(512) void k_attn_merge_tree(AttnArgs a) {
     const int slot = s0 + (tid >> 2);
     if (s0 > 0) {   // later batches (deep paths on small workgroups) fetch their keys here
       const int j = s_anc[min(slot, n_anc - 1)];
-      const float *kp = a.qkv + (size_t)(b * M + j) * n_total + (size_t)(a.n_q_heads + kvh) * D + qq * (D / 4);
+      const float *kp = a.qkv + (size_t)(b * M + j) * n_total + (size_t)(a.n_q_heads + kvh) * D + qq * 4;
 #pragma unroll
-      for (int i = 0; i < D / 16; ++i) kv4[i] = *(const f32x4 *)(kp + 4 * i);
+      for (int i = 0; i < D / 16; ++i) kv4[i] = *(const f32x4 *)(kp + 16 * i);
     }
     for (int h = 0; h < group; ++h) {
       float acc = 0.f;
 #pragma unroll
       for (int i = 0; i < D / 16; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc += kv4[i][e] * s_q[h][qq * (D / 4) + 4 * i + e];
+        for (int e = 0; e < 4; ++e) acc += kv4[i][e] * s_q[h][16 * i + 4 * qq + e];
       acc += __shfl_xor(acc, 1, 64);
       acc += __shfl_xor(acc, 2, 64);
       if (qq == 0 && slot < n_anc) s_sc[h][slot] = acc * scale;
