@@ -54,7 +54,13 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_wide(GemmArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave / WC, wc = wave - wr * WC;
   const int ln = lane & 31, g = lane >> 5;
-  const int tile = blockIdx.x, rg = blockIdx.y, split = blockIdx.z;
+  // Workgroups go round-robin over the 8 XCDs: ids 8 apart are the row groups of one (tile, split), whose weights then
+  // come through one L2 at about the same time.  Row group by row group the LM head, two rounds of workgroups and more, read them
+  // from HBM twice (128256 x 4096, 240 rows: 574 -> 539 us; products of one round are even).
+  const int n_tiles = (a.n_total + TN - 1) / TN, n_rg = (a.rows + kWideRows - 1) / kWideRows;
+  const int item = (int)(blockIdx.x >> 3) / n_rg * 8 + (blockIdx.x & 7), rg = (int)(blockIdx.x >> 3) % n_rg;
+  if (item >= n_tiles * a.n_splits) return;   // the last 8 are filled up
+  const int split = item / n_tiles, tile = item - split * n_tiles;
   const int mbt = a.rows_pad >> 5;
   const int kb_total = a.k >> 6;
   const int b0 = kb_total * split / a.n_splits, n = kb_total * (split + 1) / a.n_splits - b0;   // 64-deep blocks
@@ -104,10 +110,9 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_wide(GemmArgs a) {
     xr[i] = *(const u32x4 *)((const char *)(xg + ((size_t)(c * 4 + j) * mbt * 2 + r) * 512) + lane_off);
   };
   auto store_x1 = [&](int i, int buf) { *(u32x4 *)(lds + buf * BUF + (wave * XV + i) * 1024 + lane * 16) = xr[i]; };
-  constexpr bool SHARED_W = WR > 1;              // several wavefronts read the same weights
   auto load_w1 = [&](int set, int t, int i, int c) {
     const bf16x8 *p = (const bf16x8 *)((const char *)(wp[i] + (size_t)c * 2048 + 512 * t) + lane_off);
-    w[set][t][i] = SHARED_W ? *p : __builtin_nontemporal_load(p);
+    w[set][t][i] = *p;   // no non-temporal hint: other wavefronts or the other row group read it too
   };
   auto read_x1 = [&](int slot, int t, int buf, int m) {
     xf[slot][m] = *(const bf16x8 *)(lds + buf * BUF + (t * MB * 2 + wr * MBW * 2 + m) * 1024 + lane * 16);
@@ -274,9 +279,9 @@ __global__ __launch_bounds__(256) void k_gemm_finish(GemmArgs a) {
 
 template <int EPI>
 static void dispatch_wide(hipStream_t st, const GemmArgs &a) {
-  const int n_rg = (a.rows + kWideRows - 1) / kWideRows;
-  const dim3 grid((a.n_total + a.tile_n - 1) / a.tile_n, n_rg, a.n_splits);
-  if (EPI == EPI_HEAD || a.tile_n == 256) {   // the LM head is always in 256-column tiles
+  const int n_rg = (a.rows + kWideRows - 1) / kWideRows, wide = EPI == EPI_HEAD || a.tile_n == 256;   // the LM head always
+  const dim3 grid(((a.n_total + (wide ? 255 : 127)) / (wide ? 256 : 128) * a.n_splits + 7) / 8 * 8 * n_rg);
+  if (wide) {
     hipLaunchKernelGGL((k_gemm_wide<1, 4, 4, 2, EPI>), grid, dim3(256), 0, st, a);
   } else if constexpr (EPI != EPI_HEAD) {
     hipLaunchKernelGGL((k_gemm_wide<2, 4, 2, 1, EPI>), grid, dim3(512), 0, st, a);
