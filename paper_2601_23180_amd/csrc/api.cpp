@@ -44,10 +44,10 @@ struct Layout {
   size_t anc, parent, status, cos_t, sin_t, x, x2, h, h2, q, qkv_f32, attn_out, act, part, counters, ss_part, attn_o, attn_m, attn_l, head_l1, head_l2, head_sum, head_ent, head_idx, node_l1, node_l2, node_sum,
       node_ent, node_idx, logits, total;
   int rows_max, rows_pad_max, head_tiles, max_tiles;
-  // `counters` holds, in this order: max_tiles + 1 tile counters of the split-K matmuls, kLayerPhases
+  // `counters` holds, in this order: max_tiles + 1 tile counters of the split-K matmuls, two sets of words that tiles finished together meet at, kLayerPhases
   // barrier counters per layer, the abort word, a counter of finished rows per sequence — n_zero ints that the set-up
   // kernel clears
-  int bar_index, abort_index, done_index, n_zero;
+  int meet_index, bar_index, abort_index, done_index, n_zero;
   size_t part_phase;   // floats per partial region of one phase of the layer kernel
   size_t part_floats;  // floats of the whole partial region
 };
@@ -57,6 +57,8 @@ constexpr int kLayerSplitCap = 8;    // k splits of one matmul inside the layer 
 // Longest wait at a device-side barrier, in ticks of the 100 MHz wall clock (2 s: three orders of
 // magnitude above a whole pass).  trispec_debug_set_spin_limit changes it (tests of the expiry path).
 unsigned long long g_spin_limit = 200000000ull;
+// Longest that the workgroups of a tile wait for each other (meet_splits): 20 us, several times what they differ by
+constexpr uint32_t kMeetTicks = 2000;
 
 // Only arithmetic: the matmuls' plans are the model's.  Every call of verify and decide comes through here.
 Layout make_layout(const trispec_model &m, int batch, int max_nodes) {
@@ -103,7 +105,8 @@ Layout make_layout(const trispec_model &m, int batch, int max_nodes) {
     L.part_floats = floats;
     L.part = take(sizeof(float) * L.part_floats);
   }
-  L.bar_index = L.max_tiles + 1;
+  L.meet_index = L.max_tiles + 1;
+  L.bar_index = L.meet_index + 2 * kMeetStride * (L.max_tiles + 1);
   L.abort_index = L.bar_index + kLayerPhases * c.n_layers;
   L.done_index = L.abort_index + 1;
   L.n_zero = L.done_index + kMaxBatch;
@@ -739,8 +742,19 @@ int trispec_verify(trispec_model *m, trispec_kv *kv, const int32_t *draft_tokens
       g.next_norm_w = (l + 1 < c.n_layers) ? m->norm_attn[l + 1] : m->final_norm; g.ss_part = ss0;
       return g;
     };
-    auto launch_gemm = [&](const GemmArgs &g) {
-      if (g.kernel == GEMM_STREAM) launched = launch_gemm_stream(st, g) && launched;
+    int turn = 0;   // launches of one pass meet at two sets of counters in turn, and clear each other's
+    auto launch_gemm = [&](GemmArgs g) {
+      if (g.kernel == GEMM_STREAM) {
+        if (tiles_meet(g)) {
+          const int n = (L.max_tiles + 1) * kMeetStride;
+          g.counters = counters + L.meet_index + turn * n;
+          g.next_counters = counters + L.meet_index + (1 - turn) * n;
+          g.n_counters = L.max_tiles + 1;
+          g.meet_ticks = g_spin_limit < kMeetTicks ? (uint32_t)g_spin_limit : kMeetTicks;
+          turn = 1 - turn;
+        }
+        launched = launch_gemm_stream(st, g) && launched;
+      }
       else if (g.kernel == GEMM_HEAD) launch_gemm_head(st, g);
       else launch_gemm_wide(st, g);
     };

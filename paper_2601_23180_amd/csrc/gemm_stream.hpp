@@ -13,7 +13,7 @@
 // What bounds it: loads come back in order, so a CU's requests for the panel (from the L2) wait behind its requests
 // for weights; it draws both together at 45 - 60 GB/s, 2 bytes a column and 64 a row block and k step.  Meeting
 // the splits is bound by the size of the partial tile: it is written through to memory (32 KB a workgroup 1.7
-// us; as 8-byte stores, which leave half lines, 3.3), counted, and read back by one CU.  Without the stream's 3 us, meeting costs
+// us; as 8-byte stores, which leave half lines, 3.3), counted, and read back by one CU, or by one a row block.  Without the stream's 3 us, meeting costs
 // 3.5 us at 32 columns x 64 rows and 11 at 128.  The host weighs one against the other (plan_stream in plan.hpp).
 // Measured, us, before (128-column kernel, or tiles of 32 and 64 columns in 32-row blocks) -> now.  9 rows: 4096 x 1024 (QKV) 10.5 -> 6.3,
 // 1024 x 2048 8.9 -> 6.3, 6144 x 1024 (gate + up) 9.0 -> 6.5, 1024 x 3072 9.0 -> 6.8.  One row: 6144 x 4096 17.2 -> 15.9, 4096 x
@@ -188,6 +188,76 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
 
   TileEpilogue<EPI == EPI_HEAD ? EPI_PLAIN : EPI, TN, NT, ROWS> epi;
   constexpr bool kSplits = EPI != EPI_HEAD && EPI != EPI_SWIGLU;   // gate + up: tiles enough
+  // The tile is finished by all its workgroups, a block of 16 rows each: one CU reading 32 KB a split back and finishing 64 rows
+  // was the longest link of the chain behind the stream.  60 rows, us: 4096 x 12288 in 128 columns x 8 splits 30.9 -> 25.2 (31.6 in 64 x 4
+  // before), 6144 x 4096 in 96 x 4 23.3 -> 21.0; 111 rows, two groups of 64: 4096 x 2048 21.6 -> 16.4.  The words they meet at are
+  // 64 bytes apart: side by side, with all of them polled, the same took 2 - 4 us longer than one workgroup alone.
+  if constexpr (kSplits && RB >= kMeetBlocks) {
+    if (tile_meets(EPI, RB, a.n_splits)) {
+      const int tl_id = blockIdx.z * a.n_tiles + tile;
+      const size_t tile_elems = (size_t)ROWS * TN, stride = (size_t)gridDim.z * a.n_tiles * tile_elems;
+      const ThroughBuffer mine(a.part + (size_t)split * stride + (size_t)tl_id * tile_elems, (uint32_t)tile_elems * 4);
+#pragma unroll
+      for (int mg = 0; mg < RB / MG; ++mg)
+#pragma unroll
+        for (int u = 0; u < QW; ++u)
+          if (NQ % NW == 0 || wave * QW + u < NQ) mine.store((uint32_t)((mg * NQ + wave * QW + u) * 1024 + lane * 16), sum[mg][u]);
+      if (split == 0)   // the words that the next launch meets at; the one before this has ended
+        for (int i = tl_id + tid * (int)gridDim.z * a.n_tiles; i < a.n_counters; i += NT * (int)gridDim.z * a.n_tiles)
+          __hip_atomic_store(&a.next_counters[i * kMeetStride], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __builtin_amdgcn_s_waitcnt(0);   // this thread's partial sums are acknowledged
+      __syncthreads();
+      // Row block `split` is this workgroup's, if there is one; what does not depend on the sums is requested before the wait
+      const int n_blocks = min(RB, (a.rows - row0 + 15) >> 4);
+      TileEpilogue<EPI, TN, NT, 16> bepi;
+      RowScale<NT, 16> bscale;
+      auto request = [&](int m) {
+        bscale.issue(a, row0 + 16 * m);
+        bepi.preload(a, tile, row0 + 16 * m);
+      };
+      auto finish_block = [&](int m) {
+        constexpr int QB = (CB + NW - 1) / NW, SG = QB > 1 ? 4 : 8;   // fragments a wavefront, splits side by side
+        f32x4 bsum[QB];
+        for (int s = 0; s < a.n_splits; s += SG) {
+          f32x4 v[SG][QB];
+#pragma unroll
+          for (int q = 0; q < SG; ++q)
+#pragma unroll
+            for (int u = 0; u < QB; ++u) {
+              const int f = min(wave + u * NW, CB - 1);
+              v[q][u] = *(const f32x4 *)(a.part + (size_t)min(s + q, a.n_splits - 1) * stride + (size_t)tl_id * tile_elems + (m * CB + f) * 256 + lane * 4);
+            }
+#pragma unroll
+          for (int q = 0; q < SG; ++q)
+#pragma unroll
+            for (int u = 0; u < QB; ++u) {
+              if (s + q == 0) bsum[u] = v[q][u];
+              else if (s + q < a.n_splits) bsum[u] += v[q][u];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < QB; ++u) {
+          const int f = wave + u * NW;
+          if (CB % NW == 0 || f < CB)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tl[(4 * q4 + e) * LD + f * 16 + lc] = bsum[u][e];
+        }
+        bscale.finish(a, row0 + 16 * m, s_tmp, s_rs);   // ends with a barrier
+        bepi.apply(a, [&](int lr, int c) { return *(const f32x4 *)(tl + lr * LD + c); }, s_rs, tile, row0 + 16 * m);
+      };
+      if (split < n_blocks) request(split);
+      if (tid == 0) s_last = (int)meet_splits(&a.counters[tl_id * kMeetStride], a.n_splits, split, split < n_blocks, a.meet_ticks);
+      __syncthreads();
+      uint32_t take = s_last;
+      if (split < n_blocks && (take >> split & 1u)) finish_block(split);
+      for (take &= ~(1u << split); take != 0; take &= take - 1) {   // blocks of workgroups that have left
+        __syncthreads();   // the block before has been read
+        request(__builtin_ctz(take));
+        finish_block(__builtin_ctz(take));
+      }
+      return;
+    }
+  }
   if (kSplits && a.n_splits > 1) {
     // partial tiles [split][tile][fragment][lane]: written through, and read by the last workgroup to
     // arrive with the same mapping (nobody reads them earlier in this launch, so no stale line exists)

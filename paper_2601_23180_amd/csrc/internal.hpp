@@ -98,6 +98,7 @@ struct GemmSeg {
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3, EPI_PLAIN = 4 };
 // gemm_stream.hpp, kernels_gemm.hip, kernels_gemm_wide.hip, kernels_layer.hip
 enum { GEMM_STREAM = 0, GEMM_HEAD = 1, GEMM_WIDE = 2, GEMM_LAYER = 3 };
+constexpr int kMeetStride = 16;   // ints between the words that the tiles of the streaming kernel meet at: lines of their own
 struct GemmArgs {
   // fp32 path: x is [rows, K] fp32; matrices, outputs and residual stream are fp32, row by row.
   // bf16 path: x is the bf16 hi panel [rows_pad, K], the lo panel follows x_panel elements later.
@@ -124,7 +125,10 @@ struct GemmArgs {
   const float *bias;   // PLAIN epilogue: [n_total] added to every row, or nullptr
   float *part;         // [n_splits][n_tiles][rows * tile_n] split-K partial tiles: rows of columns, stream in
                        // accumulator fragments; more than 128 rows always in 128-column tiles
-  int32_t *counters;   // [n_tiles + 1], zero between launches
+  int32_t *counters;   // [n_tiles + 1], zero when a launch starts
+  int32_t *next_counters;   // those of the next launch, n_counters, which this one clears
+  int32_t n_counters;
+  uint32_t meet_ticks;      // how long the workgroups of a tile wait for each other, of 100 MHz
   // QKV epilogue
   const float *cos_t, *sin_t;
   float *qkv_f32;      // [rows][n_total] rotated q, k and v in fp32

@@ -36,27 +36,46 @@ constexpr bool stream_built(int epi, int tile_n, int rb) {
   return tile_n == 16 || tile_n == 32 || tile_n == 64 || (tile_n == 128 && rb <= 4);
 }
 
+// Tiles of three row blocks and more, in as many splits at least: the workgroups of a tile finish it together, a block of 16 rows
+// each.  One workgroup with two blocks after another takes longer than the last to arrive with the whole tile (128 rows in 4 splits: 44.1 ->
+// 44.9 us), and two blocks are too little to share out.
+constexpr int kMeetBlocks = 3;
+constexpr bool tile_meets(int epi, int rb, int n_splits) {
+  return epi != EPI_HEAD && epi != EPI_SWIGLU && rb >= kMeetBlocks && n_splits >= rb;
+}
+
 // Decomposition of one matmul over at most 128 rows into (column tile, k split) workgroups of the streaming
 // kernel (gemm_stream.hpp): the tile width and the number of splits with the smallest estimated time.
 //
 // The estimate.  A workgroup takes 3 us to its first data.  It then draws its weights and its share of the
 // activation panel, 2 bytes a column and 64 a row block and k step, at 45 (one row block) to 60 GB/s; the chip draws no
 // more than 6.3 TB/s of weights.  Finishing a tile takes 0.012 us a row block and column, meeting the other splits
-// 0.8 us more and 0.002 a split, row block and column: publish the partial tile, count, read all of them.  So wide tiles draw less of
-// the panel and narrow ones meet sooner.  256 workgroups at a time: one a CU, as most tiles fill it (16 and 32 columns
+// 0.8 us more and 0.002 a split, row block and column: publish the partial tile, count, read all of them.  A tile whose workgroups
+// finish it together (tile_meets) takes 1.2 us, 0.001 a row block and column, 0.0008 a split and column, 0.05 a split and 0.15 of
+// its stream instead (the slowest one's lead).  So wide tiles draw less of the panel and narrow ones meet sooner.  256 workgroups at a time: one a CU, as most tiles fill it (16 and 32 columns
 // over at most 32 rows would fit one to four times, by ring depth).  What it does not know: the ring's depth (launch_one in
 // gemm_stream.hpp), and the epilogues apart (QKV in wide tiles takes 1 to 4 us more than estimated).  Eight and more splits
 // and more than 64 rows cost less than estimated.
 //
 // Estimated / measured, us (kernel times over cold weights; * chosen):
-//   4096 x 4096, 60 rows    32 x 2 16.8 / 17.0   64 x 4* 15.5 / 15.7   128 x 8 23.5 / 18.4   16 x 1 23.4 / 18.3   32 x 1 26.4 / 21.2
-//   4096 x 12288, 60 rows   64 x 4* 28.6 / 32.4   128 x 8 34.1 / 30.9   32 x 2 38.6 / 36.4   64 x 2 47.2 / 44.8   32 x 1 70.1 / 58.1
-//   6144 x 4096 (QKV), 60   96 x 4* 19.5 / 23.0   64 x 2 21.0 / 22.3   128 x 4 22.8 / 24.7   96 x 2 25.2 / 26.6   32 x 1 26.4 / 23.7
+// By one workgroup:
+//   4096 x 4096, 60 rows    32 x 2 16.8 / 17.0   64 x 4 15.5 / 16.5   128 x 8 23.5 / 18.4   16 x 1 23.4 / 18.3   32 x 1 26.4 / 21.2
+//   4096 x 12288, 60 rows   64 x 4 28.6 / 31.6   128 x 8 34.1 / 30.9   32 x 2 38.6 / 36.4   64 x 2 47.2 / 44.8   32 x 1 70.1 / 58.1
+//   6144 x 4096 (QKV), 60   96 x 4 19.5 / 23.3   64 x 2 21.0 / 22.3   128 x 4 22.8 / 24.7   96 x 2 25.2 / 26.6   32 x 1 26.4 / 23.7
 //   24576 x 4096 (gate + up), 60   96* 39.6 / 43.0   112 41.1 / 53.2   48 56.4 / 56.5   64 61.5 / 56.9   32 76.1 / 67.0
-//   2048 x 2048, 60 rows    32 x 4* 9.1 / 9.0   16 x 2 9.7 / 9.7   32 x 2 11.3 / 10.8   64 x 8 12.6 / 10.8
-//   2048 x 6144, 60 rows    32 x 4* 14.6 / 13.8   64 x 8 15.9 / 15.2   16 x 2 19.6 / 17.1   32 x 2 22.2 / 19.7
-//   2048 x 2048, 111 rows   32 x 4* 13.8 / 11.7   16 x 2 15.1 / 12.7   32 x 2 17.7 / 14.3   64 x 4 19.5 / 15.6
-//   2048 x 6144, 111 rows   32 x 4* 23.7 / 19.7   64 x 8 26.3 / 20.6   64 x 4 30.4 / 24.3   16 x 2 33.7 / 25.7
+//   2048 x 2048, 60 rows    32 x 4 9.1 / 8.9   16 x 2 9.7 / 9.7   32 x 2 11.3 / 10.8   64 x 8 12.6 / 10.8
+//   2048 x 6144, 60 rows    32 x 4 14.6 / 14.0   64 x 8 15.9 / 15.2   16 x 2 19.6 / 17.1   32 x 2 22.2 / 19.7
+//   2048 x 2048, 111 rows   32 x 4* 13.8 / 11.5   16 x 2 15.1 / 12.7   32 x 2 17.7 / 14.3   64 x 4 19.5 / 15.6
+//   2048 x 6144, 111 rows   32 x 4 23.7 / 19.8   64 x 8 26.3 / 20.6   64 x 4 30.4 / 24.3   16 x 2 33.7 / 25.7
+// All of the tile together:
+//   4096 x 4096, 60 rows    64 x 4* 15.5 / 15.9   128 x 8 18.0 / 17.6
+//   4096 x 12288, 60 rows   128 x 8* 30.0 / 25.2   64 x 4 30.5 / 28.6   128 x 7 31.8 / 30.1
+//   6144 x 4096 (QKV), 60   96 x 4* 18.8 / 21.0   128 x 5 20.7 / 20.3
+//   2048 x 2048, 60 rows    32 x 4* 9.4 / 8.8   64 x 8 10.2 / 11.2
+//   2048 x 6144, 60 rows    64 x 8* 13.7 / 13.0   32 x 4 15.5 / 13.5   128 x 16 18.4 / 14.4
+//   2048 x 6144, 111 rows   64 x 8* 21.1 / 16.7;   4096 x 2048 (QKV, norms), 111 rows   128 x 4 in two row groups 21.6 -> 16.4
+//   1024 x 3072, 37 rows    32 x 8* 7.9 / 8.1   16 x 4 8.4 / 8.5;   1472 x 4032, 46 rows    32 x 5* 9.9 / 10.2   64 x 11 10.2 / 11.1
+// Over few rows:
 //   1024 x 2048, 9 rows     16 x 4* 5.2 / 6.4   32 x 4 5.9 / 6.6   16 x 2 6.2 / 6.6   32 x 2 7.2 / 7.3   16 x 1 7.6 / 6.5
 //   1024 x 3072, 9 rows     16 x 4* 5.8 / 6.8   32 x 4 6.6 / 7.4   16 x 2 7.3 / 7.4   32 x 2 8.7 / 8.4   16 x 1 9.7 / 8.2
 // Of the tilings measured the chosen one is the fastest or within 5 % of it.
@@ -85,10 +104,12 @@ inline SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim,
     const int tiles = (n_cols + tn - 1) / tn;
     const double rate = rb == 1 ? 45e3 : 60e3, chip_us = 2.0 * n_cols * k / 6.3e6;
     for (int sp = 1; sp <= 16 && sp <= steps && (sp == 1 || tiles * groups * sp <= 256); ++sp) {
+      if (tile_meets(epi, rb, sp) && steps < 8 * sp) continue;   // a step for each of eight wavefronts
       const int rounds = (tiles * groups * sp + 255) / 256;
       const double own_us = rounds * ((steps + sp - 1) / sp) * 32.0 * (2.0 * tn + 64.0 * rb) / rate;
       double us = 3.0 * rounds + (own_us > chip_us ? own_us : chip_us) + 0.012 * rb * tn;
-      if (sp > 1) us += 0.8 + 0.002 * sp * rb * tn;
+      if (tile_meets(epi, rb, sp)) us += 1.2 + 0.001 * rb * tn + 0.0008 * sp * tn + 0.05 * sp + 0.15 * own_us;
+      else if (sp > 1) us += 0.8 + 0.002 * sp * rb * tn;
       if (us < best_us) {
         best_us = us;
         best.tile_n = tn;
@@ -102,6 +123,11 @@ inline SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim,
 }
 // Row groups of one plan: a QKV tile of 128 columns over more than 64 rows takes them in two groups of 64
 inline int row_groups(int epi, const SplitPlan &p, int rows) { return epi == EPI_QKV && p.tile_n == 128 && rows > 64 ? 2 : 1; }
+// The same of one launch
+inline bool tiles_meet(const GemmArgs &g) {
+  const bool groups = g.epi == EPI_QKV && g.tile_n == 128 && g.rows > 64;
+  return g.kernel == GEMM_STREAM && tile_meets(g.epi, groups ? 4 : row_blocks(g.rows), g.n_splits);
+}
 // Tiles that meet at a counter: row groups have their own
 inline int counted_tiles(int epi, const SplitPlan &p, int rows) { return p.n_tiles * row_groups(epi, p, rows); }
 // Floats of its partial tiles

@@ -1,0 +1,39 @@
+"""The k splits of a tile meet: every workgroup of the tile finishes row blocks of it, or the last to arrive finishes
+those of workgroups that have left.  With a wait of one tick (10 ns) most leave; the sums are added in the same
+order, so that a pass leaves the same bits either way, also when passes of other sizes take turns on its counters."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_23180_amd import binding
+from workloads import SHAPES, gen_tree
+from test_gpu_parity import full_check, make_case
+
+pytestmark = pytest.mark.gpu
+
+# batch, nodes, hidden, query heads, kv heads, head_dim, ffn, qk_norm: 3, 4, 6 and 8 row blocks, the last one ragged or without
+# any row; more and fewer splits than blocks; q and k with norms of their own (two groups of 64 rows over more than 64)
+SIZES = [(1, 33, 1024, 8, 4, 128, 1536, 0), (1, 48, 512, 4, 2, 64, 4096, 1), (1, 60, 2048, 16, 8, 128, 6144, 0),
+         (4, 16, 4096, 8, 8, 128, 4096, 0), (1, 65, 512, 4, 4, 128, 1024, 1), (3, 27, 1472, 12, 4, 64, 4032, 0),
+         (3, 37, 2048, 16, 8, 128, 6144, 1), (2, 64, 1024, 8, 8, 128, 3072, 0)]
+
+
+@pytest.mark.parametrize("size", SIZES, ids=["rows%d_%d" % (s[0] * s[1], s[2]) for s in SIZES])
+def test_splits_that_leave(size):
+    batch, nodes, hidden, nq, nkv, d, ffn, norm = size
+    shape = SHAPES["tiny_bf16"].with_(n_layers=3, hidden=hidden, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=ffn,
+                                      qk_norm=bool(norm), vocab=300, lm_head_std=3 / hidden ** 0.5)
+    seed = 900 + hidden + nodes
+    case = make_case(shape, seed, [20 + 17 * b for b in range(batch)], [gen_tree(nodes, 9, 4, seed + b) for b in range(batch)])
+    stay, _, _ = full_check(case, thresholds=(0.5,))
+    lib = binding.lib()
+    try:
+        lib.trispec_debug_set_spin_limit(1)
+        leave = case.run_gpu(0.5)
+        torch.cuda.synchronize()
+    finally:
+        lib.trispec_debug_set_spin_limit(0)
+    again = case.run_gpu(0.5)
+    assert leave["status"][0] == 0 and again["status"][0] == 0
+    for other in (leave, again):
+        assert np.array_equal(stay["logits"], other["logits"])
