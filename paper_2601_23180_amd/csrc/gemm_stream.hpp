@@ -189,8 +189,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
   TileEpilogue<EPI == EPI_HEAD ? EPI_PLAIN : EPI, TN, NT, ROWS> epi;
   constexpr bool kSplits = EPI != EPI_HEAD && EPI != EPI_SWIGLU;   // gate + up: tiles enough
   // The tile is finished by all its workgroups, a block of 16 rows each: one CU reading 32 KB a split back and finishing 64 rows
-  // was the longest link of the chain behind the stream.  60 rows, us: 4096 x 12288 in 128 columns x 8 splits 30.9 -> 25.2 (31.6 in 64 x 4
-  // before), 6144 x 4096 in 96 x 4 23.3 -> 21.0; 111 rows, two groups of 64: 4096 x 2048 21.6 -> 16.4.  The words they meet at are
+  // was the longest link of the chain behind the stream.  60 rows, us: 4096 x 12288 in 128 columns x 8 splits 30.9 -> 28.1 (31.6 in 64 x 4
+  // before), 6144 x 4096 in 96 x 4 23.3 -> 21.7; 111 rows, two groups of 64: 4096 x 2048 21.6 -> 16.4.  The words they meet at are
   // 64 bytes apart: side by side, with all of them polled, the same took 2 - 4 us longer than one workgroup alone.
   if constexpr (kSplits && RB >= kMeetBlocks) {
     if (tile_meets(EPI, RB, a.n_splits)) {

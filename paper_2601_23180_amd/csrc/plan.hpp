@@ -69,10 +69,10 @@ constexpr bool tile_meets(int epi, int rb, int n_splits) {
 //   2048 x 6144, 111 rows   32 x 4 23.7 / 19.8   64 x 8 26.3 / 20.6   64 x 4 30.4 / 24.3   16 x 2 33.7 / 25.7
 // All of the tile together:
 //   4096 x 4096, 60 rows    64 x 4* 15.5 / 15.9   128 x 8 18.0 / 17.6
-//   4096 x 12288, 60 rows   128 x 8* 30.0 / 25.2   64 x 4 30.5 / 28.6   128 x 7 31.8 / 30.1
-//   6144 x 4096 (QKV), 60   96 x 4* 18.8 / 21.0   128 x 5 20.7 / 20.3
+//   4096 x 12288, 60 rows   128 x 8* 30.0 / 28.1   128 x 7 31.8 / 30.1
+//   6144 x 4096 (QKV), 60   96 x 4* 18.8 / 21.7   128 x 5 20.7 / 20.3
 //   2048 x 2048, 60 rows    32 x 4* 9.4 / 8.8   64 x 8 10.2 / 11.2
-//   2048 x 6144, 60 rows    64 x 8* 13.7 / 13.0   32 x 4 15.5 / 13.5   128 x 16 18.4 / 14.4
+//   2048 x 6144, 60 rows    64 x 8* 13.7 / 14.0   32 x 4, by one workgroup, 14.0
 //   2048 x 6144, 111 rows   64 x 8* 21.1 / 16.7;   4096 x 2048 (QKV, norms), 111 rows   128 x 4 in two row groups 21.6 -> 16.4
 //   1024 x 3072, 37 rows    32 x 8* 7.9 / 8.1   16 x 4 8.4 / 8.5;   1472 x 4032, 46 rows    32 x 5* 9.9 / 10.2   64 x 11 10.2 / 11.1
 // Over few rows:
