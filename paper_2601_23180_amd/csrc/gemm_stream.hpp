@@ -45,8 +45,18 @@ struct StreamShape {
   static constexpr int kBlk = NW * CB, MG = kBlk * RB <= 150 ? RB : (RB % 2 == 0 && kBlk * (RB / 2) <= 150 ? RB / 2 : (RB % 4 == 0 && kBlk * (RB / 4) <= 150 ? RB / 4 : 1));
 };
 
-// RB: 16-row blocks, CB: 16-column blocks of the tile, NW: wavefronts, D: steps in flight
-template <int RB, int CB, int NW, int D, int EPI>
+// The arguments of k_gemm_stream, read again: what a rare path needs of them is not held in registers through the common one
+__device__ __forceinline__ const GemmArgs &args_again() {
+  auto p = (const __attribute__((address_space(4))) GemmArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const GemmArgs *)p;
+}
+
+// RB: 16-row blocks, CB: 16-column blocks of the tile, NW: wavefronts, D: steps in flight.  MEET: the workgroups of a tile finish it
+// together (tile_meets in plan.hpp), in a kernel of its own: with both ways to finish in one, tiles that one workgroup
+// finishes held what the other way needs (QKV, 48 rows x 16 columns: 96 -> 150 vector registers, 100 scalar ones spilt; 64 x 32: 20
+// bytes of scratch a lane).
+template <int RB, int CB, int NW, int D, int EPI, bool MEET>
 __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
   constexpr int NT = 64 * NW, ROWS = RB * 16, TN = CB * 16, LD = TN + 4;
   // 32-row blocks of the activation panel: as many as the rows need, or the four of two row groups
@@ -108,7 +118,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
 
   RowScale<NT, SROWS, (RB <= 4 ? 128 : 64) * SROWS / NT> scale;   // as many entries a row are requested ahead
   constexpr bool kScaleLate = RB > 4;   // no registers to spare: behind the stream
-  if (!kScaleLate && a.n_splits == 1) scale.issue(a, row0);
+  if (!MEET && !kScaleLate && a.n_splits == 1) scale.issue(a, row0);
   __builtin_amdgcn_sched_barrier(0);   // requested before the ring: loads come back in order
 
   f32x4 acc[CB][RB];
@@ -119,7 +129,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
 
   bf16x8 w[D][CB], x[D][2 * RB];
   // A run that is no whole number of rounds requests its last step again: no branch around any load, behind
-  // which a wait would drain everything.  launch_one picks D so that this is one step at most.
+  // which a wait would drain everything.  launch_ring picks D so that this is one step at most.
   auto load = [&](int slot, int s_) {
     const int s = min(s_, last);
 #pragma unroll
@@ -143,7 +153,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
 #pragma unroll
   for (int d = 0; d < D; ++d) load(d, d);
   __builtin_amdgcn_sched_barrier(0);
-  if (!kScaleLate && a.n_splits == 1) scale.partial(a, row0, s_tmp);
+  if (!MEET && !kScaleLate && a.n_splits == 1) scale.partial(a, row0, s_tmp);
   int s0 = 0;
   for (; s0 + D < ns; s0 += D) {
 #pragma unroll
@@ -157,7 +167,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
   for (int d = 0; d < D; ++d)
     if (s0 + d < ns) mul(d);   // wave-uniform
 
-  if (kScaleLate && a.n_splits == 1) {
+  if (!MEET && kScaleLate && a.n_splits == 1) {
     scale.issue(a, row0);
     scale.partial(a, row0, s_tmp);
   }
@@ -186,78 +196,77 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
     }
   }
 
-  TileEpilogue<EPI == EPI_HEAD ? EPI_PLAIN : EPI, TN, NT, ROWS> epi;
-  constexpr bool kSplits = EPI != EPI_HEAD && EPI != EPI_SWIGLU;   // gate + up: tiles enough
   // The tile is finished by all its workgroups, a block of 16 rows each: one CU reading 32 KB a split back and finishing 64 rows
   // was the longest link of the chain behind the stream.  60 rows, us: 4096 x 12288 in 128 columns x 8 splits 30.9 -> 28.1 (31.6 in 64 x 4
   // before), 6144 x 4096 in 96 x 4 23.3 -> 21.7; 111 rows, two groups of 64: 4096 x 2048 21.6 -> 16.4.  The words they meet at are
   // 64 bytes apart: side by side, with all of them polled, the same took 2 - 4 us longer than one workgroup alone.
-  if constexpr (kSplits && RB >= kMeetBlocks) {
-    if (tile_meets(EPI, RB, a.n_splits)) {
-      const int tl_id = blockIdx.z * a.n_tiles + tile;
-      const size_t tile_elems = (size_t)ROWS * TN, stride = (size_t)gridDim.z * a.n_tiles * tile_elems;
-      const ThroughBuffer mine(a.part + (size_t)split * stride + (size_t)tl_id * tile_elems, (uint32_t)tile_elems * 4);
+  if constexpr (MEET) {
+    const int tl_id = blockIdx.z * a.n_tiles + tile;
+    const size_t tile_elems = (size_t)ROWS * TN, stride = (size_t)gridDim.z * a.n_tiles * tile_elems;
+    const ThroughBuffer mine(a.part + (size_t)split * stride + (size_t)tl_id * tile_elems, (uint32_t)tile_elems * 4);
 #pragma unroll
-      for (int mg = 0; mg < RB / MG; ++mg)
+    for (int mg = 0; mg < RB / MG; ++mg)
 #pragma unroll
-        for (int u = 0; u < QW; ++u)
-          if (NQ % NW == 0 || wave * QW + u < NQ) mine.store((uint32_t)((mg * NQ + wave * QW + u) * 1024 + lane * 16), sum[mg][u]);
-      if (split == 0)   // the words that the next launch meets at; the one before this has ended
-        for (int i = tl_id + tid * (int)gridDim.z * a.n_tiles; i < a.n_counters; i += NT * (int)gridDim.z * a.n_tiles)
-          __hip_atomic_store(&a.next_counters[i * kMeetStride], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_s_waitcnt(0);   // this thread's partial sums are acknowledged
-      __syncthreads();
-      // Row block `split` is this workgroup's, if there is one; what does not depend on the sums is requested before the wait
-      const int n_blocks = min(RB, (a.rows - row0 + 15) >> 4);
-      TileEpilogue<EPI, TN, NT, 16> bepi;
-      RowScale<NT, 16> bscale;
-      auto request = [&](int m) {
-        bscale.issue(a, row0 + 16 * m);
-        bepi.preload(a, tile, row0 + 16 * m);
-      };
-      auto finish_block = [&](int m) {
-        constexpr int QB = (CB + NW - 1) / NW, SG = QB > 1 ? 4 : 8;   // fragments a wavefront, splits side by side
-        f32x4 bsum[QB];
-        for (int s = 0; s < a.n_splits; s += SG) {
-          f32x4 v[SG][QB];
+      for (int u = 0; u < QW; ++u)
+        if (NQ % NW == 0 || wave * QW + u < NQ) mine.store((uint32_t)((mg * NQ + wave * QW + u) * 1024 + lane * 16), sum[mg][u]);
+    if (split == 0)   // the words that the next launch meets at; the one before this has ended
+      for (int i = tl_id + tid * (int)gridDim.z * a.n_tiles; i < a.n_counters; i += NT * (int)gridDim.z * a.n_tiles)
+        __hip_atomic_store(&a.next_counters[i * kMeetStride], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0);   // this thread's partial sums are acknowledged
+    __syncthreads();
+    // Row block `split` is this workgroup's, if there is one; what does not depend on the sums is requested before the wait
+    const int n_blocks = min(RB, (a.rows - row0 + 15) >> 4);
+    TileEpilogue<EPI, TN, NT, 16> bepi;
+    RowScale<NT, 16> bscale;
+    auto request = [&](const GemmArgs &g, int m) {
+      bscale.issue(g, row0 + 16 * m);
+      bepi.preload(g, tile, row0 + 16 * m);
+    };
+    auto finish_block = [&](const GemmArgs &g, int m) {
+      constexpr int QB = (CB + NW - 1) / NW, SG = QB > 1 ? 4 : 8;   // fragments a wavefront, splits side by side
+      f32x4 bsum[QB];
+      for (int s = 0; s < g.n_splits; s += SG) {
+        f32x4 v[SG][QB];
 #pragma unroll
-          for (int q = 0; q < SG; ++q)
+        for (int q = 0; q < SG; ++q)
 #pragma unroll
-            for (int u = 0; u < QB; ++u) {
-              const int f = min(wave + u * NW, CB - 1);
-              v[q][u] = *(const f32x4 *)(a.part + (size_t)min(s + q, a.n_splits - 1) * stride + (size_t)tl_id * tile_elems + (m * CB + f) * 256 + lane * 4);
-            }
+          for (int u = 0; u < QB; ++u) {
+            const int f = min(wave + u * NW, CB - 1);
+            v[q][u] = *(const f32x4 *)(g.part + (size_t)min(s + q, g.n_splits - 1) * stride + (size_t)tl_id * tile_elems + (m * CB + f) * 256 + lane * 4);
+          }
 #pragma unroll
-          for (int q = 0; q < SG; ++q)
+        for (int q = 0; q < SG; ++q)
 #pragma unroll
-            for (int u = 0; u < QB; ++u) {
-              if (s + q == 0) bsum[u] = v[q][u];
-              else if (s + q < a.n_splits) bsum[u] += v[q][u];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < QB; ++u) {
-          const int f = wave + u * NW;
-          if (CB % NW == 0 || f < CB)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) tl[(4 * q4 + e) * LD + f * 16 + lc] = bsum[u][e];
-        }
-        bscale.finish(a, row0 + 16 * m, s_tmp, s_rs);   // ends with a barrier
-        bepi.apply(a, [&](int lr, int c) { return *(const f32x4 *)(tl + lr * LD + c); }, s_rs, tile, row0 + 16 * m);
-      };
-      if (split < n_blocks) request(split);
-      if (tid == 0) s_last = (int)meet_splits(&a.counters[tl_id * kMeetStride], a.n_splits, split, split < n_blocks, a.meet_ticks);
-      __syncthreads();
-      uint32_t take = s_last;
-      if (split < n_blocks && (take >> split & 1u)) finish_block(split);
-      for (take &= ~(1u << split); take != 0; take &= take - 1) {   // blocks of workgroups that have left
-        __syncthreads();   // the block before has been read
-        request(__builtin_ctz(take));
-        finish_block(__builtin_ctz(take));
+          for (int u = 0; u < QB; ++u) {
+            if (s + q == 0) bsum[u] = v[q][u];
+            else if (s + q < g.n_splits) bsum[u] += v[q][u];
+          }
       }
-      return;
+#pragma unroll
+      for (int u = 0; u < QB; ++u) {
+        const int f = wave + u * NW;
+        if (CB % NW == 0 || f < CB)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) tl[(4 * q4 + e) * LD + f * 16 + lc] = bsum[u][e];
+      }
+      bscale.finish(g, row0 + 16 * m, s_tmp, s_rs);   // ends with a barrier
+      bepi.apply(g, [&](int lr, int c) { return *(const f32x4 *)(tl + lr * LD + c); }, s_rs, tile, row0 + 16 * m);
+    };
+    if (split < n_blocks) request(a, split);
+    if (tid == 0) s_last = (int)meet_splits(&a.counters[tl_id * kMeetStride], a.n_splits, split, split < n_blocks, a.meet_ticks);
+    __syncthreads();
+    uint32_t take = s_last;
+    if (split < n_blocks && (take >> split & 1u)) finish_block(a, split);
+    for (take &= ~(1u << split); take != 0; take &= take - 1) {   // blocks of workgroups that have left
+      const GemmArgs &again = args_again();
+      __syncthreads();   // the block before has been read
+      request(again, __builtin_ctz(take));
+      finish_block(again, __builtin_ctz(take));
     }
+    return;
   }
+  TileEpilogue<EPI == EPI_HEAD ? EPI_PLAIN : EPI, TN, NT, ROWS> epi;
+  constexpr bool kSplits = EPI != EPI_HEAD && EPI != EPI_SWIGLU;   // gate + up: tiles enough
   if (kSplits && a.n_splits > 1) {
     // partial tiles [split][tile][fragment][lane]: written through, and read by the last workgroup to
     // arrive with the same mapping (nobody reads them earlier in this launch, so no stale line exists)
@@ -316,8 +325,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
     epi.apply(a, [&](int lr, int c) { return *(const f32x4 *)(tl + lr * LD + c); }, s_rs, tile, row0);
 }
 
-template <int RB, int CB, int EPI>
-void launch_one(hipStream_t st, const GemmArgs &a) {
+template <int RB, int CB, int EPI, bool MEET>
+void launch_ring(hipStream_t st, const GemmArgs &a) {
   using S = StreamShape<RB, CB>;
   const dim3 grid(a.n_tiles, a.n_splits, RB == 4 ? (a.rows + 63) / 64 : 1), block(64 * S::NW);
   // The deepest ring that divides the steps of a wavefront, for a ring deeper than the run requests its last step again
@@ -326,12 +335,19 @@ void launch_one(hipStream_t st, const GemmArgs &a) {
   const int steps = a.k / 32, each = steps / (S::NW * a.n_splits);
   const int even = steps % (S::NW * a.n_splits) == 0 ? each : 2;
   if constexpr (S::D == 8) {
-    if (even % 8 == 0) { hipLaunchKernelGGL((k_gemm_stream<RB, CB, S::NW, 8, EPI>), grid, block, 0, st, a); return; }
+    if (even % 8 == 0) { hipLaunchKernelGGL((k_gemm_stream<RB, CB, S::NW, 8, EPI, MEET>), grid, block, 0, st, a); return; }
   }
   if constexpr (S::D >= 4) {
-    if (even % 4 == 0) { hipLaunchKernelGGL((k_gemm_stream<RB, CB, S::NW, 4, EPI>), grid, block, 0, st, a); return; }
+    if (even % 4 == 0) { hipLaunchKernelGGL((k_gemm_stream<RB, CB, S::NW, 4, EPI, MEET>), grid, block, 0, st, a); return; }
   }
-  hipLaunchKernelGGL((k_gemm_stream<RB, CB, S::NW, 2, EPI>), grid, block, 0, st, a);
+  hipLaunchKernelGGL((k_gemm_stream<RB, CB, S::NW, 2, EPI, MEET>), grid, block, 0, st, a);
+}
+template <int RB, int CB, int EPI>
+void launch_one(hipStream_t st, const GemmArgs &a) {
+  if constexpr (tile_meets(EPI, RB, kMaxStreamSplits)) {
+    if (tile_meets(EPI, RB, a.n_splits)) return launch_ring<RB, CB, EPI, true>(st, a);
+  }
+  launch_ring<RB, CB, EPI, false>(st, a);
 }
 
 // False, and nothing launched: not built

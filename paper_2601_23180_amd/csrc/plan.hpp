@@ -39,7 +39,7 @@ constexpr bool stream_built(int epi, int tile_n, int rb) {
 // Tiles of three row blocks and more, in as many splits at least: the workgroups of a tile finish it together, a block of 16 rows
 // each.  One workgroup with two blocks after another takes longer than the last to arrive with the whole tile (128 rows in 4 splits: 44.1 ->
 // 44.9 us), and two blocks are too little to share out.
-constexpr int kMeetBlocks = 3;
+constexpr int kMeetBlocks = 3, kMaxStreamSplits = 16;   // a word of meet_splits has room for 16
 constexpr bool tile_meets(int epi, int rb, int n_splits) {
   return epi != EPI_HEAD && epi != EPI_SWIGLU && rb >= kMeetBlocks && n_splits >= rb;
 }
@@ -53,7 +53,7 @@ constexpr bool tile_meets(int epi, int rb, int n_splits) {
 // 0.8 us more and 0.002 a split, row block and column: publish the partial tile, count, read all of them.  A tile whose workgroups
 // finish it together (tile_meets) takes 1.2 us, 0.001 a row block and column, 0.0008 a split and column, 0.05 a split and 0.15 of
 // its stream instead (the slowest one's lead).  So wide tiles draw less of the panel and narrow ones meet sooner.  256 workgroups at a time: one a CU, as most tiles fill it (16 and 32 columns
-// over at most 32 rows would fit one to four times, by ring depth).  What it does not know: the ring's depth (launch_one in
+// over at most 32 rows would fit one to four times, by ring depth).  What it does not know: the ring's depth (launch_ring in
 // gemm_stream.hpp), and the epilogues apart (QKV in wide tiles takes 1 to 4 us more than estimated).  Eight and more splits
 // and more than 64 rows cost less than estimated.
 //
@@ -103,7 +103,7 @@ inline SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim,
     if (!stream_built(epi, tn, rb)) continue;
     const int tiles = (n_cols + tn - 1) / tn;
     const double rate = rb == 1 ? 45e3 : 60e3, chip_us = 2.0 * n_cols * k / 6.3e6;
-    for (int sp = 1; sp <= 16 && sp <= steps && (sp == 1 || tiles * groups * sp <= 256); ++sp) {
+    for (int sp = 1; sp <= kMaxStreamSplits && sp <= steps && (sp == 1 || tiles * groups * sp <= 256); ++sp) {
       if (tile_meets(epi, rb, sp) && steps < 8 * sp) continue;   // a step for each of eight wavefronts
       const int rounds = (tiles * groups * sp + 255) / 256;
       const double own_us = rounds * ((steps + sp - 1) / sp) * 32.0 * (2.0 * tn + 64.0 * rb) / rate;
