@@ -1,7 +1,7 @@
 """The reference that the attention's long loops take exponents against, a running maximum per row: contexts whose
 later tiles hold much larger scores than the first for some rows of a wavefront and not for others.  The forms are
-those whose wavefronts share the keys of a tile out (four groups of one row block, four of two, two of four) and the
-256-row workgroups."""
+those whose wavefronts share the keys of a tile out (four groups of one row block, four of two, two of four), also in
+several 64-row workgroups side by side, and the 128-row and 256-row workgroups whose wavefronts see every key."""
 import numpy as np
 import pytest
 
@@ -16,12 +16,15 @@ pytestmark = pytest.mark.gpu
 
 TB = SHAPES["tiny_bf16"].with_(n_layers=1, vocab=600, lm_head_std=0.2)
 MUCH = 8.0   # log2 units
-# name: (nodes, query heads over 2 kv heads, contexts, keys of a tile, key groups, keys of a split of the first sequence)
+# name: (nodes, query heads, kv heads, contexts, rows of a workgroup, keys of a tile, key groups, keys of a split); splits of two
+# tiles and more.  test_attn_plans.py asks the planner for the last four.
 FORMS = {
-    "rows18": (9, 4, (16500, 300), 128, 4, 320),
-    "rows52": (26, 4, (9000, 8001), 128, 4, 256),
-    "rows74": (37, 4, (3001, 130), 128, 2, 256),
-    "rows200": (100, 4, (6200,), 64, 1, 256),
+    "rows18": (9, 4, 2, (16500, 300), 128, 128, 4, 384),
+    "rows52": (26, 4, 2, (9000, 8001), 128, 128, 4, 256),
+    "rows74": (37, 4, 2, (8190, 130), 128, 128, 2, 256),
+    "rows100": (50, 32, 16, (600, 513, 130), 128, 128, 1, 256),
+    "rows200": (100, 4, 2, (6200,), 64, 128, 4, 256),
+    "rows200_kv8": (50, 32, 8, (6200,), 256, 64, 1, 256),
 }
 
 
@@ -48,11 +51,11 @@ def queries(case, b=0, get=None):
 def outgrown(case, form):
     """Over the wavefronts of the first sequence: how many have a row whose largest score in the second tile of a
     split exceeds that of the first by much, beside a row for which it does not."""
-    nodes, heads, ctx, kt, groups, kps = FORMS[form]
-    q, k, d = queries(case), case.k_ctx[0][0], case.shape.head_dim
+    nodes, heads, kv_heads, ctx, _, kt, groups, kps = FORMS[form]
+    q, k, d, per = queries(case), case.k_ctx[0][0], case.shape.head_dim, heads // kv_heads
     found = 0
-    for kvh in range(2):
-        rows = np.concatenate([q[:, kvh * (heads // 2) + al] for al in range(heads // 2)])   # rows in the kernel's order
+    for kvh in range(kv_heads):
+        rows = np.concatenate([q[:, kvh * per + al] for al in range(per)])   # rows in the kernel's order
         s = rows @ k[kvh].T * (np.log2(np.e) / np.sqrt(d))
         for first in range(0, ctx[0] - 2 * kt, kps):
             for kw in range(0, kt, kt // groups):
@@ -72,9 +75,9 @@ GROWTH = {"jumps": (1, 1, 8, 1, 25, 2, 1), "mild": (1, 4, 2, 6, 1, 5, 1)}
 def test_growing_scores(form, growth, head_dim, paged):
     """Bars of test_gpu_parity.py.  The high + low parts of a query (2^-17 of it) put an error of 2^-17 of the scores'
     spread, at most 20 log2 units, on a score: 1e-4 of a probability, and of a logit of up to 4."""
-    nodes, heads, ctx = FORMS[form][:3]
+    nodes, heads, kv_heads, ctx = FORMS[form][:4]
     seed = 1200 + len(form)
-    case = context_case(TB.with_(n_q_heads=heads, head_dim=head_dim), seed, ctx,
+    case = context_case(TB.with_(n_q_heads=heads, n_kv_heads=kv_heads, head_dim=head_dim), seed, ctx,
                         [gen_tree(nodes, 8, 4, seed + b) for b in range(len(ctx))], GROWTH[growth])
     assert growth != "jumps" or outgrown(case, form) > 10
     full_check(case, thresholds=(0.0, 0.5), paged=paged)
@@ -84,12 +87,12 @@ def test_growing_scores(form, growth, head_dim, paged):
 def test_a_node_does_not_depend_on_its_siblings(form):
     """One slot is a key that the query of one child of the root, and no other, is drawn to by 20 log2 units.  That
     child's token changes; every other node's logits stay the same to the last bit."""
-    nodes, heads, ctx = FORMS[form][:3]
+    nodes, heads, kv_heads, ctx = FORMS[form][:4]
     star = np.array([-1] + [0] * (nodes - 1), dtype=np.int32)
-    case = context_case(TB.with_(n_q_heads=heads), 1300, ctx, [star] * len(ctx))
-    d = case.shape.head_dim
-    for kvh in range(2):
-        q = queries(case)[nodes - 1, kvh * (heads // 2)]
+    case = context_case(TB.with_(n_q_heads=heads, n_kv_heads=kv_heads), 1300, ctx, [star] * len(ctx))
+    d, asked = case.shape.head_dim, queries(case)
+    for kvh in range(kv_heads):
+        q = asked[nodes - 1, kvh * (heads // kv_heads)]
         case.k_ctx[0][0, kvh, 200] = q * (20.0 / np.log2(np.e) * np.sqrt(d) / (q @ q))   # in the second tile of a split
     model = device_model(case.shape, case.seed)
     drawn = case.run_gpu(0.0, model=model)["logits"]
@@ -103,8 +106,8 @@ def test_a_node_does_not_depend_on_its_siblings(form):
 def test_large_values_do_not_overflow(form):
     """Cached values of about 1e37: the sums of probability times value stay in the range of fp32 as long as no
     probability exceeds 1."""
-    nodes, heads, ctx = FORMS[form][:3]
-    shape, seed = TB.with_(n_q_heads=heads), 1400 + len(form)
+    nodes, heads, kv_heads, ctx = FORMS[form][:4]
+    shape, seed = TB.with_(n_q_heads=heads, n_kv_heads=kv_heads), 1400 + len(form)
     case = context_case(shape, seed, ctx, [gen_tree(nodes, 8, 4, seed + b) for b in range(len(ctx))],
                         GROWTH["mild"], v_scale=2.0 ** 123)
     ws = WeightSource(shape, seed)

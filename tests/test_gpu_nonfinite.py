@@ -29,14 +29,21 @@ def star(n):
 
 
 # ------------------------------------------------------------------ attention
-# (query heads over 2 kv heads, contexts, tree, spoilt node): k_attn_few over 32 and 64 rows, workgroups of 128
-# and 256 rows with blocks of draft nodes, draft nodes in the merge
+# (query heads, kv heads, contexts, tree, spoilt node), named for the form that the planner gives them
+# (test_attn_plans.py asks it): k_attn_few, or workgroups of 64, 128 and 256 rows with blocks of draft nodes of their
+# own or the draft nodes in the merge
 DRAFTS = {
-    "few64_root": (2, (300,), star(40), 0),
-    "own128_root": (8, (300,), star(40), 0),
-    "own128_inner": (4, (300,), gen_tree(100, 8, 4, 1), 47),
-    "own256_inner": (4, (6200,), gen_tree(100, 8, 4, 1), 47),
-    "in_merge_root": (4, (16380, 300, 0, 77), star(40), 0),
+    "few64_root": (2, 2, (300,), star(40), 0),
+    "own64_root": (8, 2, (300,), star(40), 0),
+    "own64_inner": (4, 2, (300,), gen_tree(100, 8, 4, 1), 47),
+    "own128_root": (16, 8, (600,), star(100), 0),
+    "own128_inner": (16, 8, (600,), gen_tree(100, 8, 4, 1), 47),
+    "own128_shared_keys_root": (2, 1, (300,), star(40), 0),
+    "own256_root": (32, 8, (6200,), star(50), 0),
+    "own256_inner": (16, 8, (6200,), gen_tree(100, 8, 4, 1), 47),
+    "merge64_root": (64, 16, (300, 77), star(40), 0),
+    "merge128_root": (16, 16, (1000, 300, 0, 77), star(40), 0),
+    "merge256_root": (64, 16, (1000, 300, 0, 77), star(40), 0),
 }
 
 
@@ -45,7 +52,7 @@ DRAFTS = {
 def test_a_spoilt_node_reaches_every_descendant(name, paged):
     """The draft nodes are added up in blocks of 32.  A node with a NaN score that is a row's only ancestor in its
     block must not pass for a block without ancestors."""
-    heads, ctx, parents, hit = DRAFTS[name]
+    heads, kv_heads, ctx, parents, hit = DRAFTS[name]
     n = len(parents)
     below = np.zeros(n, dtype=bool)
     alone = []                                   # rows that see nothing else of the spoilt node's block
@@ -58,7 +65,7 @@ def test_a_spoilt_node_reaches_every_descendant(name, paged):
         if below[i] and [j for j in path if j // 32 == hit // 32] == [hit]:
             alone.append(i)
     assert len(alone) > 2
-    case = synthetic_case(TB.with_(n_q_heads=heads), 700 + len(name), ctx, [parents] * len(ctx))
+    case = synthetic_case(TB.with_(n_q_heads=heads, n_kv_heads=kv_heads), 700 + len(name), ctx, [parents] * len(ctx))
     model = device_model(case.shape, case.seed)
     clean = case.run_gpu(0.0, model=model, paged=paged)["logits"].copy()
     bad = case.shape.vocab - 1                   # drafted nowhere else
@@ -73,13 +80,17 @@ def test_a_spoilt_node_reaches_every_descendant(name, paged):
         assert np.abs(got[:, ~below] - clean[:, ~below]).max() <= 2e-3
 
 
-# (query heads, nodes, contexts, first keys that are NaN: whole splits of the context, none in part)
+# (query heads, kv heads, nodes, contexts, first keys that are NaN: whole splits of the context, none in part)
 CONTEXTS = {
-    "few32": (4, 9, (600,), 128),
-    "few64": (4, 25, (600,), 128),
-    "own128": (4, 100, (600,), 256),
-    "own256": (4, 100, (6200,), 256),
-    "in_merge": (4, 40, (16380, 600, 700, 513), 512),
+    "few32": (4, 2, 9, (600,), 128),
+    "few64": (4, 2, 25, (600,), 128),
+    "own64": (4, 2, 100, (600,), 256),
+    "own128": (16, 8, 100, (600,), 128),
+    "own128_shared_keys": (2, 1, 40, (300,), 128),
+    "own256": (32, 8, 50, (6200,), 256),
+    "merge64": (64, 16, 37, (300, 290), 256),
+    "merge128": (16, 16, 40, (1000, 600, 700, 513), 256),
+    "merge256": (64, 16, 37, (1000, 600, 700, 513), 256),
 }
 
 
@@ -87,8 +98,8 @@ CONTEXTS = {
 @pytest.mark.parametrize("name", list(CONTEXTS))
 def test_a_stretch_of_spoilt_context_is_not_skipped(name, paged):
     """Keys that are all NaN over exactly one split of the context must not pass for a split without keys."""
-    heads, nodes, ctx, spoilt = CONTEXTS[name]
-    case = synthetic_case(TB.with_(n_q_heads=heads), 800 + len(name), ctx, [gen_tree(nodes, 8, 4, 3)] * len(ctx))
+    heads, kv_heads, nodes, ctx, spoilt = CONTEXTS[name]
+    case = synthetic_case(TB.with_(n_q_heads=heads, n_kv_heads=kv_heads), 800 + len(name), ctx, [gen_tree(nodes, 8, 4, 3)] * len(ctx))
     for k in case.k_ctx:
         k[:, :, :spoilt] = np.nan
     got = case.run_gpu(0.0, paged=paged)["logits"]

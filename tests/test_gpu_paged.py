@@ -11,7 +11,7 @@ from paper_2601_23180_amd import KVCache, PagedKVCache
 from workloads import SHAPES, gen_chain, gen_context_tokens, gen_draft_tokens, gen_tree, tree_depths
 from gpu_helpers import Case, device_model
 from helpers import oracle_weights
-from test_gpu_parity import LAYER_SHAPE, TB, full_check, make_case
+from test_gpu_parity import LAYER_SHAPE, LONG, TB, full_check, make_case
 
 pytestmark = pytest.mark.gpu
 
@@ -45,10 +45,12 @@ def test_paged_cache_against_the_oracle(name, shape, ctx_lens, tree, mode):
 
 def test_long_contexts_paged():
     """Contexts beyond what the oracle can prefill (N(0,1) caches): 40000 keys (157 pages, 63 key
-    splits), and a two-sequence batch of 240 rows per kv head that takes the 256-row workgroups."""
+    splits), and a two-sequence batch of 240 rows per kv head, in 64-row workgroups over 2 kv heads and in 256-row
+    ones over 8."""
     from workloads import gen_kv_cache
-    for ctx_lens, n_nodes, n_q_heads in (((40000,), 33, 4), ((6500, 300), 60, 8)):
-        shape, seed = TB.with_(n_layers=1, n_q_heads=n_q_heads), 33
+    for name in ("ctx40000", "ctx6500_300_rows240", "ctx6500_300_rows240_kv8"):
+        ctx_lens, n_nodes, n_q_heads, n_kv_heads = LONG[name]
+        shape, seed = TB.with_(n_layers=1, n_q_heads=n_q_heads, n_kv_heads=n_kv_heads), 33
         batch = len(ctx_lens)
         parents = [gen_tree(n_nodes, 8, 4, seed + b) for b in range(batch)]
         k, v = gen_kv_cache(shape, batch, max(ctx_lens), seed, 0)

@@ -482,20 +482,27 @@ def test_pass_replayed_from_a_captured_graph_equals_eager():
         assert np.array_equal(ver.logits.cpu().numpy(), eager["logits"]), rep
 
 
-@pytest.mark.parametrize("ctx_lens,n_nodes,n_q_heads", [
-    ((40000,), 33, 4), ((1000,), 33, 4),
-    ((7000,), 60, 8), ((6144,), 40, 8), ((6500, 300), 60, 8), ((6100,), 60, 8), ((6400,), 128, 8),
-], ids=["ctx40000", "ctx1000", "ctx7000_rows240", "ctx6144_rows160", "ctx6500_300_rows240", "ctx6100_rows240",
-        "ctx6400_nodes128_rows512"])
-def test_long_context_with_synthetic_cache(ctx_lens, n_nodes, n_q_heads):
+# contexts, nodes, query heads, kv heads
+LONG = {
+    "ctx40000": ((40000,), 33, 4, 2), "ctx1000": ((1000,), 33, 4, 2), "ctx7000_rows240": ((7000,), 60, 8, 2),
+    "ctx6144_rows160": ((6144,), 40, 8, 2), "ctx6500_300_rows240": ((6500, 300), 60, 8, 2),
+    "ctx6100_rows240": ((6100,), 60, 8, 2), "ctx6400_nodes128_rows512": ((6400,), 128, 8, 2),
+    "ctx7000_rows240_kv8": ((7000,), 60, 32, 8), "ctx6500_300_rows240_kv8": ((6500, 300), 60, 32, 8),
+    "ctx6400_nodes128_rows512_kv8": ((6400,), 128, 32, 8),
+}
+
+
+@pytest.mark.parametrize("name", list(LONG))
+def test_long_context_with_synthetic_cache(name):
     """Contexts beyond what the oracle can prefill: N(0,1) caches as in the full-size workloads.
     40000 keys: 63 key splits of 640 keys (the merge walks more than one batch of splits, a split
-    ends inside a 128-key tile); 1000 keys: splits shorter than a tile pair.  The cases with more
-    than 128 query rows per kv head and 6144 keys or more take the 256-row workgroups with 64-key
-    tiles (a ragged last tile, a second sequence whose splits are mostly empty); 6100 keys stays
-    just below that switch, on two 128-row groups."""
+    ends inside a 128-key tile); 1000 keys: splits of one tile.  Over 2 kv heads the larger trees take
+    workgroups of 64 rows (512 rows: of 128); over 8, where those would outnumber the CUs, 240 rows take two
+    groups of 128, or of 256 with a second sequence (whose splits are mostly empty), and 512 rows two groups of
+    256 with 64-key tiles, splits of 576 keys (test_attn_plans.py asks the planner)."""
     from workloads import gen_kv_cache
-    shape, seed = TB.with_(n_layers=1, n_q_heads=n_q_heads), 33
+    ctx_lens, n_nodes, n_q_heads, n_kv_heads = LONG[name]
+    shape, seed = TB.with_(n_layers=1, n_q_heads=n_q_heads, n_kv_heads=n_kv_heads), 33
     batch = len(ctx_lens)
     parents = [gen_tree(n_nodes, 8, 4, seed + b) for b in range(batch)]
     k, v = gen_kv_cache(shape, batch, max(ctx_lens), seed, 0)

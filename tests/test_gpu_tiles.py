@@ -120,30 +120,30 @@ def test_adapter_edges(name):
         assert err.max() <= 3e-4, (b, err.max())     # bf16 hi + lo operands, as test_feature_layers_and_adapter
 
 
-# Who evaluates the draft nodes of an attention call, and with how many rows a workgroup:
-# (batch, nodes, query heads over 2 kv heads, contexts)
+# Who evaluates the draft nodes of an attention call, and with how many rows a workgroup (test_attn_plans.py asks the planner):
+# (batch, nodes, query heads, kv heads, contexts)
 ATTN_CASES = {
-    "rows18_own_workgroups": (1, 9, 4, (300,)),
-    "rows64_page_ends": (2, 32, 4, (256, 257)),
-    "rows58_batch": (3, 29, 4, (0, 31, 1500)),
-    "rows4_one_node_long": (1, 1, 8, (9000,)),
-    "rows200_own_workgroups": (1, 100, 4, (300,)),
-    "rows512_chain_blocks": (1, 128, 8, (65,)),
-    "rows128_unequal": (8, 32, 8, (13000, 300, 64, 0, 77, 12999, 500, 9)),
+    "rows18_own_workgroups": (1, 9, 4, 2, (300,)),
+    "rows64_page_ends": (2, 32, 4, 2, (256, 257)),
+    "rows58_batch": (3, 29, 4, 2, (0, 31, 1500)),
+    "rows4_one_node_long": (1, 1, 8, 2, (9000,)),
+    "rows200_own_workgroups": (1, 100, 4, 2, (300,)),
+    "rows512_chain_blocks": (1, 128, 8, 2, (65,)),
+    "rows128_unequal": (8, 32, 8, 2, (13000, 300, 64, 0, 77, 12999, 500, 9)),
     # few rows over many keys: the wavefronts share the keys of a tile out (four, four of eight, two of eight)
-    "rows18_shared_keys": (2, 9, 4, (16500, 300)),
-    "rows52_shared_keys": (2, 26, 4, (9000, 8001)),
-    "rows74_shared_keys": (3, 37, 4, (3001, 0, 130)),
-    # 32 splits of 512 keys fill the chip, paged or not: the draft nodes stay with the merge
-    "rows80_in_merge": (4, 40, 4, (16380, 128, 0, 5000)),
+    "rows18_shared_keys": (2, 9, 4, 2, (16500, 300)),
+    "rows52_shared_keys": (2, 26, 4, 2, (9000, 8001)),
+    "rows74_shared_keys": (3, 37, 4, 2, (3001, 0, 130)),
+    # 4 splits for each of 64 (sequence, kv head) fill the chip: the draft nodes stay with the merge
+    "rows80_in_merge": (4, 40, 32, 16, (1000, 128, 0, 500)),
 }
 
 
 def attn_case(name):
     from gpu_helpers import Case
     from workloads import gen_draft_tokens, gen_kv_cache, tree_depths
-    batch, nodes, heads, ctx = ATTN_CASES[name]
-    shape, seed = TB.with_(n_q_heads=heads, vocab=600), 500 + len(name)
+    batch, nodes, heads, kv_heads, ctx = ATTN_CASES[name]
+    shape, seed = TB.with_(n_q_heads=heads, n_kv_heads=kv_heads, vocab=600), 500 + len(name)
     if nodes == 128:
         parents = [np.arange(-1, nodes - 1, dtype=np.int32)]
     else:
