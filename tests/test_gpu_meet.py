@@ -12,10 +12,12 @@ from test_gpu_parity import full_check, make_case
 pytestmark = pytest.mark.gpu
 
 # batch, nodes, hidden, query heads, kv heads, head_dim, ffn, qk_norm: 3, 4, 6 and 8 row blocks, the last one ragged or without
-# any row; more and fewer splits than blocks; q and k with norms of their own (two groups of 64 rows over more than 64)
+# any row; as many splits as blocks and more; q and k with norms of their own (two groups of 64 rows over more than 64).
+# test_plans.py asks the planner which products meet.
 SIZES = [(1, 33, 1024, 8, 4, 128, 1536, 0), (1, 48, 512, 4, 2, 64, 4096, 1), (1, 60, 2048, 16, 8, 128, 6144, 0),
-         (4, 16, 4096, 8, 8, 128, 4096, 0), (1, 65, 512, 4, 4, 128, 1024, 1), (3, 27, 1472, 12, 4, 64, 4032, 0),
-         (3, 37, 2048, 16, 8, 128, 6144, 1), (2, 64, 1024, 8, 8, 128, 3072, 0)]
+         (4, 16, 4096, 8, 8, 128, 4096, 0), (1, 65, 1792, 3, 3, 128, 1024, 0), (3, 27, 1472, 12, 4, 64, 4032, 0),
+         (3, 37, 2048, 16, 8, 128, 6144, 1), (2, 64, 1024, 8, 8, 128, 3072, 0), (2, 23, 1536, 6, 6, 64, 1024, 0),
+         (5, 21, 2688, 4, 4, 64, 1024, 0)]
 
 
 @pytest.mark.parametrize("size", SIZES, ids=["rows%d_%d" % (s[0] * s[1], s[2]) for s in SIZES])

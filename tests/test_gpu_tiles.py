@@ -71,6 +71,14 @@ WIDTHS = [
     (3, 32, 4160, 1, 1, 64, 64, 1), (3, 33, 64, 32, 4, 128, 6720, 0), (2, 53, 2752, 24, 4, 128, 64, 1),
     (6, 18, 8320, 1, 1, 64, 64, 1), (2, 55, 64, 5, 1, 64, 64, 1), (1, 123, 4160, 1, 1, 64, 64, 0),
     (4, 31, 2688, 7, 1, 128, 64, 0), (1, 125, 64, 1, 1, 64, 18496, 0), (4, 32, 64, 5, 1, 64, 4160, 0),
+    # three row blocks and more: the k splits of a tile finished by one workgroup, and by all of them
+    (5, 12, 384, 1, 1, 64, 64, 0), (2, 31, 576, 1, 1, 64, 64, 1), (1, 83, 576, 1, 1, 64, 64, 1),
+    (1, 41, 640, 1, 1, 64, 64, 1), (4, 26, 704, 1, 1, 64, 64, 1), (3, 13, 640, 1, 1, 128, 64, 1),
+    (1, 108, 3584, 1, 1, 64, 64, 1), (1, 48, 64, 105, 15, 128, 64, 0), (1, 49, 64, 105, 15, 128, 64, 0),
+    (2, 23, 1536, 6, 6, 64, 64, 0), (5, 11, 1280, 8, 8, 64, 64, 0), (1, 73, 1792, 3, 3, 128, 64, 0),
+    (5, 21, 2688, 4, 4, 64, 64, 0), (2, 39, 640, 48, 6, 64, 64, 0), (3, 12, 2816, 21, 3, 64, 64, 0),
+    (1, 60, 4288, 21, 3, 64, 64, 1), (1, 43, 2688, 15, 15, 128, 64, 0), (1, 51, 1472, 45, 15, 128, 64, 0),
+    (1, 45, 1600, 45, 15, 128, 64, 0),
 ]
 CASES += [("widths_rows%d_%d" % (w[0] * w[1], i), w[0], w[1],
            TB.with_(hidden=w[2], n_q_heads=w[3], n_kv_heads=w[4], head_dim=w[5], ffn=w[6], qk_norm=bool(w[7]), vocab=200,
@@ -85,13 +93,23 @@ def test_tile_edges(name, batch, nodes, shape):
 
 
 # The adapter's plain product: (batch, nodes, hidden, adapter width).  Up to 128 rows, the streaming kernel: one split,
-# several, several that need more tile counters than the layers do (one split instead); more rows: one split in 128- and
+# several, finished by one workgroup or by all of a tile, several that need more tile counters than the layers do (one
+# split instead); more rows: one split in 128- and
 # in 256-column tiles, k splits finished by the second launch; widths that end inside a tile.
 ADAPTERS = {
     "rows23_splits": (1, 23, 1472, 132),
     "rows64_no_counters": (1, 64, 1024, 2052),
     "rows100_one_split": (1, 100, 256, 200),
     "rows100_splits_ragged_k": (1, 100, 1472, 132),
+    "rows34_one_split": (1, 34, 64, 132),
+    "rows37_splits": (1, 37, 576, 132),
+    "rows37_meet": (1, 37, 832, 132),
+    "rows57_one_split": (1, 57, 64, 200),
+    "rows60_meet": (1, 60, 1024, 132),
+    "rows75_one_split": (1, 75, 64, 200),
+    "rows68_splits": (1, 68, 448, 132),
+    "rows90_meet": (3, 30, 4928, 132),
+    "rows124_meet": (2, 62, 2368, 132),
     "rows250_splits": (5, 50, 1024, 260),
     "rows130_one_split": (2, 65, 64, 200),
     "rows130_wide_tiles": (2, 65, 64, 16500),

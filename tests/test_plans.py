@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 pytestmark = pytest.mark.skipif(shutil.which(B.HIPCC) is None, reason="no hipcc")
 QKV, RESID, SWIGLU, HEAD, PLAIN = range(5)
 STREAM, HEADK, WIDE = range(3)
-Plan = collections.namedtuple("Plan", "kernel width tiles splits counters floats built")
+Plan = collections.namedtuple("Plan", "kernel width tiles splits counters floats built meets")
 
 
 @pytest.fixture(scope="module")
@@ -117,6 +117,50 @@ def test_the_gpu_cases_reach_every_width(plans):
     assert not want - got, sorted(want - got)
 
 
+def finishes(shapes, got):
+    """(product, width, row blocks of a tile, one split or who finishes the splits) of the streaming kernel."""
+    for s, p in zip(shapes, got):
+        if p.kernel == STREAM and s[0] in (QKV, RESID, PLAIN):
+            groups = p.counters // p.tiles
+            rb = 4 if groups > 1 else rows_laid_out(RESID, p, s[3]) // 16
+            assert p.meets == (rb >= 3 and p.splits >= rb), (s, p)
+            yield s[0], p.width, rb, "together" if p.meets else "one split" if p.splits == 1 else "alone"
+
+
+def meet_cases():
+    """The products of every case of test_gpu_meet.py."""
+    from test_gpu_meet import SIZES
+    from workloads import SHAPES
+    return [layer_products(batch, nodes, SHAPES["tiny_bf16"].with_(hidden=hidden, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=ffn,
+                                                                   qk_norm=bool(norm)))
+            for batch, nodes, hidden, nq, nkv, d, ffn, norm in SIZES]
+
+
+def test_the_gpu_cases_finish_tiles_every_way(plans):
+    """test_gpu_tiles.py and test_gpu_meet.py, tiles of three row blocks and more: in one split, several that one workgroup
+    finishes, several that all of them finish."""
+    from test_gpu_tiles import ADAPTERS, CASES
+    shapes = [p for _, batch, nodes, shape in CASES for p in layer_products(batch, nodes, shape)] + sum(meet_cases(), [])
+    shapes += [(PLAIN, dim, hidden, batch * nodes, 128, 0) for batch, nodes, hidden, dim in ADAPTERS.values()]
+    got = set(finishes(shapes, plans(shapes)))
+    ways = ("one split", "alone", "together")
+    want = {(epi, w, rb, way) for way in ways for rb in (3, 4, 6, 8) for epi, w in ((QKV, 16), (QKV, 32), (QKV, 64), (QKV, 96), (QKV, 128),
+            (RESID, 16), (RESID, 32), (RESID, 64), (PLAIN, 32)) if w < 96 or rb <= 4}
+    # never planned for products of up to 30M weights
+    want -= {(QKV, 64, 8, "one split"), (QKV, 64, 8, "alone"), (RESID, 64, 3, "alone")}
+    assert not want - got, sorted(want - got)
+
+
+def test_the_gpu_cases_that_meet(plans):
+    """test_gpu_meet.py: products of every case are finished by all workgroups of a tile, over every number of row blocks."""
+    seen = set()
+    for shapes in meet_cases():
+        meet = {(f[0], f[2]) for f in finishes(shapes, plans(shapes)) if f[3] == "together"}
+        assert meet, shapes
+        seen |= meet
+    assert seen == {(epi, rb) for epi in (QKV, RESID) for rb in (3, 4, 6, 8)}, sorted(seen)
+
+
 def test_the_gpu_cases_of_the_adapter(plans):
     """What the cases of test_gpu_tiles.py are named for."""
     from test_gpu_tiles import ADAPTERS, TB
@@ -125,6 +169,9 @@ def test_the_gpu_cases_of_the_adapter(plans):
     layers = layer_products(1, 1, TB.with_(hidden=ADAPTERS["rows64_no_counters"][2], ffn=256))
     counters = max(p.counters for rows in (16, 32, 48, 64, 96, 128)
                    for p in plans([(s[0], s[1], s[2], rows, s[4], s[5]) for s in layers]) if p.kernel == STREAM)
+    for name, p in planned.items():
+        if p.kernel == STREAM and name != "rows64_no_counters":
+            assert ("meet" in name) == bool(p.meets) and ("one_split" in name) == (p.splits == 1), (name, p)
     p = planned["rows64_no_counters"]
     assert p.kernel == STREAM and p.splits > 1 and p.tiles > counters
     for name in ("rows23_splits", "rows100_splits_ragged_k"):
