@@ -125,27 +125,18 @@ __device__ __forceinline__ bool publish_then_count(int32_t *counter, int expecte
   return *s_flag != 0;
 }
 
-// The workgroups of a tile share its finish out: one thread of each calls this after its workgroup's partial sums are
-// acknowledged.  Bits 0 - 7 of the word count arrivals, bit 8 + s says that workgroup s has left.  Returns the
-// workgroups whose share the caller takes: its own once all have arrived, and for the last to arrive also those of workgroups that
-// had left by then.  A workgroup without a share, or that has waited for `ticks` of the 100 MHz wall clock, leaves: the
-// others need not be resident, and no share is taken twice or not at all, because arriving and leaving are changes of one word.
-// At most 16 workgroups.  The word is cleared before the next launch that uses it.
-__device__ __forceinline__ uint32_t meet_splits(int32_t *word, int expected, int self, bool share, uint32_t ticks) {
-  const uint32_t before = __hip_atomic_fetch_add(word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if ((int)(before & 255u) == expected - 1) return before >> 8 | 1u << self;
-  if (!share) return 0;
-  const unsigned long long t0 = wall_clock64();
-  for (;;) {
-    uint32_t now = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const bool late = wall_clock64() - t0 >= ticks;
-    if ((int)(now & 255u) != expected && late)
-      now = __hip_atomic_fetch_or(word, (int32_t)(256u << self), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((int)(now & 255u) == expected) return 1u << self;
-    if (late) return 0;
-    __builtin_amdgcn_s_sleep(1);
-  }
-}
+// The word in device memory that the workgroups of a tile meet at (meet_splits); they wait for `ticks` of the 100 MHz wall clock
+struct MeetWord {
+  int32_t *word;
+  uint32_t ticks;
+  unsigned long long t0;
+  __device__ __forceinline__ uint32_t add(int n) { return __hip_atomic_fetch_add(word, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+  __device__ __forceinline__ uint32_t load() { return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+  __device__ __forceinline__ uint32_t set(uint32_t bits) { return __hip_atomic_fetch_or(word, (int32_t)bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+  __device__ __forceinline__ void start_clock() { t0 = wall_clock64(); }
+  __device__ __forceinline__ bool late() const { return wall_clock64() - t0 >= ticks; }
+  __device__ __forceinline__ void nap() const { __builtin_amdgcn_s_sleep(1); }
+};
 
 // Sum over a 64-lane wavefront, fixed butterfly order (deterministic).
 __device__ __forceinline__ float wave_sum(float v) {

@@ -27,6 +27,7 @@
 #pragma once
 
 #include "gemm_tile.hpp"
+#include "meet.hpp"
 #include "plan.hpp"
 
 namespace ts {
@@ -253,7 +254,10 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_stream(GemmArgs a) {
       bepi.apply(g, [&](int lr, int c) { return *(const f32x4 *)(tl + lr * LD + c); }, s_rs, tile, row0 + 16 * m);
     };
     if (split < n_blocks) request(a, split);
-    if (tid == 0) s_last = (int)meet_splits(&a.counters[tl_id * kMeetStride], a.n_splits, split, split < n_blocks, a.meet_ticks);
+    if (tid == 0) {
+      MeetWord word{&a.counters[tl_id * kMeetStride], a.meet_ticks, 0};
+      s_last = (int)meet_splits(word, a.n_splits, split, split < n_blocks);
+    }
     __syncthreads();
     uint32_t take = s_last;
     if (split < n_blocks && (take >> split & 1u)) finish_block(a, split);

@@ -17,13 +17,18 @@ STREAM, HEADK, WIDE = range(3)
 Plan = collections.namedtuple("Plan", "kernel width tiles splits counters floats built meets")
 
 
+def host_program(tmp_path_factory, name):
+    exe = str(tmp_path_factory.mktemp("plans") / name)
+    r = subprocess.run([B.HIPCC, "-O1", *[f for f in B.FLAGS if f != "-O3"], "--cuda-host-only", "-o", exe,
+                        os.path.join(HERE, "plans", name + ".cpp")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return exe
+
+
 @pytest.fixture(scope="module")
 def plans(tmp_path_factory):
     """Plans of a list of (epilogue, columns, k, rows, head_dim, qk_norm)."""
-    exe = str(tmp_path_factory.mktemp("plans") / "plan_report")
-    r = subprocess.run([B.HIPCC, "-O1", *[f for f in B.FLAGS if f != "-O3"], "--cuda-host-only", "-o", exe,
-                        os.path.join(HERE, "plans", "plan_report.cpp")], capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr[-3000:]
+    exe = host_program(tmp_path_factory, "plan_report")
 
     def ask(shapes):
         text = "\n".join(" ".join(str(int(x)) for x in s) for s in shapes)
@@ -159,6 +164,15 @@ def test_the_gpu_cases_that_meet(plans):
         assert meet, shapes
         seen |= meet
     assert seen == {(epi, rb) for epi in (QKV, RESID) for rb in (3, 4, 6, 8)}, sorted(seen)
+
+
+def test_no_share_of_a_tile_is_taken_twice_or_not_at_all(tmp_path_factory):
+    """meet_splits through every order of the steps of two to four workgroups, random ones of up to 16, workgroups leaving
+    early or not: the program ends with a message where a share is not taken exactly once, after all have arrived."""
+    r = subprocess.run([host_program(tmp_path_factory, "meet_orders")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+    orders, departures, takeovers = map(int, r.stdout.split())
+    assert orders > 200000 and departures >= takeovers > 10000
 
 
 def test_the_gpu_cases_of_the_adapter(plans):
