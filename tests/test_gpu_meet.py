@@ -1,6 +1,6 @@
 """The k splits of a tile meet: every workgroup of the tile finishes row blocks of it, or the last to arrive finishes
-those of workgroups that have left.  With a wait of one tick (10 ns) most leave; the sums are added in the same
-order, so that a pass leaves the same bits either way, also when passes of other sizes take turns on its counters."""
+those of workgroups that have left.  With a wait of one tick (10 ns) many leave, as the words that they met at show; the sums
+are added in the same order, so that a pass leaves the same bits either way."""
 import numpy as np
 import pytest
 import torch
@@ -28,14 +28,27 @@ def test_splits_that_leave(size):
     seed = 900 + hidden + nodes
     case = make_case(shape, seed, [20 + 17 * b for b in range(batch)], [gen_tree(nodes, 9, 4, seed + b) for b in range(batch)])
     stay, _, _ = full_check(case, thresholds=(0.5,))
+    ver, kv, pos = stay["_ver"], stay["_kv"], torch.from_numpy(case.positions).cuda()
+
+    def again():
+        """One more pass over the same cache slots: logits, and the workspace as it leaves it."""
+        out = ver.verify(kv, stay["_tok"], case.parents, pos, 0.5)
+        torch.cuda.synchronize()
+        assert out["status"].item() == 0
+        return ver.logits.cpu().numpy(), ver.workspace.view(torch.int32).cpu().numpy()
+    before = again()
     lib = binding.lib()
     try:
         lib.trispec_debug_set_spin_limit(1)
-        leave = case.run_gpu(0.5)
-        torch.cuda.synchronize()
+        leave = again()
     finally:
         lib.trispec_debug_set_spin_limit(0)
-    again = case.run_gpu(0.5)
-    assert leave["status"][0] == 0 and again["status"][0] == 0
-    for other in (leave, again):
-        assert np.array_equal(stay["logits"], other["logits"])
+    after = again()
+    for logits, _ in (before, leave, after):
+        assert np.array_equal(stay["logits"], logits)
+    # nothing in the workspace tells the passes apart but the words of the last launch that met there: as many arrivals (bits
+    # 0 - 7), and a bit for each workgroup that has left
+    changed = before[1] != leave[1]
+    assert np.array_equal(before[1][changed] & 255, leave[1][changed] & 255)
+    departures = [sum(bin(w >> 8).count("1") for w in words[changed].tolist()) for words in (before[1], leave[1])]
+    assert departures[1] > departures[0]
