@@ -238,17 +238,22 @@ struct AttnPlan {
 // 15.2 / 15.1 us for 9 nodes, 17.3 / 23.8 for 30; four sequences of 2048 keys 14.6 / 17.1).
 //
 // Else: workgroups of 64, 128 or 256 rows and a number of key splits, with the smallest estimated time of the context kernel
-// and the merge together.  A context kernel takes a fixed time (launch, queries and first tile, partials out) and a time per key
-// of its split; beyond 256 workgroups, one a CU, that comes again.  256 rows stage a key once for all rows of a tree;
+// and the merge together.  A context kernel takes a fixed time (launch, queries and first tile) and a time per key of its split, 15 % more
+// when every CU has a workgroup, and the partials' way out; beyond 256 workgroups, one a CU, that comes again.  256 rows, and 128 rows
+// that leave no wavefront without a row, have a least time whatever the split.  256 rows stage a key once for all rows of a tree;
 // 64 rows by eight wavefronts that share a tile's keys out are the fastest per row, two wavefronts a SIMD, and leave
 // half the partials of 128 rows, but every row group reads the keys again.  The draft nodes have workgroups of their own
-// where those fit beside the context, else they are the merge's, by the node: 0.24 us for every node that the longest
-// path goes beyond 8 (chains: 60 nodes over 4096 keys, 32 heads, 38.2 + 21.9 us in the merge, with fewer splits and own workgroups 20.2 + 6.0).
-// Fitted to 64-, 128- and 256-row forms in 1 to 32 splits, 57 shapes of 24 to 240 rows, 700 to 16384 keys, one to four sequences, head_dim 64
-// and 128: the chosen one is on average 1.6 % slower than the fastest, at worst 17 %.  Before (256 / (sequences * heads * row groups)
-// splits, rounded up, of 256 keys at least, so that three sequences left a second round of 8 workgroups) -> now, us, context + merge:
-//   120 rows   8192 keys 19.6 + 10.0 -> 19.9 + 7.0, 16384 30.8 + 10.0 -> 28.0 + 7.2, 1024 14.0 + 4.8 -> 12.6 + 4.1, three sequences of 8192 57.0 + 11.3 -> 40.8 + 9.6
-//   240 rows   8192 keys 25.1 + 13.2 -> 28.7 + 7.9, 4096 17.4 + 9.4 -> 19.8 + 8.0, 2048 16.3 + 8.9 -> 16.6 + 4.8
+// where those fit beside the context, else they are the merge's, by the node: 0.18 us for every node that the longest
+// path goes beyond 8.  The merge takes its partials 20 at a time (16 with draft nodes, fewer wavefronts a CU beyond 8 or with 8 heads).
+//
+// Fitted to 451 shapes of 9 to 512 rows, 200 to 16384 keys, one to four sequences, head_dim 64 and 128, groups of 1 to 8, each in about ten
+// divisions.  Of 140 others the chosen division is on average 1.1 % slower than the fastest, at worst 15 % (four sequences of 46 nodes, 744 keys,
+// head_dim 64: 18.6 against 16.1 us); two are 4 and 5 % slower than 128 rows (256 over 6144 keys and more) in 256 workgroups.  With constants from
+// fewer shapes 18 of 140 were, 256 rows over 2048 keys by 4 us a layer.  us, context + merge, 128 or 256 rows in 256 workgroups of 256 keys
+// at least -> now, kv heads 8:
+//   120 rows   8192 keys 19.7 + 9.9 -> 20.6 + 4.8, 16384 31.3 + 9.7 -> 28.9 + 6.4, 1024 13.7 + 4.5 -> 10.7 + 4.2, three sequences of 8192 61.7 + 12.0 -> 40.2 + 8.4
+//   240 rows   8192 keys 26.8 + 13.7 -> 27.9 + 7.3, 4096 17.5 + 9.7 -> 18.7 + 7.3, 2048 15.2 + 5.2 -> 14.6 + 5.1, a chain over 4096 17.4 + 18.2 -> 19.5 + 5.7
+//   256 rows   2048 keys 15.4 + 5.4 -> 15.4 + 5.4;   four sequences of 240 rows   16384 keys 125 + 21.7 -> 122 + 17.8
 inline AttnPlan plan_attn(int batch, int n_kv, int group, int head_dim, int n_nodes, int depth, int max_keys, bool paged) {
   const int p_rows = group * n_nodes, n_draft = (n_nodes + 31) / 32;
   AttnPlan best;
@@ -272,12 +277,16 @@ inline AttnPlan plan_attn(int batch, int n_kv, int group, int head_dim, int n_no
     return best;
   }
   best.few = false;
+  const bool narrow = head_dim < 128;
+  const double rows_k = p_rows * batch * n_kv * 1e-3;
   double best_us = 1e30;
   for (int rows = 64; rows <= 256; rows *= 2) {
     if ((rows == 64 && p_rows <= 64) || (rows == 256 && p_rows <= 128)) continue;   // 128 rows with at most 64 are the 64-row form
     const int groups = (p_rows + rows - 1) / rows, per_split = batch * n_kv * groups;
-    const double fixed = (rows == 256 ? 13.5 : (rows == 64 ? 9.3 : 8.9)) * (head_dim < 128 ? 0.67 : 1.0);
-    const double per_key = (rows == 256 || (rows == 128 && p_rows > 96) ? 0.033 : (rows == 128 && p_rows > 64 ? 0.021 : 0.018)) * (head_dim < 128 ? 0.58 : 1.0);
+    const bool all_rows = rows == 128 && p_rows > 96;   // every wavefront of a 128-row workgroup has rows
+    const double fixed = rows == 256 ? 8.1 : (rows == 64 ? 8.05 : (all_rows ? 5.3 : 6.45));
+    const double per_key = rows == 256 ? 0.0367 : (rows == 64 ? 0.0148 : (all_rows ? 0.03 : (p_rows > 64 ? 0.0236 : 0.0174)));
+    const double least = rows == 256 ? 21.0 : (all_rows ? 12.6 : 0.0);
     // every split starts at a multiple of the kernel's key tile, in a paged cache of the largest
     const int unit = rows == 256 && !paged ? 64 : 128;
     for (int s = 1; s <= kMaxAttnSplits; ++s) {
@@ -286,9 +295,17 @@ inline AttnPlan plan_attn(int batch, int n_kv, int group, int head_dim, int n_no
       const int n = max_keys > kps ? (max_keys + kps - 1) / kps : 1;
       if (n != s) continue;
       const bool own = (n + n_draft) * per_split <= 256;
-      const int rounds = (n * per_split + 255) / 256;
-      const double mb = (double)(n + (own ? n_draft : 0)) * p_rows * batch * n_kv * (head_dim + 2) * 4e-6;   // partials
-      const double us = fixed + per_key * kps * rounds + (own ? 3.0 + 0.30 * mb : 7.0 + 0.36 * mb + 0.24 * (depth > 8 ? depth - 8 : 0));
+      const int parts = n + (own ? n_draft : 0), rounds = (n * per_split + 255) / 256;
+      const double side_by_side = (double)n * per_split / rounds + (own ? n_draft * per_split : 0);
+      const double crowd = side_by_side < 128 ? 0.0 : (side_by_side < 256 ? side_by_side / 128 - 1 : 1.0);
+      const double mb = rows_k * (head_dim + 2) * 4e-3;   // of one split's partials
+      double us = fixed + per_key * kps * (1 + 0.15 * crowd);
+      us = rounds * (us > least ? us : least) * (!narrow ? 1.0 : (rows == 256 || all_rows ? 0.73 : 0.675)) + 0.115 * mb * n;
+      if (own)
+        us += 3.3 + 0.235 * rows_k + 0.128 * mb * parts + 2.5 * ((parts - 1) / 20);
+      else
+        us += 4.2 + (narrow ? 0.5 : 1.0) * rows_k * (1 + (n > 8 ? 0.9 : 0.0) + (group == 8 ? 0.9 : 0.0)) + 0.043 * mb * n +
+              3.8 * ((n - 1) / 16) + 0.18 * (depth > 8 ? depth - 8 : 0);
       if (us < best_us) {
         best_us = us;
         best.rows_per_wg = rows;

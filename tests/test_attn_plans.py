@@ -75,11 +75,28 @@ def form(p):
     return "%s%d" % ("few" if p.few else "merge" if p.mode == IN_MERGE else "own", p.rows)
 
 
+def test_the_form_chosen_is_about_the_fastest_measured(plans):
+    """tests/plans/attn_measured.txt: 151 shapes in up to 22 forms each.  Medians of the same form differ by up to 3 % from run to run."""
+    with open(os.path.join(HERE, "plans", "attn_measured.txt")) as f:
+        lines = [line.split("|") for line in f if not line.startswith("#")]
+    shapes = [tuple(map(int, a.split())) + (0,) for a, _ in lines]
+    over = []
+    for s, p, (_, forms) in zip(shapes, plans(shapes), lines):
+        us, before = {}, None
+        for name, t in zip(*[iter(forms.split())] * 2):
+            us[name.rstrip("*")] = sum(map(float, t.split("+")))
+            before = us[name.rstrip("*")] if name.endswith("*") else before
+        mine = us["%dx%d" % (p.rows, p.splits)]   # a form that is not in the file has to be measured first
+        over.append(mine / min(us.values()) - 1)
+        assert over[-1] < 0.08 and (before is None or mine < 1.03 * before), (s, p, us)
+    assert np.mean(over) < 0.006, np.mean(over)
+
+
 def test_the_gpu_cases_reach_every_form(plans):
     seen = set()
     for name, (shape, batch, nodes, ctx, kind) in FORMS.items():
         for p in ask_both(plans, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, [parents_of(kind, nodes, b) for b in range(batch)], ctx):
-            assert not p.few, (name, p)
+            assert form(p) == name.split("_")[0], (name, p)
             seen.add((p.rows, key_groups(p, shape.n_q_heads // shape.n_kv_heads * nodes), p.mode, shape.head_dim))
     for rows_groups in ((64, 4), (128, 1), (128, 2), (256, 1)):
         for mode in (IN_MERGE, OWN):
@@ -127,15 +144,15 @@ def test_the_cases_of_long_contexts_and_draft_blocks(plans):
     from workloads import gen_tree
     got = {n: ask_both(plans, heads, kv, 128, [gen_tree(nodes, 8, 4, 33 + b) for b in range(len(ctx))], ctx)
            for n, (ctx, nodes, heads, kv) in LONG.items()}
-    assert got["ctx40000"][0][3:5] == (640, 63) and got["ctx1000"][0].keys == 128
+    assert got["ctx40000"][0][3:5] == (768, 53) and got["ctx1000"][0].keys == 128
     for name, p in got.items():
-        rows = [64 if "rows" in name else 128] * 2
+        rows = [128 if name == "ctx1000" else 64] * 2
         if "kv8" in name:
             rows = [128 if name == "ctx7000_rows240_kv8" else 256] * 2
         elif "rows512" in name:
             rows = [128, 128]
         assert [p[0].rows, p[1].rows] == rows, (name, p)
-    assert got["ctx6400_nodes128_rows512_kv8"][0].keys == 576
+    assert got["ctx6400_nodes128_rows512_kv8"][0].keys == 448
     for name, (batch, nodes, heads, kv, ctx) in ATTN_CASES.items():
         tree = np.arange(-1, nodes - 1) if nodes == 128 else gen_tree(nodes, 8, 4, 500 + len(name)) if nodes > 1 else np.array([-1])
         for p in ask_both(plans, heads, kv, 128, [tree], ctx):

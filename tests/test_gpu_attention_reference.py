@@ -19,12 +19,12 @@ MUCH = 8.0   # log2 units
 # name: (nodes, query heads, kv heads, contexts, rows of a workgroup, keys of a tile, key groups, keys of a split); splits of two
 # tiles and more.  test_attn_plans.py asks the planner for the last four.
 FORMS = {
-    "rows18": (9, 4, 2, (16500, 300), 128, 128, 4, 384),
+    "rows18": (9, 4, 2, (16500, 300), 128, 128, 4, 512),
     "rows52": (26, 4, 2, (9000, 8001), 128, 128, 4, 256),
-    "rows74": (37, 4, 2, (8190, 130), 128, 128, 2, 256),
+    "rows74": (37, 16, 8, (2050, 130), 128, 128, 2, 256),
     "rows100": (50, 32, 16, (600, 513, 130), 128, 128, 1, 256),
-    "rows200": (100, 4, 2, (6200,), 64, 128, 4, 256),
-    "rows200_kv8": (50, 32, 8, (6200,), 256, 64, 1, 256),
+    "rows100_kv2": (50, 4, 2, (3001,), 64, 128, 4, 256),
+    "rows200": (50, 64, 16, (1000, 600, 130), 256, 64, 1, 384),
 }
 
 

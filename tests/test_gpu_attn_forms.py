@@ -11,23 +11,23 @@ W8 = TB.with_(n_q_heads=16, n_kv_heads=8)                 # 2 query heads to eac
 W16 = TB.with_(n_q_heads=32, n_kv_heads=16)
 G4 = TB.with_(n_q_heads=8, n_kv_heads=2)
 D64 = TB.with_(n_q_heads=24, n_kv_heads=8, head_dim=64)   # groups of 3
-# (model, sequences, nodes, contexts, tree or chain)
+# (model, sequences, nodes, contexts, tree or chain), named for who evaluates the draft nodes and the rows of a workgroup
 FORMS = {
-    "rows64_in_merge": (W8, 1, 60, (8100,), "tree"),
-    "rows64_three_sequences": (W8, 3, 51, (4100, 77, 0), "tree"),
-    "rows64_own": (W8, 1, 51, (1030,), "tree"),
-    "rows128_own": (W8, 3, 60, (2050, 20, 700), "tree"),
-    "rows120_chain": (W8, 1, 60, (4001,), "chain"),
-    "rows128_in_merge": (W16, 3, 60, (2050, 700, 131), "tree"),
-    "rows96_own": (W8, 1, 37, (3001,), "chain"),
-    "rows96_in_merge": (W16, 4, 40, (4100, 3, 640, 1499), "tree"),
-    "rows240_in_merge": (W16.with_(n_q_heads=64), 2, 60, (2050, 1000), "tree"),
-    "rows240_own": (W8.with_(n_q_heads=32), 1, 60, (2050,), "chain"),
-    "rows256_chain_own": (G4, 2, 128, (9001, 300), "chain"),
-    "d64_rows160_in_merge": (W16.with_(n_q_heads=64, head_dim=64), 3, 40, (2050, 128, 0), "tree"),
-    "d64_rows69": (D64, 1, 23, (6001,), "tree"),
-    "d64_rows180": (D64, 1, 60, (5003,), "tree"),
-    "rows200_ragged": (G4, 1, 50, (8190,), "tree"),
+    "own64_rows120": (W8, 1, 60, (8100,), "tree"),
+    "merge64_three_sequences": (W8, 3, 51, (4100, 77, 0), "tree"),
+    "own64_rows102": (W8, 1, 51, (1030,), "tree"),
+    "own128_three_sequences": (W8, 3, 60, (2050, 20, 700), "tree"),
+    "own128_rows120_chain": (W8, 1, 60, (4001,), "chain"),
+    "merge128_rows120": (W16, 3, 60, (2050, 700, 131), "tree"),
+    "own64_rows74_chain": (W8, 1, 37, (3001,), "chain"),
+    "merge128_rows80": (W16, 4, 40, (4100, 3, 640, 1499), "tree"),
+    "own256_rows240": (W16.with_(n_q_heads=64), 2, 60, (2050, 1000), "tree"),
+    "own128_rows240_chain": (W8.with_(n_q_heads=32), 1, 60, (2050,), "chain"),
+    "own256_rows512_chain": (G4, 2, 128, (9001, 300), "chain"),
+    "merge256_d64_rows160": (W16.with_(n_q_heads=64, head_dim=64), 3, 40, (2050, 128, 0), "tree"),
+    "own128_d64_rows69": (D64, 1, 23, (6001,), "tree"),
+    "own64_d64_rows180": (D64, 1, 60, (5003,), "tree"),
+    "own64_rows200": (G4, 1, 50, (8190,), "tree"),
 }
 
 

@@ -36,12 +36,12 @@ DRAFTS = {
     "few64_root": (2, 2, (300,), star(40), 0),
     "own64_root": (8, 2, (300,), star(40), 0),
     "own64_inner": (4, 2, (300,), gen_tree(100, 8, 4, 1), 47),
-    "own128_root": (16, 8, (600,), star(100), 0),
-    "own128_inner": (16, 8, (600,), gen_tree(100, 8, 4, 1), 47),
+    "own128_root": (16, 8, (2050,), star(100), 0),
+    "own128_inner": (16, 8, (2050,), gen_tree(100, 8, 4, 1), 47),
     "own128_shared_keys_root": (2, 1, (300,), star(40), 0),
-    "own256_root": (32, 8, (6200,), star(50), 0),
-    "own256_inner": (16, 8, (6200,), gen_tree(100, 8, 4, 1), 47),
-    "merge64_root": (64, 16, (300, 77), star(40), 0),
+    "own256_root": (64, 16, (1000, 300, 0), star(50), 0),
+    "own256_inner": (32, 16, (4100,), gen_tree(100, 8, 4, 1), 47),
+    "merge64_root": (16, 8, (600,), star(100), 0),
     "merge128_root": (16, 16, (1000, 300, 0, 77), star(40), 0),
     "merge256_root": (64, 16, (1000, 300, 0, 77), star(40), 0),
 }
@@ -85,10 +85,10 @@ CONTEXTS = {
     "few32": (4, 2, 9, (600,), 128),
     "few64": (4, 2, 25, (600,), 128),
     "own64": (4, 2, 100, (600,), 256),
-    "own128": (16, 8, 100, (600,), 128),
+    "own128": (16, 8, 100, (2050,), 256),
     "own128_shared_keys": (2, 1, 40, (300,), 128),
-    "own256": (32, 8, 50, (6200,), 256),
-    "merge64": (64, 16, 37, (300, 290), 256),
+    "own256": (64, 16, 50, (1000, 600, 513), 384),
+    "merge64": (16, 8, 100, (600,), 128),
     "merge128": (16, 16, 40, (1000, 600, 700, 513), 256),
     "merge256": (64, 16, 37, (1000, 600, 700, 513), 256),
 }

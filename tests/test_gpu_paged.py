@@ -44,7 +44,7 @@ def test_paged_cache_against_the_oracle(name, shape, ctx_lens, tree, mode):
 
 
 def test_long_contexts_paged():
-    """Contexts beyond what the oracle can prefill (N(0,1) caches): 40000 keys (157 pages, 63 key
+    """Contexts beyond what the oracle can prefill (N(0,1) caches): 40000 keys (157 pages, 53 key
     splits), and a two-sequence batch of 240 rows per kv head, in 64-row workgroups over 2 kv heads and in 256-row
     ones over 8."""
     from workloads import gen_kv_cache

@@ -495,11 +495,11 @@ LONG = {
 @pytest.mark.parametrize("name", list(LONG))
 def test_long_context_with_synthetic_cache(name):
     """Contexts beyond what the oracle can prefill: N(0,1) caches as in the full-size workloads.
-    40000 keys: 63 key splits of 640 keys (the merge walks more than one batch of splits, a split
+    40000 keys: 53 key splits of 768 keys (the merge walks more than one batch of splits, a split
     ends inside a 128-key tile); 1000 keys: splits of one tile.  Over 2 kv heads the larger trees take
     workgroups of 64 rows (512 rows: of 128); over 8, where those would outnumber the CUs, 240 rows take two
-    groups of 128, or of 256 with a second sequence (whose splits are mostly empty), and 512 rows two groups of
-    256 with 64-key tiles, splits of 576 keys (test_attn_plans.py asks the planner)."""
+    groups of 128, or one of 256 with a second sequence (whose splits are mostly empty), and 512 rows two groups of
+    256 with 64-key tiles, splits of 448 keys (test_attn_plans.py asks the planner)."""
     from workloads import gen_kv_cache
     ctx_lens, n_nodes, n_q_heads, n_kv_heads = LONG[name]
     shape, seed = TB.with_(n_layers=1, n_q_heads=n_q_heads, n_kv_heads=n_kv_heads), 33

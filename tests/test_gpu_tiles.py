@@ -151,7 +151,7 @@ ATTN_CASES = {
     # few rows over many keys: the wavefronts share the keys of a tile out (four, four of eight, two of eight)
     "rows18_shared_keys": (2, 9, 4, 2, (16500, 300)),
     "rows52_shared_keys": (2, 26, 4, 2, (9000, 8001)),
-    "rows74_shared_keys": (3, 37, 4, 2, (3001, 0, 130)),
+    "rows74_shared_keys": (2, 37, 16, 8, (2050, 130)),
     # 4 splits for each of 64 (sequence, kv head) fill the chip: the draft nodes stay with the merge
     "rows80_in_merge": (4, 40, 32, 16, (1000, 128, 0, 500)),
 }
