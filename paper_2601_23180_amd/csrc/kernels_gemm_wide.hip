@@ -28,16 +28,11 @@
 // megabyte: one workgroup reading them serially after the last arrival, as the narrow kernels do,
 // took 15 - 20 us of a 77 us projection.
 #include "gemm_tile.hpp"
+#include "plan.hpp"
 
 namespace ts {
 
-namespace {
-
-constexpr int kWideRows = 128;      // rows per workgroup
-
-}  // namespace
-
-template <int WR, int WC, int MBW, int NBW, int EPI>
+template <int WR, int WC, int MBW, int NBW, int EPI, bool APART>
 __global__ __launch_bounds__(WR * WC * 64) void k_gemm_wide(GemmArgs a) {
   static_assert(WR * MBW * 32 == kWideRows, "the wavefronts cover 128 rows");
   constexpr int NW = WR * WC, NT = NW * 64;
@@ -55,12 +50,20 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_wide(GemmArgs a) {
   const int wr = wave / WC, wc = wave - wr * WC;
   const int ln = lane & 31, g = lane >> 5;
   // Workgroups go round-robin over the 8 XCDs: ids 8 apart are the row groups of one (tile, split), whose weights then
-  // come through one L2 at about the same time.  Row group by row group the LM head, two rounds of workgroups and more, read them
-  // from HBM twice (128256 x 4096, 240 rows: 574 -> 539 us; products of one round are even).
-  const int n_tiles = (a.n_total + TN - 1) / TN, n_rg = (a.rows + kWideRows - 1) / kWideRows;
-  const int item = (int)(blockIdx.x >> 3) / n_rg * 8 + (blockIdx.x & 7), rg = (int)(blockIdx.x >> 3) % n_rg;
-  if (item >= n_tiles * a.n_splits) return;   // the last 8 are filled up
-  const int split = item / n_tiles, tile = item - split * n_tiles;
+  // come through one L2 at about the same time (LM head 128256 x 4096 over 240 rows 617 -> 546 us against one group after the other, 594
+  // with the hint below; 128-column tiles, one round of workgroups: passes of 81 models of eight layers 1.4 % shorter on average, from 3.6 %
+  // shorter to 0.4 % longer).  APART: one row group after the other (wide_apart in plan.hpp).
+  int tile, rg, split;
+  if constexpr (APART) {
+    tile = blockIdx.x; rg = blockIdx.y; split = blockIdx.z;
+  } else {
+    const int n_tiles = (a.n_total + TN - 1) / TN, n_rg = (a.rows + kWideRows - 1) / kWideRows;
+    const int item = (int)(blockIdx.x >> 3) / n_rg * 8 + (blockIdx.x & 7);
+    if (item >= n_tiles * a.n_splits) return;   // the last 8 are filled up
+    rg = (int)(blockIdx.x >> 3) % n_rg;
+    split = item / n_tiles;
+    tile = item - split * n_tiles;
+  }
   const int mbt = a.rows_pad >> 5;
   const int kb_total = a.k >> 6;
   const int b0 = kb_total * split / a.n_splits, n = kb_total * (split + 1) / a.n_splits - b0;   // 64-deep blocks
@@ -112,7 +115,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_wide(GemmArgs a) {
   auto store_x1 = [&](int i, int buf) { *(u32x4 *)(lds + buf * BUF + (wave * XV + i) * 1024 + lane * 16) = xr[i]; };
   auto load_w1 = [&](int set, int t, int i, int c) {
     const bf16x8 *p = (const bf16x8 *)((const char *)(wp[i] + (size_t)c * 2048 + 512 * t) + lane_off);
-    w[set][t][i] = *p;   // no non-temporal hint: other wavefronts or the other row group read it too
+    w[set][t][i] = APART ? __builtin_nontemporal_load(p) : *p;   // no hint where other wavefronts or the other row group read it too
   };
   auto read_x1 = [&](int slot, int t, int buf, int m) {
     xf[slot][m] = *(const bf16x8 *)(lds + buf * BUF + (t * MB * 2 + wr * MBW * 2 + m) * 1024 + lane * 16);
@@ -280,11 +283,15 @@ __global__ __launch_bounds__(256) void k_gemm_finish(GemmArgs a) {
 template <int EPI>
 static void dispatch_wide(hipStream_t st, const GemmArgs &a) {
   const int n_rg = (a.rows + kWideRows - 1) / kWideRows, wide = EPI == EPI_HEAD || a.tile_n == 256;   // the LM head always
-  const dim3 grid(((a.n_total + (wide ? 255 : 127)) / (wide ? 256 : 128) * a.n_splits + 7) / 8 * 8 * n_rg);
-  if (wide) {
-    hipLaunchKernelGGL((k_gemm_wide<1, 4, 4, 2, EPI>), grid, dim3(256), 0, st, a);
-  } else if constexpr (EPI != EPI_HEAD) {
-    hipLaunchKernelGGL((k_gemm_wide<2, 4, 2, 1, EPI>), grid, dim3(512), 0, st, a);
+  const int n_tiles = (a.n_total + (wide ? 255 : 127)) / (wide ? 256 : 128);
+  const dim3 grid((n_tiles * a.n_splits + 7) / 8 * 8 * n_rg);
+  if constexpr (EPI == EPI_HEAD) {
+    if (wide_apart(a.n_total, a.k, a.rows)) hipLaunchKernelGGL((k_gemm_wide<1, 4, 4, 2, EPI, true>), dim3(n_tiles, n_rg), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_gemm_wide<1, 4, 4, 2, EPI, false>), grid, dim3(256), 0, st, a);
+  } else if (wide) {
+    hipLaunchKernelGGL((k_gemm_wide<1, 4, 4, 2, EPI, false>), grid, dim3(256), 0, st, a);
+  } else {
+    hipLaunchKernelGGL((k_gemm_wide<2, 4, 2, 1, EPI, false>), grid, dim3(512), 0, st, a);
   }
   if constexpr (EPI != EPI_HEAD) {
     if (a.n_splits > 1)

@@ -158,6 +158,7 @@ inline SplitPlan plan_head(int n_cols, int k, int rows, int rows_pad) {
 // entries per row of the sums of squares that a matmul with tiles of tile_n columns leaves
 inline int ss_tiles_of(int n, int tile_n) { return tile_n < kGemmTileN ? (n + tile_n - 1) / tile_n : tiles_of(n); }
 
+constexpr int kWideRows = 128;   // rows of a workgroup of kernels_gemm_wide.hip
 // Decomposition of one matmul over a panel of 256 rows, LM head also 128 (kernels_gemm_wide.hip): the tile width
 // and the number of k splits with the smallest estimated time.  Fitted to products of 1024 to 4096 wide models: a 64-deep
 // chunk takes a workgroup 1.65 us on a 128 x 256 tile and 1.0 us on a 128 x 128 tile, a workgroup about 6 us beside its
@@ -165,7 +166,7 @@ inline int ss_tiles_of(int n, int tile_n) { return tile_n < kGemmTileN ? (n + ti
 // partial tiles, written and read back at about 6.5 TB/s.  Estimated / measured, us, 240 rows: 6144 x 1024 in one split 22.0 / 21.7,
 // two 19.4 / 18.8; 2048 x 6144 in four 34.1 / 33.6, eight 24.7 / 25.0; 4096 x 14336 (256 columns) in eight 64.0 / 65.2.
 inline SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_part_floats) {
-  const int kb = k / 64, n_rg = rows_pad / 128;
+  const int kb = k / 64, n_rg = rows_pad / kWideRows;
   SplitPlan best;
   best.kernel = GEMM_WIDE;
   best.tile_n = 256;
@@ -191,6 +192,17 @@ inline SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_
     }
   }
   return best;
+}
+// LM head of the wide kernel: one row group after the other, weights with the non-temporal hint, instead of the row groups of a tile
+// side by side?  Where one group is all there is.  And where the workgroups are more than one round and the last group is short: behind
+// full groups its workgroups, with a few rows to write out, fill the last round, which side by side is as long as the first.  us a pass of one
+// layer, side by side -> apart: 132 rows, 36608 columns x 704 167.9 -> 129.3, x 4096 333.6 -> 288.8, 102400 x 4096 587 -> 544; 192 rows 175 -> 152, 347 ->
+// 318, 603 -> 582; 208 rows, 36608 x 704 177 -> 167, x 4096 350 -> 334.  But then the weights come from memory again, once they are
+// past the memory-side cache: 208 rows, 151936 x 2560 565 -> 581, 192 rows, 151936 x 4096 739 -> 756; 240 rows gain nothing.
+constexpr bool wide_apart(int n_cols, int k, int rows) {
+  const int groups = (rows + kWideRows - 1) / kWideRows, last = rows - (groups - 1) * kWideRows;
+  const double mb = 2e-6 * n_cols * k;
+  return groups == 1 || ((n_cols + 255) / 256 * groups > 256 && mb <= 850 && last <= (mb <= 320 ? 96 : 64));
 }
 constexpr size_t kWidePartFloats = (size_t)12 << 20;   // partial tiles of one wide matmul: at most 48 MB
 

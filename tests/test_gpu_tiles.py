@@ -46,6 +46,10 @@ CASES = [
     ("rows256_splits", 4, 64, TB.with_(hidden=1024, ffn=1472, n_q_heads=8, vocab=1024, lm_head_std=0.2)),
     ("rows250_many_splits_qk_norm", 5, 50, TB.with_(hidden=256, ffn=4096, qk_norm=True, lm_head_std=0.4)),
     ("rows129_odd_chunks", 3, 43, TB.with_(hidden=320, ffn=448, lm_head_std=0.4)),
+    # LM head in more than one round of workgroups: row groups one after the other (a last one of 1 and of 96 rows), and side by side
+    ("rows129_vocab_apart", 3, 43, TB.with_(hidden=192, ffn=64, vocab=33001, lm_head_std=0.5)),
+    ("rows224_vocab_apart", 4, 56, TB.with_(hidden=64, ffn=64, vocab=32769, lm_head_std=0.8)),
+    ("rows225_vocab_side_by_side", 5, 45, TB.with_(hidden=64, ffn=64, vocab=33001, lm_head_std=0.8)),
 ]
 
 

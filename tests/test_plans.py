@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 pytestmark = pytest.mark.skipif(shutil.which(B.HIPCC) is None, reason="no hipcc")
 QKV, RESID, SWIGLU, HEAD, PLAIN = range(5)
 STREAM, HEADK, WIDE = range(3)
-Plan = collections.namedtuple("Plan", "kernel width tiles splits counters floats built meets")
+Plan = collections.namedtuple("Plan", "kernel width tiles splits counters floats built meets apart")
 
 
 def host_program(tmp_path_factory, name):
@@ -194,3 +194,16 @@ def test_the_gpu_cases_of_the_adapter(plans):
     assert planned["rows250_splits"].kernel == WIDE and planned["rows250_splits"].splits > 1
     assert planned["rows130_one_split"][:2] == (WIDE, 128) and planned["rows130_one_split"].splits == 1
     assert planned["rows130_wide_tiles"][:2] == (WIDE, 256) and planned["rows130_wide_tiles"].splits == 1
+
+
+def test_row_groups_of_the_head(plans):
+    """One after the other where one is all there is, or where a short last one fills the last of several rounds of workgroups and the
+    weights are no more than the memory-side cache serves twice; the cases of test_gpu_tiles.py."""
+    from test_gpu_tiles import CASES
+    named = {c[0]: c for c in CASES if c[0].endswith(("vocab_apart", "vocab_side_by_side"))}
+    shapes = [(HEAD, c[3].vocab, c[3].hidden, c[1] * c[2], 128, 0) for c in named.values()]
+    shapes += [(HEAD, 50257, 1472, 96, 128, 0), (HEAD, 32768, 4096, 132, 128, 0), (HEAD, 102400, 4096, 192, 128, 0),
+               (HEAD, 102400, 4096, 193, 128, 0), (HEAD, 128256, 4096, 132, 128, 0), (HEAD, 36608, 704, 225, 128, 0)]
+    got = plans(shapes)
+    assert len(named) == 3 and all(p.kernel == WIDE for p in got)
+    assert [p.apart for p in got] == [n.endswith("apart") for n in named] + [1, 0, 1, 0, 0, 0]
