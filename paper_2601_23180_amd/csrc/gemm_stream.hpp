@@ -23,7 +23,7 @@
 // 2048 x 2048 16.3 -> 12.3, 12288 x 2048 29.4 -> 25.4, 2048 x 6144 22.2 -> 19.9.
 //
 // The accumulators are added up in fragment order (16-byte LDS accesses); partial tiles go to memory in the
-// same order, so that the last workgroup to arrive adds its splits lane by lane and only the sum is turned into rows.
+// same order, so that whoever finishes a tile or a row block of it adds the splits lane by lane and only the sum is turned into rows.
 #pragma once
 
 #include "gemm_tile.hpp"

@@ -163,7 +163,7 @@ __global__ void k_qkv_epilogue_f32(GemmArgs a, const float *qkv) {
   const int d = a.head_dim, half = d >> 1, n_q = a.n_q_heads, n_kv = a.n_kv_heads;
   const size_t off = (size_t)r * a.n_total + (size_t)hh * d + j;
   float lo = qkv[off], hi = qkv[off + half];
-  if (a.q_norm_w != nullptr && hh < n_q + n_kv) {   // RMSNorm over the head (uniform branch)
+  if (hh < n_q + n_kv) {   // RMSNorm over the head (uniform branch)
     s_sq[j] = lo * lo + hi * hi;
     __syncthreads();
     float ss = 0.f;

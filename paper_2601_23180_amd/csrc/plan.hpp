@@ -38,7 +38,7 @@ constexpr bool stream_built(int epi, int tile_n, int rb) {
 
 // Tiles of three row blocks and more, in as many splits at least: the workgroups of a tile finish it together, a block of 16 rows
 // each.  One workgroup with two blocks after another takes longer than the last to arrive with the whole tile (128 rows in 4 splits: 44.1 ->
-// 44.9 us), and two blocks are too little to share out.
+// 44.9 us).  Tiles of two blocks, and two blocks by one workgroup in one round trip, have not been measured.
 constexpr int kMeetBlocks = 3, kMaxStreamSplits = 16;   // a word of meet_splits has room for 16
 constexpr bool tile_meets(int epi, int rb, int n_splits) {
   return epi != EPI_HEAD && epi != EPI_SWIGLU && rb >= kMeetBlocks && n_splits >= rb;
@@ -78,7 +78,7 @@ constexpr bool tile_meets(int epi, int rb, int n_splits) {
 // Over few rows:
 //   1024 x 2048, 9 rows     16 x 4* 5.2 / 6.4   32 x 4 5.9 / 6.6   16 x 2 6.2 / 6.6   32 x 2 7.2 / 7.3   16 x 1 7.6 / 6.5
 //   1024 x 3072, 9 rows     16 x 4* 5.8 / 6.8   32 x 4 6.6 / 7.4   16 x 2 7.3 / 7.4   32 x 2 8.7 / 8.4   16 x 1 9.7 / 8.2
-// Of the tilings measured the chosen one is the fastest or within 5 % of it.
+// Of the tilings measured the chosen one is the fastest or within 5 % of it, but for QKV 6144 x 4096 over 60 rows: 7 %, as the epilogue has no term.
 inline SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim, bool qk_norm) {
   const int steps = k / 32;
   SplitPlan best;
@@ -104,7 +104,7 @@ inline SplitPlan plan_stream(int epi, int n_cols, int k, int rows, int head_dim,
     const int tiles = (n_cols + tn - 1) / tn;
     const double rate = rb == 1 ? 45e3 : 60e3, chip_us = 2.0 * n_cols * k / 6.3e6;
     for (int sp = 1; sp <= kMaxStreamSplits && sp <= steps && (sp == 1 || tiles * groups * sp <= 256); ++sp) {
-      if (tile_meets(epi, rb, sp) && steps < 8 * sp) continue;   // a step for each of eight wavefronts
+      if (tile_meets(epi, rb, sp) && steps < 8 * sp) continue;   // a step for each of eight wavefronts; tiles of four are not told apart
       const int rounds = (tiles * groups * sp + 255) / 256;
       const double own_us = rounds * ((steps + sp - 1) / sp) * 32.0 * (2.0 * tn + 64.0 * rb) / rate;
       double us = 3.0 * rounds + (own_us > chip_us ? own_us : chip_us) + 0.012 * rb * tn;
