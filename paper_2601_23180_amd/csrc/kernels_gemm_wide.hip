@@ -50,9 +50,9 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_wide(GemmArgs a) {
   const int wr = wave / WC, wc = wave - wr * WC;
   const int ln = lane & 31, g = lane >> 5;
   // Workgroups go round-robin over the 8 XCDs: ids 8 apart are the row groups of one (tile, split), whose weights then
-  // come through one L2 at about the same time (LM head 128256 x 4096 over 240 rows 617 -> 546 us against one group after the other, 594
-  // with the hint below; 128-column tiles, one round of workgroups: passes of 81 models of eight layers 1.4 % shorter on average, from 3.6 %
-  // shorter to 0.4 % longer).  APART: one row group after the other (wide_apart in plan.hpp).
+  // come through one L2 at about the same time (LM head 128256 x 4096 over 240 rows: 1187 MB into the L2s against 2187 for one group after the
+  // other, 617 -> 546 us, 594 with the hint below).  Products of one round of workgroups, against one group after the other and, in 256 columns, the hint: 36 gate + up
+  // 8 % shorter on average, but 28672 x 4096 107.9 -> 108.4, 4096 x 14336 in 8 splits 55.2 -> 56.0; 128 columns: passes of 81 models 1.4 % shorter, at worst 0.4 % longer.  APART: one row group after the other (wide_apart in plan.hpp).
   int tile, rg, split;
   if constexpr (APART) {
     tile = blockIdx.x; rg = blockIdx.y; split = blockIdx.z;

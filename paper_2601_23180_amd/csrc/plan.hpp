@@ -265,7 +265,7 @@ struct AttnPlan {
 // at least -> now, kv heads 8:
 //   120 rows   8192 keys 19.7 + 9.9 -> 20.6 + 4.8, 16384 31.3 + 9.7 -> 28.9 + 6.4, 1024 13.7 + 4.5 -> 10.7 + 4.2, three sequences of 8192 61.7 + 12.0 -> 40.2 + 8.4
 //   240 rows   8192 keys 26.8 + 13.7 -> 27.9 + 7.3, 4096 17.5 + 9.7 -> 18.7 + 7.3, 2048 15.2 + 5.2 -> 14.6 + 5.1, a chain over 4096 17.4 + 18.2 -> 19.5 + 5.7
-//   256 rows   2048 keys 15.4 + 5.4 -> 15.4 + 5.4;   four sequences of 240 rows   16384 keys 125 + 21.7 -> 122 + 17.8
+//   256 rows   2048 keys 15.4 + 5.4 -> 15.4 + 5.4;   four sequences of 240 rows   16384 keys 129.6 + 21.7 -> 130.0 + 18.6
 inline AttnPlan plan_attn(int batch, int n_kv, int group, int head_dim, int n_nodes, int depth, int max_keys, bool paged) {
   const int p_rows = group * n_nodes, n_draft = (n_nodes + 31) / 32;
   AttnPlan best;
