@@ -120,6 +120,7 @@ struct GemmArgs {
   int32_t kernel;      // GEMM_*
   int32_t tile_n;      // output columns per workgroup: 128; stream 16 .. 128; more than 128 rows 128 or 256
   int32_t epi;
+  uint32_t tiles_inv;  // more than 128 rows, k splits: wide_tiles_inv of the tiles
   const float *norm_w; // fp32 path: weight of the RMSNorm of x's rows, or nullptr: x as it is
   float *out;          // PLAIN epilogue, fp32 path's LM head: [rows][n_total] fp32
   const float *bias;   // PLAIN epilogue: [n_total] added to every row, or nullptr

@@ -51,17 +51,20 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_wide(GemmArgs a) {
   const int ln = lane & 31, g = lane >> 5;
   // Workgroups go round-robin over the 8 XCDs: ids 8 apart are the row groups of one (tile, split), whose weights then
   // come through one L2 at about the same time (LM head 128256 x 4096 over 240 rows: 1187 MB into the L2s against 2187 for one group after the
-  // other, 617 -> 546 us, 594 with the hint below).  Products of one round of workgroups, against one group after the other and, in 256 columns, the hint: 36 gate + up
-  // 8 % shorter on average, but 28672 x 4096 107.9 -> 108.4, 4096 x 14336 in 8 splits 55.2 -> 56.0; 128 columns: passes of 81 models 1.4 % shorter, at worst 0.4 % longer.  APART: one row group after the other (wide_apart in plan.hpp).
+  // other, 617 -> 546 us, 594 with the hint below).  Products of one round of workgroups, on the same buffers, against one group after the other: passes of
+  // 81 models 1.5 % shorter (128 columns, at worst 0.2 % longer) and 0.4 % (256 columns, at worst 0.3 % longer).
+  // APART: one row group after the other (wide_apart in plan.hpp).
   int tile, rg, split;
   if constexpr (APART) {
     tile = blockIdx.x; rg = blockIdx.y; split = blockIdx.z;
   } else {
-    const int n_tiles = (a.n_total + TN - 1) / TN, n_rg = (a.rows + kWideRows - 1) / kWideRows;
-    const int item = (int)(blockIdx.x >> 3) / n_rg * 8 + (blockIdx.x & 7);
+    // no division: it is on the way to the first load (with three of them products of 8 - 15 us took 1 us more, passes of 81 models 1.4 %)
+    static_assert(kMaxRows <= 2 * kWideRows, "one row group or two");
+    const int n_tiles = (a.n_total + TN - 1) / TN, two = a.rows > kWideRows;
+    const int item = (int)(blockIdx.x >> 3 >> two) * 8 + (blockIdx.x & 7);
     if (item >= n_tiles * a.n_splits) return;   // the last 8 are filled up
-    rg = (int)(blockIdx.x >> 3) % n_rg;
-    split = item / n_tiles;
+    rg = (int)(blockIdx.x >> 3) & two;
+    split = a.n_splits == 1 ? 0 : wide_split(item, n_tiles, a.tiles_inv);
     tile = item - split * n_tiles;
   }
   const int mbt = a.rows_pad >> 5;
@@ -281,10 +284,11 @@ __global__ __launch_bounds__(256) void k_gemm_finish(GemmArgs a) {
 }
 
 template <int EPI>
-static void dispatch_wide(hipStream_t st, const GemmArgs &a) {
+static void dispatch_wide(hipStream_t st, GemmArgs a) {
   const int n_rg = (a.rows + kWideRows - 1) / kWideRows, wide = EPI == EPI_HEAD || a.tile_n == 256;   // the LM head always
   const int n_tiles = (a.n_total + (wide ? 255 : 127)) / (wide ? 256 : 128);
   const dim3 grid((n_tiles * a.n_splits + 7) / 8 * 8 * n_rg);
+  a.tiles_inv = wide_tiles_inv(n_tiles);
   if constexpr (EPI == EPI_HEAD) {
     if (wide_apart(a.n_total, a.k, a.rows)) hipLaunchKernelGGL((k_gemm_wide<1, 4, 4, 2, EPI, true>), dim3(n_tiles, n_rg), dim3(256), 0, st, a);
     else hipLaunchKernelGGL((k_gemm_wide<1, 4, 4, 2, EPI, false>), grid, dim3(256), 0, st, a);

@@ -193,6 +193,9 @@ inline SplitPlan plan_wide(int epi, int n_cols, int k, int rows_pad, size_t max_
   }
   return best;
 }
+// Work items of a product in k splits are split * n_tiles + tile, at most a few hundred (kWidePartFloats).  item / n_tiles without a division:
+constexpr uint32_t wide_tiles_inv(int n_tiles) { return n_tiles == 1 ? 0u : (uint32_t)((1ull << 32) / n_tiles + 1); }
+constexpr int wide_split(int item, int n_tiles, uint32_t inv) { return n_tiles == 1 ? item : (int)((unsigned long long)(uint32_t)item * inv >> 32); }
 // LM head of the wide kernel: one row group after the other, weights with the non-temporal hint, instead of the row groups of a tile
 // side by side?  Where one group is all there is.  And where the workgroups are more than one round and the last group is short: behind
 // full groups its workgroups, with a few rows to write out, fill the last round, which side by side is as long as the first.  us a pass of one

@@ -6,6 +6,9 @@
 #include "plan.hpp"
 
 int main() {
+  for (int tiles = 1; tiles <= 512; ++tiles)   // the wide kernel's item / tiles
+    for (int item = 0; item < 16 * tiles; ++item)
+      if (ts::wide_split(item, tiles, ts::wide_tiles_inv(tiles)) != item / tiles) return 1;
   int epi, n, k, rows, d, norm;
   while (scanf("%d %d %d %d %d %d", &epi, &n, &k, &rows, &d, &norm) == 6) {
     const ts::SplitPlan p = ts::plan_any(epi, n, k, rows, d, norm != 0);
